@@ -117,8 +117,8 @@ def _layers(c):
     return [k for k in (c["K1"], c["K2"], c["K3"], c["K4"]) if k]
 
 
-def prepare(case, seed):
-    """Weights and activations on the GPU, the buffers the chain writes and the policy that owns its semaphores."""
+def _inputs(case, seed):
+    """Activations and weights of a case on the GPU, in the library's layouts, from the seed alone."""
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     dt = DTYPES[case["dtype"]]
@@ -126,38 +126,52 @@ def prepare(case, seed):
     def normal(*shape, std=1.0):
         return torch.randn(shape, generator=g, device="cuda", dtype=torch.float32).mul_(std).to(dt)
 
+    if case["kind"] == "conv":
+        x = normal(case["B"], case["H"], case["W"], case["C"])
+        ws, cin = [], case["C"]
+        for k in _layers(case):
+            ws.append(normal(k, 3, 3, cin, std=math.sqrt(2.0 / (9 * cin))))
+            cin = k
+        return dict(x=x, ws=ws)
+    K1, N2, kv = case["K1"], case["N2"], {}
+    if case["kind"] == "mlp":
+        M, k2 = case["M"], case["N1"]
+        rows1 = 2 * k2 if case["mid"] == "swiglu" else k2
+    else:
+        b, k2, cached = case["batch"], case["heads"] * 128, case["cached"]
+        M, rows1 = b * case["seq"], 3 * k2
+        if cached:
+            kv = dict(k_cache=normal(b, cached, k2), v_cache=normal(b, cached, k2))
+    X = normal(M, K1)
+    W1t = normal(rows1, K1, std=1.0 / math.sqrt(K1))
+    W2t = normal(N2, k2, std=1.0 / math.sqrt(k2))
+    return dict(X=X, W1t=W1t, W2t=W2t, kv=kv)
+
+
+def prepare(case, seed):
+    """Weights and activations on the GPU, the buffers the chain writes and the policy that owns its semaphores."""
+    t = _inputs(case, seed)
+    dt = DTYPES[case["dtype"]]
+
     def empty(*shape):
         return torch.empty(shape, device="cuda", dtype=dt)
 
     pol = ds.SyncPolicy(KINDS[case["policy"]])
     common = dict(policy=pol, mode=MODES[case["mode"]])
     if case["kind"] == "conv":
-        ks = _layers(case)
-        x = normal(case["B"], case["H"], case["W"], case["C"])
-        ws, outs, cin = [], [], case["C"]
-        for k in ks:
-            ws.append(normal(k, 3, 3, cin, std=math.sqrt(2.0 / (9 * cin))))
-            outs.append(empty(case["B"], case["H"], case["W"], k))
-            cin = k
-        return dict(kind="conv", x=x, ws=ws, outs=outs, common=common)
-    K1, N2 = case["K1"], case["N2"]
+        outs = [empty(case["B"], case["H"], case["W"], k) for k in _layers(case)]
+        return dict(kind="conv", x=t["x"], ws=t["ws"], outs=outs, common=common)
+    X, W1t, W2t = t["X"], t["W1t"], t["W2t"]
     if case["kind"] == "mlp":
-        M, N1, mid = case["M"], case["N1"], MIDS[case["mid"]]
-        rows1, k2, extra = (2 * N1 if mid == ds.MID_SWIGLU else N1), N1, {}
+        N1, extra = case["N1"], dict(mid=MIDS[case["mid"]])
     else:
-        b, s, heads, cached = case["batch"], case["seq"], case["heads"], case["cached"]
-        M, E, mid = b * s, heads * 128, ds.MID_CAUSAL_ATTN
-        N1 = rows1 = 3 * E
-        k2 = E
-        extra = dict(T=empty(M, E), batch=b, seq=s, heads=heads, head_dim=128)
-        if cached:
-            extra.update(k_cache=normal(b, cached, E), v_cache=normal(b, cached, E))
-    X = normal(M, K1)
-    W1t = normal(rows1, K1, std=1.0 / math.sqrt(K1))
-    W2t = normal(N2, k2, std=1.0 / math.sqrt(k2))
+        E = case["heads"] * 128
+        N1 = 3 * E
+        extra = dict(mid=ds.MID_CAUSAL_ATTN, T=empty(X.shape[0], E), batch=case["batch"], seq=case["seq"], heads=case["heads"],
+                     head_dim=128, **t["kv"])
     if case.get("packed"):   # static weights: packed once, when a model is loaded
         W1t, W2t = ds.pack_weights_kblocked(W1t), ds.pack_weights_kblocked(W2t)
-    return dict(kind="gemm", a=(X, W1t, empty(M, N1), W2t, empty(M, N2)), extra=dict(extra, mid=mid), common=common)
+    return dict(kind="gemm", a=(X, W1t, empty(X.shape[0], N1), W2t, empty(X.shape[0], case["N2"])), extra=extra, common=common)
 
 
 def run(state):
@@ -211,3 +225,55 @@ def tolerance(case):
     if case["dtype"] == "fp16":
         return {"rel": 1.8e-3, "max": 2.0e-2} if attn else {"rel": 1.2e-3, "max": 8.0e-3}
     return {"rel": 1.5e-2, "max": 0.28} if attn else {"rel": 1.2e-2, "max": 6.0e-2}
+
+
+def _conv64(x, w):
+    """3x3 convolution with padding 1, NHWC, as nine shifted products."""
+    B, H, W, C = x.shape
+    xp = torch.zeros(B, H + 2, W + 2, C, device=x.device, dtype=x.dtype)
+    xp[:, 1:-1, 1:-1] = x
+    y = torch.zeros(B * H * W, w.shape[0], device=x.device, dtype=x.dtype)
+    for r in range(3):
+        for q in range(3):
+            y += xp[:, r:r + H, q:q + W].reshape(-1, C) @ w[:, r, q].t()
+    return y.view(B, H, W, -1)
+
+
+def _attention64(c, qkv, kv):
+    """Causal attention of the new tokens over the cached and the new ones, one head of one sequence at a time."""
+    b, s, heads, cached, E = c["batch"], c["seq"], c["heads"], c["cached"], c["heads"] * 128
+    T = torch.empty(b * s, E, device=qkv.device, dtype=qkv.dtype)
+    hidden = torch.ones(s, cached + s, device=qkv.device, dtype=torch.bool).triu(cached + 1)
+    for i in range(b):
+        rows = slice(i * s, (i + 1) * s)
+        for h in range(heads):
+            cols = slice(h * 128, (h + 1) * 128)
+            q, k, v = (qkv[rows, j * E + h * 128:j * E + (h + 1) * 128] for j in range(3))
+            if cached:
+                k, v = torch.cat([kv["k_cache"][i, :, cols].double(), k]), torch.cat([kv["v_cache"][i, :, cols].double(), v])
+            p = (q @ k.t() / math.sqrt(128.0)).masked_fill_(hidden, -math.inf)
+            T[rows, cols] = torch.softmax(p, dim=1) @ v
+    return T
+
+
+def exact(case, seed):
+    """The chain in 64 bits with plain torch, nothing rounded on the way."""
+    t = _inputs(case, seed)
+    if case["kind"] == "conv":
+        x, outs = t["x"].double(), []
+        for i, w in enumerate(t["ws"]):
+            x = _conv64(x, w.double())
+            if i < len(t["ws"]) - 1:
+                x = torch.relu_(x)
+            outs.append(x)
+        return outs
+    H = t["X"].double() @ t["W1t"].double().t()
+    W2 = t["W2t"].double().t()
+    if case["kind"] == "attn":
+        T = _attention64(case, H, t["kv"])
+        return [H, T @ W2, T]
+    if case["mid"] == "swiglu":
+        H = torch.nn.functional.silu(H[:, :case["N1"]]) * H[:, case["N1"]:]
+    else:
+        H = torch.nn.functional.gelu(H) if case["mid"] == "gelu" else torch.relu(H)
+    return [H, H @ W2]
