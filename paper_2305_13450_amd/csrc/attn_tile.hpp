@@ -10,8 +10,9 @@
 // (lane % 32) and rows 8*(v/4) + 4*(lane/32) + v%4, so the 8 accumulator values v0..v0+7 of a
 // lane are 8 keys of its query, and since the order of the 16 K-slots of an MFMA is free as
 // long as both operands agree, they can be fed straight back as the B operand while V^T is
-// read with the same key permutation.  Row maxima and sums are then in-lane reductions plus
-// one exchange between the two half-waves.
+// read with the same key permutation: runs of 4 keys of one d, which the transposing LDS read
+// (ds_read_b64_tr_b16) gathers from rows of V as they lie in memory.  Row maxima are in-lane
+// reductions plus one exchange between the two half-waves; the sums are a product with ones.
 //
 // Dependencies: the tile reads the Q columns of its own rows and the K and V columns of all
 // rows of its sequence up to its last row, from the QKV GeMM before it; it posts like any
@@ -29,7 +30,29 @@ constexpr int ATT_BQ = 128;      // query rows per tile (32 per wave)
 constexpr int ATT_BK = 64;       // keys per block
 constexpr int ATT_D = 128;       // head dimension
 constexpr int ATT_BLK_BYTES = ATT_BK * ATT_D * 2;       // one block of K or V rows (16 KB)
-constexpr int ATT_LDS_BYTES = 4 * ATT_BLK_BYTES;        // two K buffers, raw V rows, V^T
+constexpr int ATT_LDS_BYTES = 4 * ATT_BLK_BYTES;        // rings of at least two K and two V blocks
+
+// Position of the 16-byte chunk of row `key` of V in its LDS row.  A transposing read takes, per group of
+// 16 lanes, 32 bytes of each of 4 consecutive keys (64 bytes with the neighbouring group): the low
+// bits of the key choose the 64-byte window, so that those 4 keys lie in different banks.
+__device__ __forceinline__ uint32_t att_vswz(uint32_t key) { return ((key & 3u) << 2) | ((key >> 2) & 3u); }
+
+// Four 16-bit elements per lane, transposed: the 16 lanes of a group address a 4 x 16 tile (lane i: row
+// i / 4, elements 4 * (i % 4) ..), and lane i receives column i.
+template <typename T> struct TrRead;
+template <> struct TrRead<__bf16> {
+    typedef __bf16 T4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ T4 read(const char* p) {
+        return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) T4*)(p));
+    }
+};
+template <> struct TrRead<_Float16> {
+    typedef _Float16 T4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ T4 read(const char* p) {
+        typedef __fp16 H4 __attribute__((ext_vector_type(4)));
+        return __builtin_bit_cast(T4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((__attribute__((address_space(3))) H4*)(p)));
+    }
+};
 
 // Wait for everything an attention tile reads from the QKV GeMM: producer row tiles y0..y1,
 // and in each the column tiles holding this head's Q, K and V columns.
@@ -70,7 +93,17 @@ constexpr uint32_t ATT_PART_FLOATS = 256 * 64 + 2 * 256;
 // re-reads the queries and leaves 65 KB of partial results).
 constexpr uint32_t ATT_MIN_PART_BLOCKS = 4;
 
-template <typename T, bool SYNC, class DR>
+// What bounds it: the longest tiles of a causal stage are one serial chain of key blocks, walked by one
+// wave per SIMD: per block 36 MFMAs (0.5 us), 32 scores per lane through exp2 and conversion (as
+// much again), and all four waves reading the whole block from LDS.  So V is transposed by the read
+// (writing V^T back to LDS element by element took longer than everything else together), a block has
+// one barrier, half of the next block's scores are multiplied beside the exponentials, and the
+// operands' offsets fit few registers (with more, the loop reloaded them from scratch memory and waited
+// for the DMA in flight each time).  12 heads, 2048 tokens, bf16: the longest tile (32 blocks) 185 -> 76 us,
+// of which about 20 are waits for K and V; the whole chain 438 -> 372 us.
+// NBUF: blocks in the LDS rings of K and V: 4 where the tile has the CU to itself, 2 where two workgroups
+// share it (and cover each other's waits).
+template <typename T, bool SYNC, int NBUF, class DR>
 __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc& s, uint32_t head, uint32_t tyz,
                                           uint32_t rel_ticket, char* lds, uint64_t t_enter, DR& dr) {
     using M = Mma<T>;
@@ -137,130 +170,186 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[i][v] = 0.0f;
-    float m_run = -INFINITY, l_run = 0.0f;
+    // the sum of a query's weights: one more block of O^T, with rows of ones in the place of V^T (every
+    // row holds the sum over both half-waves' keys)
+    V8 ones;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ones[j] = (T)1.0f;
+    f32x16 lsum;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) lsum[v] = 0.0f;
+    float m_run = -INFINITY;
     const float sc = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(128) * log2(e)
 
-    // LDS: two K buffers [64 keys][128 d] (16-byte chunks swizzled by key & 15), one buffer of
-    // V rows in the same layout and the V^T block [128 d][64 keys] (8-byte chunks swizzled by d & 15).
-    // While block kb is used, the K and V rows of block kb+1 are DMA'd into LDS (no registers
-    // held); V is transposed LDS to LDS at the top of the next iteration.
+    // LDS: NBUF blocks of K rows and NBUF of V rows ([64 keys][128 d], 16-byte chunks swizzled), DMA'd
+    // from global memory.  Step kb multiplies the scores of block kb+1 and the values of block kb, so
+    // it requests K of block kb+NBUF and V of block kb+NBUF-1 into the slots the step before has left.
+    // The compiler waits for every DMA in flight before a transposing read, so with slots to spare
+    // the requests go out behind the step's last such read and have a whole step to land.
+    constexpr bool LATE = NBUF > 2;
+    const uint32_t wave_q_first = min(q0 + wave * 32, seq - 1);
     const uint32_t wave_q_last = min(q0 + wave * 32 + 31, seq - 1);
-    char* const ldsVraw = lds + 2 * ATT_BLK_BYTES;
-    char* const ldsV = lds + 3 * ATT_BLK_BYTES;
-    auto fetch = [&](uint32_t kb) __attribute__((always_inline)) {
-        const uint32_t k0 = kb * ATT_BK;
-        char* ldsKn = lds + (kb & 1u) * ATT_BLK_BYTES;
+    char* const ldsK = lds;
+    char* const ldsV = lds + NBUF * ATT_BLK_BYTES;
+    // a lane's 16 bytes of rows tid/16, tid/16 + 16, .. of a block (both swizzles repeat every 16 rows)
+    const uint32_t frow = tid >> 4;
+    const uint32_t fck = ((tid & 15u) ^ frow) * 16u, fcv = ((tid & 15u) ^ att_vswz(frow)) * 16u;
+    auto fetch = [&](uint32_t kb, bool v) __attribute__((always_inline)) {
+        char* dst = (v ? ldsV : ldsK) + (kb % NBUF) * ATT_BLK_BYTES + wave * 1024;
+        const uint32_t k0 = kb * ATT_BK, fc = v ? fcv : fck;      // position in key order: cache first
+        if (k0 + ATT_BK <= cached || (k0 >= cached && k0 + ATT_BK <= cached + seq)) {   // a block of one source, whole
+            const bool in_cache = k0 < cached;
+            const char* g = in_cache ? (const char*)((v ? Vc : Kc) + ((size_t)b * cached + k0) * ldkv + head * ATT_D)
+                                     : (const char*)(QKV + (size_t)(seq_row0 + k0 - cached) * ld + (v ? 2 * E : E) + head * ATT_D);
+            const uint32_t pitch = 2u * (in_cache ? ldkv : ld), off = frow * pitch + fc;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {                             // 4 x 16 bytes per lane for K, and for V
-            const uint32_t idx = i * 256 + tid, row = idx >> 4, slot = idx & 15u, chunk = slot ^ (row & 15u);
-            const uint32_t key = k0 + row;                        // position in key order: cache first
-            const char *gk, *gv;
-            if (key < cached) {
-                const size_t r = ((size_t)b * cached + key) * ldkv + head * ATT_D;
-                gk = (const char*)(Kc + r); gv = (const char*)(Vc + r);
-            } else {
-                const uint32_t krow = seq_row0 + min(key - cached, seq - 1);
-                gk = (const char*)(QKV + (size_t)krow * ld + E + head * ATT_D);
-                gv = gk + E * 2;
+            for (int i = 0; i < 4; ++i) dma16(g + (size_t)i * 16u * pitch + off, dst + i * 4096);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t key = k0 + i * 16 + frow;
+                const bool c = key < cached;
+                const char* base = c ? (const char*)((v ? Vc : Kc) + (size_t)b * cached * ldkv + head * ATT_D)
+                                     : (const char*)(QKV + (size_t)seq_row0 * ld + (v ? 2 * E : E) + head * ATT_D);
+                const char* g = base + (uint64_t)(c ? key : min(key - cached, seq - 1)) * (2u * (c ? ldkv : ld));
+                dma16(g + fc, dst + i * 4096);
             }
-            dma16(gk + chunk * 16, ldsKn + (i * 256 + wave * 64) * 16);
-            dma16(gv + chunk * 16, ldsVraw + (i * 256 + wave * 64) * 16);   // V rows, same swizzle
         }
     };
-    fetch(kb_begin);
-
-    for (uint32_t kb = kb_begin; kb < kb_end; ++kb) {
-        const uint32_t k0 = kb * ATT_BK;
-        char* ldsK = lds + (kb & 1u) * ATT_BLK_BYTES;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wave's part of block kb has landed
-        __syncthreads();   // block kb's rows are in LDS for everyone; everyone is done with block kb-1
-        // V transposed, LDS to LDS: each lane takes 8 d values of one key, four times
+    // Per-lane LDS offsets.  K fragments are rows lq (and 32 + lq), chunk 2 * kk + h2; V fragments are
+    // transposed reads of 4 keys x 16 d per 16 lanes (key 4 * h2 + .., and 8 further on; 32 d further on
+    // per block of d).  The swizzles are exclusive-ors, so one offset serves all fragments of an operand.
+    const uint32_t koff = lq * 256u + ((h2 ^ (lq & 15u)) << 4);
+    const uint32_t vkey = 4u * h2 + ((lane & 15u) >> 2);
+    const uint32_t voff = vkey * 256u + (((((lane >> 4) & 1u) * 2u + ((lane & 3u) >> 1)) ^ att_vswz(vkey)) << 4) + (lane & 1u) * 8u;
+    // S^T of one 32-key half of block kb, with `between(kk)` after the MFMA of each 16-wide slice kk of d.
+    // Fragments are read two slices ahead and the order is pinned: left alone the compiler reads each
+    // fragment right before the wait for it.
+    auto scores = [&](uint32_t kb, int kh, auto&& between) __attribute__((always_inline)) {
+        const uint32_t k = (kb % NBUF) * ATT_BLK_BYTES + koff;
+        V8 kf[3];
+        auto rd = [&](int kk) __attribute__((always_inline)) { kf[kk % 3] = *(const V8*)(ldsK + (k ^ (kk * 32u)) + kh * (32 * 256)); };
+        rd(0); rd(1);
+        f32x16 acc;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t idx = i * 256 + tid, key = idx & 63u, dch = idx >> 6;      // dch: 8-wide d chunk 0..15
-            const V8 vv = *(const V8*)(ldsVraw + key * 256u + ((dch ^ (key & 15u)) << 4));
+        for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t d = dch * 8 + e;
-                const uint32_t off = d * 128u + ((((key >> 2) ^ (d & 15u)) << 3) | ((key & 3u) << 1));
-                *(T*)(ldsV + off) = vv[e];
-            }
+        for (int kk = 0; kk < 8; ++kk) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (kk + 2 < 8) rd(kk + 2);
+            acc = M::mma(kf[kk % 3], qf[kk], acc);
+            between(kk);
         }
-        __syncthreads();   // V^T complete; the raw V rows and the other K buffer are free again
-        if (kb + 1 < kb_end) fetch(kb + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        return acc;
+    };
+    auto request = [&](uint32_t kb) __attribute__((always_inline)) {   // what step kb requests
+        if (kb + NBUF < kb_end) fetch(kb + NBUF, false);
+        if (kb + NBUF - 1 < kb_end) fetch(kb + NBUF - 1, true);
+    };
+    // Everything step kb reads has landed for every wave, and every wave is done with the slots its
+    // requests go into.
+    auto arrive = [&](uint32_t kb) __attribute__((always_inline)) {
+        if (LATE && kb + NBUF - 1 < kb_end) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * (NBUF - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
 
-        if (k0 <= cached + wave_q_last) {   // blocks entirely above this wave's diagonal contribute nothing
-            // ---- S^T for the two 32-key halves of the block ----
-            f32x16 st[2];
 #pragma unroll
-            for (int kh = 0; kh < 2; ++kh) {
+    for (int p = 0; p < NBUF; ++p) {                               // in the order the steps before kb_begin would have requested them
+        if (p > 0 && kb_begin + p - 1 < kb_end) fetch(kb_begin + p - 1, true);
+        if (p == 0 || kb_begin + p < kb_end) fetch(kb_begin + p, false);
+    }
+    // the scores of the first block: its K rows are the oldest request
+    if (kb_begin + NBUF - 1 < kb_end) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * (NBUF - 1)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    f32x16 st[2];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) st[kh][v] = 0.0f;
-                const uint32_t row = kh * 32 + lq;
-#pragma unroll
-                for (int kk = 0; kk < 8; ++kk) {
-                    const uint32_t chunk = (kk * 2 + h2) ^ (row & 15u);
-                    const V8 kf = *(const V8*)(ldsK + row * 256u + chunk * 16u);
-                    st[kh] = M::mma(kf, qf[kk], st[kh]);
-                }
-            }
-            // ---- causal mask, running maximum ----
-            float mx = -INFINITY;
+    for (int kh = 0; kh < 2; ++kh) st[kh] = scores(kb_begin, kh, [](int) {});
+
+    // Blocks above a wave's diagonal contribute nothing to it: it only keeps the others company.
+    const uint32_t kb_live = min(kb_end, (cached + wave_q_last) / ATT_BK + 1);
+    uint32_t kb = kb_begin;
+    for (; kb < kb_live; ++kb) {
+        const uint32_t k0 = kb * ATT_BK;
+        arrive(kb);
+        if (!LATE) request(kb);
+        // ---- causal mask (blocks on the diagonal and at the end only), running maximum ----
+        if (k0 + ATT_BK - 1 > cached + wave_q_first) {
 #pragma unroll
             for (int kh = 0; kh < 2; ++kh)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const uint32_t key = k0 + kh * 32 + 8 * (v / 4) + 4 * h2 + (v % 4);
-                    float x = st[kh][v] * sc;
-                    if (key > cached + qi || key >= cached + seq) x = -INFINITY;
-                    st[kh][v] = x;
-                    mx = fmaxf(mx, x);
+                    if (key > cached + qi || key >= cached + seq) st[kh][v] = -INFINITY;
                 }
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m_run, mx);
-            // a query beyond the sequence end or with no visible key yet keeps m = -inf: guard the exps
-            const float m_use = (m_new == -INFINITY) ? 0.0f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);   // arguments are <= 0 or -inf: v_exp_f32 as is
-            float psum = 0.0f;
-#pragma unroll
-            for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float p = __builtin_amdgcn_exp2f(st[kh][v] - m_use);
-                    st[kh][v] = p;
-                    psum += p;
-                }
-            psum += __shfl_xor(psum, 32);
-            l_run = l_run * alpha + psum;
-            m_run = m_new;
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // no query of the wave has a new maximum: O stays
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) o[i][v] *= alpha;
-            }
-            // ---- O^T += V^T P^T : 4 steps of 16 keys ----
-#pragma unroll
-            for (int step = 0; step < 4; ++step) {
-                const int kh = step >> 1, v0 = (step & 1) * 8;
-                V8 pf;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) pf[j] = (T)st[kh][v0 + j];
-                const uint32_t kbase = kh * 32 + (step & 1) * 16;          // keys kbase+4h..+3 and kbase+8+4h..+3
-#pragma unroll
-                for (int db = 0; db < 4; ++db) {
-                    const uint32_t d = db * 32 + lq;
-                    const uint32_t c0 = ((kbase >> 2) + h2) ^ (d & 15u), c1 = ((kbase >> 2) + 2 + h2) ^ (d & 15u);
-                    const T4 lo = *(const T4*)(ldsV + d * 128u + (c0 << 3));
-                    const T4 hi = *(const T4*)(ldsV + d * 128u + (c1 << 3));
-                    V8 vf;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) { vf[j] = lo[j]; vf[4 + j] = hi[j]; }
-                    o[db] = M::mma(vf, pf, o[db]);
-                }
-            }
         }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, st[kh][v]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32)) * sc;
+        // The reference value of the exponentials follows the maximum unless the new one would carry less
+        // than a sixteenth of the weight summed so far (and less than 2^8): most steps then do without the
+        // 80 multiplications.  A key that carries more gets the weight 1, which 16 bits hold exactly: with
+        // a reference that always lagged, the rounding of rows with few keys reached 2.7e-2 of a row's
+        // RMS at 2048 tokens in bf16.  The weights are summed as they were rounded.
+        const bool lag = mx <= m_run || (mx <= m_run + 8.0f && 16.0f * __builtin_amdgcn_exp2f(mx - m_run) <= lsum[0]);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!lag) != 0, 0)) {
+            // (each query by its own scores alone, whatever the other queries of the wave do)
+            const float m_new = lag ? m_run : mx;
+            // no visible key yet: both are -inf and there is nothing to scale
+            const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) lsum[v] *= alpha;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[i][v] *= alpha;
+        }
+        const float m_use = (m_run == -INFINITY) ? 0.0f : m_run;
+        // ---- weights of this block; the first half's registers then take the next block's scores, whose
+        // MFMAs run beside the exponentials of the second half (past the wave's last block they multiply
+        // whatever the slot holds, and nothing reads the result) ----
+        V8 pf[4];
+        auto weight = [&](int kh, int v) __attribute__((always_inline)) {
+            // arguments are <= 8 or -inf: v_exp_f32 as is
+            pf[kh * 2 + (v >> 3)][v & 7] = (T)__builtin_amdgcn_exp2f(__builtin_fmaf(st[kh][v], sc, -m_use));
+        };
+#pragma unroll
+        for (int v = 0; v < 16; ++v) weight(0, v);
+        st[0] = scores(kb + 1, 0, [&](int kk) __attribute__((always_inline)) { weight(1, 2 * kk); weight(1, 2 * kk + 1); });
+        st[1] = scores(kb + 1, 1, [](int) {});
+        // ---- O^T += V^T P^T : 4 steps of 16 keys, fragments of a step read while the one before is multiplied ----
+        const uint32_t vb = (kb % NBUF) * ATT_BLK_BYTES + voff;
+        T4 vf[2][4][2];
+        auto rdv = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+            for (int db = 0; db < 4; ++db)                         // keys 16*ks + 4*h2 ..+3 and 16*ks + 8 + 4*h2 ..+3 of 32 d
+#pragma unroll
+                for (int c = 0; c < 2; ++c) vf[ks & 1][db][c] = TrRead<T>::read(ldsV + (vb ^ (db * 64u + c * 32u)) + (ks * 16 + c * 8) * 256);
+        };
+        rdv(0);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks < 3) rdv(ks + 1);
+            lsum = M::mma(ones, pf[ks], lsum);
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+                o[db] = M::mma(__builtin_shufflevector(vf[ks & 1][db][0], vf[ks & 1][db][1], 0, 1, 2, 3, 4, 5, 6, 7), pf[ks], o[db]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (LATE) request(kb);
     }
+    for (; kb < kb_end; ++kb) {
+        arrive(kb);
+        request(kb);
+    }
+    float l_run = lsum[0];
 
     dr.peek();   // the look at the dispatch queues for the next tile travels while the result is stored
     // ---- keys split over several workgroups: leave the part, carry on only as the last to arrive ----

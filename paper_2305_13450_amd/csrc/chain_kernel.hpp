@@ -24,7 +24,7 @@ __device__ __forceinline__ void run_tile(const ChainArgs& args, const TileId t, 
     if constexpr (AMODE == A_DENSE && MIDK != 0) {
         if (s.op == OP_ATTN) {   // middle stage of the attention chain
             if constexpr (MIDK == 2) attn_decode_tile<T, SYNC>(args, s, t.tx, t.ty, t.rel, lds, t_enter, dr);   // token generation (seq = 1)
-            else attn_tile<T, SYNC>(args, s, t.tx, t.ty, t.rel, lds, t_enter, dr);
+            else attn_tile<T, SYNC, (Cfg::LDS_BYTES >= 8 * ATT_BLK_BYTES ? 4 : 2)>(args, s, t.tx, t.ty, t.rel, lds, t_enter, dr);
             return;
         }
     }
