@@ -219,7 +219,8 @@ int tuned_tile(const TuneKey& k) {
     return it == g_tuned.end() ? 0 : it->second;
 }
 
-uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, uint32_t slots, uint32_t kt, uint32_t seg);
+uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, uint32_t slots, uint32_t kt, uint32_t seg,
+                      uint32_t min_steps = 16);
 
 // Pick one macro-tile for both stages by simulating the fine-grained schedule of the chain
 // on `slots` workgroup slots for every candidate shape (host_model.h).  A stage that would leave
@@ -281,22 +282,71 @@ int policy_dep_kind_conv(int kind) {
 // Workgroups per output tile for a stage with `tiles` output tiles and `kt` K steps whose
 // dependency segments start every `seg` steps: split when the stage would leave at least half
 // of the slots idle, as far as one wave of slots allows, keeping every part at least 16 steps
-// long (the partial tiles and the arrival count cost about 10 us per stage) and starting on a
-// segment boundary.  `tuned_off`: the autotuner found this chain faster without.
+// min_steps long (the partial tiles and the arrival count cost about 10 us per stage; with the small
+// tiles of the three-per-CU shape less, see fit_triple) and starting on a segment boundary.
+// `tuned_off`: the autotuner found this chain faster without.
 // (Splitting a stage of more tiles than slots so that it ends in a fuller last round was measured
 // and is not done: LLaMA MLP at 2048 tokens, 344 producer tiles on 256 slots as 688 halves, three
 // rounds of 64 steps instead of two of 128: 275 -> 283 us; the 88 MB of partial tiles and the
 // finishing workgroups cost more than the shorter last round gains.)
-uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, uint32_t slots, uint32_t kt, uint32_t seg) {
+uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, uint32_t slots, uint32_t kt, uint32_t seg,
+                      uint32_t min_steps) {
     const uint32_t want = pol ? pol->params.ksplit : 0;
     if (want == 1 || seg == 0 || (want == 0 && tuned_off)) return 1;
     static const uint32_t cand[] = {8, 6, 4, 3, 2};
     for (uint32_t S : cand) {
         if (kt % S || (kt / S) % seg) continue;
         if (want > 1) { if (S <= want) return S; continue; }
-        if (tiles * S <= slots && kt / S >= 16) return S;
+        if (tiles * S <= slots && kt / S >= min_steps) return S;
     }
     return 1;
+}
+
+// Splits along K of a chain of 64x64 tiles of which three share a CU.  The parts of ALL stages are kept resident at
+// once where they can be, to begin with an equal share of the slots for each: tiles are then named by the
+// block index, a consumer's weights are under way while its producers run, and no draws or late polls
+// of hundreds of workgroups stand between the stages (256 x 4096 x 2048 x 4096: 31 us resident, 53 us with more
+// parts drawn from the queues; 8192 x 2752 x 8192 at 256 tokens 61 against 77 us).  Parts are at least 12 K
+// steps long (28 x 30 x 256 convolutions 28.5 us with parts of 12, 37.3 us unsplit).
+// kt, seg: K steps and steps between dependency segments of each stage (kt = 0: not a GeMM).
+void fit_triple(Plan& p, const sync_policy* pol, bool tuned_off, const uint32_t (&kt)[4], const uint32_t (&seg)[4]) {
+    const uint32_t slots = (uint32_t)p.slots, min_steps = 12u;
+    for (int s = 0; s < p.n_stages; ++s)
+        if (kt[s]) p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], slots / (uint32_t)p.n_stages, kt[s], seg[s], min_steps);
+    if (pol && pol->params.ksplit) return;
+    for (;;) {
+        uint32_t total = 0;
+        int most = -1;
+        for (int s = 0; s < p.n_stages; ++s) {
+            const uint32_t parts = p.n_tiles[s] * p.ksplit[s];
+            total += parts;
+            if (kt[s] && p.ksplit[s] > 1 && (most < 0 || parts > p.n_tiles[most] * p.ksplit[most])) most = s;
+        }
+        if (total <= slots || most < 0) return;
+        p.ksplit[most] = choose_split(pol, tuned_off, p.n_tiles[most], p.n_tiles[most] * p.ksplit[most] - 1, kt[most], seg[most], min_steps);
+    }
+}
+
+// Would every tile of the chain, unsplit, have a workgroup of the three-per-CU shape resident at once?  Then that
+// shape is the fastest measured (1 to 400 tokens of seven pairs of layers, token generation, convolutions of images
+// of 7 to 60 pixels: 0.6 to 1 of the time of the shape chosen by the model below); beyond that its 64 x 64 tiles
+// move too many bytes per flop (12288 x 6144 x 12288 at 192 tokens: 175 against 135 us).
+bool triple_fits(const std::array<uint32_t, 4>& cols, uint32_t M, int n_stages, uint32_t other_tiles, int cus) {
+    const TileShape* ts = tile_shape(TILE_64x64_TRIPLE);
+    uint64_t tiles = other_tiles;
+    for (int s = 0; s < n_stages; ++s) tiles += (uint64_t)cdiv(cols[s], ts->cols) * cdiv(M, ts->rows);
+    return tiles <= (uint64_t)cus * ts->occupancy;
+}
+
+// Do the 64x192 tiles of a stage split into (nearly) as many equal parts as there are CUs?  Where both stages of a
+// chain do, every CU is busy to the end and rows of A are read a third as often as by 64-wide tiles: 12288 x 6144 x
+// 12288 at 128 tokens 114 against 120 us, at 64 tokens 89 both, at 1 token, where A is one row and what counts is
+// the size of the partial tiles, 72 against 69 us.
+bool wide_fills(uint32_t M, uint32_t N, uint32_t K, int cus) {
+    const TileShape* ts = tile_shape(DEPSYNC_TILE_64x192);
+    if (N % ts->cols) return false;
+    const uint32_t tiles = N / ts->cols * cdiv(M, ts->rows);
+    return tiles * choose_split(nullptr, false, tiles, (uint32_t)cus, K / 64, (uint32_t)ts->cols / 64) * 10 >= (uint32_t)cus * 9;
 }
 
 // Fill in tile counts, arrival counters and partial-tile offsets once grids and splits are known.
@@ -377,6 +427,12 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
+    // (whether StridedSync divides the producer's columns depends on the tile: what it accepts stays as it is)
+    const bool by_stride = !attn && effective_kind(d, pol, pol ? default_kind(d) : DEPSYNC_ROWSYNC) == DEPSYNC_STRIDEDSYNC;
+    if (!tile && !gate_up && !by_stride && (!attn || d->seq == 1) &&
+        triple_fits({(uint32_t)d->N1, (uint32_t)d->N2, 0, 0}, d->M, 2, attn ? (uint32_t)d->batch * d->heads : 0u, cus))
+        tile = (!attn && d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) ? DEPSYNC_TILE_64x192
+                                                                                                              : TILE_64x64_TRIPLE;
     if (!tile) tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0);
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
@@ -447,12 +503,12 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     p.n_sems = off;
     p.slots = cus * ts->occupancy;
     // split along K where a stage is much smaller than the chip (not the prompt-phase attention stage)
-    p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], p.slots, d->K1 / 64, 1);
+    p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], (uint32_t)p.stage_slots[0], d->K1 / 64, 1);
     if (attn && d->seq == 1) {
         // token generation: the keys of a (head, sequence) pair over up to 8 workgroups, at least 256
         // keys each, as far as one wave of slots allows
         uint32_t ks = std::min<uint32_t>(8u, ((uint32_t)d->cached + 1u) / 256u);
-        while (ks > 1 && p.n_tiles[1] * ks > (uint32_t)p.slots) --ks;
+        while (ks > 1 && p.n_tiles[1] * ks > (uint32_t)p.slots / (ts->occupancy > 2 ? 3u : 1u)) --ks;
         p.ksplit[1] = std::max<uint32_t>(ks, 1u);
         p.part_floats[1] = 130;
     } else if (attn) {
@@ -472,7 +528,12 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     {
         const uint32_t dk = p.dep_kind[last];
         const uint32_t seg = (dk == DEP_ROW) ? 1u : p.out_tn[last - 1] / 64;
-        p.ksplit[last] = choose_split(pol, tuned_off, p.n_tiles[last], p.stage_slots[last], K2 / 64, seg);
+        p.ksplit[last] = choose_split(pol, tuned_off, p.n_tiles[last], (uint32_t)p.stage_slots[last], K2 / 64, seg);
+        if (ts->occupancy > 2 && !mixed) {
+            uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, 0, 0}, segs[4] = {1, 1, 1, 1};
+            kts[last] = K2 / 64; segs[last] = seg;
+            fit_triple(p, pol, tuned_off, kts, segs);
+        }
     }
     if (int rc = finish_split(p); rc != DEPSYNC_OK) return rc;
     const double M = d->M, w1c = gate_up ? 2.0 * d->N1 : d->N1;
@@ -539,6 +600,8 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
+    if (!tile && triple_fits({(uint32_t)d->K[0], (uint32_t)d->K[1], n > 2 ? (uint32_t)d->K[2] : 0u, n > 3 ? (uint32_t)d->K[3] : 0u}, M, n, 0, cus))
+        tile = TILE_64x64_TRIPLE;
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
         tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, 1);
@@ -575,14 +638,17 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         }
         p.n_sems += p.sem_count[s];
     }
-    p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], p.stage_slots[0], 9u * d->C / 64, 1);
+    p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], (uint32_t)p.stage_slots[0], 9u * d->C / 64, 1);
+    uint32_t kts[4] = {9u * (uint32_t)d->C / 64, 0, 0, 0}, segs[4] = {1, 1, 1, 1};
     for (int s = 1; s < n; ++s) {
         uint32_t seg = 1;                                   // CONV_ROW: the whole halo is waited for by every part
         // per filter row or per (filter row, channel tile): the wait at a filter row's first tap
         // also covers its other two taps, so parts must be whole filter rows
         if (p.dep_kind[s] != DEP_CONV_ROW) seg = 3u * cin[s] / 64;
-        p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], p.stage_slots[s], 9u * cin[s] / 64, seg);
+        p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], (uint32_t)p.stage_slots[s], 9u * cin[s] / 64, seg);
+        kts[s] = 9u * cin[s] / 64; segs[s] = seg;
     }
+    if (tile_shape(tile)->occupancy > 2 && !mixed) fit_triple(p, pol, tuned_off, kts, segs);
     if (int rc = finish_split(p); rc != DEPSYNC_OK) return rc;
     const double Md = (double)M;
     p.flops = 0.0;
@@ -636,11 +702,13 @@ int plan_copy(const depsync_copy_chain_desc* d, const sync_policy* pol, int n_cu
     return DEPSYNC_OK;
 }
 
+int public_tile(int tile) { return tile == TILE_64x64_TRIPLE ? DEPSYNC_TILE_64x64 : tile; }
+
 void fill_plan_info(const Plan& p, depsync_plan_info* o) {
     std::memset(o, 0, sizeof(*o));
-    o->tile_prod = p.tile[0];
-    o->tile_cons = p.tile[p.n_stages - 1];
-    o->tile_mid = p.n_stages >= 3 ? p.tile[1] : 0;
+    o->tile_prod = public_tile(p.tile[0]);
+    o->tile_cons = public_tile(p.tile[p.n_stages - 1]);
+    o->tile_mid = p.n_stages >= 3 ? public_tile(p.tile[1]) : 0;
     o->prod_grid_x = p.grid_x[0]; o->prod_grid_y = p.grid_y[0];
     o->cons_grid_x = p.grid_x[p.n_stages - 1]; o->cons_grid_y = p.grid_y[p.n_stages - 1];
     o->n_prod = p.n_tiles[0];
@@ -1402,7 +1470,7 @@ const char* depsync_strerror(int status) {
 int depsync_last_hip_error(void) { return g_last_hip_error; }
 
 int depsync_tile_shape(int tile, int* rows, int* cols) {
-    const TileShape* ts = tile_shape(tile);
+    const TileShape* ts = tile < DEPSYNC_TILE__COUNT ? tile_shape(tile) : nullptr;
     if (!ts || !rows || !cols) return DEPSYNC_EINVAL;
     *rows = ts->rows;
     *cols = ts->cols;

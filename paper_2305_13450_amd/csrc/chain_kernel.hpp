@@ -14,6 +14,7 @@
 #include "attn_decode.hpp"
 #include "attn_tile.hpp"
 #include "gemm_tile.hpp"
+#include "launch.h"
 #include "sync_device.hpp"
 
 namespace depsync {
@@ -55,7 +56,8 @@ template <class Cfg, typename T, bool SYNC, uint32_t AMODE, int MIDK>
 __global__ __launch_bounds__(256, Cfg::MINB) void chain_kernel(const ChainArgs args) {
     // One LDS object only: with a second one the compiler can no longer tell the DMA writes
     // into the idle stage from the fragment reads of the current stage and serialises them.
-    static_assert(Cfg::LDS_BYTES >= ATT_LDS_BYTES, "the attention tile stages its K and V blocks in the same LDS");
+    static_assert(MIDK != 1 || Cfg::LDS_BYTES >= ATT_LDS_BYTES, "the attention tile stages its K and V blocks in the same LDS");
+    static_assert(MIDK != 2 || Cfg::LDS_BYTES >= DEC_LDS_BYTES, "so does the token-generation tile its partial results");
     __shared__ __attribute__((aligned(1024))) char lds[Cfg::LDS_BYTES];
 
     if constexpr (!SYNC) {
@@ -92,6 +94,8 @@ using Cfg64x192 = TileCfg<64, 192, 2, 2, 1, 4>;     // 128 KB: three K steps in 
 using Cfg128x192Deep = TileCfg<128, 192, 2, 2, 1, 4>;   // 160 KB: three K steps in flight
 using Cfg128x128Deep = TileCfg<128, 128, 2, 2, 1, 4>;   // 128 KB: three K steps in flight
 
+using Cfg64x64Triple = TileCfg<64, 64, 2, 2, 3, 3>;   // 3 x 48 KB
+
 template <class Cfg, typename T, uint32_t AMODE, int MIDK>
 static hipError_t launch_cfg(bool sync, uint32_t n_blocks, hipStream_t stream, const ChainArgs& a) {
     if (sync)
@@ -117,6 +121,9 @@ static hipError_t launch_family(int tile, bool sync, uint32_t n_blocks, hipStrea
         case 11: return launch_cfg<Cfg64x192, T, AMODE, MIDK>(sync, n_blocks, stream, a);
         case 12: return launch_cfg<Cfg128x192Deep, T, AMODE, MIDK>(sync, n_blocks, stream, a);
         case 13: return launch_cfg<Cfg128x128Deep, T, AMODE, MIDK>(sync, n_blocks, stream, a);
+        case TILE_64x64_TRIPLE:
+            if constexpr (MIDK != 1) return launch_cfg<Cfg64x64Triple, T, AMODE, MIDK>(sync, n_blocks, stream, a);
+            return hipErrorInvalidValue;   // (not planned: the prompt-phase attention tile does not fit its LDS)
         default: return hipErrorInvalidValue;
     }
 }

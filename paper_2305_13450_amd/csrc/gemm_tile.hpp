@@ -93,7 +93,9 @@ __device__ __forceinline__ void store_out16(void* p, V8 v) {
     if constexpr (THROUGH) {
         u32x4 bits;
         __builtin_memcpy(&bits, &v, 16);
-        asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(bits) : "memory");
+        // (the wait states a store of more than 8 bytes needs after a vector instruction has written its
+        // data registers, and before one overwrites them, are not inserted for an asm statement: spelled out)
+        asm volatile("s_nop 1\n\tglobal_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(bits) : "memory");
     } else {
         *(V8*)p = v;
     }
@@ -592,7 +594,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
             // beside the accumulators hold (PARTS_IN_FLIGHT) are issued before the first of them
             // is added; the adds stay in K order.
             constexpr int ACCF = FM * FN * 16;                                   // accumulator floats per lane
-            constexpr int ROOM = Cfg::MINB == 1 ? (472 - ACCF < 192 ? 472 - ACCF : 192) : 216 - ACCF;
+            constexpr int ROOM = Cfg::MINB == 1 ? (472 - ACCF < 192 ? 472 - ACCF : 192) : (Cfg::MINB == 2 ? 216 : 112) - ACCF;
             constexpr int PARTS_IN_FLIGHT = ROOM / ACCF > 8 ? 8 : ROOM / ACCF;
             if constexpr (PARTS_IN_FLIGHT >= 1) {
                 constexpr int NV = FM * FN * 4;                                  // 16-byte loads per lane and part
@@ -649,61 +651,66 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     // ---- epilogue: activation, round to 16 bits, store ----
     // Accumulator layout of the 32x32 block: lane holds column (lane % 32) and rows
     // 8*(v/4) + 4*(lane/32) + v%4 for v = 0..15, i.e. a lane's values run DOWN a column.  Each
-    // wave therefore transposes its sub-tile through its own piece of the (now idle) operand
-    // staging area and writes it out as 16-byte row segments: a twelfth of the store
-    // instructions, and whole lines instead of 2-byte pieces for the write-through stores.
+    // wave therefore transposes its sub-tile, 32 rows at a time and in fp32, through its own piece of the
+    // (now idle) operand staging area, and a loop over 16-byte row segments applies the activation,
+    // rounds and stores: whole lines instead of 2-byte pieces for the write-through stores.  The loop is
+    // what keeps the code short: with the activation unrolled over the accumulators a kernel was 70 to 290
+    // KB of straight code, executed once per tile and fetched from memory each time a chain's weights
+    // had swept it out of the L2.
     __syncthreads();   // every wave has read its last operand fragments
     if (wctx.ok && finish) {
-        constexpr int PAD = (4 * Cfg::WTM * (Cfg::WTN * 2 + 16) <= Cfg::LDS_BYTES) ? 16 : 0;
-        constexpr int PITCH = Cfg::WTN * 2 + PAD;                   // bytes per sub-tile row in LDS
-        static_assert(4 * Cfg::WTM * PITCH <= Cfg::LDS_BYTES, "the transposed sub-tiles fit the staging area");
-        char* const reg = lds + wave * (Cfg::WTM * PITCH);
+        constexpr int PITCH = Cfg::WTN * 4 + 16;                    // bytes per row in LDS
+        static_assert(4 * 32 * PITCH <= Cfg::LDS_BYTES, "a block row of every wave fits the staging area");
+        char* const reg = lds + wave * (32 * PITCH);
         const uint32_t act = s.act;
-        const uint32_t colw = lane & 31u, rowh = (lane >> 5) * 4u;
         const uint32_t wtn_out = gate_up ? Cfg::WTN / 2 : Cfg::WTN;  // output columns of this wave
-        if (gate_up) {
-            if constexpr (FN >= 2) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int jp = 0; jp < FN / 2; ++jp)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const uint32_t r = i * 32 + 8 * (v / 4) + rowh + (v % 4), c = jp * 32 + colw;
-                            const float g = acc[i][2 * jp][v], u = acc[i][2 * jp + 1][v];
-                            *(T*)(reg + r * PITCH + c * 2) = (T)(silu_f(g) * u);
-                        }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const uint32_t r = i * 32 + 8 * (v / 4) + rowh + (v % 4), c = j * 32 + colw;
-                        float x = acc[i][j][v];
-                        if (act == ACT_GELU) x = gelu_erf(x);
-                        else if (act == ACT_RELU) x = fmaxf(x, 0.0f);
-                        *(T*)(reg + r * PITCH + c * 2) = (T)x;
-                    }
-        }
-        dr.grab();   // the counters read by peek() have arrived by now: start the next tile's draw
-        // the region is private to the wave: its own LDS writes are ordered before its reads
-        T* Cp = (T*)s.C;
-        const uint32_t ldc = s.ldc;
         const uint32_t cpr = wtn_out / 8;                            // 16-byte chunks per row
-        const uint32_t row0 = m0 + wm * Cfg::WTM, col0 = n0 + wn * wtn_out;
-        for (uint32_t idx = lane; idx < Cfg::WTM * cpr; idx += 64) {
-            const uint32_t r = idx / cpr, ch = idx % cpr;
-            const uint32_t row = row0 + r, col = col0 + ch * 8;
-            if (row >= sM || col >= sN) continue;
-            const V8 val = *(const V8*)(reg + r * PITCH + ch * 16);
-            T* dst = Cp + (size_t)row * ldc + col;
-            if (col + 8 <= sN) {
-                store_out16<THROUGH>(dst, val);
-            } else {
-                for (uint32_t e = 0; e < sN - col; ++e) store_out<THROUGH>(dst + e, (T)val[e]);
+        const uint32_t col0 = n0 + wn * wtn_out;
+        const uint32_t r_first = lane / cpr, ch_first = lane % cpr, r_step = 64 / cpr, ch_step = 64 % cpr;
+        T* const Cp = (T*)s.C;
+        const uint32_t ldc = s.ldc;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            // the region is private to the wave: its own LDS writes are ordered before its reads
+            char* const w = reg + ((lane >> 5) * 4u) * PITCH + (lane & 31u) * 4u;
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) *(float*)(w + (8 * (v / 4) + (v % 4)) * PITCH + j * 128) = acc[i][j][v];
+            if (i == 0) dr.grab();   // the counters read by peek() have arrived by now: start the next tile's draw
+            const uint32_t row0 = m0 + wm * Cfg::WTM + i * 32;
+            const uint32_t rows = row0 < sM ? min(sM - row0, 32u) : 0u;
+            uint32_t r = r_first, ch = ch_first;
+#pragma unroll 1
+            for (; r < rows; r += r_step, ch += ch_step) {
+                if (ch >= cpr) { ch -= cpr; if (++r >= rows) break; }
+                const uint32_t col = col0 + ch * 8;
+                if (col >= sN) continue;
+                float x[8];
+                // gate and up columns alternate in blocks of 32
+                const char* src = reg + r * PITCH + (gate_up ? (ch >> 2) * 256 + (ch & 3u) * 32 : ch * 32);
+                __builtin_memcpy(x, __builtin_assume_aligned(src, 16), 32);
+                if (gate_up) {
+                    float u[8];
+                    __builtin_memcpy(u, __builtin_assume_aligned(src + 128, 16), 32);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = silu_f(x[e]) * u[e];
+                } else if (act == ACT_GELU) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = gelu_erf(x[e]);
+                } else if (act == ACT_RELU) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = fmaxf(x[e], 0.0f);
+                }
+                V8 val;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) val[e] = (T)x[e];
+                T* dst = Cp + (size_t)(row0 + r) * ldc + col;
+                if (col + 8 <= sN) {
+                    store_out16<THROUGH>(dst, val);
+                } else {
+                    for (uint32_t e = 0; e < sN - col; ++e) store_out<THROUGH>(dst + e, (T)val[e]);
+                }
             }
         }
     }

@@ -11,7 +11,11 @@ struct TileShape {
     int wave_cols;        // columns of one wave's sub-tile (gate/up fusion needs a multiple of 64)
 };
 
-// nullptr for ids outside [1, 13].
+// Shapes the library uses beside the public DEPSYNC_TILE_* ids: 64x64 with three stages, three workgroups per CU
+// (chosen by the planner, reported as DEPSYNC_TILE_64x64; not for chains with prompt-phase attention).
+constexpr int TILE_64x64_TRIPLE = 14;
+
+// nullptr for ids outside [1, TILE_64x64_TRIPLE].
 const TileShape* tile_shape(int tile);
 
 // Launch n_blocks workgroups of the chain kernel for macro-tile `tile`, element type `dtype`

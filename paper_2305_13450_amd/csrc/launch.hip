@@ -141,8 +141,9 @@ const TileShape* tile_shape(int tile) {
         {64, 192, 1, 96},
         {128, 192, 1, 96},
         {128, 128, 1, 64},
+        {64, 64, 3, 32},
     };
-    if (tile < 1 || tile > 13) return nullptr;
+    if (tile < 1 || tile > TILE_64x64_TRIPLE) return nullptr;
     return &shapes[tile];
 }
 
