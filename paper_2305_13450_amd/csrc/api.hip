@@ -330,12 +330,22 @@ void fit_triple(Plan& p, const sync_policy* pol, bool tuned_off, const uint32_t 
 // Would every tile of the chain, unsplit, have a workgroup of the three-per-CU shape resident at once?  Then that
 // shape is the fastest measured (1 to 400 tokens of seven pairs of layers, token generation, convolutions of images
 // of 7 to 60 pixels: 0.6 to 1 of the time of the shape chosen by the model below); beyond that its 64 x 64 tiles
-// move too many bytes per flop (12288 x 6144 x 12288 at 192 tokens: 175 against 135 us).
-bool triple_fits(const std::array<uint32_t, 4>& cols, uint32_t M, int n_stages, uint32_t other_tiles, int cus) {
+// move too many bytes per flop (12288 x 6144 x 12288 at 192 tokens: 175 against 135 us).  Not where a stage ends up with
+// long parts on half of the CUs or fewer: its weights then stream through two steps of 16 KB per part, and a
+// deeper pipeline is ahead (8192 x 2752 x 8192, whose 43 K steps do not divide, at one token 39.8 against 34.3 us).
+// cols, kt: output columns and K steps of the GeMM stages; other_tiles: tiles of an attention stage.
+bool triple_fits(const std::array<uint32_t, 4>& cols, const std::array<uint32_t, 4>& kt, uint32_t M, int n, uint32_t other_tiles, int cus) {
     const TileShape* ts = tile_shape(TILE_64x64_TRIPLE);
-    uint64_t tiles = other_tiles;
-    for (int s = 0; s < n_stages; ++s) tiles += (uint64_t)cdiv(cols[s], ts->cols) * cdiv(M, ts->rows);
-    return tiles <= (uint64_t)cus * ts->occupancy;
+    const uint32_t slots = (uint32_t)(cus * ts->occupancy);
+    uint64_t total = other_tiles;
+    for (int s = 0; s < n; ++s) {
+        const uint64_t tiles = (uint64_t)cdiv(cols[s], ts->cols) * cdiv(M, ts->rows);
+        total += tiles;
+        if (total > slots) return false;
+        const uint32_t S = choose_split(nullptr, false, (uint32_t)tiles, slots / (uint32_t)(n + (other_tiles ? 1 : 0)), kt[s], 1, 12u);
+        if (2 * tiles * S <= (uint64_t)cus && kt[s] / S > 32) return false;
+    }
+    return true;
 }
 
 // Do the 64x192 tiles of a stage split into (nearly) as many equal parts as there are CUs?  Where both stages of a
@@ -430,7 +440,8 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     // (whether StridedSync divides the producer's columns depends on the tile: what it accepts stays as it is)
     const bool by_stride = !attn && effective_kind(d, pol, pol ? default_kind(d) : DEPSYNC_ROWSYNC) == DEPSYNC_STRIDEDSYNC;
     if (!tile && !gate_up && !by_stride && (!attn || d->seq == 1) &&
-        triple_fits({(uint32_t)d->N1, (uint32_t)d->N2, 0, 0}, d->M, 2, attn ? (uint32_t)d->batch * d->heads : 0u, cus))
+        triple_fits({(uint32_t)d->N1, (uint32_t)d->N2, 0, 0}, {(uint32_t)d->K1 / 64, K2 / 64, 0, 0}, d->M, 2,
+                    attn ? (uint32_t)d->batch * d->heads : 0u, cus))
         tile = (!attn && d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) ? DEPSYNC_TILE_64x192
                                                                                                               : TILE_64x64_TRIPLE;
     if (!tile) tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0);
@@ -600,8 +611,11 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
-    if (!tile && triple_fits({(uint32_t)d->K[0], (uint32_t)d->K[1], n > 2 ? (uint32_t)d->K[2] : 0u, n > 3 ? (uint32_t)d->K[3] : 0u}, M, n, 0, cus))
-        tile = TILE_64x64_TRIPLE;
+    if (!tile) {
+        std::array<uint32_t, 4> cols{}, kt{};
+        for (int i = 0; i < n; ++i) { cols[i] = (uint32_t)d->K[i]; kt[i] = 9u * cin[i] / 64; }
+        if (triple_fits(cols, kt, M, n, 0, cus)) tile = TILE_64x64_TRIPLE;
+    }
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
         tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, 1);
