@@ -908,6 +908,13 @@ int launch_chain(sync_policy* pol, const Plan& p, ChainArgs& a, depsync_mode mod
     bool mixed = false;   // stages of differing macro-tile shapes: one launch (one kernel) per stage
     for (int s = 1; s < p.n_stages; ++s) mixed = mixed || p.tile[s] != p.tile[0];
     const bool all_resident = !mixed && total <= (uint32_t)p.slots;
+    // Two streams where the earlier stages' tiles all fit on the chip at once: the launch on the caller's stream draws
+    // them all before it turns to its own stage, and side launches would only take its slots away and
+    // draw by compare-and-swap against it.  They are left out (as the paper leaves out its wait kernel when both kernels
+    // fit the GPU together, Section IV-C), and what remains is the one-dispatch form: 333 tokens of
+    // the 12288 x 6144 x 12288 chain (192 producer parts, 256 slots) 198 -> 168 us.
+    if (mode == DEPSYNC_MODE_FINE && pol->ev_fork && !mixed && !caller_hw && total - p.n_tiles[p.n_stages - 1] <= (uint32_t)p.slots)
+        mode = DEPSYNC_MODE_FUSED;
     if (pol->force_order == 1 && !all_resident && !caller_hw) return DEPSYNC_EINVAL;   // not a candidate for the autotuner
     bool hw;
     if (pol->force_order >= 0) hw = pol->force_order == 1;
@@ -966,16 +973,10 @@ int launch_chain(sync_policy* pol, const Plan& p, ChainArgs& a, depsync_mode mod
             pol->launches += 1;
             return DEPSYNC_OK;
         }
-        // When the last stage's launch has a workgroup of its own for every tile of the chain, all
-        // of them resident at once, a side launch could only ever find its tiles taken (it starts
-        // when the event has crossed streams, later than the caller's launch): it is left out, as
-        // the paper leaves out its wait kernel when both kernels fit the GPU together (Section IV-C).
-        const bool side_useful = !(queues && total <= (uint32_t)p.slots);
-        if (side_useful) HIP_TRY(hipEventRecord(pol->ev_fork, sp));
+        HIP_TRY(hipEventRecord(pol->ev_fork, sp));
         uint32_t off = 0;
         for (int s = 0; s < p.n_stages; ++s) {
             hipStream_t st = s == last ? sp : side[s];
-            if (s != last && !side_useful) { off += p.n_tiles[s]; continue; }
             if (s != last) HIP_TRY(hipStreamWaitEvent(st, pol->ev_fork, 0));
             // (drawing from the queues, the last stage's launch covers the whole chain from its first
             // block on, so its first blocks go straight for the first stage's queues)
@@ -992,7 +993,7 @@ int launch_chain(sync_policy* pol, const Plan& p, ChainArgs& a, depsync_mode mod
             off += p.n_tiles[s];
         }
         a.draw_cas = 0u;
-        if (side_useful) pol->side_used = true;
+        pol->side_used = true;
     } else {
         uint32_t off = 0;
         for (int s = 0; s < p.n_stages; ++s) {   // one launch per stage on the caller's stream
