@@ -70,7 +70,9 @@ typedef enum {
 
 /* How the two kernels of a chain are ordered. */
 typedef enum {
-    DEPSYNC_MODE_FINE = 0,       /* two streams, per-tile semaphores (the paper's method)  */
+    DEPSYNC_MODE_FINE = 0,       /* two streams, per-tile semaphores (the paper's method); one
+                                    dispatch on stream_producer where the tiles of all stages before
+                                    the last fit on the GPU at once                          */
     DEPSYNC_MODE_STREAMSYNC = 1, /* the same kernels on one stream (the paper's baseline)  */
     DEPSYNC_MODE_PLAIN = 2,      /* the same tile code with the sync hooks compiled out,
                                     one stream, hardware block order                        */
