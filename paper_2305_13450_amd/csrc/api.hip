@@ -1601,12 +1601,54 @@ int static_policy(hipStream_t st, sync_policy** out) {
     return DEPSYNC_OK;
 }
 
+// Tiles (head, query block, part of the keys) of an attention stage that read a row of the QKV tensor
+// whose producer tiles they have not waited for.
+int64_t uncovered_attn_waits(const StageDesc& st, uint32_t n_sems) {
+    int64_t bad = 0;
+    std::vector<uint8_t> waited(n_sems);
+    for (uint32_t head = 0; head < st.heads; ++head)
+        for (uint32_t tyz = 0; tyz < st.grid_y * st.ksplit; ++tyz) {
+            AttnSpan t;
+            std::memset(&t, 0, sizeof(t));
+            if (st.seq > 1) {
+                t = attn_span(tyz, st.ksplit, st.seq, st.cached);
+                if (t.part >= t.nparts) continue;                   // reads nothing
+            } else {
+                t.seq_row0 = tyz / st.ksplit;                       // token generation: one row
+            }
+            std::fill(waited.begin(), waited.end(), 0);
+            attn_for_each_wait(st, head, t.seq_row0, t.seq_row0 + t.q_last, [&](uint32_t x, uint32_t y) {
+                waited[policy_sem(st.dep_kind, x, y, st.prod_grid_y, st.stride)] = 1;
+            });
+            bool ok = true;
+            auto need = [&](uint32_t row, uint32_t b) {             // b: 0 Q, 1 K, 2 V
+                const uint32_t y = (t.seq_row0 + row) / st.prod_tm, c0 = b * st.heads * ATT_D + head * ATT_D;
+                for (uint32_t x = c0 / st.prod_tn; x <= (c0 + ATT_D - 1) / st.prod_tn; ++x)
+                    if (x >= st.prod_grid_x || y >= st.prod_grid_y || !waited[policy_sem(st.dep_kind, x, y, st.prod_grid_y, st.stride)]) ok = false;
+            };
+            for (uint32_t q = t.q0; q <= t.q_last; ++q) need(q, 0);
+            if (st.seq == 1) { need(0, 1); need(0, 2); }
+            else
+                for (uint32_t kb = t.kb_begin; kb < t.kb_end; ++kb) {
+                    const uint32_t k0 = kb * ATT_BK;
+                    const bool run = attn_block_in_one_run(k0, st.cached, t.q_last);
+                    for (uint32_t key = std::max(k0, st.cached); key < k0 + ATT_BK; ++key) {
+                        const uint32_t row = run ? key - st.cached : attn_key_row(key, st.cached, t.q_last);
+                        need(row, 1); need(row, 2);
+                    }
+                }
+            if (!ok) ++bad;
+        }
+    return bad;
+}
+
 // Consumer tiles (row tile, K part) of stage s whose operand slices are not all covered by a
 // wait issued at or before the K step that loads them.
 int64_t uncovered_waits(const Plan& p, const ChainArgs& a, int s) {
     const StageDesc& st = a.st[s];
     const TileShape* ts = tile_shape(p.tile[s]);
-    if (!ts || st.dep_kind == DEP_NONE || st.op != OP_GEMM) return 0;
+    if (!ts || st.dep_kind == DEP_NONE) return 0;
+    if (st.op == OP_ATTN) return uncovered_attn_waits(st, p.sem_count[s]);
     const uint32_t TM = (uint32_t)ts->rows;
     const uint32_t KT = st.K / 64, S = st.ksplit;
     const uint32_t seg_steps = dep_seg_steps(st);

@@ -26,9 +26,6 @@
 
 namespace depsync {
 
-constexpr int ATT_BQ = 128;      // query rows per tile (32 per wave)
-constexpr int ATT_BK = 64;       // keys per block
-constexpr int ATT_D = 128;       // head dimension
 constexpr int ATT_BLK_BYTES = ATT_BK * ATT_D * 2;       // one block of K or V rows (16 KB)
 constexpr int ATT_LDS_BYTES = 4 * ATT_BLK_BYTES;        // rings of at least two K and two V blocks
 
@@ -54,44 +51,25 @@ template <> struct TrRead<_Float16> {
     }
 };
 
-// Wait for everything an attention tile reads from the QKV GeMM: producer row tiles y0..y1,
-// and in each the column tiles holding this head's Q, K and V columns.
+// Wait for everything an attention tile reads from the QKV GeMM: rows row_first .. row_last, in this
+// head's Q, K and V columns.
 template <bool SYNC>
 __device__ __forceinline__ void attn_wait_qkv(WaitCtx& w, const StageDesc& s, uint32_t head, uint32_t row_first,
                                               uint32_t row_last) {
     if (!SYNC || s.dep_kind == DEP_NONE) return;
-    const uint32_t E = s.heads * ATT_D;
-    const uint32_t y0 = row_first / s.prod_tm, y1 = row_last / s.prod_tm;
     const uint32_t target = s.sem_target_base + s.sem_value;
-    for (uint32_t y = y0; y <= y1; ++y) {
-        if (s.dep_kind == DEP_ROW) {
-            const uint32_t* sem = s.sems + y * SYNC_WORD_STRIDE;
-            uint32_t v = sem_load(sem);
-            const bool polled = !sem_reached(v, target);
-            if (polled) sem_wait(w, sem, target, v);
-            count_wait(*w.args, polled);
-            continue;
-        }
-        const uint32_t nblk = (s.dep_kind == DEP_STRIDED) ? 1u : 3u;   // strided: Q, K, V share a semaphore
-        for (uint32_t b = 0; b < nblk; ++b) {
-            const uint32_t c0 = b * E + head * ATT_D;
-            for (uint32_t x = c0 / s.prod_tn; x <= (c0 + ATT_D - 1) / s.prod_tn; ++x) {
-                const uint32_t* sem = s.sems + policy_sem(s.dep_kind, x, y, s.prod_grid_y, s.stride) * SYNC_WORD_STRIDE;
-                uint32_t v = sem_load(sem);
-                const bool polled = !sem_reached(v, target);
-                if (polled) sem_wait(w, sem, target, v);
-                count_wait(*w.args, polled);
-            }
-        }
-    }
+    attn_for_each_wait(s, head, row_first, row_last, [&](uint32_t x, uint32_t y) __attribute__((always_inline)) {
+        const uint32_t* sem = s.sems + policy_sem(s.dep_kind, x, y, s.prod_grid_y, s.stride) * SYNC_WORD_STRIDE;
+        const uint32_t v = sem_load(sem);
+        const bool polled = !sem_reached(v, target);
+        if (polled) sem_wait(w, sem, target, v);
+        count_wait(*w.args, polled);
+    });
 }
 
 // Floats one part of a tile split along the keys leaves in the scratch buffer: the un-normalised
 // O^T accumulators of the 256 lanes (64 each), then every lane's running maximum and sum.
 constexpr uint32_t ATT_PART_FLOATS = 256 * 64 + 2 * 256;
-// Key blocks per part when a tile's keys are split over workgroups (at least this many: a part
-// re-reads the queries and leaves 65 KB of partial results).
-constexpr uint32_t ATT_MIN_PART_BLOCKS = 4;
 
 // What bounds it: the longest tiles of a causal stage are one serial chain of key blocks, walked by one
 // wave per SIMD: per block 36 MFMAs (0.5 us), 32 scores per lane through exp2 and conversion (as
@@ -122,16 +100,15 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
     // counts itself in; the last part to arrive combines the parts in key order, normalises,
     // stores and posts.  Tiles of few key blocks use fewer parts (the rest find nothing to do).
     const uint32_t KS = uni(s.ksplit);
-    const uint32_t qblk = tyz / KS, part = tyz % KS;
-    const uint32_t qblocks = (seq + ATT_BQ - 1) / ATT_BQ;
-    const uint32_t b = qblk / qblocks, qb = qblk % qblocks;      // sequence, query block inside it
-    const uint32_t seq_row0 = b * seq;                            // first row of the sequence
-    const uint32_t q0 = qb * ATT_BQ;                              // first query (inside the sequence)
-    const uint32_t q_last = min(q0 + ATT_BQ, seq) - 1;
+    // cached keys and values of this sequence come first in key order
+    const uint32_t cached = uni(s.cached), ldkv = uni(s.ld_cache);
+    const AttnSpan span = attn_span(tyz, KS, seq, cached);
+    const uint32_t qblk = span.qblk, part = span.part, nparts = span.nparts;
+    const uint32_t seq_row0 = span.seq_row0, b = seq_row0 / seq;  // first row of the sequence, sequence
+    const uint32_t q0 = span.q0, q_last = span.q_last;            // first and last query (inside the sequence)
+    const uint32_t kb_begin = span.kb_begin, kb_end = span.kb_end;
     const T* QKV = (const T*)uni_ptr(s.A);
     T* Tout = (T*)uni_ptr(s.C);
-    // cached keys and values of this sequence come first in key order (token generation)
-    const uint32_t cached = uni(s.cached), ldkv = uni(s.ld_cache);
     const T* Kc = (const T*)uni_ptr(s.kcache);
     const T* Vc = (const T*)uni_ptr(s.vcache);
 
@@ -140,10 +117,6 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
     uint64_t t_start = 0, t_ready = 0;
     if (tracing) t_start = now_ticks();
 
-    const uint32_t nblk = (cached + q_last) / ATT_BK + 1;         // key blocks the tile touches
-    const uint32_t chunk = max((nblk + KS - 1) / KS, ATT_MIN_PART_BLOCKS);   // key blocks per part
-    const uint32_t nparts = (nblk + chunk - 1) / chunk;           // parts that have any (<= KS)
-    const uint32_t kb_begin = part * chunk, kb_end = min(nblk, kb_begin + chunk);
     if (part >= nparts) {                                          // nothing for this part: the tile is short
         if (tracing && tid == 0) {
             TraceRec r;
@@ -197,7 +170,7 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
     auto fetch = [&](uint32_t kb, bool v) __attribute__((always_inline)) {
         char* dst = (v ? ldsV : ldsK) + (kb % NBUF) * ATT_BLK_BYTES + wave * 1024;
         const uint32_t k0 = kb * ATT_BK, fc = v ? fcv : fck;      // position in key order: cache first
-        if (k0 + ATT_BK <= cached || (k0 >= cached && k0 + ATT_BK <= cached + seq)) {   // a block of one source, whole
+        if (attn_block_in_one_run(k0, cached, q_last)) {
             const bool in_cache = k0 < cached;
             const char* g = in_cache ? (const char*)((v ? Vc : Kc) + ((size_t)b * cached + k0) * ldkv + head * ATT_D)
                                      : (const char*)(QKV + (size_t)(seq_row0 + k0 - cached) * ld + (v ? 2 * E : E) + head * ATT_D);
@@ -211,7 +184,7 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
                 const bool c = key < cached;
                 const char* base = c ? (const char*)((v ? Vc : Kc) + (size_t)b * cached * ldkv + head * ATT_D)
                                      : (const char*)(QKV + (size_t)seq_row0 * ld + (v ? 2 * E : E) + head * ATT_D);
-                const char* g = base + (uint64_t)(c ? key : min(key - cached, seq - 1)) * (2u * (c ? ldkv : ld));
+                const char* g = base + (uint64_t)(c ? key : attn_key_row(key, cached, q_last)) * (2u * (c ? ldkv : ld));
                 dma16(g + fc, dst + i * 4096);
             }
         }

@@ -103,4 +103,66 @@ __host__ __device__ __forceinline__ bool dep_segment(const StageDesc& s, uint32_
     }
 }
 
+// ---- the prompt-phase attention tile: which rows it covers, waits for and reads -------------------
+
+constexpr int ATT_BQ = 128;      // query rows per tile (32 per wave)
+constexpr int ATT_BK = 64;       // keys per block
+constexpr int ATT_D = 128;       // head dimension
+// Key blocks per part when a tile's keys are split over workgroups (at least this many: a part
+// re-reads the queries and leaves 65 KB of partial results).
+constexpr uint32_t ATT_MIN_PART_BLOCKS = 4;
+
+// Dispatch row tyz of the stage: part `part` of the keys of query block q0 .. q_last (positions inside
+// the sequence, whose rows of the QKV tensor start at seq_row0).  Its key blocks are kb_begin .. kb_end - 1, in
+// key order: the cached keys first, then the new tokens.
+struct AttnSpan {
+    uint32_t qblk, part, nparts;
+    uint32_t seq_row0, q0, q_last;
+    uint32_t kb_begin, kb_end;
+};
+__host__ __device__ __forceinline__ AttnSpan attn_span(uint32_t tyz, uint32_t ksplit, uint32_t seq, uint32_t cached) {
+    AttnSpan t;
+    t.qblk = tyz / ksplit; t.part = tyz % ksplit;
+    const uint32_t qblocks = (seq + ATT_BQ - 1) / ATT_BQ;
+    t.seq_row0 = t.qblk / qblocks * seq;
+    t.q0 = t.qblk % qblocks * ATT_BQ;
+    t.q_last = dm_min(t.q0 + ATT_BQ, seq) - 1;
+    const uint32_t nblk = (cached + t.q_last) / ATT_BK + 1;                // key blocks the query block sees
+    uint32_t chunk = (nblk + ksplit - 1) / ksplit;                         // key blocks per part
+    if (chunk < ATT_MIN_PART_BLOCKS) chunk = ATT_MIN_PART_BLOCKS;
+    t.nparts = (nblk + chunk - 1) / chunk;                                 // parts that have any (<= ksplit)
+    t.kb_begin = t.part * chunk;
+    t.kb_end = dm_min(nblk, t.kb_begin + chunk);
+    return t;
+}
+
+// Producer tiles (x, y) of the QKV GeMM a tile waits for: row tiles y of the sequence's rows up to its last query,
+// and in each the column tiles with this head's Q, K and V columns (x = 0 where a whole row shares a semaphore).
+template <class F>
+__host__ __device__ __forceinline__ void attn_for_each_wait(const StageDesc& s, uint32_t head, uint32_t row_first, uint32_t row_last, F&& f) {
+    const uint32_t E = s.heads * ATT_D;
+    for (uint32_t y = row_first / s.prod_tm; y <= row_last / s.prod_tm; ++y) {
+        if (s.dep_kind == DEP_ROW) { f(0u, y); continue; }
+        const uint32_t nblk = (s.dep_kind == DEP_STRIDED) ? 1u : 3u;       // strided: Q, K, V share a semaphore
+        for (uint32_t b = 0; b < nblk; ++b) {
+            const uint32_t c0 = b * E + head * ATT_D;
+            for (uint32_t x = c0 / s.prod_tn; x <= (c0 + ATT_D - 1) / s.prod_tn; ++x) f(x, y);
+        }
+    }
+}
+
+// A key block is read whole, also where it runs past the tile's last query (a cache whose length is no
+// multiple of 64 shifts the blocks against the rows).  What lies past that query is masked, and its rows belong to
+// producer tiles nobody has waited for: the weight 0 does not make up for whatever they hold (0 x NaN), and a line
+// read before its producer has posted would stay in this XCD's L2 for the tiles that read it later.  So those
+// positions read the last query's row again.
+// All 64 positions from k0 on are rows of one source, in a run:
+__host__ __device__ __forceinline__ bool attn_block_in_one_run(uint32_t k0, uint32_t cached, uint32_t q_last) {
+    return k0 + ATT_BK <= cached || (k0 >= cached && k0 + ATT_BK <= cached + q_last + 1);
+}
+// Row, inside the sequence, of the new token read for position key >= cached:
+__host__ __device__ __forceinline__ uint32_t attn_key_row(uint32_t key, uint32_t cached, uint32_t q_last) {
+    return dm_min(key - cached, q_last);
+}
+
 }  // namespace depsync

@@ -7,7 +7,7 @@ import torch
 import inputs
 import oracle
 import paper_2305_13450_amd as ds
-from gpu_util import TOL_BF16, row_err, run_attn_chain
+from gpu_util import TOL_BF16, TOL_FP16, row_err, run_attn_chain
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +45,31 @@ def test_rows_whatever_the_scores(shape, seq, tile, dtype):
         pol.destroy()
         ref = oracle.causal_attention(inputs.to_f64(QKV.cpu()), 1, seq, heads, 128)
         assert row_err(T, ref) <= TOL_BF16
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, TOL_BF16), (torch.float16, TOL_FP16)])
+@pytest.mark.parametrize("tile", [ds.TILE_AUTO, ds.TILE_64x64, ds.TILE_128x192, ds.TILE_128x192_DEEP])
+@pytest.mark.parametrize("seq,cached", [(300, 700), (300, 77), (257, 63), (640, 1)])
+def test_cache_ends_inside_a_key_block(seq, cached, tile, dtype, tol):
+    # A tile's last key block runs past its last query into rows it has not waited for.  They are masked,
+    # but 0 x NaN is NaN, and a line read before its producer has posted would be stale for the next
+    # query block: buffers start as NaN, are used again with other inputs, and a producer tile of the
+    # second row tile posts late.
+    heads = 2
+    grid_x = -(-3 * heads * 128 // ds.tile_shape(tile)[1]) if tile else 4
+    kv = inputs.kv_cache(1, cached, heads, 128, seed=cached, dtype=dtype)
+    Kc, Vc = kv["Kc"].cuda(), kv["Vc"].cuda()
+    print(f"cache end seq={seq} cached={cached} tile={tile} {dtype}", flush=True)
+    QKV, T, Y = (torch.full((seq, n), float("nan"), dtype=dtype, device="cuda") for n in (3 * heads * 128, heads * 128, 64))
+    for split in (1, 0):
+        pol = ds.SyncPolicy(ds.TILESYNC, ksplit=split, delay_tile=2 * grid_x, delay_iters=20000)
+        for seed in (1, 2):
+            t = inputs.attention(seq, 256, heads, 128, 64, seed=seed, dtype=dtype)
+            ds.dep_gemm_chain(t["X"].cuda(), t["Wqkv"].t().contiguous().cuda(), QKV, t["Wo"].t().contiguous().cuda(), Y, pol,
+                              mode=ds.MODE_FUSED, mid=ds.MID_CAUSAL_ATTN, tile=tile, T=T, batch=1, seq=seq, heads=heads,
+                              head_dim=128, k_cache=Kc, v_cache=Vc)
+            torch.cuda.synchronize()
+            ref = oracle.cached_attention(inputs.to_f64(QKV.cpu()), inputs.to_f64(kv["Kc"]), inputs.to_f64(kv["Vc"]), 1, seq, heads, 128)
+            assert row_err(T, ref) <= tol
+        assert pol.status().timed_out == 0
+        pol.destroy()

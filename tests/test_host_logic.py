@@ -224,6 +224,26 @@ def test_every_slice_a_consumer_tile_loads_is_covered_by_a_wait(kind):
     assert checked > 100
 
 
+@pytest.mark.parametrize("kind", [ds.ROWSYNC, ds.TILESYNC, ds.STRIDEDSYNC])
+def test_every_row_an_attention_tile_reads_is_covered_by_a_wait(kind):
+    # A tile reads its keys in blocks of 64 that start at the cache, so with a cache whose length is no
+    # multiple of 64 the last block reaches past the tile's last query, into rows of a producer tile
+    # it has not waited for: those positions must not be read.
+    checked = 0
+    for tile in [ds.TILE_AUTO] + ALL_TILES:
+        for batch, seq, cached in ((1, 300, 700), (1, 300, 77), (1, 1000, 1), (1, 1024, 1023), (1, 640, 0), (2, 256, 100), (2, 100, 63),
+                                   (1, 129, 65), (1, 16, 1500), (3, 1, 77)):
+            for ksplit in (0, 1, 3):
+                heads = 3
+                d = _fake_gemm_desc(batch * seq, 128, 3 * heads * 128, 128, mid=ds.MID_CAUSAL_ATTN, tile=tile)
+                d.T, d.ldt, d.ldw2 = 0x1000, heads * 128, heads * 128
+                d.batch, d.seq, d.heads, d.head_dim = batch, seq, heads, 128
+                d.cached, d.k_cache, d.v_cache, d.ld_cache = cached, 0x1000, 0x1000, heads * 128
+                assert ds.gemm_chain_check_waits(d, kind, n_cu=256, ksplit=ksplit) == 0, (tile, batch, seq, cached, ksplit)
+                checked += 1
+    assert checked == 14 * 10 * 3
+
+
 def test_producer_and_consumer_may_use_different_tile_shapes():
     # Section III-C: the consumer maps its rows and K steps onto the PRODUCER's tiles, so the two
     # stages need not share a macro-tile shape.  Grids, slots and waves follow each stage's own shape.
