@@ -86,20 +86,6 @@ __device__ __forceinline__ void store_out(T* p, T v) {
         *p = v;
     }
 }
-// Store eight consecutive 16-bit output elements (16-byte aligned).
-template <bool THROUGH, typename V8>
-__device__ __forceinline__ void store_out16(void* p, V8 v) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    if constexpr (THROUGH) {
-        u32x4 bits;
-        __builtin_memcpy(&bits, &v, 16);
-        // (the wait states a store of more than 8 bytes needs after a vector instruction has written its
-        // data registers, and before one overwrites them, are not inserted for an asm statement: spelled out)
-        asm volatile("s_nop 1\n\tglobal_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(bits) : "memory");
-    } else {
-        *(V8*)p = v;
-    }
-}
 // GeLU x * Phi(x) with Phi written through erfc: Phi(x) = erfc(-x / sqrt 2) / 2, and for z >= 0
 // erfc(z) = t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) exp(-z^2), t = 1 / (1 + p z), to 1.5e-7
 // absolute (Abramowitz and Stegun 7.1.26).  Working from erfc on the negative side keeps the
@@ -137,15 +123,6 @@ __device__ __forceinline__ void dep_wait(WaitCtx& w, const StageDesc& s, const D
 }
 
 // ---- the tile ------------------------------------------------------------------------------
-
-// A wave-uniform value pinned into scalar registers (so that the compiler keeps it there
-// instead of re-reading kernel arguments inside the K loop).
-__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ const char* uni_ptr(const void* p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint64_t lo = uni((uint32_t)v), hi = uni((uint32_t)(v >> 32));
-    return reinterpret_cast<const char*>(lo | (hi << 32));
-}
 
 // DEP != 0: this tile's A operand is produced by the previous stage of the chain (the tile waits
 // on semaphores before it requests a slice of A).  DEP == 1: everything it depends on is waited
@@ -432,7 +409,6 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
             // next slice (the fragments the next slice needs first go first), DMA instructions at
             // the start of a group.  The empty asm that reads the current slice's fragments is where
             // the compiler's wait for them lands, before anything of this slice is issued.
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
             for (int i = 0; i < FM; ++i) asm volatile("" ::"v"(__builtin_bit_cast(u32x4, af[buf][i])));
 #pragma unroll
@@ -544,21 +520,19 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     if (S > 1) {
         typedef float f32x4 __attribute__((ext_vector_type(4)));
         const uint32_t tile_lin = ty * s.grid_x + tx;
-        float* const part = s.partials + (size_t)tile_lin * S * (TM * TN);
+        const float* const part = reinterpret_cast<const float*>(uni_ptr(s.partials + (size_t)tile_lin * S * (TM * TN)));
         // fragment order: each lane stores 16 bytes next to its neighbours' (1 KB per instruction),
         // written through to memory so that the count below can follow without a write-back
         // of this XCD's whole L2
+        const ThroughBuf mine(reinterpret_cast<const char*>(part + (size_t)kz * (TM * TN)));
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    f32x4 v4 = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    float* dst = part + (size_t)kz * (TM * TN) + ((((i * FN + j) * 4 + q) * 256 + tid) << 2);
-                    // (the wait states a store of more than 8 bytes needs after a vector instruction has
-                    // written its data registers are not inserted for an asm statement: spelled out)
-                    asm volatile("s_nop 1\n\tglobal_store_dwordx4 %0, %1, off sc1" ::"v"(dst), "v"(v4) : "memory");
+                    const f32x4 v4 = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                    mine.store16(tid * 16u, ((i * FN + j) * 4 + q) * 4096, __builtin_bit_cast(u32x4, v4));
                 }
         // the partial is in memory before the count moves (every wave's stores, then the barrier)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -667,8 +641,9 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         const uint32_t cpr = wtn_out / 8;                            // 16-byte chunks per row
         const uint32_t col0 = n0 + wn * wtn_out;
         const uint32_t r_first = lane / cpr, ch_first = lane % cpr, r_step = 64 / cpr, ch_step = 64 % cpr;
-        T* const Cp = (T*)s.C;
+        T* const Cp = (T*)uni_ptr(s.C);
         const uint32_t ldc = s.ldc;
+        const ThroughBuf out(reinterpret_cast<const char*>(Cp));       // (an output is smaller than 4 GiB)
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             // the region is private to the wave: its own LDS writes are ordered before its reads
@@ -705,9 +680,11 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
                 V8 val;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) val[e] = (T)x[e];
-                T* dst = Cp + (size_t)(row0 + r) * ldc + col;
+                const uint32_t at = (row0 + r) * ldc + col;
+                T* dst = Cp + at;
                 if (col + 8 <= sN) {
-                    store_out16<THROUGH>(dst, val);
+                    if constexpr (THROUGH) out.store16(at * 2u, 0, __builtin_bit_cast(u32x4, val));
+                    else *(V8*)dst = val;
                 } else {
                     for (uint32_t e = 0; e < sN - col; ++e) store_out<THROUGH>(dst + e, (T)val[e]);
                 }

@@ -42,6 +42,7 @@ __device__ __forceinline__ void copy_tile(const ChainArgs& args, const StageDesc
     const uint32_t n = left < (uint64_t)s.K ? (uint32_t)left : s.K;
     const copy_u32x4* src = static_cast<const copy_u32x4*>(s.A) + u0;
     copy_u32x4* dst = static_cast<copy_u32x4*>(s.C) + u0;
+    const ThroughBuf out(uni_ptr(dst));                     // (a tile is smaller than 4 GiB)
     const bool through = SYNC && s.post_kind != DEP_NONE;   // a tile that posts writes through to memory
     dr.peek();
     if (wctx.ok) {
@@ -49,17 +50,15 @@ __device__ __forceinline__ void copy_tile(const ChainArgs& args, const StageDesc
         for (; i + 3 * 256 < n; i += 4 * 256) {             // four 16-byte loads in flight per lane
             const copy_u32x4 v0 = src[i], v1 = src[i + 256], v2 = src[i + 512], v3 = src[i + 768];
             if (through) {
-                asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(dst + i), "v"(v0) : "memory");
-                asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(dst + i + 256), "v"(v1) : "memory");
-                asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(dst + i + 512), "v"(v2) : "memory");
-                asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(dst + i + 768), "v"(v3) : "memory");
+                out.store16(i * 16u, 0, v0); out.store16(i * 16u, 4096, v1);
+                out.store16(i * 16u, 8192, v2); out.store16(i * 16u, 12288, v3);
             } else {
                 dst[i] = v0; dst[i + 256] = v1; dst[i + 512] = v2; dst[i + 768] = v3;
             }
         }
         for (; i < n; i += 256) {
             const copy_u32x4 v = src[i];
-            if (through) asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(dst + i), "v"(v) : "memory");
+            if (through) out.store16(i * 16u, 0, v);
             else dst[i] = v;
         }
     }

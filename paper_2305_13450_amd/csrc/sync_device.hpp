@@ -30,6 +30,29 @@ namespace depsync {
 #define DS_FLAG_HW_ORDER 8u
 #define DS_FLAG_TRACE 16u
 
+// A wave-uniform value pinned into scalar registers (so that the compiler keeps it there
+// instead of re-reading kernel arguments inside the K loop).
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ const char* uni_ptr(const void* p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint64_t lo = uni((uint32_t)v), hi = uni((uint32_t)(v >> 32));
+    return reinterpret_cast<const char*>(lo | (hi << 32));
+}
+
+// Write-through stores of 16 bytes, `off` bytes from a wave-uniform base.  There is no 16-byte atomic store to ask
+// for, so this is a buffer store with the scope bit (sc1) set: an instruction the compiler knows.  Written as inline
+// asm it would keep none of the wait states around it that the hardware needs and the compiler otherwise counts, such
+// as two between a store of more than 8 bytes and the next vector write of its data registers.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct ThroughBuf {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ explicit ThroughBuf(const char* uniform_base)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc((void*)uniform_base, (short)0, -1, 0x00027000)) {}   // raw, 4 GiB
+    __device__ __forceinline__ void store16(uint32_t off, uint32_t uniform_off, u32x4 bits) const {
+        __builtin_amdgcn_raw_buffer_store_b128(bits, rsrc, off, uniform_off, 16 /* sc1 */);
+    }
+};
+
 // One look at a semaphore.  The load is a relaxed atomic; the compiler fence behind it keeps
 // every later memory operation of the wave (the requests for the tiles being waited for) behind
 // the look.  On the hardware side loads return in issue order and the wave acts on the value

@@ -384,6 +384,29 @@ def test_split_k_matches_oracle_and_does_not_depend_on_timing(ksplit, kind):
         pol.destroy()
 
 
+@pytest.mark.parametrize("tile", ALL_TILES)
+def test_split_k_moves_every_partial_sum_whole(tile):
+    # Small integers, whose sums are exact in fp32 and (below 256) in bf16: one wrong dword of a partial
+    # tile shows as a wrong whole number, in every tile shape and number of parts.
+    M, K1, N1, N2 = 300, 1536, 768, 264
+    g = torch.Generator().manual_seed(3)
+    X = (torch.rand((M, K1), generator=g) < 0.1).float() * torch.randint(-2, 3, (M, K1), generator=g)
+    W1 = torch.randint(-2, 3, (K1, N1), generator=g).float()
+    W2 = (torch.rand((N1, N2), generator=g) < 0.05).float() * torch.randint(-1, 2, (N1, N2), generator=g)
+    Href = X @ W1
+    assert Href.abs().max() < 256
+    Yref = (Href.double() @ W2.double()).to(torch.bfloat16)
+    b = [t.to(torch.bfloat16) for t in (X, W1, W2)]
+    for ksplit in (2, 3, 4):
+        print(f"exact split-K tile={tile} ksplit={ksplit}", flush=True)
+        pol = ds.SyncPolicy(ds.TILESYNC, ksplit=ksplit)
+        for mode in (ds.MODE_FUSED, ds.MODE_PLAIN):
+            H, Y = run_gemm_chain(*b, pol, mode, mid=ds.MID_NONE, tile=tile)
+            assert torch.equal(H.cpu().float(), Href) and torch.equal(Y.cpu(), Yref)
+        assert pol.status().timed_out == 0
+        pol.destroy()
+
+
 def test_split_k_is_chosen_for_skinny_chains_and_swiglu():
     # few tiles on a big chip: the library splits on its own; the gated activation is applied
     # after the partial sums are added

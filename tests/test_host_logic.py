@@ -329,6 +329,16 @@ def test_k_blocked_layout_is_validated():
     assert ds._lib().depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.EINVAL
 
 
+def test_no_memory_instruction_is_written_as_inline_assembly():
+    # The compiler keeps no wait states around an asm statement: a store of more than 8 bytes needs two before
+    # the next vector write of its data registers (a 256x256 tile split along K had one), and a load's
+    # result registers count as written at once.
+    csrc = os.path.join(ROOT, "paper_2305_13450_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        for asm in re.findall(r'asm\s+volatile\s*\(\s*((?:"[^"]*"\s*)+)', open(os.path.join(csrc, f)).read()):
+            assert not re.search(r"(global|flat|buffer|scratch|ds)_(load|store|read|write|atomic)", asm), (f, asm)
+
+
 def test_bench_refuses_more_than_one_gpu():
     # the build is single-GPU: bench.py says so and exits before it touches a device
     import subprocess
