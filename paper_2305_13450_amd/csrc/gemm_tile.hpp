@@ -520,11 +520,11 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     if (S > 1) {
         typedef float f32x4 __attribute__((ext_vector_type(4)));
         const uint32_t tile_lin = ty * s.grid_x + tx;
-        const float* const part = reinterpret_cast<const float*>(uni_ptr(s.partials + (size_t)tile_lin * S * (TM * TN)));
+        const float* const part = s.partials + (size_t)tile_lin * S * (TM * TN);
         // fragment order: each lane stores 16 bytes next to its neighbours' (1 KB per instruction),
         // written through to memory so that the count below can follow without a write-back
         // of this XCD's whole L2
-        const ThroughBuf mine(reinterpret_cast<const char*>(part + (size_t)kz * (TM * TN)));
+        const ThroughBuf mine(uni_ptr(part + (size_t)kz * (TM * TN)));
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -641,9 +641,10 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         const uint32_t cpr = wtn_out / 8;                            // 16-byte chunks per row
         const uint32_t col0 = n0 + wn * wtn_out;
         const uint32_t r_first = lane / cpr, ch_first = lane % cpr, r_step = 64 / cpr, ch_step = 64 % cpr;
-        T* const Cp = (T*)uni_ptr(s.C);
-        const uint32_t ldc = s.ldc;
-        const ThroughBuf out(reinterpret_cast<const char*>(Cp));       // (an output is smaller than 4 GiB)
+        T* const Cp = (T*)s.C;
+        uint32_t ldc = uni(s.ldc);
+        asm volatile("" : "+s"(ldc));                                // (kept: the loop would read the kernel argument again per segment)
+        const ThroughBuf out(uni_ptr(Cp));                           // (an output is smaller than 4 GiB)
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             // the region is private to the wave: its own LDS writes are ordered before its reads
