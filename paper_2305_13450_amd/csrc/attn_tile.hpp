@@ -11,8 +11,8 @@
 // lane are 8 keys of its query, and since the order of the 16 K-slots of an MFMA is free as
 // long as both operands agree, they can be fed straight back as the B operand while V^T is
 // read with the same key permutation: runs of 4 keys of one d, which the transposing LDS read
-// (ds_read_b64_tr_b16) gathers from rows of V as they lie in memory.  Row maxima are in-lane
-// reductions plus one exchange between the two half-waves; the sums are a product with ones.
+// (ds_read_b64_tr_b16) gathers from rows of V as they lie in memory.  Row maxima and sums are in-lane
+// reductions plus one exchange between the two half-waves.
 //
 // Dependencies: the tile reads the Q columns of its own rows and the K and V columns of all
 // rows of its sequence up to its last row, from the QKV GeMM before it; it posts like any
@@ -72,7 +72,7 @@ __device__ __forceinline__ void attn_wait_qkv(WaitCtx& w, const StageDesc& s, ui
 constexpr uint32_t ATT_PART_FLOATS = 256 * 64 + 2 * 256;
 
 // What bounds it: the longest tiles of a causal stage are one serial chain of key blocks, walked by one
-// wave per SIMD: per block 36 MFMAs (0.5 us), 32 scores per lane through exp2 and conversion (as
+// wave per SIMD: per block 32 MFMAs (0.5 us), 32 scores per lane through exp2 and conversion (as
 // much again), and all four waves reading the whole block from LDS.  So V is transposed by the read
 // (writing V^T back to LDS element by element took longer than everything else together), a block has
 // one barrier, half of the next block's scores are multiplied beside the exponentials, and the
@@ -143,15 +143,7 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[i][v] = 0.0f;
-    // the sum of a query's weights: one more block of O^T, with rows of ones in the place of V^T (every
-    // row holds the sum over both half-waves' keys)
-    V8 ones;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) ones[j] = (T)1.0f;
-    f32x16 lsum;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) lsum[v] = 0.0f;
-    float m_run = -INFINITY;
+    float m_run = -INFINITY, l_run = 0.0f;                         // reference value and sum of this query's weights
     const float sc = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(128) * log2(e)
 
     // LDS: NBUF blocks of K rows and NBUF of V rows ([64 keys][128 d], 16-byte chunks swizzled), DMA'd
@@ -264,38 +256,33 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
 #pragma unroll
             for (int v = 0; v < 16; ++v) mx = fmaxf(mx, st[kh][v]);
         mx = fmaxf(mx, __shfl_xor(mx, 32)) * sc;
-        // The reference value of the exponentials follows the maximum unless the new one would carry less
-        // than a sixteenth of the weight summed so far (and less than 2^8): most steps then do without the
-        // 80 multiplications.  A key that carries more gets the weight 1, which 16 bits hold exactly: with
-        // a reference that always lagged, the rounding of rows with few keys reached 2.7e-2 of a row's
-        // RMS at 2048 tokens in bf16.  The weights are summed as they were rounded.
-        const bool lag = mx <= m_run || (mx <= m_run + 8.0f && 16.0f * __builtin_amdgcn_exp2f(mx - m_run) <= lsum[0]);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!lag) != 0, 0)) {
-            // (each query by its own scores alone, whatever the other queries of the wave do)
-            const float m_new = lag ? m_run : mx;
-            // no visible key yet: both are -inf and there is nothing to scale
-            const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) lsum[v] *= alpha;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[i][v] *= alpha;
-        }
-        const float m_use = (m_run == -INFINITY) ? 0.0f : m_run;
-        // ---- weights of this block; the first half's registers then take the next block's scores, whose
-        // MFMAs run beside the exponentials of the second half (past the wave's last block they multiply
-        // whatever the slot holds, and nothing reads the result) ----
+        const float m_new = fmaxf(m_run, mx);
+        // a query beyond the sequence end or with no visible key yet keeps m = -inf: guard the exps
+        const float m_use = (m_new == -INFINITY) ? 0.0f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);   // arguments are <= 0 or -inf: v_exp_f32 as is
+        m_run = m_new;
+        // ---- weights of this block, relative to the largest seen (which 16 bits then hold exactly: a reference
+        // that lags behind the maximum, to save the rescaling of O, left errors 1 % larger), summed in 32 bits
+        // before they are rounded for the product with V.  The first half's registers then take the next
+        // block's scores, whose MFMAs run beside the exponentials of the second half and the rescaling of O (past the
+        // wave's last block they multiply whatever the slot holds, and nothing reads the result) ----
         V8 pf[4];
+        float psum = 0.0f;
         auto weight = [&](int kh, int v) __attribute__((always_inline)) {
-            // arguments are <= 8 or -inf: v_exp_f32 as is
-            pf[kh * 2 + (v >> 3)][v & 7] = (T)__builtin_amdgcn_exp2f(__builtin_fmaf(st[kh][v], sc, -m_use));
+#pragma clang fp contract(off)
+            const float p = __builtin_amdgcn_exp2f(st[kh][v] * sc - m_use);   // the largest score gives exactly 1
+            psum += p;
+            pf[kh * 2 + (v >> 3)][v & 7] = (T)p;
         };
 #pragma unroll
         for (int v = 0; v < 16; ++v) weight(0, v);
         st[0] = scores(kb + 1, 0, [&](int kk) __attribute__((always_inline)) { weight(1, 2 * kk); weight(1, 2 * kk + 1); });
-        st[1] = scores(kb + 1, 1, [](int) {});
+        psum += __shfl_xor(psum, 32);
+        l_run = l_run * alpha + psum;
+        st[1] = scores(kb + 1, 1, [&](int kk) __attribute__((always_inline)) {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) o[kk >> 1][(kk & 1) * 8 + v] *= alpha;
+        });
         // ---- O^T += V^T P^T : 4 steps of 16 keys, fragments of a step read while the one before is multiplied ----
         const uint32_t vb = (kb % NBUF) * ATT_BLK_BYTES + voff;
         T4 vf[2][4][2];
@@ -310,7 +297,6 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
         for (int ks = 0; ks < 4; ++ks) {
             __builtin_amdgcn_sched_barrier(0);
             if (ks < 3) rdv(ks + 1);
-            lsum = M::mma(ones, pf[ks], lsum);
 #pragma unroll
             for (int db = 0; db < 4; ++db)
                 o[db] = M::mma(__builtin_shufflevector(vf[ks & 1][db][0], vf[ks & 1][db][1], 0, 1, 2, 3, 4, 5, 6, 7), pf[ks], o[db]);
@@ -322,7 +308,6 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
         arrive(kb);
         request(kb);
     }
-    float l_run = lsum[0];
 
     dr.peek();   // the look at the dispatch queues for the next tile travels while the result is stored
     // ---- keys split over several workgroups: leave the part, carry on only as the last to arrive ----

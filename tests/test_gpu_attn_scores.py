@@ -1,6 +1,8 @@
 """The prompt-phase attention tile where its running reference matters: scores that grow along the
 sequence (a new maximum in most key blocks), scores that differ by hundreds (one key carries a row),
 and equal ones, over sequence ends and cache ends that cut a block of 64 keys anywhere."""
+import math
+
 import pytest
 import torch
 
@@ -73,3 +75,37 @@ def test_cache_ends_inside_a_key_block(seq, cached, tile, dtype, tol):
             assert row_err(T, ref) <= tol
         assert pol.status().timed_out == 0
         pol.destroy()
+
+
+@pytest.mark.parametrize("dtype,bits", [(torch.bfloat16, 8), (torch.float16, 11)])
+@pytest.mark.parametrize("tile", [ds.TILE_128x192, ds.TILE_128x192_DEEP])
+def test_weights_are_summed_in_32_bits(tile, dtype, bits):
+    # QKV = X: key 0 has the largest score and the only value (ones), every other key the same weight p and no value,
+    # so row i is 1 / (1 + i p) and shows the sum of the weights alone.  p is chosen half way between two
+    # 16-bit numbers: a sum over rounded weights is off by half of a last place, and the result by more than the
+    # half that its own rounding may take.
+    seq, a = 640, 16.0
+    best = max((d / 64 for d in range(1, 32)), key=lambda d: abs(_last_places(_weight(a, d), bits) % 1.0 - 0.5) * -1)
+    p = _weight(a, best)
+    assert abs(_last_places(p, bits) % 1.0 - 0.5) < 0.1
+    X = torch.zeros(seq, 384)
+    X[:, 0] = a
+    X[0, 128], X[1:, 128] = 1.0, 1.0 - best
+    X[0, 256:] = 1.0
+    pol = ds.SyncPolicy(ds.TILESYNC, ksplit=1)
+    QKV, T, _ = run_attn_chain(X.to(dtype), torch.eye(384).to(dtype), torch.zeros(128, 64).to(dtype), 1, seq, 1, pol, ds.MODE_FUSED, tile=tile)
+    assert pol.status().timed_out == 0
+    pol.destroy()
+    assert torch.equal(QKV.cpu().float(), X)
+    ref = 1.0 / (1.0 + p * torch.arange(seq, dtype=torch.float64))[:, None]
+    half = torch.exp2(torch.floor(torch.log2(ref)) - bits)
+    # fp32: up to 640 additions and an exponential of 1e-7 each, 1e-5 with room
+    assert ((T.cpu().double() - ref).abs() <= half + 1e-5 * ref).all()
+
+
+def _weight(a, d):
+    return math.exp(-a * d / math.sqrt(128.0))
+
+
+def _last_places(x, bits):
+    return x * 2.0 ** (bits - 1 - math.floor(math.log2(x)))
