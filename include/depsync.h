@@ -15,8 +15,8 @@
  *  - All tensor pointers are DEVICE pointers owned by the caller.  The library never frees
  *    or reallocates them and keeps no reference after the call returns.
  *  - Calls that enqueue work are asynchronous.  On return, work enqueued later on
- *    stream_producer is ordered after the whole chain (the library forks the consumer
- *    stream off the producer stream with an event and joins it back).  One exception: a chain
+ *    stream_producer is ordered after the whole chain (its last stage runs on stream_producer and
+ *    waits for every tile of the stages before it).  One exception: a chain
  *    whose stages are split along K keeps fp32 partial tiles in a scratch buffer the policy
  *    owns, and the first chain that needs a larger one than any before it on that policy
  *    synchronises the device and reallocates it (hipFree + hipMalloc) before it enqueues.
@@ -70,9 +70,11 @@ typedef enum {
 
 /* How the two kernels of a chain are ordered. */
 typedef enum {
-    DEPSYNC_MODE_FINE = 0,       /* two streams, per-tile semaphores (the paper's method); one
-                                    dispatch on stream_producer where the tiles of all stages before
-                                    the last fit on the GPU at once                          */
+    DEPSYNC_MODE_FINE = 0,       /* two streams, per-tile semaphores (the paper's method).  Where the tiles
+                                    of all stages before the last fit on the GPU at once it is one
+                                    dispatch on stream_producer, and stream_consumer is not used.
+                                    Tiles are drawn from the dispatch queues either way, so the
+                                    chain progresses whatever else runs on the GPU           */
     DEPSYNC_MODE_STREAMSYNC = 1, /* the same kernels on one stream (the paper's baseline)  */
     DEPSYNC_MODE_PLAIN = 2,      /* the same tile code with the sync hooks compiled out,
                                     one stream, hardware block order                        */
@@ -136,9 +138,13 @@ typedef enum {
                                          one dispatch in index order, producers first, which HIP
                                          does not promise (observed on MI355X; the bounded wait turns
                                          a violation into DEPSYNC_ETIMEOUT).  Without this flag the
-                                         library names tiles by the block index only when every tile
-                                         has a resident workgroup of its own, where any start order
-                                         is safe, and draws them from the dispatch queues otherwise. */
+                                         library names tiles by the block index only in FUSED mode and
+                                         when every tile has a resident workgroup of its own, where any
+                                         start order is safe, and draws them from the dispatch queues
+                                         otherwise.  Resident means that the chain has the GPU to itself:
+                                         where chains of several policies run at the same time, use FINE
+                                         mode or DEPSYNC_FLAG_QUEUE_ORDER, whose progress does not
+                                         depend on what else holds the GPU.                          */
 
 typedef struct {
     uint32_t stride;      /* STRIDEDSYNC on a GeMM chain: distance, in producer column tiles,
@@ -336,6 +342,14 @@ int depsync_gemm_chain_plan(const depsync_gemm_chain_desc* d, const sync_policy_
                             int n_cu, depsync_plan_info* out);
 int depsync_conv_chain_plan(const depsync_conv_chain_desc* d, const sync_policy_t* pol,
                             int n_cu, depsync_plan_info* out);
+/* How the chain would be launched in `mode` (pol may be NULL: no flags, library-owned side streams):
+ * the number of kernel launches that hold its tiles, and 1 in *block_index where tiles are named by
+ * the block index instead of being drawn from the dispatch queues.  DEPSYNC_EINVAL for forms that the
+ * launch would refuse.                                                                       */
+int depsync_gemm_chain_launch_form(const depsync_gemm_chain_desc* d, const sync_policy_t* pol,
+                                   depsync_mode mode, int n_cu, int* dispatches, int* block_index);
+int depsync_conv_chain_n_launch_form(const depsync_conv_chain_n_desc* d, const sync_policy_t* pol,
+                                     depsync_mode mode, int n_cu, int* dispatches, int* block_index);
 /* For chains of more than three stages n_mid counts the tiles of all middle stages and the
  * middle grid is that of the second stage.                                                  */
 int depsync_conv_chain_n_plan(const depsync_conv_chain_n_desc* d, const sync_policy_t* pol,

@@ -36,7 +36,7 @@ EXPORTS = [
     "dep_conv_chain_n", "depsync_conv_chain_n_plan", "depsync_conv_chain_n_autotune", "depsync_workspace_bytes",
     "depsync_gemm_chain_check_waits", "depsync_conv_chain_n_check_waits", "dep_gemm_chain_static",
     "depsync_gemm_chain_autotune_policy", "depsync_conv_chain_n_autotune_policy", "depsync_gemm_chain_policy",
-    "depsync_conv_chain_n_policy",
+    "depsync_conv_chain_n_policy", "depsync_gemm_chain_launch_form", "depsync_conv_chain_n_launch_form",
 ]
 
 
@@ -149,6 +149,9 @@ def _lib() -> ctypes.CDLL:
         L.depsync_conv_chain_tuned.argtypes = [ctypes.POINTER(ConvChainDesc), vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.depsync_gemm_chain_set_tuned.argtypes = [ctypes.POINTER(GemmChainDesc), vp, i32, i32]
         L.depsync_conv_chain_set_tuned.argtypes = [ctypes.POINTER(ConvChainDesc), vp, i32, i32]
+        i32p = ctypes.POINTER(i32)
+        L.depsync_gemm_chain_launch_form.argtypes = [ctypes.POINTER(GemmChainDesc), vp, i32, i32, i32p, i32p]
+        L.depsync_conv_chain_n_launch_form.argtypes = [ctypes.POINTER(ConvChainNDesc), vp, i32, i32, i32p, i32p]
         i64p = ctypes.POINTER(ctypes.c_int64)
         L.depsync_gemm_chain_check_waits.argtypes = [ctypes.POINTER(GemmChainDesc), i32, ctypes.POINTER(PolicyParams), i32, i64p]
         L.depsync_conv_chain_n_check_waits.argtypes = [ctypes.POINTER(ConvChainNDesc), i32, ctypes.POINTER(PolicyParams), i32, i64p]
@@ -535,6 +538,14 @@ def copy_chain_plan(src, mid, dst, policy: SyncPolicy, tile_bytes: int = 0, n_cu
     _check(_lib().depsync_copy_chain_plan(ctypes.byref(d), policy.handle, n_cu, ctypes.byref(info)),
            "depsync_copy_chain_plan")
     return info
+
+
+def launch_form(desc, policy: Optional[SyncPolicy], mode: int, n_cu: int = 0) -> tuple:
+    """(kernel launches, tiles named by the block index) of a GeMM or N-convolution chain in this mode."""
+    f = _lib().depsync_gemm_chain_launch_form if isinstance(desc, GemmChainDesc) else _lib().depsync_conv_chain_n_launch_form
+    n, hw = ctypes.c_int(0), ctypes.c_int(0)
+    _check(f(ctypes.byref(desc), policy.handle if policy else None, mode, n_cu, ctypes.byref(n), ctypes.byref(hw)), "launch_form")
+    return n.value, bool(hw.value)
 
 
 def gemm_chain_check_waits(desc: GemmChainDesc, kind: int, n_cu: int = 0, **params) -> int:

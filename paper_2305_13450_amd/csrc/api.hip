@@ -890,40 +890,66 @@ void fill_common(ChainArgs& a, sync_policy* pol, const Plan& p, uint32_t epoch) 
     }
 }
 
+// How a chain is launched: in which mode's form, and whether tiles are named by the block index.
+struct LaunchForm {
+    depsync_mode mode;
+    bool block_index;
+    bool mixed;       // stages of differing macro-tile shapes: one launch (one kernel) per stage
+    bool legal;
+};
+
+// Drawn from the dispatch queues, producer tiles are always handed out before consumer tiles, whatever
+// order the hardware starts workgroups in and whatever else holds slots (Section III-B).  Named by the
+// block index (Section IV-C, "avoid custom tile order"), a chain of more tiles than resident workgroups
+// progresses only if every XCD starts the workgroups of a dispatch in index order, which HIP does not promise; so the
+// library chooses that order on its own only for the one-dispatch mode, and only when every tile's workgroup
+// is resident at once (any start order is then safe, as long as no other chain holds the slots), or when the
+// autotuner measured it for such a chain; beyond that it is the caller's explicit choice
+// (DEPSYNC_FLAG_HW_ORDER), backed by the bounded wait.
+// Two streams where the earlier stages' tiles all fit on the chip at once: the launch on the caller's stream draws
+// them all before it turns to its own stage, and side launches would only take its slots away and
+// draw by compare-and-swap against it.  They are left out (as the paper leaves out its wait kernel when both kernels
+// fit the GPU together, Section IV-C), and what remains is one dispatch that draws from the queues: 333 tokens of
+// the 12288 x 6144 x 12288 chain (192 producer parts, 256 slots) 198 -> 168 us.
+// That dispatch is not named by the block index where it could be: the two-stream mode promises progress beside
+// other chains.  The price, two-stream mode against one dispatch by the index: 256 x 1024 x 4096 x 1024 fp16 29.8 / 21.6
+// us, one token 86.5 / 78.3, four 14x14x512 convolutions 92.6 / 62.1 (with side launches 39.2, 96.5 and 91.9).
+// flags: DEPSYNC_FLAG_*; force_order: the autotuner's choice or -1; own_streams: there are side streams to fork.
+LaunchForm launch_form(const Plan& p, uint32_t flags, int force_order, bool own_streams, depsync_mode mode) {
+    uint32_t total = 0;
+    LaunchForm f{mode, false, false, true};
+    for (int s = 0; s < p.n_stages; ++s) {
+        total += p.n_tiles[s];
+        f.mixed = f.mixed || p.tile[s] != p.tile[0];
+    }
+    const bool want_queues = (flags & (DEPSYNC_FLAG_QUEUE_ORDER | DEPSYNC_FLAG_REVERSE_ORDER)) != 0;
+    const bool caller_hw = (flags & DEPSYNC_FLAG_HW_ORDER) != 0;
+    const bool all_resident = !f.mixed && total <= (uint32_t)p.slots;
+    if (mode == DEPSYNC_MODE_FINE && own_streams && !f.mixed && !caller_hw &&
+        total - p.n_tiles[p.n_stages - 1] <= (uint32_t)p.slots)
+        f.mode = DEPSYNC_MODE_FUSED;
+    if (force_order == 1 && !all_resident && !caller_hw) f.legal = false;   // not a candidate for the autotuner
+    bool hw;
+    if (force_order >= 0) hw = force_order == 1;
+    else if (want_queues) hw = false;
+    else if (caller_hw) hw = true;
+    else hw = mode == DEPSYNC_MODE_FUSED && all_resident && p.order_pref != 0;
+    f.block_index = mode == DEPSYNC_MODE_PLAIN || caller_hw || (f.mode == DEPSYNC_MODE_FUSED && hw);
+    if (mode == DEPSYNC_MODE_FINE && caller_hw && !all_resident) f.legal = false;
+    if (f.mode == DEPSYNC_MODE_FINE && f.mixed && (f.block_index || p.n_stages != 2)) f.legal = false;
+    return f;
+}
+
 int launch_chain(sync_policy* pol, const Plan& p, ChainArgs& a, depsync_mode mode, void* sp_, void* sc_) {
     hipStream_t sp = static_cast<hipStream_t>(sp_);
     const bool sync = mode != DEPSYNC_MODE_PLAIN;
     uint32_t total = 0;
     for (int s = 0; s < p.n_stages; ++s) total += p.n_tiles[s];
-    // Tile order of a one-dispatch launch.  Drawn from the dispatch queues, producer tiles are
-    // always handed out before consumer tiles, whatever order the hardware starts workgroups in
-    // (Section III-B).  Named by the block index (Section IV-C, "avoid custom tile order"), a chain
-    // of more tiles than resident workgroups progresses only if every XCD starts the workgroups of
-    // a dispatch in index order, which HIP does not promise; so the library chooses that order on
-    // its own only when every tile's workgroup is resident at once (any start order is then safe),
-    // or when the autotuner measured it for such a chain; beyond that it is the caller's explicit
-    // choice (DEPSYNC_FLAG_HW_ORDER), backed by the bounded wait.
-    const bool want_queues = (pol->params.flags & (DEPSYNC_FLAG_QUEUE_ORDER | DEPSYNC_FLAG_REVERSE_ORDER)) != 0;
-    const bool caller_hw = (pol->params.flags & DEPSYNC_FLAG_HW_ORDER) != 0;
-    bool mixed = false;   // stages of differing macro-tile shapes: one launch (one kernel) per stage
-    for (int s = 1; s < p.n_stages; ++s) mixed = mixed || p.tile[s] != p.tile[0];
-    const bool all_resident = !mixed && total <= (uint32_t)p.slots;
-    // Two streams where the earlier stages' tiles all fit on the chip at once: the launch on the caller's stream draws
-    // them all before it turns to its own stage, and side launches would only take its slots away and
-    // draw by compare-and-swap against it.  They are left out (as the paper leaves out its wait kernel when both kernels
-    // fit the GPU together, Section IV-C), and what remains is the one-dispatch form: 333 tokens of
-    // the 12288 x 6144 x 12288 chain (192 producer parts, 256 slots) 198 -> 168 us.
-    if (mode == DEPSYNC_MODE_FINE && pol->ev_fork && !mixed && !caller_hw && total - p.n_tiles[p.n_stages - 1] <= (uint32_t)p.slots)
-        mode = DEPSYNC_MODE_FUSED;
-    if (pol->force_order == 1 && !all_resident && !caller_hw) return DEPSYNC_EINVAL;   // not a candidate for the autotuner
-    bool hw;
-    if (pol->force_order >= 0) hw = pol->force_order == 1;
-    else if (want_queues) hw = false;
-    else if (caller_hw) hw = true;
-    else hw = all_resident && p.order_pref != 0;
-    if (sync && mode == DEPSYNC_MODE_FUSED && hw) a.flags |= DEPSYNC_FLAG_HW_ORDER;
-    if (sync && (a.flags & DEPSYNC_FLAG_HW_ORDER) && mode == DEPSYNC_MODE_FINE && !all_resident)
-        return DEPSYNC_EINVAL;
+    const LaunchForm form = launch_form(p, pol->params.flags, pol->force_order, pol->ev_fork != nullptr, mode);
+    if (!form.legal) return DEPSYNC_EINVAL;
+    mode = form.mode;
+    const bool mixed = form.mixed;
+    if (sync && form.block_index) a.flags |= DEPSYNC_FLAG_HW_ORDER;
 
     // With the dispatch queues a launch needs no more workgroups than fit on the chip at once:
     // each keeps drawing tiles.  With tiles named by the block index (PLAIN, HW_ORDER) a launch
@@ -957,7 +983,6 @@ int launch_chain(sync_policy* pol, const Plan& p, ChainArgs& a, depsync_mode mod
             // behind Section III-B's wait kernel: the consumer's workgroups are not started before
             // the producer's persistent workgroups hold their slots, so consumers that then fill
             // the rest of the chip wait for tiles that resident workgroups are working through.
-            if (!queues || p.n_stages != 2) return DEPSYNC_EINVAL;
             HIP_TRY(hipEventRecord(pol->ev_fork, sp));
             HIP_TRY(hipStreamWaitEvent(side[0], pol->ev_fork, 0));
             const uint32_t nb0 = blocks(p.n_tiles[0], 0);
@@ -1248,6 +1273,29 @@ int depsync_conv_chain_n_plan(const depsync_conv_chain_n_desc* d, const sync_pol
     if (rc != DEPSYNC_OK) return rc;
     fill_plan_info(p, out);
     return DEPSYNC_OK;
+}
+
+static int report_launch_form(const Plan& p, const sync_policy_t* pol, depsync_mode mode, int* dispatches, int* block_index) {
+    if (!dispatches || !block_index || mode < DEPSYNC_MODE_FINE || mode > DEPSYNC_MODE_FUSED) return DEPSYNC_EINVAL;
+    const LaunchForm f = launch_form(p, pol ? pol->params.flags : 0u, -1, !pol || pol->ev_fork, mode);
+    if (!f.legal) return DEPSYNC_EINVAL;
+    *dispatches = f.mode == DEPSYNC_MODE_FUSED ? 1 : p.n_stages;
+    *block_index = f.block_index ? 1 : 0;
+    return DEPSYNC_OK;
+}
+
+int depsync_gemm_chain_launch_form(const depsync_gemm_chain_desc* d, const sync_policy_t* pol, depsync_mode mode, int n_cu,
+                                   int* dispatches, int* block_index) {
+    Plan p;
+    if (int rc = plan_gemm(d, pol, n_cu, p); rc != DEPSYNC_OK) return rc;
+    return report_launch_form(p, pol, mode, dispatches, block_index);
+}
+
+int depsync_conv_chain_n_launch_form(const depsync_conv_chain_n_desc* d, const sync_policy_t* pol, depsync_mode mode, int n_cu,
+                                     int* dispatches, int* block_index) {
+    Plan p;
+    if (int rc = plan_conv_n(d, pol, n_cu, p); rc != DEPSYNC_OK) return rc;
+    return report_launch_form(p, pol, mode, dispatches, block_index);
 }
 
 int depsync_copy_chain_plan(const depsync_copy_chain_desc* d, const sync_policy_t* pol, int n_cu, depsync_plan_info* out) {

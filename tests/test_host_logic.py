@@ -319,6 +319,27 @@ def test_conv_chain_waits_cover_the_halo(kind):
     assert checked > 100
 
 
+def test_two_stream_mode_never_rests_on_the_block_index():
+    # Chains of several policies may run at the same time.  Tiles named by the block index then wait
+    # for workgroups that another chain's waiting ones keep from starting; drawn from the queues they do
+    # not (Section III-B).  So the default mode draws, also where its chain is one dispatch; FUSED
+    # names resident chains by the index.
+    for (M, K1, N1, N2), fine, fused in (((1, 12288, 6144, 12288), (1, False), (1, True)), ((1, 4096, 4096, 4096), (1, False), (1, True)),
+                                         ((256, 1024, 4096, 1024), (1, False), (1, True)),
+                                         ((333, 12288, 6144, 12288), (1, False), (1, False)),
+                                         ((4096, 4096, 8192, 4096), (2, False), (1, False))):
+        d = _fake_gemm_desc(M, K1, N1, N2)
+        assert ds.launch_form(d, None, ds.MODE_FINE, 256) == fine, M
+        assert ds.launch_form(d, None, ds.MODE_FUSED, 256) == fused, M
+        assert ds.launch_form(d, None, ds.MODE_STREAMSYNC, 256) == (2, False)
+        assert ds.launch_form(d, None, ds.MODE_PLAIN, 256) == (2, True)
+    c = _fake_conv_n_desc(1, 14, 14, 512, (512, 512, 512, 512))
+    assert ds.launch_form(c, None, ds.MODE_FINE, 256) == (1, False) and ds.launch_form(c, None, ds.MODE_FUSED, 256) == (1, True)
+    d = _fake_gemm_desc(512, 512, 512, 512)
+    d.tile_prod, d.tile_cons = ds.TILE_128x128, ds.TILE_64x64           # two kernels: two launches
+    assert ds.launch_form(d, None, ds.MODE_FINE, 256) == (2, False)
+
+
 def test_k_blocked_layout_is_validated():
     info = ds.PlanInfo()
     d = _fake_gemm_desc(256, 1024, 4096, 1024)
