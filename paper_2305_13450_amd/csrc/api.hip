@@ -90,6 +90,7 @@ struct sync_policy {
     uint32_t epoch;
     uint32_t queue_epoch;      // chains that drew their tiles from the dispatch queues since the last reset
     int force_order;       // autotuner only: -1 none, 0 dispatch queues, 1 hardware order
+    bool ignore_tuned;     // autotuner only: plan as if nothing were remembered for the chain's shape
     uint32_t launches;
     float* scratch;        // split-K partial tiles, grown on demand
     size_t scratch_floats;
@@ -433,7 +434,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     bool tuned_off = false;
     int order_pref = -1;
     if (!tile) {
-        const int v = tuned_tile(tune_key(d, pol ? effective_kind(d, pol, default_kind(d)) : -1));
+        const int v = pol && pol->ignore_tuned ? 0 : tuned_tile(tune_key(d, pol ? effective_kind(d, pol, default_kind(d)) : -1));
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
@@ -607,7 +608,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     bool tuned_off = false;
     int order_pref = -1;
     if (!tile) {
-        const int v = tuned_tile(tune_key(d, pol ? effective_kind(d, pol, DEPSYNC_STRIDEDSYNC) : -1));
+        const int v = pol && pol->ignore_tuned ? 0 : tuned_tile(tune_key(d, pol ? effective_kind(d, pol, DEPSYNC_STRIDEDSYNC) : -1));
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
@@ -1342,9 +1343,15 @@ int dep_copy_chain(const depsync_copy_chain_desc* d, sync_policy_t* pol, depsync
 }  // extern "C"
 
 namespace {
-// Time every macro-tile shape the chain can run with, each with and without the library's split
-// along K and with tiles drawn from the dispatch queues or named by the block index (one-dispatch mode, HIP events on the caller's stream, two passes, blocks long enough
-// to time), and remember the fastest combination.
+int plan_any(const depsync_gemm_chain_desc* d, const sync_policy* pol, Plan& p) { return plan_gemm(d, pol, 0, p); }
+int plan_any(const depsync_conv_chain_desc* d, const sync_policy* pol, Plan& p) { return plan_conv(d, pol, 0, p); }
+int plan_any(const depsync_conv_chain_n_desc* d, const sync_policy* pol, Plan& p) { return plan_conv_n(d, pol, 0, p); }
+
+// Time the library's own choice (shape 0: what it runs when nothing is remembered, with shapes and splits that
+// a remembered entry cannot name) and every macro-tile shape the chain can run with, each with and without the
+// library's split along K and with tiles drawn from the dispatch queues or named by the block index (one-dispatch
+// mode, HIP events on the caller's stream, two passes, blocks long enough to time), and remember the fastest
+// combination; where that is the library's own choice, nothing is remembered.
 template <class Desc, class Run>
 int autotune(const Desc* d, sync_policy* pol, hipStream_t sp, int reps, int* tile_out, Run run, float* best_ms_out = nullptr) {
     if (!d || !pol) return DEPSYNC_EINVAL;
@@ -1354,7 +1361,7 @@ int autotune(const Desc* d, sync_policy* pol, hipStream_t sp, int reps, int* til
     HIP_TRY(hipEventCreate(&e0));
     if (hipError_t e = hipEventCreate(&e1); e != hipSuccess) { (void)hipEventDestroy(e0); return hip_fail(e); }
     const uint32_t user_split = pol->params.ksplit;
-    int best = 0, rc = DEPSYNC_OK;
+    int best = -1, rc = DEPSYNC_OK;
     float best_ms = 0.f;
     auto time_block = [&](const Desc* dd, int n, float* per_run) -> int {
         int r = DEPSYNC_OK;
@@ -1369,12 +1376,13 @@ int autotune(const Desc* d, sync_policy* pol, hipStream_t sp, int reps, int* til
         return r;
     };
     for (int pass = 0; pass < 2 && rc == DEPSYNC_OK; ++pass) {
-        for (int t = 1; t < DEPSYNC_TILE__COUNT && rc == DEPSYNC_OK; ++t) {
-            for (int var = 0; var < (user_split == 0 ? 4 : 2) && rc == DEPSYNC_OK; ++var) {
+        for (int t = 0; t < DEPSYNC_TILE__COUNT && rc == DEPSYNC_OK; ++t) {
+            for (int var = 0; var < (t == 0 ? 1 : user_split == 0 ? 4 : 2) && rc == DEPSYNC_OK; ++var) {
                 const int off = var >> 1, hw = var & 1;
                 if (hw && (pol->params.flags & DEPSYNC_FLAG_HW_ORDER)) continue;   // already the caller's choice
                 pol->params.ksplit = off ? 1u : user_split;
-                pol->force_order = hw;
+                pol->force_order = t == 0 ? -1 : hw;
+                pol->ignore_tuned = t == 0;
                 Desc dd = *d;
                 dd.tile_prod = dd.tile_cons = t;
                 int r = run(&dd);                   // warm-up; also tells whether this shape is usable
@@ -1386,21 +1394,29 @@ int autotune(const Desc* d, sync_policy* pol, hipStream_t sp, int reps, int* til
                     r = time_block(&dd, (int)(2.0f / std::max(ms, 0.005f)) + 1, &ms);
                 if (r != DEPSYNC_OK) { rc = r; break; }
                 const int cand = t | (off ? 0x100 : 0) | (hw ? 0x200 : 0);
-                if (best == 0 || ms < best_ms) { best = cand; best_ms = ms; }
+                if (best < 0 || ms < best_ms) { best = cand; best_ms = ms; }
             }
         }
     }
     pol->params.ksplit = user_split;
     pol->force_order = -1;
+    pol->ignore_tuned = false;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != DEPSYNC_OK) return rc;
-    if (best == 0) return DEPSYNC_EINVAL;
+    if (best < 0) return DEPSYNC_EINVAL;
     {
         std::lock_guard<std::mutex> g(g_tuned_mutex);
-        g_tuned[tune_key(d, pol->kind)] = best;
+        if (best == 0) g_tuned.erase(tune_key(d, pol->kind));
+        else g_tuned[tune_key(d, pol->kind)] = best;
     }
-    if (tile_out) *tile_out = best & 0xff;
+    if (tile_out) {
+        Desc dd = *d;
+        dd.tile_prod = dd.tile_cons = 0;
+        Plan p;
+        if (int r = plan_any(&dd, pol, p); r != DEPSYNC_OK) return r;
+        *tile_out = public_tile(p.tile[0]);
+    }
     if (best_ms_out) *best_ms_out = best_ms;
     return DEPSYNC_OK;
 }

@@ -145,6 +145,23 @@ def test_conv_autotune_picks_a_tile_the_library_then_uses():
     pol.destroy()
 
 
+def test_conv_autotune_keeps_the_librarys_own_choice_where_it_is_the_fastest():
+    # The planner runs this pair with a shape that a remembered entry cannot name (three workgroups per CU: 23.5 us,
+    # the fastest one that it can 35.5): tuning must not lose it.
+    t = inputs.conv(1, 28, 30, 256, 256, 256, seed=31)
+    x, w1, w2 = t["x"].cuda(), t["w1"].cuda(), t["w2"].cuda()
+    mid, out = (torch.empty((1, 28, 30, 256), dtype=x.dtype, device="cuda") for _ in range(2))
+    pol = ds.SyncPolicy(ds.STRIDEDSYNC)
+    before = ds.conv_chain_plan(x, w1, mid, w2, out, pol)
+    assert before.slots == 3 * ds.device_info()[0]
+    ds.conv_chain_set_tuned(x, w1, mid, w2, out, pol, ds.TILE_128x128)      # an earlier entry is measured against, too
+    tile = ds.conv_chain_autotune(x, w1, mid, w2, out, pol, reps=3)
+    assert ds.conv_chain_tuned(x, w1, mid, w2, out, pol) == (0, 0) and tile == before.tile_prod
+    assert ds.conv_chain_plan(x, w1, mid, w2, out, pol).as_dict() == before.as_dict()
+    assert pol.status().timed_out == 0
+    pol.destroy()
+
+
 @pytest.mark.parametrize("kind", [ds.ROWSYNC, ds.TILESYNC, ds.STRIDEDSYNC])
 def test_conv_chain_split_k(kind):
     # 9 * C / 64 = 18 K steps: three parts are one filter row each
