@@ -148,7 +148,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     const uint32_t wave = uni(tid >> 6);
     const uint32_t wm = wave / Cfg::WN, wn = wave % Cfg::WN;
     const uint32_t sM = uni(s.M), sN = uni(s.N);
-    const bool gate_up = (s.bmode == B_GATE_UP);
+    const bool gate_up = AMODE != A_CONV3X3 && s.bmode == B_GATE_UP;
     const uint32_t tn_out = gate_up ? TN / 2 : TN;       // output columns this tile owns
     const uint32_t S = uni(s.ksplit);                      // workgroups per output tile (split along K)
     const uint32_t ty = tyz / S, kz = tyz % S;
@@ -630,7 +630,8 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     // rounds and stores: whole lines instead of 2-byte pieces for the write-through stores.  The loop is
     // what keeps the code short: with the activation unrolled over the accumulators a kernel was 70 to 290
     // KB of straight code, executed once per tile and fetched from memory each time a chain's weights
-    // had swept it out of the L2.
+    // had swept it out of the L2.  (A convolution has ReLU or nothing: its kernels hold no code for the others, which
+    // takes 2-4 % off the chains of short tiles: four of 9x59x59x64 in fp16 68.4 -> 66.2 us.)
     __syncthreads();   // every wave has read its last operand fragments
     if (wctx.ok && finish) {
         constexpr int PITCH = Cfg::WTN * 4 + 16;                    // bytes per row in LDS
@@ -671,7 +672,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
                     __builtin_memcpy(u, __builtin_assume_aligned(src + 128, 16), 32);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[e] = silu_f(x[e]) * u[e];
-                } else if (act == ACT_GELU) {
+                } else if (AMODE != A_CONV3X3 && act == ACT_GELU) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[e] = gelu_erf(x[e]);
                 } else if (act == ACT_RELU) {
