@@ -9,6 +9,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "../../include/depsync.h"
@@ -227,19 +228,22 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 // on `slots` workgroup slots for every candidate shape (host_model.h).  A stage that would leave
 // slots idle is modelled as the planner will run it: split along K into S parts, each costing
 // 1/S of the tile plus 15 % per further part for the partial tiles and the workgroup that sums them.
+// by_tile: the second stage's parts start on the first stage's tile boundaries (waits per producer tile).
+// time (nullable): the simulated time of the choice; 0.70e-6 of it are the microseconds measured on 65 to 320 tokens
+// of fifteen pairs of layers, weights from HBM, within 10 % for most and a third for the rest.
 int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t K2, bool gate_up,
-                int n_cu, int rows_halo_tiles) {
+                int n_cu, int rows_halo_tiles, bool by_tile = false, double* time = nullptr) {
     // The simulation walks every tile of every candidate shape (a millisecond of host time for
     // the largest conv pairs, which every launch with TILE_AUTO would pay): remember the answer.
     using Key = std::array<uint64_t, 4>;
-    static std::map<Key, int> memo;
+    static std::map<Key, std::pair<int, double>> memo;
     static std::mutex memo_mutex;
     const Key key = {((uint64_t)M << 32) | n_out1, ((uint64_t)K1 << 32) | N2,
-                     ((uint64_t)K2 << 32) | (uint32_t)n_cu, ((uint64_t)(uint32_t)rows_halo_tiles << 1) | (uint64_t)gate_up};
+                     ((uint64_t)K2 << 32) | (uint32_t)n_cu, ((uint64_t)(uint32_t)rows_halo_tiles << 2) | ((uint64_t)by_tile << 1) | (uint64_t)gate_up};
     {
         std::lock_guard<std::mutex> lock(memo_mutex);
         const auto it = memo.find(key);
-        if (it != memo.end()) return it->second;
+        if (it != memo.end()) { if (time) *time = it->second.second; return it->second.first; }
     }
     int best = 0;
     double best_t = 0;
@@ -253,7 +257,7 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
         // `occupancy` workgroups share a CU's matrix units, so each runs at 1/occupancy of its rate
         const uint32_t slots = (uint32_t)(n_cu * ts->occupancy);
         const uint32_t s1 = choose_split(nullptr, false, gx1 * gy, slots, K1 / 64, 1);
-        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, 1);
+        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, by_tile ? std::max(1u, tn1 / 64) : 1u);
         const double d1 = f * (double)ts->rows * ts->cols * K1 * ts->occupancy / s1 * (1.0 + 0.15 * (s1 - 1));
         const double d2 = f * (double)ts->rows * ts->cols * K2 * ts->occupancy / s2 * (1.0 + 0.15 * (s2 - 1));
         const double tm = simulate_chain((int)slots, gx1 * s1, gy, d1, gx2 * s2, gy, d2, rows_halo_tiles,
@@ -261,7 +265,8 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
         if (best == 0 || tm < best_t) { best = t; best_t = tm; }
     }
     std::lock_guard<std::mutex> lock(memo_mutex);
-    memo[key] = best;
+    memo[key] = {best, best_t};
+    if (time) *time = best_t;
     return best;
 }
 
@@ -282,9 +287,9 @@ int policy_dep_kind_conv(int kind) {
 
 // Workgroups per output tile for a stage with `tiles` output tiles and `kt` K steps whose
 // dependency segments start every `seg` steps: split when the stage would leave at least half
-// of the slots idle, as far as one wave of slots allows, keeping every part at least 16 steps
-// min_steps long (the partial tiles and the arrival count cost about 10 us per stage; with the small
-// tiles of the three-per-CU shape less, see fit_triple) and starting on a segment boundary.
+// of the slots idle, as far as one wave of slots allows, keeping every part at least min_steps
+// steps long (16: the partial tiles and the arrival count cost about 10 us per stage; with the small
+// tiles of the three-per-CU shape less, see triple_split) and starting on a segment boundary.
 // `tuned_off`: the autotuner found this chain faster without.
 // (Splitting a stage of more tiles than slots so that it ends in a fuller last round was measured
 // and is not done: LLaMA MLP at 2048 tokens, 344 producer tiles on 256 slots as 688 halves, three
@@ -309,50 +314,65 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 // of hundreds of workgroups stand between the stages (256 x 4096 x 2048 x 4096: 31 us resident, 53 us with more
 // parts drawn from the queues; 8192 x 2752 x 8192 at 256 tokens 61 against 77 us).  Parts are at least 12 K
 // steps long (28 x 30 x 256 convolutions 28.5 us with parts of 12, 37.3 us unsplit).
-// kt, seg: K steps and steps between dependency segments of each stage (kt = 0: not a GeMM).
-void fit_triple(Plan& p, const sync_policy* pol, bool tuned_off, const uint32_t (&kt)[4], const uint32_t (&seg)[4]) {
-    const uint32_t slots = (uint32_t)p.slots, min_steps = 12u;
-    for (int s = 0; s < p.n_stages; ++s)
-        if (kt[s]) p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], slots / (uint32_t)p.n_stages, kt[s], seg[s], min_steps);
+// tiles, kt, seg: output tiles, K steps and steps between dependency segments of each stage; S: its split, left
+// alone where kt = 0 (not a GeMM).
+void triple_split(const sync_policy* pol, int n, uint32_t slots, const uint32_t (&tiles)[4], const uint32_t (&kt)[4],
+                  const uint32_t (&seg)[4], uint32_t (&S)[4]) {
+    constexpr uint32_t min_steps = 12u;
+    for (int s = 0; s < n; ++s)
+        if (kt[s]) S[s] = choose_split(pol, false, tiles[s], slots / (uint32_t)n, kt[s], seg[s], min_steps);
     if (pol && pol->params.ksplit) return;
     for (;;) {
         uint32_t total = 0;
         int most = -1;
-        for (int s = 0; s < p.n_stages; ++s) {
-            const uint32_t parts = p.n_tiles[s] * p.ksplit[s];
-            total += parts;
-            if (kt[s] && p.ksplit[s] > 1 && (most < 0 || parts > p.n_tiles[most] * p.ksplit[most])) most = s;
+        for (int s = 0; s < n; ++s) {
+            total += tiles[s] * S[s];
+            if (kt[s] && S[s] > 1 && (most < 0 || tiles[s] * S[s] > tiles[most] * S[most])) most = s;
         }
         if (total <= slots || most < 0) return;
-        p.ksplit[most] = choose_split(pol, tuned_off, p.n_tiles[most], p.n_tiles[most] * p.ksplit[most] - 1, kt[most], seg[most], min_steps);
+        S[most] = choose_split(pol, false, tiles[most], tiles[most] * S[most] - 1, kt[most], seg[most], min_steps);
     }
 }
 
 // Would every tile of the chain, unsplit, have a workgroup of the three-per-CU shape resident at once?  Then that
-// shape is the fastest measured (1 to 400 tokens of seven pairs of layers, token generation, convolutions of images
-// of 7 to 60 pixels: 0.6 to 1 of the time of the shape chosen by the model below); beyond that its 64 x 64 tiles
-// move too many bytes per flop (12288 x 6144 x 12288 at 192 tokens: 175 against 135 us).  Not where a stage ends up with
-// long parts on half of the CUs or fewer: its weights then stream through two steps of 16 KB per part, and a
-// deeper pipeline is ahead (8192 x 2752 x 8192, whose 43 K steps do not divide, at one token 39.8 against 34.3 us).
-// cols, kt: output columns and K steps of the GeMM stages; other_tiles: tiles of an attention stage.
-bool triple_fits(const std::array<uint32_t, 4>& cols, const std::array<uint32_t, 4>& kt, uint32_t M, int n, uint32_t other_tiles, int cus) {
-    const TileShape* ts = tile_shape(TILE_64x64_TRIPLE);
-    const uint32_t slots = (uint32_t)(cus * ts->occupancy);
-    uint64_t total = other_tiles;
+// shape is the fastest measured (weights from HBM; 1 to 320 tokens of twenty pairs of layers, token generation,
+// convolutions of images of 7 to 60 pixels: 0.64 to 1 of the time of the shape chosen by the model), with two limits.
+// Not where the library's own split leaves a stage long parts on half of the CUs or fewer: its weights then stream
+// through two steps of 16 KB per part, and a deeper pipeline is ahead (8192 x 2752 x 8192, whose 43 K steps do not
+// divide, at one token 39.8 against 34.3 us; four 30x30x384 convolutions in parts of whole filter rows 104 against 83).
+// The other is for several row tiles: see triple_pays.
+// tiles, kt, seg: as above, kt = 0 for an attention stage.  steps, parts: of each stage as it would be split.
+bool triple_fits(int n, int cus, const uint32_t (&tiles)[4], const uint32_t (&kt)[4], const uint32_t (&seg)[4],
+                 uint32_t (&steps)[4], uint32_t (&parts)[4]) {
+    const uint32_t slots = (uint32_t)(cus * tile_shape(TILE_64x64_TRIPLE)->occupancy);
+    uint64_t total = 0;
+    for (int s = 0; s < n; ++s) total += tiles[s];
+    if (total > slots) return false;
+    uint32_t S[4] = {1, 1, 1, 1};
+    triple_split(nullptr, n, slots, tiles, kt, seg, S);
     for (int s = 0; s < n; ++s) {
-        const uint64_t tiles = (uint64_t)cdiv(cols[s], ts->cols) * cdiv(M, ts->rows);
-        total += tiles;
-        if (total > slots) return false;
-        const uint32_t S = choose_split(nullptr, false, (uint32_t)tiles, slots / (uint32_t)(n + (other_tiles ? 1 : 0)), kt[s], 1, 12u);
-        if (2 * tiles * S <= (uint64_t)cus && kt[s] / S > 32) return false;
+        parts[s] = tiles[s] * S[s]; steps[s] = kt[s] / S[s];
+        if (2 * parts[s] <= (uint32_t)cus && steps[s] > 32) return false;
     }
     return true;
 }
 
+// Two GeMMs of several row tiles that fit, with parts that add up to more than 140 steps: 64 x 64 tiles read every
+// element of A and B 64 times from LDS, and a step takes 0.44 us with one part per CU and half as much again with
+// three, whatever the HBM delivers.  Chains of shorter parts are ahead by 5 to 50 % all the same; these only where the
+// model, whose time is known to 10 %, has nothing better (4096 x 11008 x 4096 at 128 tokens 84 against 171 us).  Turned
+// away: 12288 x 3072 x 12288 at 192 tokens 118 against 89 us, 8192 x 8192 x 8192 at 128 117 against 102, 12288 x 6144
+// x 12288 at 128 126 against 112.  (Not seen: 11008 x 4096 x 1024 at 256 and 320 tokens, 84 and 96 against 74 and 87.)
+bool triple_pays(const uint32_t (&steps)[4], const uint32_t (&parts)[4], int cus, double model_time) {
+    double us = 0.0;
+    for (int s = 0; s < 2; ++s) us += steps[s] * (0.44 + 0.154 * std::max(0.0, (double)parts[s] / cus - 1.0));
+    return 1.1 * us <= 0.70e-6 * model_time;
+}
+
 // Do the 64x192 tiles of a stage split into (nearly) as many equal parts as there are CUs?  Where both stages of a
-// chain do, every CU is busy to the end and rows of A are read a third as often as by 64-wide tiles: 12288 x 6144 x
-// 12288 at 128 tokens 114 against 120 us, at 64 tokens 89 both, at 1 token, where A is one row and what counts is
-// the size of the partial tiles, 72 against 69 us.
+// chain of 33 to 64 rows do, that shape is used: 12288 x 6144 x 12288 at 64 tokens 92.4 us, three-per-CU 92.3 (with
+// K-blocked weights 85.9 and 81.0; at 33 tokens 89.3 and 83.1).  At 32 rows and fewer three-per-CU is clearly ahead (83
+// against 89).  All with weights from HBM.
 bool wide_fills(uint32_t M, uint32_t N, uint32_t K, int cus) {
     const TileShape* ts = tile_shape(DEPSYNC_TILE_64x192);
     if (N % ts->cols) return false;
@@ -438,13 +458,30 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
+    const int kind = effective_kind(d, pol, pol ? default_kind(d) : DEPSYNC_ROWSYNC);
     // (whether StridedSync divides the producer's columns depends on the tile: what it accepts stays as it is)
-    const bool by_stride = !attn && effective_kind(d, pol, pol ? default_kind(d) : DEPSYNC_ROWSYNC) == DEPSYNC_STRIDEDSYNC;
-    if (!tile && !gate_up && !by_stride && (!attn || d->seq == 1) &&
-        triple_fits({(uint32_t)d->N1, (uint32_t)d->N2, 0, 0}, {(uint32_t)d->K1 / 64, K2 / 64, 0, 0}, d->M, 2,
-                    attn ? (uint32_t)d->batch * d->heads : 0u, cus))
-        tile = (!attn && d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) ? DEPSYNC_TILE_64x192
-                                                                                                              : TILE_64x64_TRIPLE;
+    if (!tile && !gate_up && (attn ? d->seq == 1 : kind != DEPSYNC_STRIDEDSYNC)) {
+        const uint32_t rows = cdiv(d->M, 64), seg[4] = {1, 1, 1, 1};
+        uint32_t steps[4], parts[4];
+        if (attn) {
+            const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, (uint32_t)d->batch * d->heads, cdiv(d->N2, 64) * rows, 0};
+            const uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, K2 / 64, 0};
+            if (triple_fits(3, cus, tiles, kts, seg, steps, parts)) tile = TILE_64x64_TRIPLE;
+        } else {
+            const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, cdiv(d->N2, 64) * rows, 0, 0};
+            const uint32_t kts[4] = {(uint32_t)d->K1 / 64, K2 / 64, 0, 0};
+            if (triple_fits(2, cus, tiles, kts, seg, steps, parts)) {
+                tile = TILE_64x64_TRIPLE;
+                if (rows == 1) {
+                    if (d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
+                } else if (steps[0] + steps[1] > 140) {
+                    double model_time = 0.0;
+                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, 0, kind != DEPSYNC_ROWSYNC, &model_time);
+                    if (!triple_pays(steps, parts, cus, model_time)) tile = other;
+                }
+            }
+        }
+    }
     if (!tile) tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0);
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
@@ -478,7 +515,6 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     for (int s = 0; s < p.n_stages; ++s) { p.n_tiles[s] = p.grid_x[s] * p.grid_y[s]; p.ksplit[s] = 1; }
 
     // dependency of stage s on stage s-1, per policy
-    const int kind = effective_kind(d, pol, pol ? default_kind(d) : DEPSYNC_ROWSYNC);
     uint32_t off = 0;
     for (int s = 1; s < p.n_stages; ++s) {
         uint32_t dk = policy_dep_kind_gemm(kind);
@@ -541,10 +577,10 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         const uint32_t dk = p.dep_kind[last];
         const uint32_t seg = (dk == DEP_ROW) ? 1u : p.out_tn[last - 1] / 64;
         p.ksplit[last] = choose_split(pol, tuned_off, p.n_tiles[last], (uint32_t)p.stage_slots[last], K2 / 64, seg);
-        if (ts->occupancy > 2 && !mixed) {
+        if (tile == TILE_64x64_TRIPLE) {
             uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, 0, 0}, segs[4] = {1, 1, 1, 1};
             kts[last] = K2 / 64; segs[last] = seg;
-            fit_triple(p, pol, tuned_off, kts, segs);
+            triple_split(pol, p.n_stages, (uint32_t)p.slots, p.n_tiles, kts, segs, p.ksplit);
         }
     }
     if (int rc = finish_split(p); rc != DEPSYNC_OK) return rc;
@@ -612,10 +648,19 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
+    const int kind = effective_kind(d, pol, DEPSYNC_STRIDEDSYNC);
+    // Parts of a later stage start on its dependency segments.  CONV_ROW: the whole halo is waited for by every
+    // part; per filter row or per (filter row, channel tile): the wait at a filter row's first tap also
+    // covers its other two taps, so parts must be whole filter rows.
+    uint32_t kts[4] = {0, 0, 0, 0}, segs[4] = {1, 1, 1, 1};
+    for (int i = 0; i < n; ++i) {
+        kts[i] = 9u * cin[i] / 64;
+        if (i > 0 && policy_dep_kind_conv(kind) != DEP_CONV_ROW) segs[i] = 3u * cin[i] / 64;
+    }
     if (!tile) {
-        std::array<uint32_t, 4> cols{}, kt{};
-        for (int i = 0; i < n; ++i) { cols[i] = (uint32_t)d->K[i]; kt[i] = 9u * cin[i] / 64; }
-        if (triple_fits(cols, kt, M, n, 0, cus)) tile = TILE_64x64_TRIPLE;
+        uint32_t tiles[4] = {0, 0, 0, 0}, steps[4], parts[4];
+        for (int i = 0; i < n; ++i) tiles[i] = cdiv(d->K[i], 64) * cdiv(M, 64);
+        if (triple_fits(n, cus, tiles, kts, segs, steps, parts)) tile = TILE_64x64_TRIPLE;
     }
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
@@ -628,7 +673,6 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     p.amode = A_CONV3X3;
     p.dtype = d->dtype;
     p.order_pref = order_pref;
-    const int kind = effective_kind(d, pol, DEPSYNC_STRIDEDSYNC);
     for (int s = 0; s < n; ++s) {
         p.tile[s] = (mixed && s == n - 1) ? d->tile_cons : tile;
         const TileShape* ts = tile_shape(p.tile[s]);
@@ -653,17 +697,9 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         }
         p.n_sems += p.sem_count[s];
     }
-    p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], (uint32_t)p.stage_slots[0], 9u * d->C / 64, 1);
-    uint32_t kts[4] = {9u * (uint32_t)d->C / 64, 0, 0, 0}, segs[4] = {1, 1, 1, 1};
-    for (int s = 1; s < n; ++s) {
-        uint32_t seg = 1;                                   // CONV_ROW: the whole halo is waited for by every part
-        // per filter row or per (filter row, channel tile): the wait at a filter row's first tap
-        // also covers its other two taps, so parts must be whole filter rows
-        if (p.dep_kind[s] != DEP_CONV_ROW) seg = 3u * cin[s] / 64;
-        p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], (uint32_t)p.stage_slots[s], 9u * cin[s] / 64, seg);
-        kts[s] = 9u * cin[s] / 64; segs[s] = seg;
-    }
-    if (tile_shape(tile)->occupancy > 2 && !mixed) fit_triple(p, pol, tuned_off, kts, segs);
+    for (int s = 0; s < n; ++s)
+        p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], (uint32_t)p.stage_slots[s], kts[s], segs[s]);
+    if (tile == TILE_64x64_TRIPLE) triple_split(pol, n, (uint32_t)p.slots, p.n_tiles, kts, segs, p.ksplit);
     if (int rc = finish_split(p); rc != DEPSYNC_OK) return rc;
     const double Md = (double)M;
     p.flops = 0.0;

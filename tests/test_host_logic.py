@@ -319,6 +319,24 @@ def test_conv_chain_waits_cover_the_halo(kind):
     assert checked > 100
 
 
+def test_three_tiles_to_a_cu_only_where_the_splits_they_get_keep_parts_short():
+    # the rule is judged on the splits the stages would really get: over several row tiles long parts are slower
+    # than larger tiles (117 against 102 us, 118 against 89), and a later convolution may only be split at
+    # filter rows, which per-halo-row waits do not ask for (104 against 83 us, 68 against 81)
+    info = ds.PlanInfo()
+    for (M, K1, N1, N2), triple in (((128, 4096, 4096, 4096), True), ((256, 1024, 4096, 1024), True), ((64, 8192, 8192, 8192), True),
+                                    ((128, 4096, 11008, 4096), True), ((65, 8192, 8192, 8192), False),
+                                    ((192, 12288, 3072, 12288), False), ((128, 12288, 6144, 12288), False)):
+        d = _fake_gemm_desc(M, K1, N1, N2)
+        assert ds._lib().depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.OK
+        assert (info.slots == 768) == triple, (M, K1, N1, N2)
+        assert ds.gemm_chain_check_waits(d, ds.TILESYNC, n_cu=256) == 0
+    c = _fake_conv_n_desc(1, 30, 30, 384, (384,) * 4)
+    assert ds._lib().depsync_conv_chain_n_plan(ctypes.byref(c), None, 256, ctypes.byref(info)) == ds.OK and info.slots != 768
+    c = _fake_conv_n_desc(1, 14, 14, 512, (512,) * 4)
+    assert ds._lib().depsync_conv_chain_n_plan(ctypes.byref(c), None, 256, ctypes.byref(info)) == ds.OK and info.slots == 768
+
+
 def test_two_stream_mode_never_rests_on_the_block_index():
     # Chains of several policies may run at the same time.  Tiles named by the block index then wait
     # for workgroups that another chain's waiting ones keep from starting; drawn from the queues they do
