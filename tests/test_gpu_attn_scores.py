@@ -1,4 +1,4 @@
-"""The prompt-phase attention tile where its running reference matters: scores that grow along the
+"""The prompt-phase attention tile where its running maximum matters: scores that grow along the
 sequence (a new maximum in most key blocks), scores that differ by hundreds (one key carries a row),
 and equal ones, over sequence ends and cache ends that cut a block of 64 keys anywhere."""
 import math
@@ -31,7 +31,7 @@ def _scaled(shape, seq, heads, dtype):
 
 # Output and weights are rounded to 16 bits once each: 2^-9 of the largest of 128 elements (3.5 RMS of a
 # random row) is 7e-3, and a row's weights, each off by up to 2^-9, add 1e-3 times 4 standard
-# deviations: 2e-2 covers both.
+# deviations: 2e-2 covers both; fp16 rounds to an eighth of that, 4e-3 is its bound throughout the suite.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("tile", [ds.TILE_128x192, ds.TILE_128x192_DEEP])   # two and four blocks in LDS
 @pytest.mark.parametrize("seq", [1 * 64 + 1, 2 * 128, 3 * 128 - 1, 449, 640])
@@ -46,7 +46,7 @@ def test_rows_whatever_the_scores(shape, seq, tile, dtype):
         assert pol.status().timed_out == 0
         pol.destroy()
         ref = oracle.causal_attention(inputs.to_f64(QKV.cpu()), 1, seq, heads, 128)
-        assert row_err(T, ref) <= TOL_BF16
+        assert row_err(T, ref) <= (TOL_BF16 if dtype == torch.bfloat16 else TOL_FP16)
 
 
 @pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, TOL_BF16), (torch.float16, TOL_FP16)])

@@ -6,7 +6,7 @@ import torch
 import inputs
 import oracle
 import paper_2305_13450_amd as ds
-from gpu_util import TOL_BF16, TOL_MID, mid_err, rel_err, run_conv_chain, run_gemm_chain
+from gpu_util import TOL_BF16, TOL_FP16, TOL_MID, mid_err, rel_err, row_err, run_conv_chain, run_gemm_chain
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +47,50 @@ def test_convolutions(B, H, W, kind):
         for other in res[1:]:
             assert all(torch.equal(a, b) for a, b in zip(res[0], other))
 
+
+
+@pytest.mark.parametrize("mid,act", [(ds.MID_NONE, oracle.ACT_NONE), (ds.MID_RELU, oracle.ACT_RELU), (ds.MID_GELU, oracle.ACT_GELU)])
+@pytest.mark.parametrize("M", [1, 65, 130])
+def test_fp16_and_the_other_middles(M, mid, act):
+    t = inputs.mlp(M, 1024, 320, 136, seed=M, dtype=torch.float16)
+    print(f"small tiles fp16 M={M} mid={mid}", flush=True)
+    Href, Yref = oracle.gemm_chain(inputs.to_f64(t["X"]), inputs.to_f64(t["W1"]), inputs.to_f64(t["W2"]), act)
+    for kind in (ds.TILESYNC, ds.ROWSYNC):
+        pol = ds.SyncPolicy(kind)
+        res = [run_gemm_chain(t["X"], t["W1"], t["W2"], pol, mode, mid=mid) for mode in MODES]
+        assert pol.status().timed_out == 0
+        pol.destroy()
+        # an intermediate may be off by its own rounding (2^-11) and as much again
+        assert mid_err(res[0][0], Href, ulp=2.0 ** -10) <= TOL_MID and rel_err(res[0][1], Yref) <= TOL_FP16
+        for other in res[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(res[0], other))
+
+
+# keys of a (head, sequence) pair: too few for a second part, one more part than fits a third of the slots
+# otherwise, and the most parts a pair can have
+@pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, TOL_BF16), (torch.float16, TOL_FP16)])
+@pytest.mark.parametrize("batch,cached,heads", [(1, 300, 2), (5, 511, 13), (4, 1000, 16), (1, 2600, 3)])
+def test_token_generation(batch, cached, heads, dtype, tol):
+    E, K1, N2 = heads * 128, 512, 200
+    t = inputs.attention(batch, K1, heads, 128, N2, seed=heads, dtype=dtype)
+    kv = inputs.kv_cache(batch, cached, heads, 128, seed=cached, dtype=dtype)
+    X, Wq, Wo = t["X"].cuda(), t["Wqkv"].t().contiguous().cuda(), t["Wo"].t().contiguous().cuda()
+    Kc, Vc = kv["Kc"].cuda(), kv["Vc"].cuda()
+    kw = dict(mid=ds.MID_CAUSAL_ATTN, batch=batch, seq=1, heads=heads, head_dim=128, k_cache=Kc, v_cache=Vc)
+    print(f"small tiles generation {batch}x{cached} heads={heads} {dtype}", flush=True)
+    for kind in (ds.STRIDEDSYNC, ds.ROWSYNC):
+        pol = ds.SyncPolicy(kind)
+        res = []
+        for mode in MODES:
+            QKV, T, Y = (torch.full((batch, n), float("nan"), dtype=dtype, device="cuda") for n in (3 * E, E, N2))
+            assert ds.gemm_chain_plan(X, Wq, QKV, Wo, Y, pol, T=T, **kw).slots == 3 * ds.device_info()[0]
+            ds.dep_gemm_chain(X, Wq, QKV, Wo, Y, pol, mode=mode, T=T, **kw)
+            torch.cuda.synchronize()
+            res.append((QKV, T, Y))
+        assert pol.status().timed_out == 0
+        pol.destroy()
+        QKV, T, Y = res[0]
+        assert row_err(T, oracle.cached_attention(inputs.to_f64(QKV.cpu()), inputs.to_f64(kv["Kc"]), inputs.to_f64(kv["Vc"]), batch, 1, heads, 128)) <= tol
+        assert rel_err(Y, oracle.gemm(inputs.to_f64(T.cpu()), inputs.to_f64(t["Wo"]))) <= tol
+        for other in res[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(res[0], other))
