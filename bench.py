@@ -22,11 +22,12 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2516.6   # 256 CU x 4096 flop/clk/CU x 2.4 GHz, dense
 
 # HBM-side bytes of one chain from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (each scaled by what the
-# same counter reads for a 1 GiB copy), per workload and launch mode; see profiles/*.md for the runs.
+# same counter reads for a 1 GiB copy), per workload and tile, all stages in one dispatch; see profiles/*.md for the runs.
 MEASURED_TRAFFIC_BYTES = {
-    ("gpt3_mlp", 2048, "fused"): (1035398 + 74933) * 1024,
-    ("gpt3_attn", 2048, "fused"): (1278478 + 82272) * 1024,
-    ("vgg_conv", 50176, "fused"): (327659 + 52046) * 1024,    # 56x56x256, batch 16 (the default conv shape)
+    ("gpt3_mlp", 2048, "256x192"): (1034024 + 74913) * 1024,
+    ("gpt3_attn", 2048, "256x192"): (1024481 + 81079) * 1024,
+    ("vgg_conv", 50176, "128x128"): (342122 + 52039) * 1024,    # 56x56x256, batch 16 (the default conv shape)
+    ("vgg_conv", 50176, "256x256"): (405363 + 62336) * 1024,
 }
 
 
@@ -610,7 +611,10 @@ def main():
     ss, plain = r["ss"], r["plain"]
     roof, tflops = roofline(plan, lat)
     default_shape = args.w_layout == "rows" and (args.workload != "vgg_conv" or (args.hw, args.channels, args.batch) == (56, 256, 16))
-    roof["traffic"] = MEASURED_TRAFFIC_BYTES.get((args.workload, M, best_mode)) if default_shape else None
+    # (the two-stream mode is one dispatch as well where all stages before the last fit on the chip)
+    one_dispatch = best_mode == "fused" or (best_mode == "fine" and plan.n_prod + plan.n_mid <= plan.slots)
+    roof["traffic"] = (MEASURED_TRAFFIC_BYTES.get((args.workload, M, tile_label(ds, plan.tile_prod)))
+                       if default_shape and one_dispatch else None)
     roof["traffic_source"] = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this command, recorded in profiles/ "
                               "(a constant from that run, not measured in this one)") if roof["traffic"] else None
     roof["kernel"] = "chain_kernel (all dispatches of one chain; one dispatch in fused mode)"
@@ -626,8 +630,8 @@ def main():
         "dtype": "bf16", "data": "synthetic",
         "config": {"workload": wl.name, "M": M, "policy": best_pol, "launch": best_mode,
                    # tile order of the headline variant: the library draws tiles from its dispatch queues (producer tiles
-                   # always handed out first) unless every tile has a resident workgroup of its own
-                   "order": "block index" if n_tiles <= plan.slots else "dispatch queues",
+                   # always handed out first) unless, in one-dispatch mode, every tile has a resident workgroup of its own
+                   "order": "block index" if best_mode == "fused" and n_tiles <= plan.slots else "dispatch queues",
                    "tile": ds.tile_shape(plan.tile_prod),
                    "tile_name": tile_label(ds, plan.tile_prod),
                    "tiles_producer": plan.n_prod, "tiles_middle": plan.n_mid, "tiles_consumer": plan.n_cons,
