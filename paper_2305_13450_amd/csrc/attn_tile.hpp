@@ -77,8 +77,8 @@ constexpr uint32_t ATT_PART_FLOATS = 256 * 64 + 2 * 256;
 // (writing V^T back to LDS element by element took longer than everything else together), a block has
 // one barrier, half of the next block's scores are multiplied beside the exponentials, and the
 // operands' offsets fit few registers (with more, the loop reloaded them from scratch memory and waited
-// for the DMA in flight each time).  12 heads, 2048 tokens, bf16: the longest tile (32 blocks) 185 -> 76 us,
-// of which about 20 are waits for K and V; the whole chain 438 -> 372 us.
+// for the DMA in flight each time).  12 heads, 2048 tokens, bf16: the longest tile (32 blocks) 185 -> 76 to
+// 84 us (two boards), of which about 20 are waits for K and V; the whole chain 438 -> 372 us by this.
 // NBUF: blocks in the LDS rings of K and V: 4 where the tile has the CU to itself, 2 where two workgroups
 // share it (and cover each other's waits).
 template <typename T, bool SYNC, int NBUF, class DR>
