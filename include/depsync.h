@@ -160,8 +160,8 @@ typedef struct {
                              of Tables I and IV).  0 = the library splits stages that would leave
                              most of the chip idle; 1 = never; n = n parts wherever K divides so
                              that parts start on dependency boundaries.  The parts leave fp32
-                             partial tiles in a scratch buffer the policy owns; the last to arrive
-                             adds them in K order, so results do not depend on timing.           */
+                             partial tiles in a scratch buffer the policy owns; they are added in K
+                             order, whoever comes last, so results do not depend on timing.      */
 } depsync_policy_params;
 
 #define DEPSYNC_FLAG_TRACE 16u        /* record per-tile start / ready / end times (FINE and

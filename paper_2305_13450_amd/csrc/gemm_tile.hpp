@@ -259,6 +259,16 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         }
     }
 
+    // How the parts of a tile split along K are put together.  SLICED: every part finishes a slice of the tile's rows.
+    // Else the last part to arrive finishes the whole tile: a part of a 64 x 64 tile is 16 KB, which one workgroup
+    // reads back in the round trip that a slice would take too (64 x 4096 x 1536 x 4096 20.2 us, by slices 22.8), two
+    // workgroups on a CU cover each other's exchange, and the largest tiles, hardly ever split, have no registers to
+    // spare for the code (256 x 192: 93 spilled around the tile loop, the 2048-token chain 500 -> 510 us).
+    constexpr bool SLICED = Cfg::MINB == 1 && FM * FN > 1 && FM * FN <= 9;
+    // this part of a tile split along K has been started (see the exchange of partial tiles below)
+    if (SLICED && S > 1 && tid == 0)
+        __hip_atomic_fetch_add(s.arrive + (ty * s.grid_x + tx) * SYNC_WORD_STRIDE, 1u << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
     f32x16 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -516,8 +526,8 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     dr.peek();   // the look at the dispatch queues for this workgroup's next tile travels during the epilogue
 
     // ---- split-K: leave the partial tile, and carry on only as the last part to arrive ----
-    bool finish = true;
-    if (S > 1) {
+    bool finish = !SLICED || S == 1;
+    if (!SLICED && S > 1) {
         typedef float f32x4 __attribute__((ext_vector_type(4)));
         const uint32_t tile_lin = ty * s.grid_x + tx;
         const float* const part = s.partials + (size_t)tile_lin * S * (TM * TN);
@@ -632,64 +642,238 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     // KB of straight code, executed once per tile and fetched from memory each time a chain's weights
     // had swept it out of the L2.  (A convolution has ReLU or nothing: its kernels hold no code for the others, which
     // takes 2-4 % off the chains of short tiles: four of 9x59x59x64 in fp16 68.4 -> 66.2 us.)
-    __syncthreads();   // every wave has read its last operand fragments
-    if (wctx.ok && finish) {
-        constexpr int PITCH = Cfg::WTN * 4 + 16;                    // bytes per row in LDS
-        static_assert(4 * 32 * PITCH <= Cfg::LDS_BYTES, "a block row of every wave fits the staging area");
-        char* const reg = lds + wave * (32 * PITCH);
-        const uint32_t act = s.act;
-        const uint32_t wtn_out = gate_up ? Cfg::WTN / 2 : Cfg::WTN;  // output columns of this wave
-        const uint32_t cpr = wtn_out / 8;                            // 16-byte chunks per row
-        const uint32_t col0 = n0 + wn * wtn_out;
-        const uint32_t r_first = lane / cpr, ch_first = lane % cpr, r_step = 64 / cpr, ch_step = 64 % cpr;
-        T* const Cp = (T*)s.C;
-        uint32_t ldc = uni(s.ldc);
-        asm volatile("" : "+s"(ldc));                                // (kept: the loop would read the kernel argument again per segment)
-        const ThroughBuf out(uni_ptr(Cp));                           // (an output is smaller than 4 GiB)
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            // the region is private to the wave: its own LDS writes are ordered before its reads
-            char* const w = reg + ((lane >> 5) * 4u) * PITCH + (lane & 31u) * 4u;
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) *(float*)(w + (8 * (v / 4) + (v % 4)) * PITCH + j * 128) = acc[i][j][v];
-            if (i == 0) dr.grab();   // the counters read by peek() have arrived by now: start the next tile's draw
-            const uint32_t row0 = m0 + wm * Cfg::WTM + i * 32;
-            const uint32_t rows = row0 < sM ? min(sM - row0, 32u) : 0u;
-            uint32_t r = r_first, ch = ch_first;
+    constexpr int PITCH = Cfg::WTN * 4 + 16;                    // bytes per row of a wave's piece of the staging area
+    constexpr int BR = FM >= 3 ? 2 : 1;                         // block rows transposed at a time
+    constexpr int WROWS = BR * 32;                              // rows of a piece (a slice of a split tile, at most half of the wave's rows, fits too)
+    static_assert(WROWS >= FM * 16, "half of the wave's rows");
+    constexpr int SLOT = Cfg::LDS_BYTES - 64;                   // word of the staging area behind all four pieces
+    static_assert(4 * WROWS * PITCH <= SLOT, "the pieces of every wave fit the staging area");
+    char* const reg = lds + wave * (WROWS * PITCH);
+    const uint32_t act = s.act;
+    T* const Cp = (T*)s.C;
+    const uint32_t wtn_out = gate_up ? Cfg::WTN / 2 : Cfg::WTN;  // output columns of this wave
+    const uint32_t cpr = wtn_out / 8;                            // 16-byte chunks per row
+    const uint32_t col0 = n0 + wn * wtn_out;
+    const uint32_t r_first = lane / cpr, ch_first = lane % cpr, r_step = 64 / cpr, ch_step = 64 % cpr;
+    uint32_t ldc = uni(s.ldc);
+    asm volatile("" : "+s"(ldc));                                // (kept: the loop would read the kernel argument again per segment)
+    const ThroughBuf out(uni_ptr(Cp));                           // (an output is smaller than 4 GiB)
+    // Rows 0 .. rows-1 of the wave's piece are rows row0 .. of the output: activation, rounding, store.
+    auto store_rows = [&](uint32_t row0, uint32_t rows) __attribute__((always_inline)) {
+        uint32_t r = r_first, ch = ch_first;
 #pragma unroll 1
-            for (; r < rows; r += r_step, ch += ch_step) {
-                if (ch >= cpr) { ch -= cpr; if (++r >= rows) break; }
-                const uint32_t col = col0 + ch * 8;
-                if (col >= sN) continue;
-                float x[8];
-                // gate and up columns alternate in blocks of 32
-                const char* src = reg + r * PITCH + (gate_up ? (ch >> 2) * 256 + (ch & 3u) * 32 : ch * 32);
-                __builtin_memcpy(x, __builtin_assume_aligned(src, 16), 32);
-                if (gate_up) {
-                    float u[8];
-                    __builtin_memcpy(u, __builtin_assume_aligned(src + 128, 16), 32);
+        for (; r < rows; r += r_step, ch += ch_step) {
+            if (ch >= cpr) { ch -= cpr; if (++r >= rows) break; }
+            const uint32_t col = col0 + ch * 8;
+            if (col >= sN) continue;
+            float x[8];
+            // gate and up columns alternate in blocks of 32
+            const char* src = reg + r * PITCH + (gate_up ? (ch >> 2) * 256 + (ch & 3u) * 32 : ch * 32);
+            __builtin_memcpy(x, __builtin_assume_aligned(src, 16), 32);
+            if (gate_up) {
+                float u[8];
+                __builtin_memcpy(u, __builtin_assume_aligned(src + 128, 16), 32);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] = silu_f(x[e]) * u[e];
-                } else if (AMODE != A_CONV3X3 && act == ACT_GELU) {
+                for (int e = 0; e < 8; ++e) x[e] = silu_f(x[e]) * u[e];
+            } else if (AMODE != A_CONV3X3 && act == ACT_GELU) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] = gelu_erf(x[e]);
-                } else if (act == ACT_RELU) {
+                for (int e = 0; e < 8; ++e) x[e] = gelu_erf(x[e]);
+            } else if (act == ACT_RELU) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] = fmaxf(x[e], 0.0f);
+                for (int e = 0; e < 8; ++e) x[e] = fmaxf(x[e], 0.0f);
+            }
+            V8 val;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) val[e] = (T)x[e];
+            const uint32_t at = (row0 + r) * ldc + col;
+            T* dst = Cp + at;
+            if (col + 8 <= sN) {
+                if constexpr (THROUGH) out.store16(at * 2u, 0, __builtin_bit_cast(u32x4, val));
+                else *(V8*)dst = val;
+            } else {
+                for (uint32_t e = 0; e < sN - col; ++e) store_out<THROUGH>(dst + e, (T)val[e]);
+            }
+        }
+    };
+    if (!SLICED || S == 1) {
+        __syncthreads();   // every wave has read its last operand fragments
+        if (wctx.ok && finish) {
+#pragma unroll
+            for (int i0 = 0; i0 < FM; i0 += BR) {
+                // the region is private to the wave: its own LDS writes are ordered before its reads
+                char* const w = reg + ((lane >> 5) * 4u) * PITCH + (lane & 31u) * 4u;
+#pragma unroll
+                for (int i = i0; i < FM && i < i0 + BR; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) *(float*)(w + ((i - i0) * 32 + 8 * (v / 4) + (v % 4)) * PITCH + j * 128) = acc[i][j][v];
+                if (i0 == 0) dr.grab();   // the counters read by peek() have arrived by now: start the next tile's draw
+                const uint32_t row0 = m0 + wm * Cfg::WTM + i0 * 32;
+                constexpr uint32_t most = BR * 32;
+                store_rows(row0, row0 < sM ? min(sM - row0, FM - i0 < BR ? (uint32_t)(FM - i0) * 32u : most) : 0u);
+            }
+        }
+    } else {
+        // ---- split along K: the parts exchange partial tiles, and each finishes a slice of the rows ----
+        // The wave's rows come in groups of 4 (what one half of a wave holds of a column in 4 accumulator registers:
+        // group 2 * (4 * i + q) + h, registers 4 * q .. 4 * q + 3 of block row i, lanes of half h).  Slice z, the groups
+        // slice_lo(z) .. slice_lo(z + 1) - 1 of those that have rows of the matrix, is finished by part z: it leaves
+        // everything but that slice in the scratch buffer, waits for the other parts to have done the same, adds
+        // their partials to its own in K order (the same bits whoever comes last), and stores and posts the slice.
+        // With one part finishing the whole tile, the last to arrive, that workgroup alone read S - 1 partial tiles
+        // back at one CU's rate behind a write-through of its own (64 x 192 tiles split in eight: 13 us).
+        //
+        // A part waits only if every part of its tile has been started: those are held by resident workgroups that
+        // end without its help.  If one has not been (the chip is shared with other work), the part leaves its own
+        // slice in the buffer as well, says so and goes on; the last part to publish finishes such slices.
+        // Consumers see one post per tile, as without the split, by the last part to leave.
+        // The tile's word, zero between chains: parts that have published in bits 0-7, slices left behind in bits 8-15,
+        // parts that have left in bits 16-23, parts that have started in bits 24-31.
+        constexpr uint32_t PUBLISHED = 1u, LEFT = 1u << 16;
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        const uint32_t tile_lin = ty * s.grid_x + tx;
+        const float* const part = s.partials + (size_t)tile_lin * S * (TM * TN);
+        uint32_t* const word = s.arrive + tile_lin * SYNC_WORD_STRIDE;
+        volatile uint32_t* const slot = reinterpret_cast<uint32_t*>(lds + SLOT);
+        const uint32_t tile_rows = min(sM - m0, (uint32_t)TM);
+        const uint32_t wave_row0 = wm * Cfg::WTM;
+        const uint32_t groups = (min(tile_rows, (uint32_t)Cfg::WTM) + 3) / 4;          // with rows of the matrix, first row of waves
+        const uint32_t my_groups = tile_rows > wave_row0 ? (min(tile_rows - wave_row0, (uint32_t)Cfg::WTM) + 3) / 4 : 0;
+        auto slice_lo = [&](uint32_t z) __attribute__((always_inline)) { return (z * groups + S - 1) / S; };
+        const uint32_t h = lane >> 5;
+        const uint32_t own_lo = slice_lo(kz), own_hi = slice_lo(kz + 1);
+
+        uint32_t seen = 0;
+        if (tid == 0) seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // in flight beside the stores
+        // The own slice goes to LDS, transposed.  The rest goes to the buffer in fragment order: each lane stores 16 bytes
+        // next to its neighbours' (1 KB per instruction), written through to memory so that the count can follow
+        // without a write-back of this XCD's whole L2.
+        const ThroughBuf mine(uni_ptr(part + (size_t)kz * (TM * TN)));
+        char* const w = reg + (lane & 31u) * 4u;
+        __syncthreads();   // every wave has read its last operand fragments
+#pragma unroll
+        for (int u = 0; u < FM * 4; ++u) {
+            const uint32_t g = 2 * u + h;
+            if (2 * u < my_groups) {
+                if (g >= own_lo && g < own_hi) {
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) *(float*)(w + (4 * (g - own_lo) + e) * PITCH + j * 128) = acc[u / 4][j][4 * (u % 4) + e];
+                } else if (g < my_groups) {
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        const f32x16& c = acc[u / 4][j];
+                        const f32x4 v4 = {c[4 * (u % 4)], c[4 * (u % 4) + 1], c[4 * (u % 4) + 2], c[4 * (u % 4) + 3]};
+                        mine.store16(tid * 16u, (((u / 4) * FN + j) * 4 + u % 4) * 4096, __builtin_bit_cast(u32x4, v4));
+                    }
                 }
-                V8 val;
+            }
+        }
+        // the partial is in memory before the count moves (every wave's stores, then the barrier)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        constexpr uint32_t AGAIN = 1u << 8;                      // slot: bit z: finish slice z; AGAIN: leave the own slice as well
+        if (tid == 0) {
+            uint32_t todo = 0;
+            if (own_lo != own_hi && (seen >> 24) != S) {
+                todo = AGAIN;
+            } else {
+                const uint32_t old = __hip_atomic_fetch_add(word, PUBLISHED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool last = (old & 0xffu) == S - 1;
+                if (own_lo != own_hi && (last || parts_wait(wctx, word, S))) todo = 1u << kz;
+                if (last) todo |= (old >> 8) & 0xffu;
+            }
+            *slot = todo;
+        }
+        __syncthreads();
+        uint32_t todo = uni(*slot);
+        dr.grab();   // the counters read by peek() have arrived by now: start the next tile's draw
+        if (todo == AGAIN) {
+#pragma unroll 1
+            for (uint32_t u = own_lo / 2; u < (min(own_hi, my_groups) + 1) / 2; ++u) {
+                const uint32_t g = 2 * u + h;
+                if (g < own_lo || g >= min(own_hi, my_groups)) continue;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) val[e] = (T)x[e];
-                const uint32_t at = (row0 + r) * ldc + col;
-                T* dst = Cp + at;
-                if (col + 8 <= sN) {
-                    if constexpr (THROUGH) out.store16(at * 2u, 0, __builtin_bit_cast(u32x4, val));
-                    else *(V8*)dst = val;
-                } else {
-                    for (uint32_t e = 0; e < sN - col; ++e) store_out<THROUGH>(dst + e, (T)val[e]);
+                for (int j = 0; j < FN; ++j) {
+                    f32x4 v4;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v4[e] = *(const float*)(w + (4 * (g - own_lo) + e) * PITCH + j * 128);
+                    mine.store16(tid * 16u + (((u >> 2) * FN + j) * 4 + (u & 3u)) * 4096u, 0, __builtin_bit_cast(u32x4, v4));
                 }
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();                                     // (and everyone has read the slot)
+            if (tid == 0) {
+                const uint32_t old = __hip_atomic_fetch_add(word, PUBLISHED + (0x100u << kz), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                *slot = (old & 0xffu) == S - 1 ? ((old >> 8) & 0xffu) | (1u << kz) : 0u;
+            }
+            __syncthreads();
+            todo = uni(*slot);
+        }
+        // Sum of the S <= Z parts of a slice (groups lo .. hi - 1) in K order, in fragment order, to its place in LDS.  The
+        // partials were written on other CUs and a read costs a round trip of a microsecond or two whatever its size: the
+        // loads of all parts of NB pieces (8 rows x 32 columns per wave) are in flight together.
+        auto sum_slice = [&](uint32_t lo, uint32_t hi, bool own, auto zc, auto nbc) __attribute__((always_inline)) {
+            constexpr int Z = decltype(zc)::value, NB = decltype(nbc)::value;
+            const uint32_t n_end = (hi + 1) / 2 * FN;
+#pragma unroll 1
+            for (uint32_t n0 = lo / 2 * FN; n0 < n_end; n0 += NB) {
+                f32x4 t[NB][Z];
+#pragma unroll
+                for (int z = 0; z < Z; ++z) {
+                    if ((uint32_t)z >= S || (own && (uint32_t)z == kz)) continue;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const uint32_t n = min(n0 + b, n_end - 1), u = n / FN, j = n % FN;
+                        t[b][z] = *(const f32x4*)(part + (size_t)z * (TM * TN) + (((u >> 2) * FN + j) * 4 + (u & 3u)) * 1024 + tid * 4);
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const uint32_t n = n0 + b, u = n / FN, j = n % FN, g = 2 * u + h;
+                    if (n >= n_end || g < lo || g >= hi) continue;
+                    char* const p = w + (4 * (g - lo)) * PITCH + j * 128;
+                    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int z = 0; z < Z; ++z) {
+                        if ((uint32_t)z >= S) continue;
+                        if (own && (uint32_t)z == kz) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) sum[e] += *(const float*)(p + e * PITCH);
+                        } else {
+                            sum += t[b][z];
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) *(float*)(p + e * PITCH) = sum[e];
+                }
+            }
+        };
+#pragma unroll 1
+        for (uint32_t i = 0; i < S; ++i) {                       // the own slice first: it lies in LDS
+            const uint32_t z0 = kz + i < S ? kz + i : kz + i - S;
+            if (!((todo >> z0) & 1u)) continue;
+            const uint32_t lo = slice_lo(z0), hi = min(slice_lo(z0 + 1), my_groups);
+            if (lo < hi) {
+                if (S <= 3) sum_slice(lo, hi, i == 0, std::integral_constant<int, 3>(), std::integral_constant<int, 6>());
+                else sum_slice(lo, hi, i == 0, std::integral_constant<int, 8>(), std::integral_constant<int, 2>());
+                const uint32_t row0 = m0 + wave_row0 + 4 * lo;
+                if (wctx.ok) store_rows(row0, min(4 * (hi - lo), sM - row0));
+            }
+        }
+        // The last part to leave clears the word and, every slice being in memory, posts.
+        if (SYNC && s.post_kind != DEP_NONE) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+        if (tid == 0) {
+            if (SYNC && !THROUGH && s.post_kind != DEP_NONE) write_back_l2();
+            const uint32_t old = __hip_atomic_fetch_add(word, LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (((old >> 16) & 0xffu) == S - 1) {
+                __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (SYNC && s.post_kind != DEP_NONE) post_sem(args, s, tile_lin, tx, ty);
             }
         }
     }

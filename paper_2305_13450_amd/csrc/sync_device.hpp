@@ -119,12 +119,37 @@ __device__ __forceinline__ void sem_wait(WaitCtx& w, const uint32_t* sem, uint32
     }
 }
 
+// One lane: wait until all S parts of a tile split along K have published their partial tiles (bits 0-7 of the tile's
+// word).  Every part has been started, so the wait is as long as the parts differ; false if the spin limit expired.
+__device__ __forceinline__ bool parts_wait(WaitCtx& w, const uint32_t* word, uint32_t S) {
+    const uint32_t limit = w.args->spin_limit;
+    for (uint32_t spins = 0; (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffu) != S;) {
+        if (limit != 0 && ++spins >= limit) { note_timeout(w); return false; }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    __atomic_signal_fence(__ATOMIC_ACQUIRE);
+    return true;
+}
+
 __device__ __forceinline__ void count_wait(const ChainArgs& a, bool polled) {
     if ((a.flags & DS_FLAG_COUNT) && threadIdx.x == 0) {
         __hip_atomic_fetch_add(&a.status->waits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (polled)
             __hip_atomic_fetch_add(&a.status->polling_waits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+}
+
+__device__ __forceinline__ void write_back_l2() { asm volatile("buffer_wbl2 sc1\n\ts_waitcnt vmcnt(0)" ::: "memory"); }
+
+// One lane: increment the semaphore of tile (x, y), whose output is in memory.
+__device__ __forceinline__ void post_sem(const ChainArgs& a, const StageDesc& s, uint32_t tile_lin, uint32_t x, uint32_t y) {
+    if (a.delay_tile == tile_lin + 1) {
+        for (uint32_t i = 0; i < a.delay_iters; ++i) __builtin_amdgcn_s_sleep(127);
+    }
+    const uint32_t idx = policy_sem(s.post_kind, x, y, s.grid_y, s.post_stride);
+    __hip_atomic_fetch_add(&s.post_sems[idx * SYNC_WORD_STRIDE], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.flags & DS_FLAG_COUNT)
+        __hip_atomic_fetch_add(&a.status->posts, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // post (Section III-D): called by all threads of the workgroup after the tile's stores.
@@ -135,10 +160,6 @@ __device__ __forceinline__ void post_tile(const ChainArgs& a, const StageDesc& s
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (a.delay_tile == tile_lin + 1) {
-            for (uint32_t i = 0; i < a.delay_iters; ++i) __builtin_amdgcn_s_sleep(127);
-        }
-        uint32_t idx = policy_sem(s.post_kind, x, y, s.grid_y, s.post_stride);
         // Release: the tile's output was stored with agent-scope (write-through) stores, all of
         // which have completed (vmcnt(0) of every wave, then the barrier), so no write-back of
         // the L2 is needed before the semaphore moves; a relaxed increment is enough.  (A
@@ -146,10 +167,8 @@ __device__ __forceinline__ void post_tile(const ChainArgs& a, const StageDesc& s
         // between that write-back and the increment when it sees no vector memory operation
         // pending, which let consumers on other XCDs read stale memory.)  A tile that was stored
         // with ordinary stores has the write-back and its wait spelled out here.
-        if constexpr (!THROUGH) asm volatile("buffer_wbl2 sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
-        __hip_atomic_fetch_add(&s.post_sems[idx * SYNC_WORD_STRIDE], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (a.flags & DS_FLAG_COUNT)
-            __hip_atomic_fetch_add(&a.status->posts, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (!THROUGH) write_back_l2();
+        post_sem(a, s, tile_lin, x, y);
     }
 }
 
