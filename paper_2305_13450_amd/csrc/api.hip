@@ -28,9 +28,8 @@ thread_local int g_last_hip_error = 0;
 constexpr uint32_t WS_TICKET = 0;        // 4 stages x 8 dispatch counters, one per 128-byte line
 constexpr uint32_t WS_TICKET_WORDS = 32 * SYNC_WORD_STRIDE;
 constexpr uint32_t WS_STATUS = WS_TICKET_WORDS;          // StatusBlock, 8 words
-constexpr uint32_t WS_ZERO_PAGE = WS_STATUS + 64;        // 64 words = 256 zero bytes (never written after init)
 constexpr uint32_t WS_SEMS = 2048;                       // one semaphore per 128-byte line
-static_assert(WS_ZERO_PAGE + 64 <= WS_SEMS && WS_SEMS % SYNC_WORD_STRIDE == 0, "counters, status and zero page end before the semaphores");
+static_assert(WS_STATUS + 8 <= WS_SEMS && WS_SEMS % SYNC_WORD_STRIDE == 0, "counters and status end before the semaphores");
 
 // What follows the fixed part differs between a policy's own workspace (hipMalloc'ed by
 // sync_policy_create) and the smaller one inside the library's static device array.
@@ -918,7 +917,6 @@ void fill_common(ChainArgs& a, sync_policy* pol, const Plan& p, uint32_t epoch) 
         fill_stage_geometry(st, p, s);
         st.partials = pol->scratch ? pol->scratch + p.partial_off[s] : nullptr;
         st.arrive = pol->ws + pol->lay.arrive + p.arrive_off[s] * SYNC_WORD_STRIDE;
-        st.zero_page = pol->ws + WS_ZERO_PAGE;
         if (s > 0) {
             st.sems = pol->ws + WS_SEMS + p.sem_off[s] * SYNC_WORD_STRIDE;
             st.sem_target_base = epoch * p.sem_value[s];
@@ -1657,7 +1655,7 @@ int depsync_device_info(int* n_cu, int* clock_khz) {
 
 // ---- allocation-free entry point -----------------------------------------------------------
 
-// Workspace of dep_gemm_chain_static: dispatch counters, status, zero page, semaphores and
+// Workspace of dep_gemm_chain_static: dispatch counters, status, semaphores and
 // arrival counters (STATIC_LAYOUT), then the split-K partial tiles.  In host code this name is
 // only a handle for hipGetSymbolAddress; the device address it returns (one per GPU) is what
 // kernels and fills are given.

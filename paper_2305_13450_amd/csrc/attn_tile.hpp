@@ -159,25 +159,28 @@ __device__ __forceinline__ void attn_tile(const ChainArgs& args, const StageDesc
     // a lane's 16 bytes of rows tid/16, tid/16 + 16, .. of a block (both swizzles repeat every 16 rows)
     const uint32_t frow = tid >> 4;
     const uint32_t fck = ((tid & 15u) ^ frow) * 16u, fcv = ((tid & 15u) ^ att_vswz(frow)) * 16u;
+    const OperandBuf bufN((const char*)QKV), bufC((const char*)(cached ? Kc : QKV)), bufCV((const char*)(cached ? Vc : QKV));
     auto fetch = [&](uint32_t kb, bool v) __attribute__((always_inline)) {
         char* dst = (v ? ldsV : ldsK) + (kb % NBUF) * ATT_BLK_BYTES + wave * 1024;
         const uint32_t k0 = kb * ATT_BK, fc = v ? fcv : fck;      // position in key order: cache first
+        const uint32_t colN = ((v ? 2 * E : E) + head * ATT_D) * 2u, colC = head * ATT_D * 2u;
         if (attn_block_in_one_run(k0, cached, q_last)) {
             const bool in_cache = k0 < cached;
-            const char* g = in_cache ? (const char*)((v ? Vc : Kc) + ((size_t)b * cached + k0) * ldkv + head * ATT_D)
-                                     : (const char*)(QKV + (size_t)(seq_row0 + k0 - cached) * ld + (v ? 2 * E : E) + head * ATT_D);
             const uint32_t pitch = 2u * (in_cache ? ldkv : ld), off = frow * pitch + fc;
+            const uint32_t first = in_cache ? (b * cached + k0) * pitch + colC : (seq_row0 + k0 - cached) * pitch + colN;
+            if (in_cache) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dma16(g + (size_t)i * 16u * pitch + off, dst + i * 4096);
+                for (int i = 0; i < 4; ++i) (v ? bufCV : bufC).dma16(off, first + (uint32_t)i * 16u * pitch, dst + i * 4096);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bufN.dma16(off, first + (uint32_t)i * 16u * pitch, dst + i * 4096);
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t key = k0 + i * 16 + frow;
-                const bool c = key < cached;
-                const char* base = c ? (const char*)((v ? Vc : Kc) + (size_t)b * cached * ldkv + head * ATT_D)
-                                     : (const char*)(QKV + (size_t)seq_row0 * ld + (v ? 2 * E : E) + head * ATT_D);
-                const char* g = base + (uint64_t)(c ? key : attn_key_row(key, cached, q_last)) * (2u * (c ? ldkv : ld));
-                dma16(g + fc, dst + i * 4096);
+                if (key < cached) (v ? bufCV : bufC).dma16((b * cached + key) * (2u * ldkv) + colC + fc, 0, dst + i * 4096);
+                else bufN.dma16((seq_row0 + attn_key_row(key, cached, q_last)) * (2u * ld) + colN + fc, 0, dst + i * 4096);
             }
         }
     };

@@ -48,7 +48,6 @@ struct StageDesc {
     uint32_t op, amode, bmode, act;
     // conv geometry (A_CONV3X3): image height, width, input channels
     uint32_t H, W, Cin;
-    const void* zero_page;     // >= 256 zero bytes, source for padded taps
     // attention (OP_ATTN): A = QKV, C = T
     uint32_t batch, seq, heads, head_dim;
     // keys and values of earlier tokens (token generation, Fig. 2b): [batch][cached] rows of ld_cache

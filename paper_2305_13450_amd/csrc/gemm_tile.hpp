@@ -3,7 +3,7 @@
 // 256 threads = 4 wave64s in a WM x WN grid; each wave owns a (TM/WM) x (TN/WN) sub-tile built
 // from 32x32 accumulator blocks of v_mfma_f32_32x32x16 (bf16 or f16 in, fp32 accumulate).
 // Operand tiles of 64 K-elements (128-byte rows) are DMA'd from global memory straight into
-// LDS (global_load_lds_dwordx4), two to eight stages deep (a ring per operand), with the 16-byte
+// LDS (buffer_load_dwordx4 lds), two to eight stages deep (a ring per operand), with the 16-byte
 // chunks of every row XOR swizzled so that the 128-bit fragment reads are free of bank conflicts.
 //
 // The tile is the unit the synchronisation subsystem works on (Fig. 4a of the paper): a
@@ -67,12 +67,22 @@ template <> struct Mma<_Float16> {
 // share one per-lane offset.
 __device__ __forceinline__ uint32_t swz(uint32_t r) { return (r & 7u) ^ ((r >> 3) & 1u); }
 
-typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-__device__ __forceinline__ void dma16(const char* g, char* l) {
-    __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)l, 16, 0, 0);
-}
+// Operand reads, `off` (per lane) and `uniform_off` bytes from a wave-uniform base, 16 bytes per lane straight to LDS at
+// l + 16 * lane.  A buffer instruction rather than global_load_lds: no address arithmetic per lane, and the compiler
+// counts it exactly.  global_load_lds is a FLAT instruction that touches LDS; with one in flight every wait for an
+// LDS read became a wait for all of them (2048 tokens of the 12288 x 6144 x 12288 chain 507 -> 499 us, one token of
+// 1024 x 1024 x 1024 14.1 -> 13.1).  (An operand is smaller than 4 GiB; `bytes` is where it ends: reads at
+// and past that offset, 0xfffffff0 at the latest, give zeros.)
+struct OperandBuf {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ explicit OperandBuf(const char* uniform_base, uint32_t bytes = 0xffffffffu)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc((void*)uniform_base, (short)0, (int)bytes, 0x00027000)) {}
+    __device__ __forceinline__ void dma16(uint32_t off, uint32_t uniform_off, char* l) const {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)l, 16, off, uniform_off, 0, 0);
+    }
+};
 // Store one 16-bit output element.  With the synchronisation hooks compiled in, the store is an
 // agent-scope store: it is written through this XCD's L2 to memory, so that the post needs no
 // write-back of the whole L2 before the semaphore moves.
@@ -156,12 +166,10 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     constexpr uint32_t BK = Cfg::BK, ROWB = Cfg::ROWB;
     const uint32_t KT = uni(s.K / BK);
     const uint32_t kb = kz * (KT / S), ke = kb + KT / S;   // this workgroup's K steps
-    const char* const Abase = uni_ptr(s.A);
-    const char* const Bbase = uni_ptr(s.B);
+    const OperandBuf bufA(uni_ptr(s.A), AMODE == A_CONV3X3 ? uni(s.M * s.lda * 2u) : 0xffffffffu), bufB(uni_ptr(s.B));
     const uint32_t bkstep = uni(s.b_kstep_bytes);
     // conv geometry (unused otherwise)
     const uint32_t cH = uni(s.H), cW = uni(s.W), cCin = uni(s.Cin);
-    const char* const zero_page = uni_ptr(s.zero_page);
 
     WaitCtx wctx{&args, rel_ticket, true};
     const bool tracing = SYNC && (args.flags & DS_FLAG_TRACE) && args.trace != nullptr && rel_ticket < args.trace_cap;
@@ -205,7 +213,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         uint32_t kbytes_b;   // byte offset of the K step in B
         uint32_t tap, c0;    // conv: filter tap 0..8 and first input channel of the step
         int fr, fs;
-        long shift;
+        uint32_t shift;      // (of 32 bits, like the offsets it is added to)
     } nx;
     // (A and B may be requested a different number of steps ahead, so each has its own "next")
     auto set_next_A = [&](uint32_t kt) __attribute__((always_inline)) {
@@ -214,7 +222,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
             const uint32_t k0 = kt * BK;
             nx.tap = k0 / cCin; nx.c0 = k0 % cCin;
             nx.fr = (int)(nx.tap / 3) - 1; nx.fs = (int)(nx.tap % 3) - 1;
-            nx.shift = ((long)nx.fr * (long)cW + nx.fs) * (long)cCin * 2 + (long)nx.c0 * 2;
+            nx.shift = (uint32_t)((nx.fr * (int)cW + nx.fs) * (int)cCin + (int)nx.c0) * 2u;
         }
     };
     auto set_next_B = [&](uint32_t kt) __attribute__((always_inline)) {
@@ -223,19 +231,19 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     // One 1 KB DMA instruction of the B (weights) or A operand of the next K step into `stage`.
     auto dma_B = [&](uint32_t stage, int i) __attribute__((always_inline)) {
         char* l = lds + Cfg::B_BASE + stage * Cfg::B_BYTES + wave * (NIB * 1024);
-        dma16(Bbase + nx.kbytes_b + offB[i], l + i * 1024);
+        bufB.dma16(offB[i], nx.kbytes_b, l + i * 1024);
     };
     auto dma_A = [&](uint32_t stage, int i) __attribute__((always_inline)) {
         char* l = lds + stage * Cfg::A_BYTES + wave * (NIA * 1024);
-        const char* src;
         if constexpr (AMODE == A_CONV3X3) {
-            const int y = (int)(pixyx[i] >> 16) + nx.fr, x = (int)(pixyx[i] & 0xffffu) + nx.fs;
-            const bool valid = (y >= 0) && (y < (int)cH) && (x >= 0) && (x < (int)cW);
-            src = valid ? Abase + nx.shift + offA[i] : zero_page + lpos * 16u;
+            // a tap outside the image reads past the end of the tensor, which the buffer's range check turns into zeros
+            // (every lane takes part in every request: the waits count instructions)
+            const uint32_t y = (pixyx[i] >> 16) + (uint32_t)nx.fr, x = (pixyx[i] & 0xffffu) + (uint32_t)nx.fs;   // (-1: a large number)
+            const bool valid = y < cH && x < cW;
+            bufA.dma16(valid ? offA[i] + nx.shift : 0xfffffff0u, 0, l + i * 1024);
         } else {
-            src = Abase + nx.kbytes + offA[i];
+            bufA.dma16(offA[i], nx.kbytes, l + i * 1024);
         }
-        dma16(src, l + i * 1024);
     };
     auto issue_B = [&](uint32_t stage) __attribute__((always_inline)) {
 #pragma unroll
@@ -478,11 +486,10 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         if constexpr (DEP == 2) seg = uni((kreq < ke && kreq == seg_next) ? 1u : 0u);
         nx.kbytes_b = uni(nx.kbytes_b);
         if constexpr (AMODE == A_CONV3X3) {
-            uint32_t lo = uni((uint32_t)(uint64_t)nx.shift), hi = uni((uint32_t)((uint64_t)nx.shift >> 32));
+            nx.shift = uni(nx.shift);
             uint32_t fr = uni((uint32_t)nx.fr), fs = uni((uint32_t)nx.fs);
-            asm volatile("s_waitcnt vmcnt(%6) lgkmcnt(0)\n\ts_barrier"
-                         : "+s"(lo), "+s"(hi), "+s"(fr), "+s"(fs), "+s"(nx.kbytes_b), "+s"(seg) : "n"(OUTSTANDING) : "memory");
-            nx.shift = (long)((uint64_t)lo | ((uint64_t)hi << 32));
+            asm volatile("s_waitcnt vmcnt(%5) lgkmcnt(0)\n\ts_barrier"
+                         : "+s"(nx.shift), "+s"(fr), "+s"(fs), "+s"(nx.kbytes_b), "+s"(seg) : "n"(OUTSTANDING) : "memory");
             nx.fr = (int)fr; nx.fs = (int)fs;
         } else {
             nx.kbytes = uni(nx.kbytes);
