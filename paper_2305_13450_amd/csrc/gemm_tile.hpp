@@ -161,11 +161,15 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     const bool gate_up = AMODE != A_CONV3X3 && s.bmode == B_GATE_UP;
     const uint32_t tn_out = gate_up ? TN / 2 : TN;       // output columns this tile owns
     const uint32_t S = uni(s.ksplit);                      // workgroups per output tile (split along K)
-    const uint32_t ty = tyz / S, kz = tyz % S;
+    // (No division by a runtime value where it can be helped: each is some forty dependent instructions, and the tiles
+    // of short chains have nothing to hide them behind.)
+    uint32_t ty = tyz, kz = 0;
+    if (S > 1) { ty = uni(tyz / S); kz = tyz - ty * S; }
     const uint32_t m0 = ty * TM, n0 = tx * tn_out;
     constexpr uint32_t BK = Cfg::BK, ROWB = Cfg::ROWB;
     const uint32_t KT = uni(s.K / BK);
-    const uint32_t kb = kz * (KT / S), ke = kb + KT / S;   // this workgroup's K steps
+    const uint32_t k_steps = S > 1 ? uni(KT / S) : KT;
+    const uint32_t kb = kz * k_steps, ke = kb + k_steps;   // this workgroup's K steps
     const OperandBuf bufA(uni_ptr(s.A), AMODE == A_CONV3X3 ? uni(s.M * s.lda * 2u) : 0xffffffffu), bufB(uni_ptr(s.B));
     const uint32_t bkstep = uni(s.b_kstep_bytes);
     // conv geometry (unused otherwise)
@@ -180,6 +184,13 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     const uint32_t lrow = lane / Cfg::LPR, lpos = lane % Cfg::LPR;
     uint32_t offA[NIA], offB[NIB];
     uint32_t pixyx[AMODE == A_CONV3X3 ? NIA : 1];   // conv: (y << 16) | x of the output pixel of each DMA row
+    // conv: pixel of the first row by division, the others RPD pixels on (rows past the end of the matrix are never
+    // stored: any coordinates inside the image do)
+    uint32_t px = 0, py = 0;
+    if constexpr (AMODE == A_CONV3X3) {
+        const uint32_t rem = min(m0 + wave * NIA * Cfg::RPD + lrow, sM - 1) % (cH * cW);
+        py = rem / cW; px = rem - py * cW;
+    }
 #pragma unroll
     for (int i = 0; i < NIA; ++i) {
         const uint32_t r = (wave * NIA + i) * Cfg::RPD + lrow;
@@ -187,8 +198,9 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         const uint32_t m = min(m0 + r, sM - 1);
         offA[i] = m * s.lda * 2u + c * 16u;
         if constexpr (AMODE == A_CONV3X3) {
-            const uint32_t rem = m % (cH * cW);
-            pixyx[i] = ((rem / cW) << 16) | (rem % cW);
+            pixyx[i] = (py << 16) | px;
+            px += Cfg::RPD;
+            while (px >= cW) { px -= cW; py = py + 1 == cH ? 0 : py + 1; }
         }
     }
 #pragma unroll
@@ -211,19 +223,34 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     struct NextStep {
         uint32_t kbytes;     // byte offset of the K step in a row of A
         uint32_t kbytes_b;   // byte offset of the K step in B
-        uint32_t tap, c0;    // conv: filter tap 0..8 and first input channel of the step
-        int fr, fs;
+        uint32_t c0;         // conv: first input channel of the step
+        int fr, fs;          // and its filter tap (-1..1 each)
         uint32_t shift;      // (of 32 bits, like the offsets it is added to)
     } nx;
     // (A and B may be requested a different number of steps ahead, so each has its own "next")
     auto set_next_A = [&](uint32_t kt) __attribute__((always_inline)) {
         nx.kbytes = kt * ROWB;
         if constexpr (AMODE == A_CONV3X3) {
-            const uint32_t k0 = kt * BK;
-            nx.tap = k0 / cCin; nx.c0 = k0 % cCin;
-            nx.fr = (int)(nx.tap / 3) - 1; nx.fs = (int)(nx.tap % 3) - 1;
+            uint32_t tap = 0;
+            nx.c0 = 0;
+            if (kt != 0) { tap = kt * BK / cCin; nx.c0 = kt * BK - tap * cCin; }
+            nx.fr = (int)(tap / 3) - 1; nx.fs = (int)(tap % 3) - 1;
             nx.shift = (uint32_t)((nx.fr * (int)cW + nx.fs) * (int)cCin + (int)nx.c0) * 2u;
         }
+    };
+    // conv: the K step after the one set last.  (A step on is BK channels on in memory, over the end of a tap too; from
+    // the last tap of a filter row to the next row it is a row of pixels less three.)
+    const uint32_t row_jump = AMODE == A_CONV3X3 ? uni((cW - 3) * cCin * 2u) : 0u;
+    auto step_next_A = [&]() __attribute__((always_inline)) {
+        nx.shift += ROWB;
+        nx.c0 += BK;
+        const bool tap_end = nx.c0 == cCin;
+        nx.c0 = tap_end ? 0u : nx.c0;
+        nx.fs += tap_end ? 1 : 0;
+        const bool row_end = nx.fs == 2;
+        nx.fs = row_end ? -1 : nx.fs;
+        nx.fr += row_end ? 1 : 0;
+        nx.shift += row_end ? row_jump : 0u;
     };
     auto set_next_B = [&](uint32_t kt) __attribute__((always_inline)) {
         nx.kbytes_b = kt * bkstep;
@@ -376,7 +403,8 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
 #pragma unroll
     for (int p = 0; p < NSA - 1; ++p) {
         const int pb = p - (NSA - NSB);    // B's step issued alongside A's step p
-        set_next_A(min(kb + (uint32_t)p, ke - 1));
+        if (AMODE != A_CONV3X3 || p == 0) set_next_A(min(kb + (uint32_t)p, ke - 1));
+        else if (kb + (uint32_t)p < ke) step_next_A();
         if (pb >= 0) set_next_B(min(kb + (uint32_t)pb, ke - 1));
         // the weights of the step go out before the look at the semaphores (the load/wait reordering
         // of Section IV-C), so the poll's round trip is not added to their latency
@@ -480,7 +508,8 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         // it (with a branch in that gap it did: the dependent tiles' steps were 7 % slower than
         // the same steps of a tile without dependencies).
         const uint32_t kreq = k + (NSA - 1);
-        set_next_A(min(kreq, ke - 1));
+        if constexpr (AMODE == A_CONV3X3) { if (kreq < ke) step_next_A(); }   // (past the end the last step again)
+        else set_next_A(min(kreq, ke - 1));
         set_next_B(min(k + (NSB - 1), ke - 1));
         uint32_t seg = 0;
         if constexpr (DEP == 2) seg = uni((kreq < ke && kreq == seg_next) ? 1u : 0u);
@@ -661,7 +690,9 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     const uint32_t wtn_out = gate_up ? Cfg::WTN / 2 : Cfg::WTN;  // output columns of this wave
     const uint32_t cpr = wtn_out / 8;                            // 16-byte chunks per row
     const uint32_t col0 = n0 + wn * wtn_out;
-    const uint32_t r_first = lane / cpr, ch_first = lane % cpr, r_step = 64 / cpr, ch_step = 64 % cpr;
+    constexpr uint32_t CPR = Cfg::WTN / 8, CPR_GU = Cfg::WTN / 16;
+    const uint32_t r_first = gate_up ? lane / CPR_GU : lane / CPR, ch_first = lane - r_first * cpr;
+    const uint32_t r_step = gate_up ? 64 / CPR_GU : 64 / CPR, ch_step = gate_up ? 64 % CPR_GU : 64 % CPR;
     uint32_t ldc = uni(s.ldc);
     asm volatile("" : "+s"(ldc));                                // (kept: the loop would read the kernel argument again per segment)
     const ThroughBuf out(uni_ptr(Cp));                           // (an output is smaller than 4 GiB)

@@ -52,6 +52,20 @@ def test_conv_chain_one_pixel_wide_and_tiny_images():
         pol.destroy()
 
 
+@pytest.mark.parametrize("B,H,W", [(1, 40, 1), (3, 9, 2), (2, 6, 7), (3, 5, 8), (2, 7, 9), (1, 3, 70)])
+@pytest.mark.parametrize("tile,ksplit", [(ds.TILE_256x64, 1), (ds.TILE_64x64, 2), (ds.TILE_128x128_DEEP, 2)])
+def test_conv_chain_pixels_and_taps_are_stepped_through(B, H, W, tile, ksplit):
+    # Rows of a tile are 8 pixels apart: several image rows at once where W < 8, none or one beyond.  128 channels in two
+    # parts: the second starts in the middle of a tap (K step 9 of 18).
+    print(f"conv {B}x{H}x{W} tile={tile} ksplit={ksplit}", flush=True)
+    t = inputs.conv(B, H, W, 128, 128, 64, seed=5)
+    mid_ref, out_ref = _oracle(t)
+    pol = ds.SyncPolicy(ds.ROWSYNC, ksplit=ksplit)
+    mid, out = run_conv_chain(t["x"], t["w1"], t["w2"], pol, ds.MODE_FINE, tile=tile)
+    assert mid_err(mid, mid_ref) <= TOL_MID and rel_err(out, out_ref) <= TOL_BF16
+    pol.destroy()
+
+
 def test_conv_chain_delayed_halo_row_is_waited_for():
     # 28x28x128 image: a row tile of 64 pixels spans 2.3 image rows, so a consumer tile reads three or
     # four producer row tiles (its own and the halo above and below).  Delaying a halo producer must
