@@ -138,11 +138,16 @@ int device_cus(int n_cu) {
     return cus;
 }
 
-// Relative time per flop of the macro-tile shapes on a fully occupied CU, from measurements of
-// the GPT-3 and LLaMA MLP chains at M = 1 .. 2048 on MI355X (128x192 = 1): smaller tiles read more
-// LDS and L2 bytes per flop.  With these factors the model picks the tile measured fastest on all
-// ten of those chains.
-double tile_cost_factor(int tile, bool conv) {
+// Relative time per flop of the macro-tile shapes on a fully occupied CU (128x192 = 1): smaller tiles read more LDS and L2
+// bytes per flop.  From 123 chains of nine pairs of layers (1024 to 12288 wide, plain and gated) at 70 to 2048 tokens,
+// every shape timed with weights from HBM: the choice is 1.3 % behind the fastest shape in the geometric mean and 18 % at
+// worst.  (The factors before were those of an older tile kernel: 3.5 % and 24 %; 8192 x 8192 x 8192 at 2048 tokens 470 us with
+// 256x128, 425 with 256x256; 12288 x 6144 x 12288 at 1200 tokens 404 with 128x192, 348 with 256x128.)
+// one_row: the chain has no more rows than a tile.
+// former: those factors, for these chains.  Whether StridedSync can divide the producer's columns depends on the
+// tile, and what it accepts stays as it is; attention chains, whose middle stage the model does not know, they serve (2048
+// tokens 336 us with the 256x192 tile they choose, 379 with 256x256; 300 tokens over 700 cached 115 with 128x192, 119 and more with others).
+double tile_cost_factor(int tile, bool one_row, bool former, bool conv) {
     if (conv) {
         // the implicit-GeMM gather of A (a row of pixels per DMA row, taps that re-read their
         // neighbours' rows) moves the order: measured on the VGG pairs at batch 16
@@ -157,21 +162,60 @@ double tile_cost_factor(int tile, bool conv) {
             default: break;
         }
     }
+    if (former) {
+        switch (tile) {
+            case DEPSYNC_TILE_256x256: return 1.30;
+            case DEPSYNC_TILE_256x128: return 1.04;
+            case DEPSYNC_TILE_128x256: return 1.10;
+            case DEPSYNC_TILE_64x128: return 1.6;
+            case DEPSYNC_TILE_128x128_DEEP: return 1.45;
+            default: break;
+        }
+    }
     switch (tile) {
-        case DEPSYNC_TILE_256x256: return 1.30;   // its synchronised variant spills registers around the tile loop
-        case DEPSYNC_TILE_256x128: return 1.04;
-        case DEPSYNC_TILE_128x256: return 1.10;
+        case DEPSYNC_TILE_256x256: return 0.81;   // and FIXED_STEPS_256x256
+        case DEPSYNC_TILE_256x128: return 0.98;
+        case DEPSYNC_TILE_128x256: return 1.15;
         case DEPSYNC_TILE_128x128: return 1.20;
-        case DEPSYNC_TILE_64x128: return 1.6;
+        case DEPSYNC_TILE_64x128: return one_row ? 1.37 : 2.07;   // one row of tiles: the weights are read once with any shape
         case DEPSYNC_TILE_64x64: return 2.3;
-        case DEPSYNC_TILE_256x192: return 0.93;   // one workgroup per CU, three stages of A: ahead once its tiles fill the chip
+        case DEPSYNC_TILE_256x192: return 0.93;
         case DEPSYNC_TILE_128x192: return 1.00;
         case DEPSYNC_TILE_256x64: return 1.3;
         case DEPSYNC_TILE_64x64_DEEP: return 4.0;   // one workgroup per CU: only ever worth it when tiles are few
         case DEPSYNC_TILE_64x192: return 2.0;       // likewise
         case DEPSYNC_TILE_128x192_DEEP: return 1.10;   // one workgroup per CU, 4 stages: ahead of 128x192 only
-        case DEPSYNC_TILE_128x128_DEEP: return 1.45;   // where that tile would have to split along K
+        case DEPSYNC_TILE_128x128_DEEP: return 1.31;   // where that tile would have to split along K
         default: return 2.4;
+    }
+}
+// What a 256x256 tile costs beside its K loop, in K steps: 256 accumulators a lane leave no registers for the code around it.
+constexpr uint32_t FIXED_STEPS_256x256 = 10;
+
+// Convolution tiles in microseconds: a K step with one tile on the CU and with as many as share it, what a tile costs
+// beside its steps (it has only 9 to 72 of them) and what a split along K adds.  Fitted to 54 pairs of convolutions (64
+// to 512 channels, images of 14 to 224 pixels, batches of 1 to 32), every shape timed: the choice is 2.5 % behind the fastest
+// shape in the geometric mean, 20 % at worst; one factor per shape was 17 % and 56 % behind.  (8x56x56x320 206 us with 256x64,
+// 117 with 256x192; 32x28x28x512 305 with 128x128, 237 with 256x256; 16x56x56x256 143 and 132.)  Chains of three and four
+// keep the factors (`former`): the model knows two stages, and of six such chains whose shape it would have changed two
+// lost 9 % (three of 6x47x51x320 144 -> 156 us; four of 11x9x9x448 76 -> 83).
+struct ConvTileCost { float step_alone, step_shared, fixed, split; };
+ConvTileCost conv_tile_cost(int tile) {
+    switch (tile) {
+        case DEPSYNC_TILE_256x256: return {1.44f, 1.44f, 13.0f, 23.1f};
+        case DEPSYNC_TILE_256x128: return {0.90f, 0.90f, 15.9f, 7.7f};
+        case DEPSYNC_TILE_128x256: return {0.83f, 0.83f, 14.9f, 9.9f};
+        case DEPSYNC_TILE_128x128: return {0.58f, 0.97f, 6.7f, 6.3f};
+        case DEPSYNC_TILE_64x128: return {0.32f, 0.57f, 6.5f, 4.9f};
+        case DEPSYNC_TILE_64x64: return {0.27f, 0.40f, 7.1f, 6.0f};
+        case DEPSYNC_TILE_256x192: return {1.00f, 1.00f, 12.7f, 15.1f};
+        case DEPSYNC_TILE_128x192: return {0.64f, 1.17f, 8.5f, 10.4f};
+        case DEPSYNC_TILE_256x64: return {0.75f, 1.32f, 6.0f, 3.6f};
+        case DEPSYNC_TILE_64x64_DEEP: return {0.30f, 0.30f, 8.1f, 7.0f};
+        case DEPSYNC_TILE_64x192: return {0.57f, 0.57f, 12.9f, 11.5f};
+        case DEPSYNC_TILE_128x192_DEEP: return {0.69f, 0.69f, 15.8f, 10.5f};
+        case DEPSYNC_TILE_128x128_DEEP: return {0.62f, 0.62f, 12.9f, 7.7f};
+        default: return {1.0f, 2.0f, 10.0f, 10.0f};
     }
 }
 
@@ -228,17 +272,19 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 // slots idle is modelled as the planner will run it: split along K into S parts, each costing
 // 1/S of the tile plus 15 % per further part for the partial tiles and the workgroup that sums them.
 // by_tile: the second stage's parts start on the first stage's tile boundaries (waits per producer tile).
+// conv_seg: not 0 for convolutions, K steps between the places where parts of the second may start.
+// former: by the former factors (see tile_cost_factor).
 // time (nullable): the simulated time of the choice; 0.70e-6 of it are the microseconds measured on 65 to 320 tokens
 // of fifteen pairs of layers, weights from HBM, within 10 % for most and a third for the rest.
 int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t K2, bool gate_up,
-                int n_cu, int rows_halo_tiles, bool by_tile = false, double* time = nullptr) {
+                int n_cu, uint32_t conv_seg, bool by_tile = false, bool former = false, double* time = nullptr) {
     // The simulation walks every tile of every candidate shape (a millisecond of host time for
     // the largest conv pairs, which every launch with TILE_AUTO would pay): remember the answer.
     using Key = std::array<uint64_t, 4>;
     static std::map<Key, std::pair<int, double>> memo;
     static std::mutex memo_mutex;
-    const Key key = {((uint64_t)M << 32) | n_out1, ((uint64_t)K1 << 32) | N2,
-                     ((uint64_t)K2 << 32) | (uint32_t)n_cu, ((uint64_t)(uint32_t)rows_halo_tiles << 2) | ((uint64_t)by_tile << 1) | (uint64_t)gate_up};
+    const Key key = {((uint64_t)M << 32) | n_out1, ((uint64_t)K1 << 32) | N2, ((uint64_t)K2 << 32) | (uint32_t)n_cu,
+                     ((uint64_t)conv_seg << 3) | ((uint64_t)former << 2) | ((uint64_t)by_tile << 1) | (uint64_t)gate_up};
     {
         std::lock_guard<std::mutex> lock(memo_mutex);
         const auto it = memo.find(key);
@@ -252,15 +298,23 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
         const uint32_t tn1 = gate_up ? ts->cols / 2 : ts->cols;
         const uint32_t gy = cdiv(M, ts->rows);
         const uint32_t gx1 = cdiv(n_out1, tn1), gx2 = cdiv(N2, ts->cols);
-        const double f = tile_cost_factor(t, rows_halo_tiles > 0);
+        const double f = tile_cost_factor(t, gy == 1, former, conv_seg != 0);
+        const double fixed = t == DEPSYNC_TILE_256x256 && !former ? 64.0 * FIXED_STEPS_256x256 : 0.0;
         // `occupancy` workgroups share a CU's matrix units, so each runs at 1/occupancy of its rate
         const uint32_t slots = (uint32_t)(n_cu * ts->occupancy);
         const uint32_t s1 = choose_split(nullptr, false, gx1 * gy, slots, K1 / 64, 1);
-        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, by_tile ? std::max(1u, tn1 / 64) : 1u);
-        const double d1 = f * (double)ts->rows * ts->cols * K1 * ts->occupancy / s1 * (1.0 + 0.15 * (s1 - 1));
-        const double d2 = f * (double)ts->rows * ts->cols * K2 * ts->occupancy / s2 * (1.0 + 0.15 * (s2 - 1));
-        const double tm = simulate_chain((int)slots, gx1 * s1, gy, d1, gx2 * s2, gy, d2, rows_halo_tiles,
-                                         /*stream_sync=*/false);
+        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, conv_seg && !former ? conv_seg : by_tile ? std::max(1u, tn1 / 64) : 1u);
+        double d1 = f * (double)ts->rows * ts->cols * (K1 + fixed * s1) * ts->occupancy / s1 * (1.0 + 0.15 * (s1 - 1));
+        double d2 = f * (double)ts->rows * ts->cols * (K2 + fixed * s2) * ts->occupancy / s2 * (1.0 + 0.15 * (s2 - 1));
+        if (conv_seg && !former) {
+            const ConvTileCost c = conv_tile_cost(t);
+            auto part = [&](uint64_t parts, uint32_t steps, uint32_t s) {
+                return (parts <= (uint64_t)n_cu ? c.step_alone : c.step_shared) * (double)steps / s + c.fixed + (s > 1 ? c.split : 0.0);
+            };
+            d1 = part((uint64_t)gx1 * gy * s1, K1 / 64, s1);
+            d2 = part((uint64_t)gx2 * gy * s2, K2 / 64, s2);
+        }
+        const double tm = simulate_chain((int)slots, gx1 * s1, gy, d1, gx2 * s2, gy, d2, conv_seg ? 1 : 0, /*stream_sync=*/false);
         if (best == 0 || tm < best_t) { best = t; best_t = tm; }
     }
     std::lock_guard<std::mutex> lock(memo_mutex);
@@ -475,13 +529,13 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
                     if (d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
                 } else if (steps[0] + steps[1] > 140) {
                     double model_time = 0.0;
-                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, 0, kind != DEPSYNC_ROWSYNC, &model_time);
+                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, 0, kind != DEPSYNC_ROWSYNC, false, &model_time);
                     if (!triple_pays(steps, parts, cus, model_time)) tile = other;
                 }
             }
         }
     }
-    if (!tile) tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0);
+    if (!tile) tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, attn || kind == DEPSYNC_STRIDEDSYNC);
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
     if (!ts || !tsc) return DEPSYNC_EINVAL;
@@ -663,7 +717,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     }
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
-        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, 1);
+        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, segs[1], false, n > 2);
     }
     if (!tile_shape(tile) || (mixed && !tile_shape(d->tile_cons))) return DEPSYNC_EINVAL;
 
