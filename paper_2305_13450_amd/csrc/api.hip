@@ -453,6 +453,13 @@ int finish_split(Plan& p) {
     return DEPSYNC_OK;
 }
 
+// Has the policy's workspace a semaphore for every tile of the first stage?  Where it has not, chains of more rows than any
+// measured, the former choice stands: what it accepts is accepted.
+bool fits_sems(const sync_policy* pol, int tile, uint32_t M, uint32_t cols) {
+    const TileShape* ts = tile_shape(tile);
+    return (uint64_t)cdiv(M, ts->rows) * cdiv(cols, ts->cols) <= (pol ? pol->lay : HEAP_LAYOUT).max_sems;
+}
+
 int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p) {
     if (!d) return DEPSYNC_EINVAL;
     if (d->M <= 0 || d->K1 <= 0 || d->N1 <= 0 || d->N2 <= 0) return DEPSYNC_EINVAL;
@@ -535,7 +542,12 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
             }
         }
     }
-    if (!tile) tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, attn || kind == DEPSYNC_STRIDEDSYNC);
+    if (!tile) {
+        const bool former = attn || kind == DEPSYNC_STRIDEDSYNC;
+        tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, former);
+        if (!former && !fits_sems(pol, tile, d->M, gate_up ? 2 * (uint32_t)d->N1 : (uint32_t)d->N1))
+            tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, true);
+    }
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
     if (!ts || !tsc) return DEPSYNC_EINVAL;
@@ -718,6 +730,8 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
         tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, segs[1], false, n > 2);
+        if (n == 2 && !fits_sems(pol, tile, M, d->K[0]))
+            tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, segs[1], false, true);
     }
     if (!tile_shape(tile) || (mixed && !tile_shape(d->tile_cons))) return DEPSYNC_EINVAL;
 

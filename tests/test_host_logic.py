@@ -148,6 +148,19 @@ def test_planner_auto_tile_matches_the_measured_choice(K1, N1, N2, mid, M, tile)
         assert info.tile_prod == tile and info.tile_cons == tile
 
 
+@pytest.mark.parametrize("B,HW,C,tile", [
+    (16, 56, 256, ds.TILE_256x256), (32, 28, 512, ds.TILE_256x256), (8, 56, 320, ds.TILE_256x192), (32, 28, 192, ds.TILE_128x192),
+    (4, 224, 64, ds.TILE_256x64), (8, 112, 128, ds.TILE_128x128), (4, 56, 256, ds.TILE_64x128),
+])
+def test_conv_planner_takes_the_shape_measured_fastest(B, HW, C, tile):
+    d = ds.ConvChainDesc()
+    d.B, d.H, d.W, d.C, d.K1, d.K2, d.dtype = B, HW, HW, C, C, C, ds.BF16
+    d.inp = d.w1 = d.mid = d.w2 = d.out = 0x1000
+    info = ds.PlanInfo()
+    assert ds._lib().depsync_conv_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.OK
+    assert info.tile_prod == tile and info.tile_cons == tile
+
+
 def test_conv_planner():
     d = ds.ConvChainDesc()
     d.B, d.H, d.W, d.C, d.K1, d.K2, d.dtype = 4, 56, 56, 256, 256, 256, ds.BF16
