@@ -300,9 +300,9 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     // workgroups on a CU cover each other's exchange, and the largest tiles, hardly ever split, have no registers to
     // spare for the code (256 x 192: 93 spilled around the tile loop, the 2048-token chain 500 -> 510 us).
     constexpr bool SLICED = Cfg::MINB == 1 && FM * FN > 1 && FM * FN <= 9;
-    // this part of a tile split along K has been started (see the exchange of partial tiles below)
+    // this part of a tile split along K has been started (see the exchange below)
     if (SLICED && S > 1 && tid == 0)
-        __hip_atomic_fetch_add(s.arrive + (ty * s.grid_x + tx) * SYNC_WORD_STRIDE, 1u << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(s.arrive + (ty * s.grid_x + tx) * SYNC_WORD_STRIDE, SPLIT_STARTED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     f32x16 acc[FM][FN];
 #pragma unroll
@@ -766,13 +766,11 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         // end without its help.  If one has not been (the chip is shared with other work), the part leaves its own
         // slice in the buffer as well, says so and goes on; the last part to publish finishes such slices.
         // Consumers see one post per tile, as without the split, by the last part to leave.
-        // The tile's word, zero between chains: parts that have published in bits 0-7, slices left behind in bits 8-15,
-        // parts that have left in bits 16-23, parts that have started in bits 24-31.
-        constexpr uint32_t PUBLISHED = 1u, LEFT = 1u << 16;
+        // (What is done with the tile's word, in order: split_word.hpp.)
         typedef float f32x4 __attribute__((ext_vector_type(4)));
         const uint32_t tile_lin = ty * s.grid_x + tx;
         const float* const part = s.partials + (size_t)tile_lin * S * (TM * TN);
-        uint32_t* const word = s.arrive + tile_lin * SYNC_WORD_STRIDE;
+        PartsWord word{s.arrive + tile_lin * SYNC_WORD_STRIDE, wctx};
         volatile uint32_t* const slot = reinterpret_cast<uint32_t*>(lds + SLOT);
         const uint32_t tile_rows = min(sM - m0, (uint32_t)TM);
         const uint32_t wave_row0 = wm * Cfg::WTM;
@@ -783,7 +781,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         const uint32_t own_lo = slice_lo(kz), own_hi = slice_lo(kz + 1);
 
         uint32_t seen = 0;
-        if (tid == 0) seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // in flight beside the stores
+        if (tid == 0) seen = word.load();   // in flight beside the stores
         // The own slice goes to LDS, transposed.  The rest goes to the buffer in fragment order: each lane stores 16 bytes
         // next to its neighbours' (1 KB per instruction), written through to memory so that the count can follow
         // without a write-back of this XCD's whole L2.
@@ -812,23 +810,11 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         // the partial is in memory before the count moves (every wave's stores, then the barrier)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        constexpr uint32_t AGAIN = 1u << 8;                      // slot: bit z: finish slice z; AGAIN: leave the own slice as well
-        if (tid == 0) {
-            uint32_t todo = 0;
-            if (own_lo != own_hi && (seen >> 24) != S) {
-                todo = AGAIN;
-            } else {
-                const uint32_t old = __hip_atomic_fetch_add(word, PUBLISHED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const bool last = (old & 0xffu) == S - 1;
-                if (own_lo != own_hi && (last || parts_wait(wctx, word, S))) todo = 1u << kz;
-                if (last) todo |= (old >> 8) & 0xffu;
-            }
-            *slot = todo;
-        }
+        if (tid == 0) *slot = split_publish(word, S, kz, own_lo != own_hi, split_all_started(seen, S));
         __syncthreads();
         uint32_t todo = uni(*slot);
         dr.grab();   // the counters read by peek() have arrived by now: start the next tile's draw
-        if (todo == AGAIN) {
+        if (todo == SPLIT_AGAIN) {
 #pragma unroll 1
             for (uint32_t u = own_lo / 2; u < (min(own_hi, my_groups) + 1) / 2; ++u) {
                 const uint32_t g = 2 * u + h;
@@ -843,10 +829,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();                                     // (and everyone has read the slot)
-            if (tid == 0) {
-                const uint32_t old = __hip_atomic_fetch_add(word, PUBLISHED + (0x100u << kz), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                *slot = (old & 0xffu) == S - 1 ? ((old >> 8) & 0xffu) | (1u << kz) : 0u;
-            }
+            if (tid == 0) *slot = split_publish_whole(word, S, kz);
             __syncthreads();
             todo = uni(*slot);
         }
@@ -901,18 +884,16 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
                 if (wctx.ok) store_rows(row0, min(4 * (hi - lo), sM - row0));
             }
         }
-        // The last part to leave clears the word and, every slice being in memory, posts.
+        // (the part's slices are in memory before it leaves)
         if (SYNC && s.post_kind != DEP_NONE) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
         }
         if (tid == 0) {
             if (SYNC && !THROUGH && s.post_kind != DEP_NONE) write_back_l2();
-            const uint32_t old = __hip_atomic_fetch_add(word, LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (((old >> 16) & 0xffu) == S - 1) {
-                __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            split_leave(word, S, SYNC && args.draw_cas != 0, [&]() __attribute__((always_inline)) {
                 if (SYNC && s.post_kind != DEP_NONE) post_sem(args, s, tile_lin, tx, ty);
-            }
+            });
         }
     }
 

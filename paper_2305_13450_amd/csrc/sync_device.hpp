@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 #include "chain_args.h"
 #include "dep_map.hpp"
+#include "split_word.hpp"
 
 namespace depsync {
 
@@ -130,6 +131,17 @@ __device__ __forceinline__ bool parts_wait(WaitCtx& w, const uint32_t* word, uin
     __atomic_signal_fence(__ATOMIC_ACQUIRE);
     return true;
 }
+
+// The word of a tile split along K in device memory (see split_word.hpp).  One lane.
+struct PartsWord {
+    uint32_t* p;
+    WaitCtx& w;
+    __device__ __forceinline__ uint32_t load() const { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ uint32_t add(uint32_t v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void clear() { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+    __device__ __forceinline__ bool wait_published(uint32_t S) { return parts_wait(w, p, S); }
+};
 
 __device__ __forceinline__ void count_wait(const ChainArgs& a, bool polled) {
     if ((a.flags & DS_FLAG_COUNT) && threadIdx.x == 0) {

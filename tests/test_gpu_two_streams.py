@@ -83,6 +83,34 @@ def test_side_launches_give_the_bits_of_stream_sync(chain, kind, kw):
     pol.destroy()
 
 
+@pytest.mark.parametrize("tiles", [(ds.TILE_64x192, ds.TILE_64x64), (ds.TILE_128x128_DEEP, ds.TILE_64x128)])
+@pytest.mark.parametrize("ksplit", [2, 8])
+def test_split_tiles_of_a_side_launch_chain_after_chain(tiles, ksplit):
+    # the producer, on the side stream, may still be running when the next chain begins on the same words (M = 61: one row of tiles,
+    # of which every part finishes a slice)
+    M, K1, N1, N2 = 61, 1024, 3072, 256
+    ts = [inputs.mlp(M, K1, N1, N2, seed=s) for s in (1, 2)]
+    W1t, W2t = ts[0]["W1"].t().contiguous().cuda(), ts[0]["W2"].t().contiguous().cuda()
+    Xs = [t["X"].cuda() for t in ts]
+    H, Y = (torch.empty((M, n), dtype=torch.bfloat16, device="cuda") for n in (N1, N2))
+    print(f"side launch with split tiles {tiles} ksplit={ksplit}", flush=True)
+    for kind in (ds.ROWSYNC, ds.TILESYNC):
+        pol = ds.SyncPolicy(kind, ksplit=ksplit)
+        assert ds.launch_form(ds._gemm_desc(Xs[0], W1t, H, W2t, Y, ds.MID_GELU, tiles), pol, ds.MODE_FINE) == (2, False)
+
+        def run(i, mode):
+            ds.dep_gemm_chain(Xs[i], W1t, H, W2t, Y, pol, mode=mode, tile=tiles)
+            return H.clone(), Y.clone()
+        want = [run(i, ds.MODE_STREAMSYNC) for i in (0, 1)]
+        assert not torch.equal(want[0][1], want[1][1])
+        got = [run(it & 1, ds.MODE_FINE) for it in range(40)]             # no host sync in between
+        torch.cuda.synchronize()
+        for it, (h, y) in enumerate(got):
+            assert torch.equal(h, want[it & 1][0]) and torch.equal(y, want[it & 1][1]), it
+        assert pol.status().timed_out == 0
+        pol.destroy()
+
+
 def test_chains_of_several_policies_at_once():
     # Each of these chains could hold every slot by itself.  In the default mode they draw from the
     # queues, which progress whatever the others hold.
