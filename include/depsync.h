@@ -151,9 +151,12 @@ typedef struct {
                              between tiles that share a semaphore; 0 = derive from the chain  */
     uint32_t count;       /* STRIDEDSYNC: tiles per semaphore; 0 = derive                     */
     uint32_t flags;       /* DEPSYNC_FLAG_*                                                   */
-    uint32_t spin_limit;  /* give up a wait after this many polls, record DEPSYNC_ETIMEOUT in the
-                             status and skip the tile's stores; 0 = the default bound (2^22 polls,
-                             a few seconds), 0xffffffff = wait without bound                    */
+    uint32_t spin_limit;  /* give up the wait for a producer tile after this many polls, record
+                             DEPSYNC_ETIMEOUT in the status and skip the tile's stores; 0 = the
+                             default bound (2^22 polls, a few seconds), 0xffffffff = wait without
+                             bound.  Not for the parts of a tile split along K, which wait for one
+                             another in every mode: the bound of those waits is longer than the
+                             parts' waits for producer tiles together, and a minute at the least  */
     uint32_t delay_tile;  /* debug: producer tile (row-major index) + 1 to delay; 0 = none    */
     uint32_t delay_iters; /* debug: s_sleep iterations the delayed tile spends before its post */
     uint32_t ksplit;      /* workgroups per output tile, each over an equal part of K (the grid's z

@@ -973,7 +973,7 @@ void fill_common(ChainArgs& a, sync_policy* pol, const Plan& p, uint32_t epoch) 
     a.flags = pol->params.flags;
     // 0 selects a generous default bound (seconds), so that a dependency that can never be
     // satisfied ends in DEPSYNC_ETIMEOUT instead of a hung GPU; 0xffffffff waits without bound
-    a.spin_limit = pol->params.spin_limit == 0 ? (1u << 22)
+    a.spin_limit = pol->params.spin_limit == 0 ? DEFAULT_SPIN_LIMIT
                    : pol->params.spin_limit == 0xffffffffu ? 0u : pol->params.spin_limit;
     a.delay_tile = pol->params.delay_tile;
     a.delay_iters = pol->params.delay_iters;

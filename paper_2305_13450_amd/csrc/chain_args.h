@@ -12,6 +12,8 @@ enum AMode : uint32_t { A_DENSE = 0, A_CONV3X3 = 1, A_COPY = 2 };   // A_COPY: t
 enum BMode : uint32_t { B_DENSE = 0, B_GATE_UP = 1 };
 // Epilogue applied to the fp32 accumulators before rounding to 16 bits.
 enum Act : uint32_t { ACT_NONE = 0, ACT_GELU = 1, ACT_RELU = 2, ACT_SWIGLU = 3 };
+// Polls after which a wait is given up where the caller sets no limit (a few seconds).
+constexpr uint32_t DEFAULT_SPIN_LIMIT = 1u << 22;
 // What a stage computes.
 enum StageOp : uint32_t { OP_GEMM = 0, OP_ATTN = 1 };
 

@@ -770,7 +770,11 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         typedef float f32x4 __attribute__((ext_vector_type(4)));
         const uint32_t tile_lin = ty * s.grid_x + tx;
         const float* const part = s.partials + (size_t)tile_lin * S * (TM * TN);
-        PartsWord word{s.arrive + tile_lin * SYNC_WORD_STRIDE, wctx};
+        auto sem_waits = [&]() __attribute__((always_inline)) {   // (segments of a part, row tiles of the producer at each)
+            if constexpr (DEP == 0) return 0u;
+            else return (seg_steps ? k_steps / seg_steps : 1u) * ((TM + (AMODE == A_CONV3X3 ? 2 * (cW + 1) : 0u)) / s.prod_tm + 2);
+        };
+        PartsWord<decltype(sem_waits)> word{s.arrive + tile_lin * SYNC_WORD_STRIDE, wctx, sem_waits};
         volatile uint32_t* const slot = reinterpret_cast<uint32_t*>(lds + SLOT);
         const uint32_t tile_rows = min(sM - m0, (uint32_t)TM);
         const uint32_t wave_row0 = wm * Cfg::WTM;

@@ -120,12 +120,21 @@ __device__ __forceinline__ void sem_wait(WaitCtx& w, const uint32_t* sem, uint32
     }
 }
 
-// One lane: wait until all S parts of a tile split along K have published their partial tiles (bits 0-7 of the tile's
-// word).  Every part has been started, so the wait is as long as the parts differ; false if the spin limit expired.
-__device__ __forceinline__ bool parts_wait(WaitCtx& w, const uint32_t* word, uint32_t S) {
+// One lane: wait until all S parts of a tile split along K have published their partial tiles.  Every part has been
+// started and publishes whatever becomes of its own waits, so this wait is as long as the parts differ, which may be a
+// sibling's waits at up to sem_waits() semaphores.  The spin limit is for those; the bound of this wait, there for a word
+// that something else has written to, is longer than all of them together in any mode: for each, and once more for the
+// rest of the part, the limit (the default one at least) in units of 16 polls, whose naps last as long as sem_wait's
+// longest.  False if it expired.
+template <class SemWaits>
+__device__ __forceinline__ bool parts_wait(WaitCtx& w, const uint32_t* word, uint32_t S, SemWaits sem_waits) {
     const uint32_t limit = w.args->spin_limit;
-    for (uint32_t spins = 0; (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffu) != S;) {
-        if (limit != 0 && ++spins >= limit) { note_timeout(w); return false; }
+    uint32_t polls = 0, spins = 0, periods = 0;
+    while (split_published(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != S) {
+        if (limit != 0 && (++polls & 15u) == 0 && ++spins >= max(limit, DEFAULT_SPIN_LIMIT)) {
+            spins = 0;
+            if (++periods > sem_waits()) { note_timeout(w); return false; }
+        }
         __builtin_amdgcn_s_sleep(1);
     }
     __atomic_signal_fence(__ATOMIC_ACQUIRE);
@@ -133,14 +142,16 @@ __device__ __forceinline__ bool parts_wait(WaitCtx& w, const uint32_t* word, uin
 }
 
 // The word of a tile split along K in device memory (see split_word.hpp).  One lane.
+template <class SemWaits>
 struct PartsWord {
     uint32_t* p;
     WaitCtx& w;
+    SemWaits sem_waits;   // semaphores a part of the tile waits at, at most
     __device__ __forceinline__ uint32_t load() const { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
     __device__ __forceinline__ uint32_t add(uint32_t v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
     __device__ __forceinline__ void clear() { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
     __device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-    __device__ __forceinline__ bool wait_published(uint32_t S) { return parts_wait(w, p, S); }
+    __device__ __forceinline__ bool wait_published(uint32_t S) { return parts_wait(w, p, S, sem_waits); }
 };
 
 __device__ __forceinline__ void count_wait(const ChainArgs& a, bool polled) {

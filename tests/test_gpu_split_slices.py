@@ -56,3 +56,33 @@ def test_parts_that_end_before_others_start(tile, M):
                 assert torch.equal(h.cpu().float(), H) and torch.equal(y.cpu(), Y)
         assert pol.status().timed_out == 0
         pol.destroy()
+
+
+@pytest.mark.parametrize("tile", SLICED)
+def test_the_spin_limit_is_for_dependency_waits(tile):
+    # one launch after the other: no tile waits for a producer, and the parts of a tile wait for one another however small the limit is
+    ops, H, Y = whole_numbers(129, 1536, 768, 264)
+    print(f"spin limit tile={tile}", flush=True)
+    for ksplit in (2, 8):
+        pol = ds.SyncPolicy(ds.TILESYNC, ksplit=ksplit, spin_limit=1)
+        for mode in (ds.MODE_PLAIN, ds.MODE_STREAMSYNC):
+            for _ in range(3):
+                h, y = run_gemm_chain(*ops, pol, mode, mid=ds.MID_NONE, tile=tile)
+                assert pol.status().timed_out == 0
+                assert torch.equal(h.cpu().float(), H) and torch.equal(y.cpu(), Y)
+        pol.destroy()
+
+
+@pytest.mark.parametrize("tile", [ds.TILE_64x192, ds.TILE_128x128_DEEP, ds.TILE_256x128])
+def test_parts_wait_out_a_sibling_that_waits_for_a_late_tile(tile):
+    # One tile of the producer posts a millisecond or two late.  The consumer parts that read it wait (a few thousand polls, inside
+    # the limit), their siblings wait for them, and every row is written.
+    ops, H, Y = whole_numbers(129, 1536, 768, 264)
+    print(f"late sibling tile={tile}", flush=True)
+    for ksplit in (2, 4):
+        pol = ds.SyncPolicy(ds.TILESYNC, ksplit=ksplit, spin_limit=40000, delay_tile=1, delay_iters=400)
+        for mode in (ds.MODE_FUSED, ds.MODE_FINE):
+            h, y = run_gemm_chain(*ops, pol, mode, mid=ds.MID_NONE, tile=tile)
+            assert pol.status().timed_out == 0
+            assert torch.equal(h.cpu().float(), H) and torch.equal(y.cpu(), Y)
+        pol.destroy()
