@@ -453,14 +453,8 @@ int finish_split(Plan& p) {
     return DEPSYNC_OK;
 }
 
-// Has the policy's workspace a semaphore for every tile of the first stage?  Where it has not, chains of more rows than any
-// measured, the former choice stands: what it accepts is accepted.
-bool fits_sems(const sync_policy* pol, int tile, uint32_t M, uint32_t cols) {
-    const TileShape* ts = tile_shape(tile);
-    return (uint64_t)cdiv(M, ts->rows) * cdiv(cols, ts->cols) <= (pol ? pol->lay : HEAP_LAYOUT).max_sems;
-}
-
-int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p) {
+// former_shape: where the library chooses the tile, by the former factors (see plan_to_run).
+int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape = false) {
     if (!d) return DEPSYNC_EINVAL;
     if (d->M <= 0 || d->K1 <= 0 || d->N1 <= 0 || d->N2 <= 0) return DEPSYNC_EINVAL;
     if (d->dtype != DEPSYNC_BF16 && d->dtype != DEPSYNC_FP16) return DEPSYNC_EINVAL;
@@ -536,18 +530,14 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
                     if (d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
                 } else if (steps[0] + steps[1] > 140) {
                     double model_time = 0.0;
-                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, 0, kind != DEPSYNC_ROWSYNC, false, &model_time);
+                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, 0, kind != DEPSYNC_ROWSYNC, former_shape, &model_time);
                     if (!triple_pays(steps, parts, cus, model_time)) tile = other;
                 }
             }
         }
     }
-    if (!tile) {
-        const bool former = attn || kind == DEPSYNC_STRIDEDSYNC;
-        tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, former);
-        if (!former && !fits_sems(pol, tile, d->M, gate_up ? 2 * (uint32_t)d->N1 : (uint32_t)d->N1))
-            tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, true);
-    }
+    if (!tile)
+        tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, former_shape || attn || kind == DEPSYNC_STRIDEDSYNC);
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
     if (!ts || !tsc) return DEPSYNC_EINVAL;
@@ -676,7 +666,7 @@ depsync_conv_chain_n_desc as_chain_n(const depsync_conv_chain_desc& d) {
 // Chain of n = 2..4 3x3 convolutions: stage i is conv i, each later stage depends on the one
 // before it in the way the policy says (per halo row tile, per filter row, or per filter row
 // and channel tile).
-int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int n_cu, Plan& p) {
+int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape = false) {
     if (!d) return DEPSYNC_EINVAL;
     if (d->n < 2 || d->n > 4) return DEPSYNC_EINVAL;
     if (d->B <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0) return DEPSYNC_EINVAL;
@@ -729,9 +719,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     }
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
-        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, segs[1], false, n > 2);
-        if (n == 2 && !fits_sems(pol, tile, M, d->K[0]))
-            tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, segs[1], false, true);
+        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, segs[1], false, former_shape || n > 2);
     }
     if (!tile_shape(tile) || (mixed && !tile_shape(d->tile_cons))) return DEPSYNC_EINVAL;
 
@@ -778,10 +766,12 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     return DEPSYNC_OK;
 }
 
-int plan_conv(const depsync_conv_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p) {
+int plan_any(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape) { return plan_gemm(d, pol, n_cu, p, former_shape); }
+int plan_any(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape) { return plan_conv_n(d, pol, n_cu, p, former_shape); }
+int plan_any(const depsync_conv_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape) {
     if (!d) return DEPSYNC_EINVAL;
     const depsync_conv_chain_n_desc c = as_chain_n(*d);
-    return plan_conv_n(&c, pol, n_cu, p);
+    return plan_conv_n(&c, pol, n_cu, p, former_shape);
 }
 
 // Copy chain: two stages of ceil(bytes / tile_bytes) tiles, one row of tiles each.
@@ -916,6 +906,29 @@ int check_limits(const sync_policy* pol, const Plan& p) {
     const bool fixed = pol && pol->fixed_scratch;
     if (p.n_sems > l.max_sems || p.n_arrive > l.max_arrive) return fixed ? DEPSYNC_ELIMIT : DEPSYNC_ENOMEM;
     if (fixed && p.partial_floats > pol->scratch_floats) return DEPSYNC_ELIMIT;
+    return DEPSYNC_OK;
+}
+
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// The plan a chain runs with, on `stream` if given.  Where the policy's workspace is too small for the library's choice of a tile,
+// or its scratch buffer and nothing can be allocated because the stream is being captured, the choice by the former factors
+// stands if that fits: a coarser or finer shape, or one that splits along K where the former does not, refuses nothing that
+// was accepted.  (Semaphores: chains of more rows than any measured.  Arrival counters and, in the fixed workspace, scratch: splits
+// that the caller asks for.  192 x 384 x 12480 x 6664 gated in eight parts leaves 33 M floats with 64x128 tiles, 44 M with 256x128.)
+template <class Desc>
+int plan_to_run(const Desc* d, const sync_policy* pol, int n_cu, Plan& p, const hipStream_t* stream = nullptr) {
+    auto fits = [&](const Plan& q) {
+        return check_limits(pol, q) == DEPSYNC_OK && !(stream && !pol->fixed_scratch && q.partial_floats > pol->scratch_floats && capturing(*stream));
+    };
+    if (int rc = plan_any(d, pol, n_cu, p, false); rc != DEPSYNC_OK) return rc;
+    if (fits(p)) return DEPSYNC_OK;
+    Plan former;
+    if (plan_any(d, pol, n_cu, former, true) == DEPSYNC_OK && fits(former)) p = former;
     return DEPSYNC_OK;
 }
 
@@ -1194,12 +1207,13 @@ int gemm_chain_impl(const depsync_gemm_chain_desc* d, sync_policy* pol, depsync_
         mode != DEPSYNC_MODE_FUSED)
         return DEPSYNC_EINVAL;
     Plan p;
-    int rc = plan_gemm(d, pol, 0, p);
+    const hipStream_t st = static_cast<hipStream_t>(stream_producer);
+    int rc = plan_to_run(d, pol, 0, p, &st);
     if (rc == DEPSYNC_OK) rc = check_limits(pol, p);
     if (rc != DEPSYNC_OK) return rc;
     uint32_t epoch = 0;
     if (mode != DEPSYNC_MODE_PLAIN) {
-        rc = prepare_epoch(pol, p, static_cast<hipStream_t>(stream_producer), &epoch);
+        rc = prepare_epoch(pol, p, st, &epoch);
         if (rc != DEPSYNC_OK) return rc;
     }
     ChainArgs a;
@@ -1315,7 +1329,7 @@ int depsync_gemm_chain_plan(const depsync_gemm_chain_desc* d, const sync_policy_
                             depsync_plan_info* out) {
     if (!out) return DEPSYNC_EINVAL;
     Plan p;
-    int rc = plan_gemm(d, pol, n_cu, p);
+    int rc = plan_to_run(d, pol, n_cu, p);
     if (rc == DEPSYNC_OK) rc = check_limits(pol, p);
     if (rc != DEPSYNC_OK) return rc;
     fill_plan_info(p, out);
@@ -1326,7 +1340,7 @@ int depsync_conv_chain_plan(const depsync_conv_chain_desc* d, const sync_policy_
                             depsync_plan_info* out) {
     if (!out) return DEPSYNC_EINVAL;
     Plan p;
-    int rc = plan_conv(d, pol, n_cu, p);
+    int rc = plan_to_run(d, pol, n_cu, p);
     if (rc == DEPSYNC_OK) rc = check_limits(pol, p);
     if (rc != DEPSYNC_OK) return rc;
     fill_plan_info(p, out);
@@ -1345,12 +1359,13 @@ int dep_conv_chain_n(const depsync_conv_chain_n_desc* d, sync_policy_t* pol, dep
         mode != DEPSYNC_MODE_FUSED)
         return DEPSYNC_EINVAL;
     Plan p;
-    int rc = plan_conv_n(d, pol, 0, p);
+    const hipStream_t st = static_cast<hipStream_t>(stream_producer);
+    int rc = plan_to_run(d, pol, 0, p, &st);
     if (rc == DEPSYNC_OK) rc = check_limits(pol, p);
     if (rc != DEPSYNC_OK) return rc;
     uint32_t epoch = 0;
     if (mode != DEPSYNC_MODE_PLAIN) {
-        rc = prepare_epoch(pol, p, static_cast<hipStream_t>(stream_producer), &epoch);
+        rc = prepare_epoch(pol, p, st, &epoch);
         if (rc != DEPSYNC_OK) return rc;
     }
     ChainArgs a;
@@ -1371,7 +1386,7 @@ int dep_conv_chain(const depsync_conv_chain_desc* d, sync_policy_t* pol, depsync
 int depsync_conv_chain_n_plan(const depsync_conv_chain_n_desc* d, const sync_policy_t* pol, int n_cu, depsync_plan_info* out) {
     if (!out) return DEPSYNC_EINVAL;
     Plan p;
-    int rc = plan_conv_n(d, pol, n_cu, p);
+    int rc = plan_to_run(d, pol, n_cu, p);
     if (rc == DEPSYNC_OK) rc = check_limits(pol, p);
     if (rc != DEPSYNC_OK) return rc;
     fill_plan_info(p, out);
@@ -1390,14 +1405,14 @@ static int report_launch_form(const Plan& p, const sync_policy_t* pol, depsync_m
 int depsync_gemm_chain_launch_form(const depsync_gemm_chain_desc* d, const sync_policy_t* pol, depsync_mode mode, int n_cu,
                                    int* dispatches, int* block_index) {
     Plan p;
-    if (int rc = plan_gemm(d, pol, n_cu, p); rc != DEPSYNC_OK) return rc;
+    if (int rc = plan_to_run(d, pol, n_cu, p); rc != DEPSYNC_OK) return rc;
     return report_launch_form(p, pol, mode, dispatches, block_index);
 }
 
 int depsync_conv_chain_n_launch_form(const depsync_conv_chain_n_desc* d, const sync_policy_t* pol, depsync_mode mode, int n_cu,
                                      int* dispatches, int* block_index) {
     Plan p;
-    if (int rc = plan_conv_n(d, pol, n_cu, p); rc != DEPSYNC_OK) return rc;
+    if (int rc = plan_to_run(d, pol, n_cu, p); rc != DEPSYNC_OK) return rc;
     return report_launch_form(p, pol, mode, dispatches, block_index);
 }
 
@@ -1445,10 +1460,6 @@ int dep_copy_chain(const depsync_copy_chain_desc* d, sync_policy_t* pol, depsync
 }  // extern "C"
 
 namespace {
-int plan_any(const depsync_gemm_chain_desc* d, const sync_policy* pol, Plan& p) { return plan_gemm(d, pol, 0, p); }
-int plan_any(const depsync_conv_chain_desc* d, const sync_policy* pol, Plan& p) { return plan_conv(d, pol, 0, p); }
-int plan_any(const depsync_conv_chain_n_desc* d, const sync_policy* pol, Plan& p) { return plan_conv_n(d, pol, 0, p); }
-
 // Time the library's own choice (shape 0: what it runs when nothing is remembered, with shapes and splits that
 // a remembered entry cannot name) and every macro-tile shape the chain can run with, each with and without the
 // library's split along K and with tiles drawn from the dispatch queues or named by the block index (one-dispatch
@@ -1516,7 +1527,7 @@ int autotune(const Desc* d, sync_policy* pol, hipStream_t sp, int reps, int* til
         Desc dd = *d;
         dd.tile_prod = dd.tile_cons = 0;
         Plan p;
-        if (int r = plan_any(&dd, pol, p); r != DEPSYNC_OK) return r;
+        if (int r = plan_to_run(&dd, pol, 0, p); r != DEPSYNC_OK) return r;
         *tile_out = public_tile(p.tile[0]);
     }
     if (best_ms_out) *best_ms_out = best_ms;
@@ -1895,7 +1906,7 @@ int depsync_gemm_chain_check_waits(const depsync_gemm_chain_desc* d, depsync_pol
     if (!uncovered || !valid_kind(kind)) return DEPSYNC_EINVAL;
     const sync_policy hp = host_policy(kind, params);
     Plan p;
-    if (int rc = plan_gemm(d, &hp, n_cu, p); rc != DEPSYNC_OK) return rc;
+    if (int rc = plan_to_run(d, &hp, n_cu, p); rc != DEPSYNC_OK) return rc;
     ChainArgs a;
     std::memset(&a, 0, sizeof(a));
     fill_gemm_stages(a, d);
@@ -1910,7 +1921,7 @@ int depsync_conv_chain_n_check_waits(const depsync_conv_chain_n_desc* d, depsync
     if (!uncovered || !valid_kind(kind)) return DEPSYNC_EINVAL;
     const sync_policy hp = host_policy(kind, params);
     Plan p;
-    if (int rc = plan_conv_n(d, &hp, n_cu, p); rc != DEPSYNC_OK) return rc;
+    if (int rc = plan_to_run(d, &hp, n_cu, p); rc != DEPSYNC_OK) return rc;
     ChainArgs a;
     std::memset(&a, 0, sizeof(a));
     fill_conv_stages(a, d);

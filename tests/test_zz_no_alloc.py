@@ -94,3 +94,63 @@ def test_static_entry_rejects_what_does_not_fit():
     assert ds._lib().dep_gemm_chain_static(None, ds.ROWSYNC, None, None) == ds.EINVAL
     torch.cuda.synchronize()
     assert bool((Y == 7.0).all())                  # nothing was enqueued
+
+
+def test_static_entry_takes_a_split_that_fits_with_another_shape():
+    # the caller's eight parts (six and three here) of the library's 256x128 tiles need more scratch than there is, of 64x128 tiles not
+    t = inputs.swiglu(192, 384, 12480, 6664, seed=9)
+    X, W1t, W2t, n1 = _chain(t, ds.MID_SWIGLU)
+    (H0, Y0), (Hs, Ys), (H, Y) = (_outputs(192, n1, 6664, X.dtype) for _ in range(3))
+    print("static entry: forced split near the end of the scratch", flush=True)
+    pol = ds.SyncPolicy(ds.ROWSYNC, ksplit=8)
+    info = ds.gemm_chain_plan(X, W1t, H, W2t, Y, pol, mid=ds.MID_SWIGLU)
+    rows, cols = ds.tile_shape(info.tile_prod)
+    assert (info.n_prod + info.n_cons) * rows * cols > 32 << 20
+    with pytest.raises(ds.DepsyncError) as e:
+        ds.dep_gemm_chain_static(X, W1t, H0, W2t, Y0, ds.ROWSYNC, mid=ds.MID_SWIGLU, ksplit=8, tile=info.tile_prod)
+    assert e.value.status == ds.ELIMIT
+    ds.dep_gemm_chain_static(X, W1t, Hs, W2t, Ys, ds.ROWSYNC, mid=ds.MID_SWIGLU, ksplit=8)
+    ds.dep_gemm_chain(X, W1t, H, W2t, Y, pol, mode=ds.MODE_FUSED, mid=ds.MID_SWIGLU, tile=ds.TILE_64x128)
+    torch.cuda.synchronize()
+    assert pol.status().timed_out == 0 and same(Hs, H, "H") and same(Ys, Y, "Y")
+    pol.destroy()
+
+
+def test_a_policy_takes_a_split_that_fits_with_another_shape():
+    # 41449 tiles of 256x128 have no arrival counter each in a policy's workspace (32768), 27709 of 256x192 do
+    X = torch.empty((64, 64), dtype=torch.bfloat16, device="cuda")        # (planned only)
+    d = ds._gemm_desc(X, X, X, X, X, ds.MID_NONE, ds.TILE_AUTO)
+    d.M, d.K1, d.N1, d.N2 = 58453, 512, 23104, 72
+    d.ldx = d.ldw1 = 512
+    d.ldh = d.ldw2 = 23104
+    d.ldy = 72
+    info = ds.PlanInfo()
+    for ksplit, tile in ((1, ds.TILE_256x128), (2, ds.TILE_256x192)):
+        pol = ds.SyncPolicy(ds.ROWSYNC, ksplit=ksplit)
+        assert ds._lib().depsync_gemm_chain_plan(ctypes.byref(d), pol.handle, 0, ctypes.byref(info)) == ds.OK
+        assert info.tile_prod == tile
+        pol.destroy()
+
+
+def test_a_chain_that_needs_scratch_is_captured_by_a_policy_without():
+    # the library's choice splits the second convolution; under capture there is no scratch to allocate, and the former shape needs none
+    g = torch.Generator().manual_seed(4)
+    x = torch.randn((2, 131, 25, 64), generator=g).to(torch.bfloat16).cuda()
+    ws = [(torch.randn((k, 3, 3, c), generator=g) * (2 / (9 * c)) ** 0.5).to(torch.bfloat16).cuda() for c, k in ((64, 704), (704, 392))]
+    outs = [[torch.zeros((2, 131, 25, k), dtype=torch.bfloat16, device="cuda") for k in (704, 392)] for _ in range(2)]
+    warm, cold = ds.SyncPolicy(ds.STRIDEDSYNC), ds.SyncPolicy(ds.STRIDEDSYNC)
+    info = ds.conv_chain_plan(x, ws[0], outs[0][0], ws[1], outs[0][1], warm)
+    assert info.n_cons == 3 * info.cons_grid_x * info.cons_grid_y
+    print("capture without scratch", flush=True)
+    ds.dep_conv_chain(x, ws[0], outs[0][0], ws[1], outs[0][1], warm, mode=ds.MODE_STREAMSYNC, tile=ds.TILE_64x128)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ds.dep_conv_chain(x, ws[0], outs[1][0], ws[1], outs[1][1], cold, mode=ds.MODE_FUSED, stream_producer=torch.cuda.current_stream())
+    graph.replay()
+    torch.cuda.synchronize()
+    assert cold.status().timed_out == 0
+    assert same(outs[1][0], outs[0][0], "mid") and same(outs[1][1], outs[0][1], "out")
+    del graph
+    warm.destroy()
+    cold.destroy()
