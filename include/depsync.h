@@ -431,8 +431,11 @@ int depsync_conv_chain_set_tuned(const depsync_conv_chain_desc* d, const sync_po
  * kernel before the chain.  All calls on one GPU share that GPU's array, which keeps what the last
  * call left in it (the library re-zeroes by fill kernels on `stream` whatever must start at zero
  * when the chain's geometry changes): calls must be enqueued on one stream, or otherwise be ordered
- * one after the other; chains of this entry point that overlap on one GPU race.  The status of
- * bounded waits is not readable through this entry point.                                         */
+ * one after the other; chains of this entry point that overlap on one GPU race.  A captured chain
+ * records the re-zeroing of what it uses in front of itself and may be replayed, with other calls in
+ * between; a replay counts as a call.  (So do captured chains of a policy.  From the first capture
+ * on every chain of the workspace re-zeroes.)  The status of bounded waits is not readable through
+ * this entry point.                                                                               */
 int dep_gemm_chain_static(const depsync_gemm_chain_desc* d, depsync_policy_kind kind,
                           const depsync_policy_params* params, void* stream);
 

@@ -96,6 +96,7 @@ struct sync_policy {
     size_t scratch_floats;
     uint32_t sems_dirty;   // semaphores that may be non-zero (largest count used since they were last cleared)
     bool need_reset;
+    bool in_graphs;        // a chain has been captured: what the counters are when a chain begins, replays decide
     WsLayout lay;          // where things are in ws
     bool fixed_scratch;    // ws and scratch are parts of the static device array: never (re)allocated
 };
@@ -845,6 +846,21 @@ uint64_t geom_signature(const Plan& p) {
     return h;
 }
 
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Wait on the host for a stream that takes no part in the capture under way.
+hipError_t synchronize_beside_capture(hipStream_t stream) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // (in the other modes the call would end the capture)
+    if (hipError_t e = hipThreadExchangeStreamCaptureMode(&mode); e != hipSuccess) return e;
+    const hipError_t e = hipStreamSynchronize(stream);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return e;
+}
+
 // Two-stream launches are not joined back (see launch_chain), so a side stream's launch may still
 // be winding down when a later chain starts.  That is harmless while the workspace keeps its
 // meaning (such a launch draws with compare-and-swap and finds its epoch's queues handed out), but
@@ -853,15 +869,28 @@ uint64_t geom_signature(const Plan& p) {
 int settle_side_launches(sync_policy* pol, hipStream_t stream) {
     if (!pol->side_used || !pol->ev_side) return DEPSYNC_OK;
     hipStream_t side[4] = {pol->own_stream, pol->third_stream, pol->fourth_stream, pol->last_side};
+    const bool graph = capturing(stream);        // a graph cannot wait for what is enqueued outside it: the host does
     for (int i = 0; i < 4; ++i) {
         hipStream_t st = side[i];
         if (!st) continue;
-        const hipError_t e = hipEventRecord(pol->ev_side, st);
+        const hipError_t e = graph ? synchronize_beside_capture(st) : hipEventRecord(pol->ev_side, st);
         if (e != hipSuccess) {
             // a caller's stream that no longer exists has nothing left to order
             if (i == 3) { (void)hipGetLastError(); continue; }
             return hip_fail(e);
         }
+        if (!graph) HIP_TRY(hipStreamWaitEvent(stream, pol->ev_side, 0));
+    }
+    pol->last_side = nullptr;
+    pol->side_used = false;
+    return DEPSYNC_OK;
+}
+
+// Policies whose chains are replayed from graphs: the chain's side launches end before whatever comes next on its stream.  (A
+// replay resets the counters and cannot wait for what was enqueued outside its graph.)
+int join_side_launches(sync_policy* pol, hipStream_t* side, int n, hipStream_t stream) {
+    for (int i = 0; i < n; ++i) {
+        HIP_TRY(hipEventRecord(pol->ev_side, side[i]));
         HIP_TRY(hipStreamWaitEvent(stream, pol->ev_side, 0));
     }
     pol->last_side = nullptr;
@@ -870,17 +899,22 @@ int settle_side_launches(sync_policy* pol, hipStream_t stream) {
 }
 
 // Make semaphores/counter consistent for a launch with geometry `p`; returns the epoch.
+// A captured chain is replayed with the epoch it was recorded with, whatever the counters have come to: it records the
+// reset of what it uses in front of itself, and from then on every chain of the policy resets, since the library does not see
+// the replays.
 int prepare_epoch(sync_policy* pol, const Plan& p, hipStream_t stream, uint32_t* epoch_out) {
     uint32_t total = 0, vmax = 1;
     for (int s = 0; s < p.n_stages; ++s) { total += p.n_tiles[s]; vmax = std::max(vmax, p.sem_value[s]); }
     const uint64_t sig = geom_signature(p);
     const uint64_t next = (uint64_t)(pol->epoch + 2) * std::max(total, vmax);
-    if (pol->need_reset || sig != pol->geom_sig || next >= (1ull << 31)) {
+    if (capturing(stream)) pol->in_graphs = true;
+    if (pol->need_reset || pol->in_graphs || sig != pol->geom_sig || next >= (1ull << 31)) {
         // zero the dispatch counters and every semaphore the previous geometry may have touched,
         // once no launch of an earlier chain can still be drawing from them
         if (int rc = settle_side_launches(pol, stream); rc != DEPSYNC_OK) return rc;
         hipError_t e = launch_fill_u32(pol->ws + WS_TICKET, 0u, WS_TICKET_WORDS, stream);
-        if (e == hipSuccess) e = launch_fill_u32(pol->ws + WS_SEMS, 0u, pol->sems_dirty * SYNC_WORD_STRIDE, stream);
+        const uint32_t sems = pol->in_graphs ? std::max(pol->sems_dirty, p.n_sems) : pol->sems_dirty;
+        if (e == hipSuccess) e = launch_fill_u32(pol->ws + WS_SEMS, 0u, sems * SYNC_WORD_STRIDE, stream);
         if (e == hipSuccess && pol->need_reset) {
             // a chain gave up a wait: tiles it skipped may have left arrival counts behind, and
             // the status block still shows its time-out
@@ -907,12 +941,6 @@ int check_limits(const sync_policy* pol, const Plan& p) {
     if (p.n_sems > l.max_sems || p.n_arrive > l.max_arrive) return fixed ? DEPSYNC_ELIMIT : DEPSYNC_ENOMEM;
     if (fixed && p.partial_floats > pol->scratch_floats) return DEPSYNC_ELIMIT;
     return DEPSYNC_OK;
-}
-
-bool capturing(hipStream_t stream) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
-    return st != hipStreamCaptureStatusNone;
 }
 
 // The plan a chain runs with, on `stream` if given.  Where the policy's workspace is too small for the library's choice of a tile,
@@ -1112,7 +1140,7 @@ int launch_chain(sync_policy* pol, const Plan& p, ChainArgs& a, depsync_mode mod
             pol->epoch += 1;
             pol->queue_epoch += 1;
             pol->launches += 1;
-            return DEPSYNC_OK;
+            return pol->in_graphs ? join_side_launches(pol, side, 1, sp) : DEPSYNC_OK;
         }
         HIP_TRY(hipEventRecord(pol->ev_fork, sp));
         uint32_t off = 0;
@@ -1135,6 +1163,7 @@ int launch_chain(sync_policy* pol, const Plan& p, ChainArgs& a, depsync_mode mod
         }
         a.draw_cas = 0u;
         pol->side_used = true;
+        if (pol->in_graphs) { if (int rc = join_side_launches(pol, side, last, sp); rc != DEPSYNC_OK) return rc; }
     } else {
         uint32_t off = 0;
         for (int s = 0; s < p.n_stages; ++s) {   // one launch per stage on the caller's stream
@@ -1263,6 +1292,7 @@ int sync_policy_create(depsync_policy_kind kind, const depsync_policy_params* pa
     p->scratch = nullptr;
     p->scratch_floats = 0;
     p->need_reset = false;
+    p->in_graphs = false;
     p->lay = HEAP_LAYOUT;
     p->fixed_scratch = false;
     *out = p;

@@ -154,3 +154,82 @@ def test_a_chain_that_needs_scratch_is_captured_by_a_policy_without():
     del graph
     warm.destroy()
     cold.destroy()
+
+
+def _replays(graph, poison, results, want, between):
+    for it in range(4):
+        for t in poison:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, ref in zip(results, want):
+            assert same(got, ref, f"replay {it}")
+        between(it)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M,K1,N1,N2", [(64, 1024, 1536, 512), (640, 4096, 1536, 1024), (2048, 256, 6144, 1024)])
+@pytest.mark.parametrize("kind", [ds.ROWSYNC, ds.TILESYNC])
+def test_captured_chains_give_the_same_on_every_replay(M, K1, N1, N2, kind):
+    # resident at once, split along K, and drawn from the queues; the workspace is used by other chains between the replays
+    t, other = inputs.mlp(M, K1, N1, N2, seed=11), inputs.mlp(200, 512, 768, 320, seed=12)
+    X, W1t, W2t, n1 = _chain(t, ds.MID_GELU)
+    Xo, W1o, W2o, no = _chain(other, ds.MID_GELU)
+    (H, Y), (Hs, Ys), (Hp, Yp) = (_outputs(M, n1, N2, X.dtype) for _ in range(3))
+    (Ho, Yo), (Ho1, Yo1) = (_outputs(200, no, 320, X.dtype) for _ in range(2))
+    pol, ref = ds.SyncPolicy(kind), ds.SyncPolicy(kind)
+    print(f"capture and replay {M}x{K1}x{N1}x{N2} kind={kind}", flush=True)
+    ds.dep_gemm_chain(X, W1t, H, W2t, Y, ref, mode=ds.MODE_STREAMSYNC)
+    ds.dep_gemm_chain(Xo, W1o, Ho, W2o, Yo, ref, mode=ds.MODE_STREAMSYNC)
+    ds.dep_gemm_chain(X, W1t, Hp, W2t, Yp, pol, mode=ds.MODE_FUSED)        # (scratch is allocated here)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        st = torch.cuda.current_stream()
+        ds.dep_gemm_chain_static(X, W1t, Hs, W2t, Ys, kind, stream=st)
+        ds.dep_gemm_chain(X, W1t, Hp, W2t, Yp, pol, mode=ds.MODE_FUSED, stream_producer=st)
+
+    def between(it):
+        # the other chain, and the captured one without the graph
+        for x, w1, h, w2, y in ((Xo, W1o, Ho1, W2o, Yo1), (X, W1t, Hp, W2t, Yp), (X, W1t, Hp, W2t, Yp))[it % 2:]:
+            for out in (h, y):
+                out.fill_(float("nan"))
+            ds.dep_gemm_chain_static(x, w1, h, w2, y, kind)
+            torch.cuda.synchronize()
+            assert same(h, Ho if x is Xo else H) and same(y, Yo if x is Xo else Y)
+            for out in (h, y):
+                out.fill_(float("nan"))
+            ds.dep_gemm_chain(x, w1, h, w2, y, pol, mode=ds.MODE_FINE if it & 2 else ds.MODE_FUSED)
+            torch.cuda.synchronize()
+            assert same(h, Ho if x is Xo else H) and same(y, Yo if x is Xo else Y)
+    _replays(graph, (Hs, Ys, Hp, Yp), (Hs, Ys, Hp, Yp), (H, Y, H, Y), between)
+    assert pol.status().timed_out == 0
+    del graph
+    pol.destroy()
+    ref.destroy()
+
+
+@pytest.mark.parametrize("mode", [ds.MODE_FUSED, ds.MODE_FINE])
+def test_a_chain_captured_after_side_launches(mode):
+    # 1024 producer tiles on 512 slots: the two-stream form has side launches, which a capture and its replays must not meet
+    M, K1, N1, N2 = 4096, 128, 1024, 256
+    t = inputs.mlp(M, K1, N1, N2, seed=1)
+    X, W1t, W2t, n1 = _chain(t, ds.MID_GELU)
+    (H, Y), (Hp, Yp) = (_outputs(M, n1, N2, X.dtype) for _ in range(2))
+    pol = ds.SyncPolicy(ds.ROWSYNC)
+    assert ds.launch_form(ds._gemm_desc(X, W1t, H, W2t, Y, ds.MID_GELU, ds.TILE_64x64), pol, ds.MODE_FINE) == (2, False)
+    print(f"capture after side launches mode={mode}", flush=True)
+    ds.dep_gemm_chain(X, W1t, H, W2t, Y, pol, mode=ds.MODE_FINE, tile=ds.TILE_64x64)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ds.dep_gemm_chain(X, W1t, Hp, W2t, Yp, pol, mode=mode, tile=ds.TILE_64x64, stream_producer=torch.cuda.current_stream())
+
+    def between(it):
+        Y.fill_(float("nan"))
+        ds.dep_gemm_chain(X, W1t, H, W2t, Y, pol, mode=ds.MODE_FINE, tile=ds.TILE_64x64)
+        graph.replay()                                                     # right behind, no host sync in between
+    want = (H.clone(), Y.clone())
+    _replays(graph, (Hp, Yp), (Hp, Yp, H, Y), want * 2, between)
+    assert pol.status().timed_out == 0
+    del graph
+    pol.destroy()
