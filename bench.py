@@ -24,10 +24,10 @@ PEAK_BF16_TFLOPS = 2516.6   # 256 CU x 4096 flop/clk/CU x 2.4 GHz, dense
 # HBM-side bytes of one chain from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (each scaled by what the
 # same counter reads for a 1 GiB copy), per workload and tile, all stages in one dispatch; see profiles/*.md for the runs.
 MEASURED_TRAFFIC_BYTES = {
-    ("gpt3_mlp", 2048, "256x192"): (1034024 + 74913) * 1024,
-    ("gpt3_attn", 2048, "256x192"): (1024481 + 81079) * 1024,
-    ("vgg_conv", 50176, "128x128"): (342122 + 52039) * 1024,    # 56x56x256, batch 16 (the default conv shape)
-    ("vgg_conv", 50176, "256x256"): (405363 + 62336) * 1024,
+    ("gpt3_mlp", 2048, "256x192"): (1033787 + 74913) * 1024,
+    ("gpt3_attn", 2048, "256x192"): (1044170 + 81078) * 1024,
+    ("vgg_conv", 50176, "128x128"): (352578 + 52040) * 1024,    # 56x56x256, batch 16 (the default conv shape)
+    ("vgg_conv", 50176, "256x256"): (400891 + 61828) * 1024,
 }
 
 

@@ -143,7 +143,8 @@ int device_cus(int n_cu) {
 // bytes per flop.  From 123 chains of nine pairs of layers (1024 to 12288 wide, plain and gated) at 70 to 2048 tokens,
 // every shape timed with weights from HBM: the choice is 1.3 % behind the fastest shape in the geometric mean and 18 % at
 // worst.  (The factors before were those of an older tile kernel: 3.5 % and 24 %; 8192 x 8192 x 8192 at 2048 tokens 470 us with
-// 256x128, 425 with 256x256; 12288 x 6144 x 12288 at 1200 tokens 404 with 128x192, 348 with 256x128.)
+// 256x128, 425 with 256x256; 12288 x 6144 x 12288 at 1200 tokens 404 with 128x192, 348 with 256x128.  Of 45 chains outside the fit
+// whose shape is another for it, 4 % faster in the geometric mean, 11 are 3 to 17 % slower.)
 // one_row: the chain has no more rows than a tile.
 // former: those factors, for these chains.  Whether StridedSync can divide the producer's columns depends on the
 // tile, and what it accepts stays as it is; attention chains, whose middle stage the model does not know, they serve (2048
@@ -197,7 +198,8 @@ constexpr uint32_t FIXED_STEPS_256x256 = 10;
 // beside its steps (it has only 9 to 72 of them) and what a split along K adds.  Fitted to 54 pairs of convolutions (64
 // to 512 channels, images of 14 to 224 pixels, batches of 1 to 32), every shape timed: the choice is 2.5 % behind the fastest
 // shape in the geometric mean, 20 % at worst; one factor per shape was 17 % and 56 % behind.  (8x56x56x320 206 us with 256x64,
-// 117 with 256x192; 32x28x28x512 305 with 128x128, 237 with 256x256; 16x56x56x256 143 and 132.)  Chains of three and four
+// 117 with 256x192; 32x28x28x512 305 with 128x128, 237 with 256x256; 16x56x56x256 143 and 132.  Of 60 pairs outside the fit whose
+// shape is another for it, 22 % faster in the geometric mean, 5 are 4 to 16 % slower.)  Chains of three and four
 // keep the factors (`former`): the model knows two stages, and of six such chains whose shape it would have changed two
 // lost 9 % (three of 6x47x51x320 144 -> 156 us; four of 11x9x9x448 76 -> 83).
 struct ConvTileCost { float step_alone, step_shared, fixed, split; };
@@ -271,12 +273,13 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 // Pick one macro-tile for both stages by simulating the fine-grained schedule of the chain
 // on `slots` workgroup slots for every candidate shape (host_model.h).  A stage that would leave
 // slots idle is modelled as the planner will run it: split along K into S parts, each costing
-// 1/S of the tile plus 15 % per further part for the partial tiles and the workgroup that sums them.
+// 1/S of the tile plus 15 % per further part for the exchange of partial tiles (convolutions: see conv_tile_cost).
 // by_tile: the second stage's parts start on the first stage's tile boundaries (waits per producer tile).
 // conv_seg: not 0 for convolutions, K steps between the places where parts of the second may start.
 // former: by the former factors (see tile_cost_factor).
-// time (nullable): the simulated time of the choice; 0.70e-6 of it are the microseconds measured on 65 to 320 tokens
-// of fifteen pairs of layers, weights from HBM, within 10 % for most and a third for the rest.
+// time (nullable): the simulated time of the choice, in units of which 0.70e-6 were microseconds with the former factors and
+// kernels (65 to 320 tokens of fifteen pairs of layers, weights from HBM).  Now they are 0.41e-6 to 0.62e-6, 0.54e-6 in the middle
+// (24 chains of 75 to 1130 rows at the edge of triple_pays).
 int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t K2, bool gate_up,
                 int n_cu, uint32_t conv_seg, bool by_tile = false, bool former = false, double* time = nullptr) {
     // The simulation walks every tile of every candidate shape (a millisecond of host time for
@@ -342,8 +345,8 @@ int policy_dep_kind_conv(int kind) {
 // Workgroups per output tile for a stage with `tiles` output tiles and `kt` K steps whose
 // dependency segments start every `seg` steps: split when the stage would leave at least half
 // of the slots idle, as far as one wave of slots allows, keeping every part at least min_steps
-// steps long (16: the partial tiles and the arrival count cost about 10 us per stage; with the small
-// tiles of the three-per-CU shape less, see triple_split) and starting on a segment boundary.
+// steps long (16: the exchange of the partial tiles cost some 10 us per stage when this was chosen, 7 to 8 where
+// every part finishes a slice; with the small tiles of the three-per-CU shape less, see triple_split) and starting on a segment boundary.
 // `tuned_off`: the autotuner found this chain faster without.
 // (Splitting a stage of more tiles than slots so that it ends in a fuller last round was measured
 // and is not done: LLaMA MLP at 2048 tokens, 344 producer tiles on 256 slots as 688 halves, three
@@ -414,9 +417,11 @@ bool triple_fits(int n, int cus, const uint32_t (&tiles)[4], const uint32_t (&kt
 // Two GeMMs of several row tiles that fit, with parts that add up to more than 140 steps: 64 x 64 tiles read every
 // element of A and B 64 times from LDS, and a step takes 0.44 us with one part per CU and half as much again with
 // three, whatever the HBM delivers.  Chains of shorter parts are ahead by 5 to 50 % all the same; these only where the
-// model, whose time is known to 10 %, has nothing better (4096 x 11008 x 4096 at 128 tokens 84 against 171 us).  Turned
+// model has nothing better (4096 x 11008 x 4096 at 128 tokens 84 against 171 us).  Turned
 // away: 12288 x 3072 x 12288 at 192 tokens 118 against 89 us, 8192 x 8192 x 8192 at 128 117 against 102, 12288 x 6144
-// x 12288 at 128 126 against 112.  (Not seen: 11008 x 4096 x 1024 at 256 and 320 tokens, 84 and 96 against 74 and 87.)
+// x 12288 at 128 126 against 112.  With the present factors more are: of 40 chains that they turned away or took in
+// anew 37 were right, 20 % faster in the geometric mean (287 x 11328 x 1664 x 7776 90 -> 59 us), three 5 to 9 % slower (157 x 5632 x 5120 x 10312
+// 89 -> 97).  The scale, 0.70e-6, is still that of the former factors: a smaller one, see choose_tile, would turn away more.
 bool triple_pays(const uint32_t (&steps)[4], const uint32_t (&parts)[4], int cus, double model_time) {
     double us = 0.0;
     for (int s = 0; s < 2; ++s) us += steps[s] * (0.44 + 0.154 * std::max(0.0, (double)parts[s] / cus - 1.0));

@@ -671,7 +671,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     // ---- epilogue: activation, round to 16 bits, store ----
     // Accumulator layout of the 32x32 block: lane holds column (lane % 32) and rows
     // 8*(v/4) + 4*(lane/32) + v%4 for v = 0..15, i.e. a lane's values run DOWN a column.  Each
-    // wave therefore transposes its sub-tile, 32 rows at a time and in fp32, through its own piece of the
+    // wave therefore transposes its sub-tile, 32 or 64 rows at a time (BR) and in fp32, through its own piece of the
     // (now idle) operand staging area, and a loop over 16-byte row segments applies the activation,
     // rounds and stores: whole lines instead of 2-byte pieces for the write-through stores.  The loop is
     // what keeps the code short: with the activation unrolled over the accumulators a kernel was 70 to 290
@@ -758,7 +758,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         // group 2 * (4 * i + q) + h, registers 4 * q .. 4 * q + 3 of block row i, lanes of half h).  Slice z, the groups
         // slice_lo(z) .. slice_lo(z + 1) - 1 of those that have rows of the matrix, is finished by part z: it leaves
         // everything but that slice in the scratch buffer, waits for the other parts to have done the same, adds
-        // their partials to its own in K order (the same bits whoever comes last), and stores and posts the slice.
+        // their partials to its own in K order (the same bits whoever comes last), and stores the slice.
         // With one part finishing the whole tile, the last to arrive, that workgroup alone read S - 1 partial tiles
         // back at one CU's rate behind a write-through of its own (64 x 192 tiles split in eight: 13 us).
         //

@@ -138,9 +138,10 @@ def test_planner_auto_tile_prefers_more_tiles_for_small_m():
     (8192, 2752, 8192, ds.MID_SWIGLU, 1024, ds.TILE_256x128),
     (8192, 2752, 8192, ds.MID_SWIGLU, 2048, ds.TILE_256x128),
 ])
-def test_planner_auto_tile_matches_the_measured_choice(K1, N1, N2, mid, M, tile):
-    # the schedule model (split along K included) on a 256-CU chip picks the macro-tile that was
-    # measured fastest on these MLP chains; asked twice, it answers the same (the choice is remembered)
+def test_planner_auto_tile_on_the_mlp_chains(K1, N1, N2, mid, M, tile):
+    # the schedule model (split along K included) on a 256-CU chip picks a macro-tile within 2 % of the fastest
+    # measured on these MLP chains (gated, 2048 tokens: 256x128 260-263 us, 256x256 260-265); asked twice, it answers
+    # the same (the choice is remembered)
     d = _fake_gemm_desc(M, K1, N1, N2, mid=mid)
     info = ds.PlanInfo()
     for _ in range(2):
