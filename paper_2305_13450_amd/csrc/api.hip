@@ -114,6 +114,7 @@ struct Plan {
     uint32_t stride[4];
     uint32_t out_tm[4], out_tn[4];   // rows / columns of its own output one tile of stage s covers
     uint32_t ksplit[4];              // workgroups per output tile (split along K)
+    uint32_t k_steps[4], part_seg[4];   // of a GeMM stage: K steps, and steps between the places where a part may start
     uint32_t arrive_off[4];          // first arrival counter of the stage
     size_t partial_off[4];           // first float of the stage's partial tiles
     size_t partial_floats;           // scratch the chain needs
@@ -268,7 +269,7 @@ int tuned_tile(const TuneKey& k) {
 }
 
 uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, uint32_t slots, uint32_t kt, uint32_t seg,
-                      uint32_t min_steps = 16);
+                      uint32_t few, uint32_t min_steps = 16);
 
 // Pick one macro-tile for both stages by simulating the fine-grained schedule of the chain
 // on `slots` workgroup slots for every candidate shape (host_model.h).  A stage that would leave
@@ -306,8 +307,8 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
         const double fixed = t == DEPSYNC_TILE_256x256 && !former ? 64.0 * FIXED_STEPS_256x256 : 0.0;
         // `occupancy` workgroups share a CU's matrix units, so each runs at 1/occupancy of its rate
         const uint32_t slots = (uint32_t)(n_cu * ts->occupancy);
-        const uint32_t s1 = choose_split(nullptr, false, gx1 * gy, slots, K1 / 64, 1);
-        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, conv_seg && !former ? conv_seg : by_tile ? std::max(1u, tn1 / 64) : 1u);
+        const uint32_t s1 = choose_split(nullptr, false, gx1 * gy, slots, K1 / 64, 1, 0);
+        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, conv_seg && !former ? conv_seg : by_tile ? std::max(1u, tn1 / 64) : 1u, 0);
         double d1 = f * (double)ts->rows * ts->cols * (K1 + fixed * s1) * ts->occupancy / s1 * (1.0 + 0.15 * (s1 - 1));
         double d2 = f * (double)ts->rows * ts->cols * (K2 + fixed * s2) * ts->occupancy / s2 * (1.0 + 0.15 * (s2 - 1));
         if (conv_seg && !former) {
@@ -344,7 +345,13 @@ int policy_dep_kind_conv(int kind) {
 
 // Workgroups per output tile for a stage with `tiles` output tiles and `kt` K steps whose
 // dependency segments start every `seg` steps: split when the stage would leave at least half
-// of the slots idle, as far as one wave of slots allows, keeping every part at least min_steps
+// of the slots idle, as far as one wave of slots allows.  Into equal parts if those occupy more than `few` workgroups (half of
+// the CUs); else the parts may differ by one segment (k_part), if at least 12 or, with the longer exchange of larger tiles, 24
+// steps go by that: a prime number of steps was not split at all (16 x 6592 x 896 x 6096 35.9 -> 21.1 us; 3 x 5312 x 576 x 2624
+// 29.6 -> 15.7; 58 x 2752 x 896 x 4480 26.6 -> 20.6).  Without these limits other chains lost: 256 x 1024 x 4096 x 1024 in 320
+// parts of 13 steps instead of 256 of 16, unevenly spread over the CUs, 19.8 -> 23.1; 35 steps in two halves 57 -> 64.
+// few = 0: equal parts only (and what the caller asks for, always).
+// Every part is at least min_steps
 // steps long (16: the exchange of the partial tiles cost some 10 us per stage when this was chosen, 7 to 8 where
 // every part finishes a slice; with the small tiles of the three-per-CU shape less, see triple_split) and starting on a segment boundary.
 // `tuned_off`: the autotuner found this chain faster without.
@@ -353,16 +360,20 @@ int policy_dep_kind_conv(int kind) {
 // rounds of 64 steps instead of two of 128: 275 -> 283 us; the 88 MB of partial tiles and the
 // finishing workgroups cost more than the shorter last round gains.)
 uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, uint32_t slots, uint32_t kt, uint32_t seg,
-                      uint32_t min_steps) {
+                      uint32_t few, uint32_t min_steps) {
     const uint32_t want = pol ? pol->params.ksplit : 0;
     if (want == 1 || seg == 0 || (want == 0 && tuned_off)) return 1;
+    uint32_t equal = 1;
     static const uint32_t cand[] = {8, 6, 4, 3, 2};
     for (uint32_t S : cand) {
         if (kt % S || (kt / S) % seg) continue;
         if (want > 1) { if (S <= want) return S; continue; }
-        if (tiles * S <= slots && kt / S >= min_steps) return S;
+        if (tiles * S <= slots && kt / S >= min_steps) { equal = S; break; }
     }
-    return 1;
+    if (want > 1 || tiles * equal > few) return equal;
+    for (uint32_t S = 8; S > equal; --S)
+        if (tiles * S <= slots && kt / seg / S * seg >= min_steps && kt / equal - kt / S >= (min_steps > 12 ? 24u : 12u)) return S;
+    return equal;
 }
 
 // Splits along K of a chain of 64x64 tiles of which three share a CU.  The parts of ALL stages are kept resident at
@@ -374,10 +385,10 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 // tiles, kt, seg: output tiles, K steps and steps between dependency segments of each stage; S: its split, left
 // alone where kt = 0 (not a GeMM).
 void triple_split(const sync_policy* pol, int n, uint32_t slots, const uint32_t (&tiles)[4], const uint32_t (&kt)[4],
-                  const uint32_t (&seg)[4], uint32_t (&S)[4]) {
+                  const uint32_t (&seg)[4], uint32_t few, uint32_t (&S)[4]) {
     constexpr uint32_t min_steps = 12u;
     for (int s = 0; s < n; ++s)
-        if (kt[s]) S[s] = choose_split(pol, false, tiles[s], slots / (uint32_t)n, kt[s], seg[s], min_steps);
+        if (kt[s]) S[s] = choose_split(pol, false, tiles[s], slots / (uint32_t)n, kt[s], seg[s], few, min_steps);
     if (pol && pol->params.ksplit) return;
     for (;;) {
         uint32_t total = 0;
@@ -387,7 +398,7 @@ void triple_split(const sync_policy* pol, int n, uint32_t slots, const uint32_t 
             if (kt[s] && S[s] > 1 && (most < 0 || tiles[s] * S[s] > tiles[most] * S[most])) most = s;
         }
         if (total <= slots || most < 0) return;
-        S[most] = choose_split(pol, false, tiles[most], tiles[most] * S[most] - 1, kt[most], seg[most], min_steps);
+        S[most] = choose_split(pol, false, tiles[most], tiles[most] * S[most] - 1, kt[most], seg[most], few, min_steps);
     }
 }
 
@@ -400,13 +411,13 @@ void triple_split(const sync_policy* pol, int n, uint32_t slots, const uint32_t 
 // The other is for several row tiles: see triple_pays.
 // tiles, kt, seg: as above, kt = 0 for an attention stage.  steps, parts: of each stage as it would be split.
 bool triple_fits(int n, int cus, const uint32_t (&tiles)[4], const uint32_t (&kt)[4], const uint32_t (&seg)[4],
-                 uint32_t (&steps)[4], uint32_t (&parts)[4]) {
+                 uint32_t few, uint32_t (&steps)[4], uint32_t (&parts)[4]) {
     const uint32_t slots = (uint32_t)(cus * tile_shape(TILE_64x64_TRIPLE)->occupancy);
     uint64_t total = 0;
     for (int s = 0; s < n; ++s) total += tiles[s];
     if (total > slots) return false;
     uint32_t S[4] = {1, 1, 1, 1};
-    triple_split(nullptr, n, slots, tiles, kt, seg, S);
+    triple_split(nullptr, n, slots, tiles, kt, seg, few, S);
     for (int s = 0; s < n; ++s) {
         parts[s] = tiles[s] * S[s]; steps[s] = kt[s] / S[s];
         if (2 * parts[s] <= (uint32_t)cus && steps[s] > 32) return false;
@@ -436,7 +447,7 @@ bool wide_fills(uint32_t M, uint32_t N, uint32_t K, int cus) {
     const TileShape* ts = tile_shape(DEPSYNC_TILE_64x192);
     if (N % ts->cols) return false;
     const uint32_t tiles = N / ts->cols * cdiv(M, ts->rows);
-    return tiles * choose_split(nullptr, false, tiles, (uint32_t)cus, K / 64, (uint32_t)ts->cols / 64) * 10 >= (uint32_t)cus * 9;
+    return tiles * choose_split(nullptr, false, tiles, (uint32_t)cus, K / 64, (uint32_t)ts->cols / 64, 0) * 10 >= (uint32_t)cus * 9;
 }
 
 // Fill in tile counts, arrival counters and partial-tile offsets once grids and splits are known.
@@ -519,6 +530,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
     const int kind = effective_kind(d, pol, pol ? default_kind(d) : DEPSYNC_ROWSYNC);
+    const uint32_t few = former_shape ? 0u : (uint32_t)cus / 2;   // parts of a stage that may be unequal (choose_split)
     // (whether StridedSync divides the producer's columns depends on the tile: what it accepts stays as it is)
     if (!tile && !gate_up && (attn ? d->seq == 1 : kind != DEPSYNC_STRIDEDSYNC)) {
         const uint32_t rows = cdiv(d->M, 64), seg[4] = {1, 1, 1, 1};
@@ -526,11 +538,11 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         if (attn) {
             const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, (uint32_t)d->batch * d->heads, cdiv(d->N2, 64) * rows, 0};
             const uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, K2 / 64, 0};
-            if (triple_fits(3, cus, tiles, kts, seg, steps, parts)) tile = TILE_64x64_TRIPLE;
+            if (triple_fits(3, cus, tiles, kts, seg, few, steps, parts)) tile = TILE_64x64_TRIPLE;
         } else {
             const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, cdiv(d->N2, 64) * rows, 0, 0};
             const uint32_t kts[4] = {(uint32_t)d->K1 / 64, K2 / 64, 0, 0};
-            if (triple_fits(2, cus, tiles, kts, seg, steps, parts)) {
+            if (triple_fits(2, cus, tiles, kts, seg, few, steps, parts)) {
                 tile = TILE_64x64_TRIPLE;
                 if (rows == 1) {
                     if (d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
@@ -612,7 +624,8 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     p.n_sems = off;
     p.slots = cus * ts->occupancy;
     // split along K where a stage is much smaller than the chip (not the prompt-phase attention stage)
-    p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], (uint32_t)p.stage_slots[0], d->K1 / 64, 1);
+    p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], (uint32_t)p.stage_slots[0], d->K1 / 64, 1, few);
+    p.k_steps[0] = d->K1 / 64; p.part_seg[0] = 1;
     if (attn && d->seq == 1) {
         // token generation: the keys of a (head, sequence) pair over up to 8 workgroups, at least 256
         // keys each, as far as one wave of slots allows
@@ -637,11 +650,12 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     {
         const uint32_t dk = p.dep_kind[last];
         const uint32_t seg = (dk == DEP_ROW) ? 1u : p.out_tn[last - 1] / 64;
-        p.ksplit[last] = choose_split(pol, tuned_off, p.n_tiles[last], (uint32_t)p.stage_slots[last], K2 / 64, seg);
+        p.ksplit[last] = choose_split(pol, tuned_off, p.n_tiles[last], (uint32_t)p.stage_slots[last], K2 / 64, seg, few);
+        p.k_steps[last] = K2 / 64; p.part_seg[last] = seg;
         if (tile == TILE_64x64_TRIPLE) {
             uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, 0, 0}, segs[4] = {1, 1, 1, 1};
             kts[last] = K2 / 64; segs[last] = seg;
-            triple_split(pol, p.n_stages, (uint32_t)p.slots, p.n_tiles, kts, segs, p.ksplit);
+            triple_split(pol, p.n_stages, (uint32_t)p.slots, p.n_tiles, kts, segs, few, p.ksplit);
         }
     }
     if (int rc = finish_split(p); rc != DEPSYNC_OK) return rc;
@@ -721,7 +735,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     if (!tile) {
         uint32_t tiles[4] = {0, 0, 0, 0}, steps[4], parts[4];
         for (int i = 0; i < n; ++i) tiles[i] = cdiv(d->K[i], 64) * cdiv(M, 64);
-        if (triple_fits(n, cus, tiles, kts, segs, steps, parts)) tile = TILE_64x64_TRIPLE;
+        if (triple_fits(n, cus, tiles, kts, segs, 0, steps, parts)) tile = TILE_64x64_TRIPLE;
     }
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
@@ -758,9 +772,11 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         }
         p.n_sems += p.sem_count[s];
     }
-    for (int s = 0; s < n; ++s)
-        p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], (uint32_t)p.stage_slots[s], kts[s], segs[s]);
-    if (tile == TILE_64x64_TRIPLE) triple_split(pol, n, (uint32_t)p.slots, p.n_tiles, kts, segs, p.ksplit);
+    for (int s = 0; s < n; ++s) {
+        p.ksplit[s] = choose_split(pol, tuned_off, p.n_tiles[s], (uint32_t)p.stage_slots[s], kts[s], segs[s], 0);
+        p.k_steps[s] = kts[s]; p.part_seg[s] = segs[s];
+    }
+    if (tile == TILE_64x64_TRIPLE) triple_split(pol, n, (uint32_t)p.slots, p.n_tiles, kts, segs, 0, p.ksplit);
     if (int rc = finish_split(p); rc != DEPSYNC_OK) return rc;
     const double Md = (double)M;
     p.flops = 0.0;
@@ -988,6 +1004,12 @@ void fill_stage_geometry(StageDesc& st, const Plan& p, int s) {
     st.grid_y = p.grid_y[s];
     st.queue_by_col = p.grid_x[s] >= 8 ? 1u : 0u;
     st.ksplit = p.ksplit[s];
+    if (p.ksplit[s] > 1 && p.part_seg[s]) {
+        const uint32_t units = p.k_steps[s] / p.part_seg[s];
+        st.part_seg = p.part_seg[s];
+        st.part_steps = units / p.ksplit[s] * p.part_seg[s];
+        st.part_extra = units % p.ksplit[s];
+    }
     st.dep_kind = s > 0 ? p.dep_kind[s] : DEP_NONE;
     if (s > 0) {
         st.sem_value = p.sem_value[s];
@@ -1863,6 +1885,7 @@ int64_t uncovered_waits(const Plan& p, const ChainArgs& a, int s) {
     if (st.op == OP_ATTN) return uncovered_attn_waits(st, p.sem_count[s]);
     const uint32_t TM = (uint32_t)ts->rows;
     const uint32_t KT = st.K / 64, S = st.ksplit;
+    if (S > 1 && (st.part_seg == 0 || st.part_steps < st.part_seg)) return 1;
     const uint32_t seg_steps = dep_seg_steps(st);
     int64_t bad = 0;
     std::vector<uint8_t> waited(p.sem_count[s]);
@@ -1870,7 +1893,7 @@ int64_t uncovered_waits(const Plan& p, const ChainArgs& a, int s) {
         const uint32_t m0 = ty * TM, m_last = std::min(m0 + TM, st.M) - 1;
         for (uint32_t kz = 0; kz < S; ++kz) {
             std::fill(waited.begin(), waited.end(), 0);
-            const uint32_t kb = kz * (KT / S), ke = kb + KT / S;
+            const uint32_t kb = S > 1 ? k_part(st, kz, KT).kb : 0, ke = S > 1 ? k_part(st, kz, KT).ke : KT;
             uint32_t seg_next = kb;
             bool ok = true;
             for (uint32_t k = kb; k < ke && ok; ++k) {

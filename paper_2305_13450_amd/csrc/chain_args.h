@@ -41,10 +41,11 @@ struct StageDesc {
     uint32_t b_row_bytes, b_kstep_bytes;
     uint32_t grid_x, grid_y;   // column tiles, row tiles
     uint32_t queue_by_col;     // dispatch queue of tile (x,y): x mod 8 if set, else (y*grid_x + x) mod 8
-    // split-K: each output tile is computed by `ksplit` workgroups over equal K ranges; they leave
+    // split-K: each output tile is computed by `ksplit` workgroups over (nearly) equal K ranges, see k_part; they leave
     // fp32 partial tiles in `partials` and count in `arrive`, and the last one to arrive adds the
     // partials in K order, applies the epilogue and posts.  The dispatch sees grid_y * ksplit rows.
     uint32_t ksplit;
+    uint32_t part_steps, part_extra, part_seg;
     float* partials;           // [tile][ksplit][TM*TN] fp32, fragment order
     uint32_t* arrive;          // one counter per tile (SYNC_WORD_STRIDE words apart), zero between chains
     uint32_t op, amode, bmode, act;

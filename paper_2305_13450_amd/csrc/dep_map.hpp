@@ -54,6 +54,16 @@ __host__ __device__ __forceinline__ uint32_t dep_seg_steps(const StageDesc& s) {
     }
 }
 
+// K steps of part kz of a stage split along K: parts start on multiples of part_seg steps, the first part_extra of them
+// are one such piece longer than the others, the last one also takes what is left of the K steps.
+struct KRange { uint32_t kb, ke; };
+__host__ __device__ __forceinline__ KRange k_part(const StageDesc& s, uint32_t kz, uint32_t k_steps) {
+    KRange r;
+    r.kb = kz * s.part_steps + dm_min(kz, s.part_extra) * s.part_seg;
+    r.ke = kz + 1 == s.ksplit ? k_steps : (kz + 1) * s.part_steps + dm_min(kz + 1, s.part_extra) * s.part_seg;
+    return r;
+}
+
 // Does the A slice of K step kt start a new dependency segment, and on what?
 // kb: first K step of this workgroup's K range (0 unless the stage is split along K).
 __host__ __device__ __forceinline__ bool dep_segment(const StageDesc& s, uint32_t m0, uint32_t tm, uint32_t kt, uint32_t kb, DepRange& r) {

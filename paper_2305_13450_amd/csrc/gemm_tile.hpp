@@ -168,8 +168,8 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     const uint32_t m0 = ty * TM, n0 = tx * tn_out;
     constexpr uint32_t BK = Cfg::BK, ROWB = Cfg::ROWB;
     const uint32_t KT = uni(s.K / BK);
-    const uint32_t k_steps = S > 1 ? uni(KT / S) : KT;
-    const uint32_t kb = kz * k_steps, ke = kb + k_steps;   // this workgroup's K steps
+    uint32_t kb = 0, ke = KT;                              // this workgroup's K steps
+    if (S > 1) { const KRange r = k_part(s, kz, KT); kb = uni(r.kb); ke = uni(r.ke); }
     const OperandBuf bufA(uni_ptr(s.A), AMODE == A_CONV3X3 ? uni(s.M * s.lda * 2u) : 0xffffffffu), bufB(uni_ptr(s.B));
     const uint32_t bkstep = uni(s.b_kstep_bytes);
     // conv geometry (unused otherwise)
@@ -772,7 +772,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         const float* const part = s.partials + (size_t)tile_lin * S * (TM * TN);
         auto sem_waits = [&]() __attribute__((always_inline)) {   // (segments of a part, row tiles of the producer at each)
             if constexpr (DEP == 0) return 0u;
-            else return (seg_steps ? k_steps / seg_steps : 1u) * ((TM + (AMODE == A_CONV3X3 ? 2 * (cW + 1) : 0u)) / s.prod_tm + 2);
+            else return (seg_steps ? (ke - kb) / seg_steps + 1u : 1u) * ((TM + (AMODE == A_CONV3X3 ? 2 * (cW + 1) : 0u)) / s.prod_tm + 2);
         };
         PartsWord<decltype(sem_waits)> word{s.arrive + tile_lin * SYNC_WORD_STRIDE, wctx, sem_waits};
         volatile uint32_t* const slot = reinterpret_cast<uint32_t*>(lds + SLOT);

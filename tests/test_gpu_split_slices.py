@@ -164,3 +164,23 @@ def test_slices_of_a_middle_convolution(tile, kind):
         assert (rel_err(res[0][i], ref) <= TOL_BF16) if i == 2 else (mid_err(res[0][i], ref) <= TOL_MID), i
     assert pol.status().timed_out == 0
     pol.destroy()
+
+
+@pytest.mark.parametrize("M,K1,N1,N2", [(16, 5312, 1088, 264), (1, 6592, 1856, 72), (100, 4544, 832, 200), (300, 4288, 1472, 520)])
+def test_parts_that_differ_by_a_piece(M, K1, N1, N2):
+    # numbers of K steps that the library's own split does not divide (83, 103, 71 and 67 in the first stage)
+    ops, H, Y = whole_numbers(M, K1, N1, N2)
+    uneven = 0
+    for tile in [ds.TILE_AUTO, ds.TILE_64x64] + SLICED:
+        print(f"uneven parts M={M} K1={K1} tile={tile}", flush=True)
+        for kind in (ds.ROWSYNC, ds.TILESYNC):
+            pol = ds.SyncPolicy(kind)
+            for mode in MODES:
+                h, y = run_gemm_chain(*ops, pol, mode, mid=ds.MID_NONE, tile=tile)
+                assert torch.equal(h.cpu().float(), H) and torch.equal(y.cpu(), Y)
+            assert pol.status().timed_out == 0
+            a = [t.cuda().contiguous() for t in (ops[0], ops[1].t(), ops[2].t())]
+            plan = ds.gemm_chain_plan(a[0], a[1], torch.empty_like(h), a[2], torch.empty_like(y), pol, mid=ds.MID_NONE, tile=tile)
+            uneven += (K1 // 64) % (plan.n_prod // (plan.prod_grid_x * plan.prod_grid_y)) != 0
+            pol.destroy()
+    assert uneven >= 6

@@ -238,6 +238,15 @@ def test_every_slice_a_consumer_tile_loads_is_covered_by_a_wait(kind):
     assert checked > 100
 
 
+@pytest.mark.parametrize("kind", [ds.ROWSYNC, ds.TILESYNC])
+def test_parts_of_unequal_length_are_covered_by_waits(kind):
+    # K steps of both stages that no number of parts divides, at every tile shape and the library's own choice
+    for tile in [ds.TILE_AUTO] + ALL_TILES:
+        for (M, K1, N1, N2) in ((1, 2752, 1088, 4096), (16, 6592, 896, 6096), (90, 1088, 2752, 1024), (200, 4288, 3136, 2048)):
+            d = _fake_gemm_desc(M, K1, N1, N2, mid=ds.MID_GELU, tile=tile)
+            assert ds.gemm_chain_check_waits(d, kind, n_cu=256, ksplit=0) == 0, (tile, M, K1, N1, N2)
+
+
 @pytest.mark.parametrize("kind", [ds.ROWSYNC, ds.TILESYNC, ds.STRIDEDSYNC])
 def test_every_row_an_attention_tile_reads_is_covered_by_a_wait(kind):
     # A tile reads its keys in blocks of 64 that start at the cache, so with a cache whose length is no
