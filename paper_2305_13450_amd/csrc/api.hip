@@ -538,14 +538,15 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         if (attn) {
             const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, (uint32_t)d->batch * d->heads, cdiv(d->N2, 64) * rows, 0};
             const uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, K2 / 64, 0};
-            if (triple_fits(3, cus, tiles, kts, seg, few, steps, parts)) tile = TILE_64x64_TRIPLE;
+            if (triple_fits(3, cus, tiles, kts, seg, few, steps, parts)) tile = d->M <= 32 ? TILE_32x64 : TILE_64x64_TRIPLE;
         } else {
             const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, cdiv(d->N2, 64) * rows, 0, 0};
             const uint32_t kts[4] = {(uint32_t)d->K1 / 64, K2 / 64, 0, 0};
             if (triple_fits(2, cus, tiles, kts, seg, few, steps, parts)) {
                 tile = TILE_64x64_TRIPLE;
                 if (rows == 1) {
-                    if (d->M > 32 && wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
+                    if (d->M <= 32) tile = TILE_32x64;
+                    else if ( wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
                 } else if (steps[0] + steps[1] > 140) {
                     double model_time = 0.0;
                     const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, 0, kind != DEPSYNC_ROWSYNC, former_shape, &model_time);
@@ -652,7 +653,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         const uint32_t seg = (dk == DEP_ROW) ? 1u : p.out_tn[last - 1] / 64;
         p.ksplit[last] = choose_split(pol, tuned_off, p.n_tiles[last], (uint32_t)p.stage_slots[last], K2 / 64, seg, few);
         p.k_steps[last] = K2 / 64; p.part_seg[last] = seg;
-        if (tile == TILE_64x64_TRIPLE) {
+        if (tile == TILE_64x64_TRIPLE || tile == TILE_32x64) {
             uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, 0, 0}, segs[4] = {1, 1, 1, 1};
             kts[last] = K2 / 64; segs[last] = seg;
             triple_split(pol, p.n_stages, (uint32_t)p.slots, p.n_tiles, kts, segs, few, p.ksplit);
@@ -832,7 +833,7 @@ int plan_copy(const depsync_copy_chain_desc* d, const sync_policy* pol, int n_cu
     return DEPSYNC_OK;
 }
 
-int public_tile(int tile) { return tile == TILE_64x64_TRIPLE ? DEPSYNC_TILE_64x64 : tile; }
+int public_tile(int tile) { return tile == TILE_64x64_TRIPLE || tile == TILE_32x64 ? DEPSYNC_TILE_64x64 : tile; }
 
 void fill_plan_info(const Plan& p, depsync_plan_info* o) {
     std::memset(o, 0, sizeof(*o));

@@ -95,6 +95,11 @@ using Cfg128x192Deep = TileCfg<128, 192, 2, 2, 1, 4>;   // 160 KB: three K steps
 using Cfg128x128Deep = TileCfg<128, 128, 2, 2, 1, 4>;   // 128 KB: three K steps in flight
 
 using Cfg64x64Triple = TileCfg<64, 64, 2, 2, 3, 3>;   // 3 x 48 KB
+// Up to 32 rows.  These chains wait for weights, and half of what a 64x64 tile stages of A for them is copies of the last
+// row: with 32 rows the LDS of three workgroups holds a fourth step.  The tile has only two blocks of 32x32, so two
+// waves share one, each with every other pair of a step's K slices (one token of 12288 x 6144 x 12288 74.8 -> 72.7 us, four
+// sequences' attention tokens 72.8 -> 67.3, 2 x 3008 x 4032 x 11960 58.2 -> 45.9 with uneven parts).
+using Cfg32x64 = TileCfg<32, 64, 1, 2, 3, 4, 0, 2>;   // 3 x 48 KB
 
 template <class Cfg, typename T, uint32_t AMODE, int MIDK>
 static hipError_t launch_cfg(bool sync, uint32_t n_blocks, hipStream_t stream, const ChainArgs& a) {
@@ -124,8 +129,17 @@ static hipError_t launch_family(int tile, bool sync, uint32_t n_blocks, hipStrea
         case TILE_64x64_TRIPLE:
             if constexpr (MIDK != 1) return launch_cfg<Cfg64x64Triple, T, AMODE, MIDK>(sync, n_blocks, stream, a);
             return hipErrorInvalidValue;   // (not planned: the prompt-phase attention tile does not fit its LDS)
-        default: return hipErrorInvalidValue;
+        default: break;
     }
+    if constexpr (AMODE == A_DENSE) {
+        switch (tile) {
+            case TILE_32x64:
+                if constexpr (MIDK != 1) return launch_cfg<Cfg32x64, T, AMODE, MIDK>(sync, n_blocks, stream, a);
+                break;
+            default: break;
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace depsync

@@ -25,12 +25,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <int TM_, int TN_, int WM_, int WN_, int MINB_, int NSTAGE_, int NSTB_ = 0>
+// WK: waves that share a sub-tile, each with 1 / WK of a step's K slices; the first adds up what they have at the end.
+template <int TM_, int TN_, int WM_, int WN_, int MINB_, int NSTAGE_, int NSTB_ = 0, int WK_ = 1>
 struct TileCfg {
     static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, MINB = MINB_;
     static constexpr int BK = 64;                     // K elements per pipeline step
     static constexpr int ROWB = BK * 2;               // bytes per LDS row: one 128-byte line of the operand
-    static constexpr int KK = BK / 16;                // 16-wide K slices (one MFMA deep) per step
+    static constexpr int WK = WK_;
+    static constexpr int KK = BK / 16 / WK;           // 16-wide K slices (one MFMA deep) per step and wave
     static constexpr int RPD = 1024 / ROWB;           // operand rows one 1 KB DMA instruction fills
     static constexpr int LPR = ROWB / 16;             // lanes (16-byte chunks) per row
     static constexpr int NSTAGE = NSTAGE_;               // LDS stages of the A operand: NSTAGE-1 K steps in flight
@@ -41,7 +43,7 @@ struct TileCfg {
     static constexpr int A_BYTES = TM * ROWB, B_BYTES = TN * ROWB;
     static constexpr int B_BASE = NSTAGE * A_BYTES;      // the B stages follow the A stages
     static constexpr int LDS_BYTES = NSTAGE * A_BYTES + NSTB * B_BYTES;
-    static_assert(WM * WN == 4, "four waves per workgroup");
+    static_assert(WM * WN * WK == 4, "four waves per workgroup");
     static_assert(NSTB >= 2 && NSTAGE >= NSTB && MINB * LDS_BYTES <= 160 * 1024, "stages must fit the 160 KB LDS");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is made of 32x32 blocks");
     static_assert(TM % (4 * RPD) == 0 && TN % (4 * RPD) == 0, "each wave issues whole DMA groups");
@@ -156,7 +158,9 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = uni(tid >> 6);
-    const uint32_t wm = wave / Cfg::WN, wn = wave % Cfg::WN;
+    constexpr uint32_t NW = Cfg::WM * Cfg::WN;             // sub-tiles; wave w and, where waves share them, w + NW work on the same
+    const uint32_t kw = wave / NW, wm = wave % NW / Cfg::WN, wn = wave % Cfg::WN;
+    const bool holds = Cfg::WK == 1 || kw == 0;            // this wave holds a sub-tile after the K loop
     const uint32_t sM = uni(s.M), sN = uni(s.N);
     const bool gate_up = AMODE != A_CONV3X3 && s.bmode == B_GATE_UP;
     const uint32_t tn_out = gate_up ? TN / 2 : TN;       // output columns this tile owns
@@ -289,8 +293,9 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         const uint32_t h = lane >> 5;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-            aoff[kk] = ra * ROWB + ((((uint32_t)kk * 2u + h) ^ swz(ra)) << 4);
-            boff[kk] = rb * ROWB + ((((uint32_t)kk * 2u + h) ^ swz(rb)) << 4);
+            const uint32_t c = (kw * KK + (uint32_t)kk) * 2u + h;
+            aoff[kk] = ra * ROWB + ((c ^ swz(ra)) << 4);
+            boff[kk] = rb * ROWB + ((c ^ swz(rb)) << 4);
         }
     }
 
@@ -561,6 +566,22 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     dr.peek();   // the look at the dispatch queues for this workgroup's next tile travels during the epilogue
 
+    if constexpr (Cfg::WK > 1) {   // the waves of a sub-tile add up
+        static_assert(Cfg::WK == 2 && FM * FN == 1 && Cfg::MINB > 1, "two waves, one block each");
+        float* const half = reinterpret_cast<float*>(lds) + (wave % NW) * 1024 + lane;
+        __syncthreads();   // every wave has read its last operand fragments
+        if (!holds) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) half[v * 64] = acc[0][0][v];
+        }
+        __syncthreads();
+        if (holds) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[0][0][v] += half[v * 64];
+        }
+    }
+    constexpr uint32_t NT = 64 * NW;   // threads that hold values of the tile
+
     // ---- split-K: leave the partial tile, and carry on only as the last part to arrive ----
     bool finish = !SLICED || S == 1;
     if (!SLICED && S > 1) {
@@ -571,15 +592,17 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
         // written through to memory so that the count below can follow without a write-back
         // of this XCD's whole L2
         const ThroughBuf mine(uni_ptr(part + (size_t)kz * (TM * TN)));
+        if (holds) {
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
+                for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v4 = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    mine.store16(tid * 16u, ((i * FN + j) * 4 + q) * 4096, __builtin_bit_cast(u32x4, v4));
-                }
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 v4 = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                        mine.store16(tid * 16u, ((i * FN + j) * 4 + q) * NT * 16u, __builtin_bit_cast(u32x4, v4));
+                    }
+        }
         // the partial is in memory before the count moves (every wave's stores, then the barrier)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
@@ -616,6 +639,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
             constexpr int ACCF = FM * FN * 16;                                   // accumulator floats per lane
             constexpr int ROOM = Cfg::MINB == 1 ? (472 - ACCF < 192 ? 472 - ACCF : 192) : (Cfg::MINB == 2 ? 216 : 112) - ACCF;
             constexpr int PARTS_IN_FLIGHT = ROOM / ACCF > 8 ? 8 : ROOM / ACCF;
+            const uint32_t at = holds ? tid << 2 : 0u;   // (a wave that holds nothing adds up what nobody reads)
             if constexpr (PARTS_IN_FLIGHT >= 1) {
                 constexpr int NV = FM * FN * 4;                                  // 16-byte loads per lane and part
                 for (uint32_t z0 = 0; z0 < S; z0 += PARTS_IN_FLIGHT) {
@@ -625,9 +649,9 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
 #pragma unroll
                     for (int d = 0; d < PARTS_IN_FLIGHT; ++d) {
                         const uint32_t z = min(z0 + d, S - 1);
-                        const float* src = part + (size_t)z * (TM * TN) + (tid << 2);
+                        const float* src = part + (size_t)z * (TM * TN) + at;
 #pragma unroll
-                        for (int u = 0; u < NV; ++u) t4[d][u] = *(const f32x4*)(src + ((u * 256) << 2));
+                        for (int u = 0; u < NV; ++u) t4[d][u] = *(const f32x4*)(src + u * NT * 4);
                     }
 #pragma unroll
                     for (int d = 0; d < PARTS_IN_FLIGHT; ++d) {
@@ -648,14 +672,14 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
                 // no room for a whole part: one row of blocks of one part at a time
                 for (uint32_t z = 0; z < S; ++z) {
                     if (own && z == kz) continue;
-                    const float* src = part + (size_t)z * (TM * TN) + (tid << 2);
+                    const float* src = part + (size_t)z * (TM * TN) + at;
 #pragma unroll
                     for (int i = 0; i < FM; ++i) {
                         f32x4 t4[FN][4];
 #pragma unroll
                         for (int j = 0; j < FN; ++j)
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) t4[j][q] = *(const f32x4*)(src + ((((i * FN + j) * 4 + q) * 256) << 2));
+                            for (int q = 0; q < 4; ++q) t4[j][q] = *(const f32x4*)(src + ((i * FN + j) * 4 + q) * NT * 4);
 #pragma unroll
                         for (int j = 0; j < FN; ++j)
 #pragma unroll
@@ -735,7 +759,7 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
     };
     if (!SLICED || S == 1) {
         __syncthreads();   // every wave has read its last operand fragments
-        if (wctx.ok && finish) {
+        if (wctx.ok && finish && holds) {
 #pragma unroll
             for (int i0 = 0; i0 < FM; i0 += BR) {
                 // the region is private to the wave: its own LDS writes are ordered before its reads
