@@ -2,11 +2,11 @@
 // sequence): one workgroup per (head, sequence).  There is a single query row, so the work is
 // streaming the sequence's cached K and V rows once; the matrix cores have nothing to do here.
 //
-// The four waves split the keys: in every step a wave takes 16 consecutive keys, four lanes
-// per key (each lane owns 32 of the 128 head dimensions, so the four read one 256-byte row of
-// K and one of V as contiguous quarters; 32 + 32 values of state per lane keep the tile's
-// registers well below those of the GeMM tile it shares a kernel with).  Every lane keeps an
-// online softmax of its own keys: running maximum m, sum l and 32 un-normalised output values.  At the end the lanes of
+// The four waves split the keys: in every step a wave takes 16 consecutive keys, eight lanes
+// per key and two keys per lane (each lane owns 16 of the 128 head dimensions, in two runs of 8, so that the eight read a
+// 128-byte line of a row together; 16 + 16 values of state per lane leave the registers that the GeMM tile it shares
+// a kernel with has for two steps of K and V rows).  Every lane keeps an
+// online softmax of its own keys: running maximum m, sum l and 16 un-normalised output values.  At the end the lanes of
 // a wave are brought to the wave's maximum and summed through LDS, then the four waves are
 // combined the same way, the result is normalised, rounded and stored.  Key order: the cached
 // tokens, then the new token's own key (which the QKV GeMM has just produced, like the query).
@@ -25,7 +25,7 @@
 
 namespace depsync {
 
-constexpr int DEC_LDS_BYTES = 4 * 64 * 33 * 4 + 4 * 130 * 4;   // per-wave transposition areas + the waves' partial results
+constexpr int DEC_LDS_BYTES = 4 * 64 * 17 * 4 + 4 * 130 * 4;   // per-wave transposition areas + the waves' partial results
 static_assert(DEC_LDS_BYTES <= ATT_LDS_BYTES, "the generation tile fits the LDS of the attention tile");
 
 template <typename T, bool SYNC, class DR>
@@ -34,7 +34,7 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
     typedef T T8 __attribute__((ext_vector_type(8)));
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = uni(tid >> 6);
-    const uint32_t quarter = lane & 3u, slot = lane >> 2;        // quarter of the head dimensions, key slot in the step
+    const uint32_t oct = lane & 7u, slot = lane >> 3;            // runs of the head dimensions, key slots (slot, slot + 8) in the step
     const uint32_t heads = uni(s.heads), E = heads * ATT_D;
     const uint32_t ld = uni(s.lda), ldt = uni(s.ldc);
     const uint32_t cached = uni(s.cached), ldkv = uni(s.ld_cache);
@@ -46,6 +46,38 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
     const uint32_t b = tyz / KS, ks = tyz % KS;                  // sequence, part of its keys
     const uint32_t row = b;                                      // seq = 1: the sequence's only new row
 
+    const uint32_t n = cached + 1;                               // keys: the cache, then the new token
+    const uint32_t chunk = ((n + KS - 1) / KS + 63u) & ~63u;     // keys per part, whole steps of 64
+    const uint32_t k_begin = ks * chunk, k_end = min(n, k_begin + chunk);
+
+    // Cached keys and values of a step, requested two steps before they are multiplied: with one step in flight a CU took in
+    // 32 KB per round trip, and a part of 410 keys 10 to 22 us (7 to 16 so).  The first two are requested before the wait:
+    // nothing in the chain writes them.  Buffer loads, whose 32-bit offsets serve both operands: with 64-bit addresses the
+    // three-per-CU kernels spilled 43 registers and lost more than the steps gained (25 chains of 1 to 16 sequences 1.4 %
+    // slower than with one step in flight; so 6.3 % faster: four of 2048 tokens 67.8 -> 62.0 us, eleven of 1787 65.0 -> 55.5).
+    // (Positions past the part's last read that one again and are not counted.)
+    const uint32_t pitch = ldkv * 2u, kc_end = min(k_end, cached);
+    const uint32_t seq_off = b * cached * pitch + (head * ATT_D + oct * 8) * 2u;
+    const OperandBuf bufK((const char*)Kc), bufV((const char*)Vc);
+    struct Rows { T8 k[2][2], v[2][2]; };
+    auto fetch = [&](uint32_t k0) __attribute__((always_inline)) {
+        Rows x;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t off = seq_off + min(k0 + slot + 8 * i, kc_end - 1) * pitch;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                x.k[i][c] = __builtin_bit_cast(T8, bufK.load16(off, c * 128));
+                x.v[i][c] = __builtin_bit_cast(T8, bufV.load16(off, c * 128));
+            }
+        }
+        return x;
+    };
+    const uint32_t w_begin = k_begin + wave * 16;
+    Rows x0, x1;
+    if (w_begin < kc_end) x0 = fetch(w_begin);
+    if (w_begin + 64 < kc_end) x1 = fetch(w_begin + 64);
+
     WaitCtx wctx{&args, rel_ticket, true};
     const bool tracing = SYNC && (args.flags & DS_FLAG_TRACE) && args.trace != nullptr && rel_ticket < args.trace_cap;
     uint64_t t_start = 0, t_ready = 0;
@@ -53,61 +85,63 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
     attn_wait_qkv<SYNC>(wctx, s, head, row, row);
     if (tracing) t_ready = now_ticks();
 
-    // this lane's quarter of the query, scaled to the base-2 softmax: 32 values
+    // this lane's part of the query, scaled to the base-2 softmax: 16 values
     const float sc = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(128) * log2(e)
-    float q[32];
+    float q[16];
     {
-        const T* qp = QKV + (size_t)row * ld + head * ATT_D + quarter * 32;
+        const T* qp = QKV + (size_t)row * ld + head * ATT_D + oct * 8;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const T8 v = *(const T8*)(qp + c * 8);
+        for (int c = 0; c < 2; ++c) {
+            const T8 v = *(const T8*)(qp + c * 64);
 #pragma unroll
             for (int e = 0; e < 8; ++e) q[c * 8 + e] = (float)v[e] * sc;
         }
     }
-    float o[32];
+    float o[16];
 #pragma unroll
-    for (int j = 0; j < 32; ++j) o[j] = 0.0f;
+    for (int j = 0; j < 16; ++j) o[j] = 0.0f;
     float m_run = -INFINITY, l_run = 0.0f;
-
-    const uint32_t n = cached + 1;                               // keys: the cache, then the new token
-    const uint32_t chunk = ((n + KS - 1) / KS + 63u) & ~63u;     // keys per part, whole steps of 64
-    const uint32_t k_begin = ks * chunk, k_end = min(n, k_begin + chunk);
-    for (uint32_t k0 = k_begin + wave * 16; k0 < k_end; k0 += 64) {
-        const uint32_t key = k0 + slot;
-        const bool live = key < k_end;
-        const uint32_t kk = live ? key : n - 1;
-        const T *kp, *vp;
-        if (kk < cached) {
-            const size_t r = ((size_t)b * cached + kk) * ldkv + head * ATT_D + quarter * 32;
-            kp = Kc + r; vp = Vc + r;
-        } else {
-            kp = QKV + (size_t)row * ld + E + head * ATT_D + quarter * 32;
-            vp = kp + E;
+    auto step = [&](const Rows& x, uint32_t k0, uint32_t end) __attribute__((always_inline)) {
+        float sv[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            float dot = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) dot = __builtin_fmaf(q[c * 8 + e], (float)x.k[i][c][e], dot);
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) dot += __shfl_xor(dot, d);   // the whole score, in all eight lanes
+            sv[i] = k0 + slot + 8 * i < end ? dot : -INFINITY;
         }
-        T8 kv[4], vv[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) kv[c] = *(const T8*)(kp + c * 8);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) vv[c] = *(const T8*)(vp + c * 8);
-        float dot = 0.0f;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) dot = __builtin_fmaf(q[c * 8 + e], (float)kv[c][e], dot);
-        dot += __shfl_xor(dot, 1);                               // the four quarters: the whole score, in all four lanes
-        dot += __shfl_xor(dot, 2);
-        const float x = live ? dot : -INFINITY;
-        const float m_new = fmaxf(m_run, x);
+        const float m_new = fmaxf(m_run, fmaxf(sv[0], sv[1]));
         const float m_use = (m_new == -INFINITY) ? 0.0f : m_new;  // no live key yet: keep the exponentials finite
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
-        const float p = __builtin_amdgcn_exp2f(x - m_use);
-        l_run = l_run * alpha + p;
+        const float p0 = __builtin_amdgcn_exp2f(sv[0] - m_use), p1 = __builtin_amdgcn_exp2f(sv[1] - m_use);
+        l_run = l_run * alpha + (p0 + p1);
         m_run = m_new;
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[c * 8 + e] = __builtin_fmaf(p, (float)vv[c][e], o[c * 8 + e] * alpha);
+            for (int e = 0; e < 8; ++e) {
+                const float t = __builtin_fmaf(p0, (float)x.v[0][c][e], o[c * 8 + e] * alpha);
+                o[c * 8 + e] = __builtin_fmaf(p1, (float)x.v[1][c][e], t);
+            }
+    };
+    for (uint32_t k0 = w_begin; k0 < kc_end; k0 += 128) {        // (bounds that a wave's lanes share)
+        step(x0, k0, kc_end);
+        if (k0 + 128 < kc_end) x0 = fetch(k0 + 128);
+        if (k0 + 64 >= kc_end) break;
+        step(x1, k0 + 64, kc_end);
+        if (k0 + 192 < kc_end) x1 = fetch(k0 + 192);
+    }
+    if (k_begin < n && k_end == n && wave == 0) {                // the new token's own key comes last
+        const T* kp = QKV + (size_t)row * ld + E + head * ATT_D + oct * 8;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) { x0.k[i][c] = *(const T8*)(kp + c * 64); x0.v[i][c] = *(const T8*)(kp + E + c * 64); }
+        step(x0, 0, 1);
     }
 
     // ---- the wave's lanes to the wave's maximum, summed through LDS ----
@@ -116,24 +150,24 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
     for (int d = 1; d < 64; d <<= 1) m_w = fmaxf(m_w, __shfl_xor(m_w, d));
     const float m_wu = (m_w == -INFINITY) ? 0.0f : m_w;
     const float f = __builtin_amdgcn_exp2f(m_run - m_wu);         // 0 for lanes that saw no live key
-    float l_w = (quarter == 0) ? l_run * f : 0.0f;                // the four lanes of a key hold the same l
+    float l_w = (oct == 0) ? l_run * f : 0.0f;                    // the eight lanes of a key hold the same l
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) l_w += __shfl_xor(l_w, d);
-    float* const tr = reinterpret_cast<float*>(lds) + wave * (64 * 33);
-    float* const part = reinterpret_cast<float*>(lds) + 4 * (64 * 33) + wave * 130;   // [128 values, m, l]
+    float* const tr = reinterpret_cast<float*>(lds) + wave * (64 * 17);
+    float* const part = reinterpret_cast<float*>(lds) + 4 * (64 * 17) + wave * 130;   // [128 values, m, l]
     __syncthreads();                                              // (uniform) the LDS is free: the last tile is done with it
 #pragma unroll
-    for (int j = 0; j < 32; ++j) tr[lane * 33 + j] = o[j] * f;
+    for (int j = 0; j < 16; ++j) tr[lane * 17 + j] = o[j] * f;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // this wave's writes are in LDS
     __builtin_amdgcn_wave_barrier();
-    // each lane sums two of the 128 dimensions over the 16 key slots: dimension q * 32 + j lives in
-    // the lanes 4 * slot + q, at position j
+    // each lane sums two of the 128 dimensions over the 8 key slots: dimension c * 64 + q * 8 + j lives in
+    // the lanes 8 * slot + q, at position c * 8 + j
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        const uint32_t dim = 2 * lane + e, qd = dim >> 5, jj = dim & 31u;
+        const uint32_t dim = 2 * lane + e, qd = (dim >> 3) & 7u, jj = (dim >> 6) * 8u + (dim & 7u);
         float acc = 0.0f;
 #pragma unroll
-        for (int sl = 0; sl < 16; ++sl) acc += tr[(4 * sl + qd) * 33 + jj];
+        for (int sl = 0; sl < 8; ++sl) acc += tr[(8 * sl + qd) * 17 + jj];
         part[dim] = acc;
     }
     if (lane == 0) { part[128] = m_w; part[129] = l_w; }
@@ -141,7 +175,7 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
     __syncthreads();
 
     // ---- the four waves combined: thread t < 64 owns dimensions 2t, 2t+1 ----
-    const float* const all = reinterpret_cast<const float*>(lds) + 4 * (64 * 33);
+    const float* const all = reinterpret_cast<const float*>(lds) + 4 * (64 * 17);
     float M = -INFINITY, L = 0.0f, r0 = 0.0f, r1 = 0.0f;
     if (tid < 64) {
 #pragma unroll

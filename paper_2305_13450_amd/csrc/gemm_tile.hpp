@@ -84,6 +84,9 @@ struct OperandBuf {
     __device__ __forceinline__ void dma16(uint32_t off, uint32_t uniform_off, char* l) const {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)l, 16, off, uniform_off, 0, 0);
     }
+    __device__ __forceinline__ u32x4 load16(uint32_t off, uint32_t uniform_off) const {
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, uniform_off, 0);
+    }
 };
 // Store one 16-bit output element.  With the synchronisation hooks compiled in, the store is an
 // agent-scope store: it is written through this XCD's L2 to memory, so that the post needs no
