@@ -1900,8 +1900,8 @@ int64_t uncovered_waits(const Plan& p, const ChainArgs& a, int s) {
             for (uint32_t k = kb; k < ke && ok; ++k) {
                 if (k == seg_next) {
                     seg_next = seg_steps ? seg_next + seg_steps : 0xffffffffu;
-                    DepRange r;
-                    if (dep_segment(st, m0, TM, k, kb, r))
+                    const DepRange r = dep_segment(st, m0, TM, k, kb);
+                    if (r.any)
                         for (uint32_t y = r.y0; y <= r.y1; ++y) waited[policy_sem(st.dep_kind, r.x, y, st.prod_grid_y, st.stride)] = 1;
                 }
                 // producer tiles whose output this K step's slice of A is read from

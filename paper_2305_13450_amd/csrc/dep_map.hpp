@@ -35,6 +35,7 @@ __host__ __device__ __forceinline__ uint32_t policy_sem(uint32_t kind, uint32_t 
 
 // Range of producer row tiles and the producer column tile a K step depends on.
 struct DepRange {
+    bool any;          // there is something to wait for
     uint32_t y0, y1;   // inclusive producer row-tile range
     uint32_t x;        // producer column tile (TILE / STRIDED kinds)
 };
@@ -66,30 +67,30 @@ __host__ __device__ __forceinline__ KRange k_part(const StageDesc& s, uint32_t k
 
 // Does the A slice of K step kt start a new dependency segment, and on what?
 // kb: first K step of this workgroup's K range (0 unless the stage is split along K).
-__host__ __device__ __forceinline__ bool dep_segment(const StageDesc& s, uint32_t m0, uint32_t tm, uint32_t kt, uint32_t kb, DepRange& r) {
+// (Returned by value: filled in through a reference the range lived in scratch memory on the device, and each look at it on a
+// consumer tile's way to its first request waited for the weights in flight: one token of 12288 x 6144 x 12288 73.6 -> 68.8
+// us, 17 attention chains 1.1 % and 36 GeMM chains 1.2 % faster.)
+__host__ __device__ __forceinline__ DepRange dep_segment(const StageDesc& s, uint32_t m0, uint32_t tm, uint32_t kt, uint32_t kb) {
+    const DepRange none = {false, 0, 0, 0};
     const uint32_t m_last = dm_min(m0 + tm, s.M) - 1;
     switch (s.dep_kind) {
         case DEP_ROW:
-            if (kt != kb) return false;
-            r.y0 = m0 / s.prod_tm; r.y1 = m_last / s.prod_tm; r.x = 0;
-            return true;
+            if (kt != kb) return none;
+            return {true, m0 / s.prod_tm, m_last / s.prod_tm, 0};
         case DEP_TILE:
         case DEP_STRIDED: {
             const uint32_t k0 = kt * 64;
-            if (k0 % s.prod_tn != 0) return false;
-            r.x = k0 / s.prod_tn;
+            if (k0 % s.prod_tn != 0) return none;
+            const uint32_t x = k0 / s.prod_tn;
             // same semaphore as x - stride, which this workgroup has already waited for if that
             // segment lies inside its K range
-            if (s.dep_kind == DEP_STRIDED && r.x >= s.stride && (r.x - s.stride) * (s.prod_tn / 64) >= kb) return false;
-            r.y0 = m0 / s.prod_tm; r.y1 = m_last / s.prod_tm;
-            return true;
+            if (s.dep_kind == DEP_STRIDED && x >= s.stride && (x - s.stride) * (s.prod_tn / 64) >= kb) return none;
+            return {true, m0 / s.prod_tm, m_last / s.prod_tm, x};
         }
         case DEP_CONV_ROW: {
-            if (kt != kb) return false;
+            if (kt != kb) return none;
             const int lo = (int)m0 - (int)s.W - 1, hi = (int)m_last + (int)s.W + 1;
-            r.y0 = (uint32_t)dm_imax(lo, 0) / s.prod_tm;
-            r.y1 = (uint32_t)dm_imin(hi, (int)s.M - 1) / s.prod_tm; r.x = 0;
-            return true;
+            return {true, (uint32_t)dm_imax(lo, 0) / s.prod_tm, (uint32_t)dm_imin(hi, (int)s.M - 1) / s.prod_tm, 0};
         }
         case DEP_CONV_TAPROW:
         case DEP_CONV_TILE: {
@@ -98,18 +99,17 @@ __host__ __device__ __forceinline__ bool dep_segment(const StageDesc& s, uint32_
             const uint32_t k0 = kt * 64;
             const uint32_t tap = k0 / s.Cin, c0 = k0 % s.Cin;
             const uint32_t fr = tap / 3, fs = tap % 3;
-            if (fs != 0) return false;
-            if (s.dep_kind == DEP_CONV_TAPROW) { if (c0 != 0) return false; r.x = 0; }
-            else { if (c0 % s.prod_tn != 0) return false; r.x = c0 / s.prod_tn; }
+            uint32_t x = 0;
+            if (fs != 0) return none;
+            if (s.dep_kind == DEP_CONV_TAPROW) { if (c0 != 0) return none; }
+            else { if (c0 % s.prod_tn != 0) return none; x = c0 / s.prod_tn; }
             const int sh = ((int)fr - 1) * (int)s.W;
             const int lo = (int)m0 + sh - 1, hi = (int)m_last + sh + 1;
-            if (hi < 0 || lo > (int)s.M - 1) return false;      // whole filter row is padding
-            r.y0 = (uint32_t)dm_imax(lo, 0) / s.prod_tm;
-            r.y1 = (uint32_t)dm_imin(hi, (int)s.M - 1) / s.prod_tm;
-            return true;
+            if (hi < 0 || lo > (int)s.M - 1) return none;      // whole filter row is padding
+            return {true, (uint32_t)dm_imax(lo, 0) / s.prod_tm, (uint32_t)dm_imin(hi, (int)s.M - 1) / s.prod_tm, x};
         }
         default:
-            return false;
+            return none;
     }
 }
 

@@ -340,16 +340,16 @@ __device__ __forceinline__ void gemm_tile(const ChainArgs& args, const StageDesc
             // cost the dependent tiles 7 % on a 256x192 tile)
             if (__builtin_expect(k == seg_next, 0)) {
                 seg_next = seg_steps ? seg_next + seg_steps : 0xffffffffu;
-                DepRange dr;
-                if (!dep_segment(s, m0, TM, k, kb, dr)) return;
+                const DepRange dr = dep_segment(s, m0, TM, k, kb);
+                if (!dr.any) return;
                 bool polled = false;
                 if (k >= ready_until) {
                     const uint32_t ka = k + lane * seg_steps;          // lane's segment start
                     bool ok = true;
-                    DepRange la;
-                    if (ka < ke && (lane == 0 || seg_steps != 0) && dep_segment(s, m0, TM, ka, kb, la)) {
+                    if (ka < ke && (lane == 0 || seg_steps != 0)) {
+                        const DepRange la = dep_segment(s, m0, TM, ka, kb);
                         const uint32_t target = s.sem_target_base + s.sem_value;
-                        for (uint32_t y = la.y0; y <= la.y1; ++y) {
+                        for (uint32_t y = la.y0; la.any && y <= la.y1; ++y) {
                             const uint32_t* sem = s.sems + policy_sem(s.dep_kind, la.x, y, s.prod_grid_y, s.stride) * SYNC_WORD_STRIDE;
                             ok = ok && sem_reached(__hip_atomic_load(sem, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), target);
                         }
