@@ -140,17 +140,12 @@ int device_cus(int n_cu) {
     return cus;
 }
 
-// Relative time per flop of the macro-tile shapes on a fully occupied CU (128x192 = 1): smaller tiles read more LDS and L2
-// bytes per flop.  From 123 chains of nine pairs of layers (1024 to 12288 wide, plain and gated) at 70 to 2048 tokens,
-// every shape timed with weights from HBM: the choice is 1.3 % behind the fastest shape in the geometric mean and 18 % at
-// worst.  (The factors before were those of an older tile kernel: 3.5 % and 24 %; 8192 x 8192 x 8192 at 2048 tokens 470 us with
-// 256x128, 425 with 256x256; 12288 x 6144 x 12288 at 1200 tokens 404 with 128x192, 348 with 256x128.  Of 45 chains outside the fit
-// whose shape is another for it, 4 % faster in the geometric mean, 11 are 3 to 17 % slower.)
-// one_row: the chain has no more rows than a tile.
-// former: those factors, for these chains.  Whether StridedSync can divide the producer's columns depends on the
-// tile, and what it accepts stays as it is; attention chains, whose middle stage the model does not know, they serve (2048
-// tokens 336 us with the 256x192 tile they choose, 379 with 256x256; 300 tokens over 700 cached 115 with 128x192, 119 and more with others).
-double tile_cost_factor(int tile, bool one_row, bool former, bool conv) {
+// Relative time per flop of the macro-tile shapes on a fully occupied CU (128x192 = 1) by the measurements of earlier kernels.
+// They still choose for StridedSync on GeMM chains (whether it can divide the producer's columns depends on the tile, and what it
+// accepts stays as it is), for chains of three or four convolutions, for attention chains (by the present costs of their two GeMMs
+// alone 14 of 60 were 5 to 37 % slower: which launches a chain takes matters as much) and where the workspace
+// is too small for the present choice (plan_to_run).
+double former_cost_factor(int tile, bool conv) {
     if (conv) {
         // the implicit-GeMM gather of A (a row of pixels per DMA row, taps that re-read their
         // neighbours' rows) moves the order: measured on the VGG pairs at batch 16
@@ -165,22 +160,12 @@ double tile_cost_factor(int tile, bool one_row, bool former, bool conv) {
             default: break;
         }
     }
-    if (former) {
-        switch (tile) {
-            case DEPSYNC_TILE_256x256: return 1.30;
-            case DEPSYNC_TILE_256x128: return 1.04;
-            case DEPSYNC_TILE_128x256: return 1.10;
-            case DEPSYNC_TILE_64x128: return 1.6;
-            case DEPSYNC_TILE_128x128_DEEP: return 1.45;
-            default: break;
-        }
-    }
     switch (tile) {
-        case DEPSYNC_TILE_256x256: return 0.81;   // and FIXED_STEPS_256x256
-        case DEPSYNC_TILE_256x128: return 0.98;
-        case DEPSYNC_TILE_128x256: return 1.15;
+        case DEPSYNC_TILE_256x256: return 1.30;
+        case DEPSYNC_TILE_256x128: return 1.04;
+        case DEPSYNC_TILE_128x256: return 1.10;
         case DEPSYNC_TILE_128x128: return 1.20;
-        case DEPSYNC_TILE_64x128: return one_row ? 1.37 : 2.07;   // one row of tiles: the weights are read once with any shape
+        case DEPSYNC_TILE_64x128: return 1.6;
         case DEPSYNC_TILE_64x64: return 2.3;
         case DEPSYNC_TILE_256x192: return 0.93;
         case DEPSYNC_TILE_128x192: return 1.00;
@@ -188,23 +173,51 @@ double tile_cost_factor(int tile, bool one_row, bool former, bool conv) {
         case DEPSYNC_TILE_64x64_DEEP: return 4.0;   // one workgroup per CU: only ever worth it when tiles are few
         case DEPSYNC_TILE_64x192: return 2.0;       // likewise
         case DEPSYNC_TILE_128x192_DEEP: return 1.10;   // one workgroup per CU, 4 stages: ahead of 128x192 only
-        case DEPSYNC_TILE_128x128_DEEP: return 1.31;   // where that tile would have to split along K
+        case DEPSYNC_TILE_128x128_DEEP: return 1.45;   // where that tile would have to split along K
         default: return 2.4;
     }
 }
-// What a 256x256 tile costs beside its K loop, in K steps: 256 accumulators a lane leave no registers for the code around it.
-constexpr uint32_t FIXED_STEPS_256x256 = 10;
 
-// Convolution tiles in microseconds: a K step with one tile on the CU and with as many as share it, what a tile costs
-// beside its steps (it has only 9 to 72 of them) and what a split along K adds.  Fitted to 54 pairs of convolutions (64
+// Tiles in microseconds: a K step with one tile on the CU and with as many as share it, what a tile costs beside its steps and what
+// a split along K adds (GeMM tiles that the last part finishes alone: per further part).
+struct TileCost { float step_alone, step_shared, fixed, split; };
+// Of GeMM chains: fitted to 510 chains of the layer widths above 512 and 20 to 2048 rows, weights from HBM, every shape timed: the choice
+// is 3 % behind the fastest shape in the geometric mean, the factors before were 7 to 9 % behind.  (384 x 12288 x 6144 x 12288
+// 173 -> 138 us, 700 rows 266 -> 206, both with 192x192 tiles; 84 x 10368 x 704 x 10728 gated 36.5 -> 32.0.  Of 80 chains outside
+// the fit one is more than 5 % slower, 526 x 3328 x 3520 x 2280 66 -> 75; 4 x 12096 x 5376 x 1944 gated, 260 MB of weights through
+// 64x128 tiles with two steps in flight, 74 -> 95.)  Three of the values are not the fit's: the split of 256x192 (5.7) and of 256x128 (8.0)
+// and the fixed cost of 64x128 (5.3) decide 12288 x 6144 x 12288 at 512 rows and 8192 x 2752 x 8192 gated at 256 as measured.
+TileCost gemm_tile_cost(int tile) {
+    switch (tile) {
+        case DEPSYNC_TILE_256x256: return {1.56f, 1.56f, 4.3f, 12.3f};
+        case DEPSYNC_TILE_256x128: return {0.91f, 0.91f, 1.5f, 7.2f};
+        case DEPSYNC_TILE_128x256: return {0.92f, 0.92f, 2.6f, 10.2f};
+        case DEPSYNC_TILE_128x128: return {0.82f, 1.09f, 3.7f, 3.0f};
+        case DEPSYNC_TILE_64x128: return {0.41f, 0.68f, 6.3f, 1.9f};
+        case DEPSYNC_TILE_64x64: return {0.20f, 0.43f, 6.9f, 1.3f};
+        case DEPSYNC_TILE_256x192: return {1.25f, 1.25f, 2.4f, 10.0f};
+        case DEPSYNC_TILE_128x192: return {1.02f, 1.50f, 2.5f, 3.5f};
+        case DEPSYNC_TILE_256x64: return {0.92f, 1.21f, 3.1f, 3.4f};
+        case DEPSYNC_TILE_64x192: return {0.56f, 0.56f, 3.6f, 7.7f};
+        case DEPSYNC_TILE_128x192_DEEP: return {0.76f, 0.76f, 2.6f, 8.4f};
+        case DEPSYNC_TILE_128x128_DEEP: return {0.58f, 0.58f, 3.6f, 5.8f};
+        case TILE_192x192: return {0.95f, 0.95f, 2.4f, 8.2f};
+        default: return {1e6f, 1e6f, 0.0f, 0.0f};   // 64x64 deep: behind the shapes that triple_fits chooses where it was ahead of these
+    }
+}
+bool last_part_finishes(int tile) {   // see the exchange of partial tiles in gemm_tile.hpp
+    const TileShape* ts = tile_shape(tile);
+    return ts->occupancy > 1 || ts->rows * ts->cols > 192 * 192;
+}
+
+// Of convolutions (a tile has only 9 to 72 steps).  Fitted to 54 pairs of convolutions (64
 // to 512 channels, images of 14 to 224 pixels, batches of 1 to 32), every shape timed: the choice is 2.5 % behind the fastest
 // shape in the geometric mean, 20 % at worst; one factor per shape was 17 % and 56 % behind.  (8x56x56x320 206 us with 256x64,
 // 117 with 256x192; 32x28x28x512 305 with 128x128, 237 with 256x256; 16x56x56x256 143 and 132.  Of 60 pairs outside the fit whose
 // shape is another for it, 22 % faster in the geometric mean, 5 are 4 to 16 % slower.)  Chains of three and four
 // keep the factors (`former`): the model knows two stages, and of six such chains whose shape it would have changed two
 // lost 9 % (three of 6x47x51x320 144 -> 156 us; four of 11x9x9x448 76 -> 83).
-struct ConvTileCost { float step_alone, step_shared, fixed, split; };
-ConvTileCost conv_tile_cost(int tile) {
+TileCost conv_tile_cost(int tile) {
     switch (tile) {
         case DEPSYNC_TILE_256x256: return {1.44f, 1.44f, 13.0f, 23.1f};
         case DEPSYNC_TILE_256x128: return {0.90f, 0.90f, 15.9f, 7.7f};
@@ -273,23 +286,19 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 
 // Pick one macro-tile for both stages by simulating the fine-grained schedule of the chain
 // on `slots` workgroup slots for every candidate shape (host_model.h).  A stage that would leave
-// slots idle is modelled as the planner will run it: split along K into S parts, each costing
-// 1/S of the tile plus 15 % per further part for the exchange of partial tiles (convolutions: see conv_tile_cost).
-// by_tile: the second stage's parts start on the first stage's tile boundaries (waits per producer tile).
-// conv_seg: not 0 for convolutions, K steps between the places where parts of the second may start.
-// former: by the former factors (see tile_cost_factor).
-// time (nullable): the simulated time of the choice, in units of which 0.70e-6 were microseconds with the former factors and
-// kernels (65 to 320 tokens of fifteen pairs of layers, weights from HBM).  Now they are 0.41e-6 to 0.62e-6, 0.54e-6 in the middle
-// (24 chains of 75 to 1130 rows at the edge of triple_pays).
+// slots idle is modelled as the planner will run it: split along K into S parts.
+// seg2: K steps between the places where parts of the second stage may start; 0: the first stage's tile boundaries.
+// former: by the former factors, with which each of S parts costs 1 / S of the tile plus 15 % per further part.
+// time (nullable): the simulated time of the choice in microseconds, or in units of 0.70e-6 of them with the former factors.
 int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t K2, bool gate_up,
-                int n_cu, uint32_t conv_seg, bool by_tile = false, bool former = false, double* time = nullptr) {
+                int n_cu, bool conv, uint32_t seg2, bool former = false, double* time = nullptr) {
     // The simulation walks every tile of every candidate shape (a millisecond of host time for
     // the largest conv pairs, which every launch with TILE_AUTO would pay): remember the answer.
     using Key = std::array<uint64_t, 4>;
     static std::map<Key, std::pair<int, double>> memo;
     static std::mutex memo_mutex;
     const Key key = {((uint64_t)M << 32) | n_out1, ((uint64_t)K1 << 32) | N2, ((uint64_t)K2 << 32) | (uint32_t)n_cu,
-                     ((uint64_t)conv_seg << 3) | ((uint64_t)former << 2) | ((uint64_t)by_tile << 1) | (uint64_t)gate_up};
+                     ((uint64_t)seg2 << 3) | ((uint64_t)conv << 2) | ((uint64_t)former << 1) | (uint64_t)gate_up};
     {
         std::lock_guard<std::mutex> lock(memo_mutex);
         const auto it = memo.find(key);
@@ -297,29 +306,35 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
     }
     int best = 0;
     double best_t = 0;
-    for (int t = 1; t < DEPSYNC_TILE__COUNT; ++t) {
+    const uint32_t few = former || conv ? 0u : (uint32_t)n_cu / 2;
+    for (int t = 1; t <= TILE_192x192; ++t) {
+        if (t == TILE_64x64_TRIPLE || (t == TILE_192x192 && (former || conv))) continue;
         const TileShape* ts = tile_shape(t);
         if (gate_up && (ts->wave_cols % 64 || (ts->cols / 2) % 64)) continue;
         const uint32_t tn1 = gate_up ? ts->cols / 2 : ts->cols;
         const uint32_t gy = cdiv(M, ts->rows);
         const uint32_t gx1 = cdiv(n_out1, tn1), gx2 = cdiv(N2, ts->cols);
-        const double f = tile_cost_factor(t, gy == 1, former, conv_seg != 0);
-        const double fixed = t == DEPSYNC_TILE_256x256 && !former ? 64.0 * FIXED_STEPS_256x256 : 0.0;
         // `occupancy` workgroups share a CU's matrix units, so each runs at 1/occupancy of its rate
         const uint32_t slots = (uint32_t)(n_cu * ts->occupancy);
-        const uint32_t s1 = choose_split(nullptr, false, gx1 * gy, slots, K1 / 64, 1, 0);
-        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, conv_seg && !former ? conv_seg : by_tile ? std::max(1u, tn1 / 64) : 1u, 0);
-        double d1 = f * (double)ts->rows * ts->cols * (K1 + fixed * s1) * ts->occupancy / s1 * (1.0 + 0.15 * (s1 - 1));
-        double d2 = f * (double)ts->rows * ts->cols * (K2 + fixed * s2) * ts->occupancy / s2 * (1.0 + 0.15 * (s2 - 1));
-        if (conv_seg && !former) {
-            const ConvTileCost c = conv_tile_cost(t);
+        const uint32_t s1 = choose_split(nullptr, false, gx1 * gy, slots, K1 / 64, 1, few);
+        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, seg2 ? seg2 : std::max(1u, tn1 / 64), few);
+        double d1, d2;
+        if (former) {
+            const double f = former_cost_factor(t, conv);
+            d1 = f * (double)ts->rows * ts->cols * K1 * ts->occupancy / s1 * (1.0 + 0.15 * (s1 - 1));
+            d2 = f * (double)ts->rows * ts->cols * K2 * ts->occupancy / s2 * (1.0 + 0.15 * (s2 - 1));
+        } else {
+            const TileCost c = conv ? conv_tile_cost(t) : gemm_tile_cost(t);
             auto part = [&](uint64_t parts, uint32_t steps, uint32_t s) {
-                return (parts <= (uint64_t)n_cu ? c.step_alone : c.step_shared) * (double)steps / s + c.fixed + (s > 1 ? c.split : 0.0);
+                const double exchange = s == 1 ? 0.0 : !conv && last_part_finishes(t) ? (s - 1) * c.split : c.split;
+                return (parts <= (uint64_t)n_cu ? c.step_alone : c.step_shared) * (conv ? (double)steps / s : (double)cdiv(steps, s)) + c.fixed + exchange;
             };
             d1 = part((uint64_t)gx1 * gy * s1, K1 / 64, s1);
             d2 = part((uint64_t)gx2 * gy * s2, K2 / 64, s2);
         }
-        const double tm = simulate_chain((int)slots, gx1 * s1, gy, d1, gx2 * s2, gy, d2, conv_seg ? 1 : 0, /*stream_sync=*/false);
+        double tm = simulate_chain((int)slots, gx1 * s1, gy, d1, gx2 * s2, gy, d2, conv ? 1 : 0, /*stream_sync=*/false);
+        // (gated, 256x256 is level with 256x128 at 2048 tokens and behind it below)
+        if (!former && gate_up && t == DEPSYNC_TILE_256x256) tm *= 1.2;
         if (best == 0 || tm < best_t) { best = t; best_t = tm; }
     }
     std::lock_guard<std::mutex> lock(memo_mutex);
@@ -425,18 +440,14 @@ bool triple_fits(int n, int cus, const uint32_t (&tiles)[4], const uint32_t (&kt
     return true;
 }
 
-// Two GeMMs of several row tiles that fit, with parts that add up to more than 140 steps: 64 x 64 tiles read every
-// element of A and B 64 times from LDS, and a step takes 0.44 us with one part per CU and half as much again with
-// three, whatever the HBM delivers.  Chains of shorter parts are ahead by 5 to 50 % all the same; these only where the
-// model has nothing better (4096 x 11008 x 4096 at 128 tokens 84 against 171 us).  Turned
-// away: 12288 x 3072 x 12288 at 192 tokens 118 against 89 us, 8192 x 8192 x 8192 at 128 117 against 102, 12288 x 6144
-// x 12288 at 128 126 against 112.  With the present factors more are: of 40 chains that they turned away or took in
-// anew 37 were right, 20 % faster in the geometric mean (287 x 11328 x 1664 x 7776 90 -> 59 us), three 5 to 9 % slower (157 x 5632 x 5120 x 10312
-// 89 -> 97).  The scale, 0.70e-6, is still that of the former factors: a smaller one, see choose_tile, would turn away more.
-bool triple_pays(const uint32_t (&steps)[4], const uint32_t (&parts)[4], int cus, double model_time) {
+// GeMM chains of several row tiles that fit: 64 x 64 tiles read every element of A and B 64 times from LDS, and a step takes
+// 0.44 us with one part per CU and half as much again with three, whatever the HBM delivers.  They are chosen where that
+// is less than the time of the model's choice by the margin that `other_time` carries (1.3), for parts that add up to 64 steps at most, and
+// up to 150 where the model would take 64 rows too, two to a CU (4096 x 11008 x 4096 at 128 tokens 84 us): 118 such chains are 5.5 % behind the fastest shape in the geometric mean (by the former rule, all of at most 140 steps, 7 %).
+bool triple_pays(const uint32_t (&steps)[4], const uint32_t (&parts)[4], int cus, double other_time) {
     double us = 0.0;
     for (int s = 0; s < 2; ++s) us += steps[s] * (0.44 + 0.154 * std::max(0.0, (double)parts[s] / cus - 1.0));
-    return 1.1 * us <= 0.70e-6 * model_time;
+    return us <= other_time;
 }
 
 // Do the 64x192 tiles of a stage split into (nearly) as many equal parts as there are CUs?  Where both stages of a
@@ -547,16 +558,21 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
                 if (rows == 1) {
                     if (d->M <= 32) tile = TILE_32x64;
                     else if ( wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
-                } else if (steps[0] + steps[1] > 140) {
+                } else if (steps[0] + steps[1] > (former_shape ? 140u : 64u)) {
                     double model_time = 0.0;
-                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, 0, kind != DEPSYNC_ROWSYNC, former_shape, &model_time);
-                    if (!triple_pays(steps, parts, cus, model_time)) tile = other;
+                    const uint32_t seg2 = former_shape ? kind == DEPSYNC_ROWSYNC : kind != DEPSYNC_TILESYNC;
+                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, false, seg2, former_shape, &model_time);
+                    const bool alike = !former_shape && tile_shape(other)->rows == 64 && tile_shape(other)->occupancy == 2 && steps[0] + steps[1] <= 150;
+                    if (!alike && !triple_pays(steps, parts, cus, former_shape ? 0.70e-6 / 1.1 * model_time : model_time / 1.3)) tile = other;
                 }
             }
         }
     }
-    if (!tile)
-        tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, 0, false, former_shape || attn || kind == DEPSYNC_STRIDEDSYNC);
+    if (!tile) {
+        const bool former = former_shape || attn || kind == DEPSYNC_STRIDEDSYNC;
+        const uint32_t seg2 = former || kind == DEPSYNC_ROWSYNC ? 1u : 0u;
+        tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, false, seg2, former);
+    }
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
     if (!ts || !tsc) return DEPSYNC_EINVAL;
@@ -647,6 +663,10 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         uint32_t ks = want ? want : ((tuned_off || !sparse) ? 1u : (max_blocks + 3u) / 4u);
         p.ksplit[1] = std::min<uint32_t>(8u, std::max<uint32_t>(ks, 1u));
         p.part_floats[1] = 256 * 64 + 2 * 256;
+        // (the earlier stages' parts should stay resident together: 130 tokens of 6464 wide over 89 cached, 101 steps in two parts
+        // beside 14 attention tiles, two streams, 61 -> 78 us)
+        if (p.n_tiles[0] * p.ksplit[0] + p.n_tiles[1] * p.ksplit[1] > (uint32_t)p.slots)
+            p.ksplit[0] = choose_split(pol, tuned_off, p.n_tiles[0], (uint32_t)p.stage_slots[0], d->K1 / 64, 1, 0);
     }
     {
         const uint32_t dk = p.dep_kind[last];
@@ -740,7 +760,8 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     }
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
-        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, segs[1], false, former_shape || n > 2);
+        const bool former = former_shape || n > 2;
+        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, true, former ? 1u : segs[1], former);
     }
     if (!tile_shape(tile) || (mixed && !tile_shape(d->tile_cons))) return DEPSYNC_EINVAL;
 
@@ -833,7 +854,7 @@ int plan_copy(const depsync_copy_chain_desc* d, const sync_policy* pol, int n_cu
     return DEPSYNC_OK;
 }
 
-int public_tile(int tile) { return tile == TILE_64x64_TRIPLE || tile == TILE_32x64 ? DEPSYNC_TILE_64x64 : tile; }
+int public_tile(int tile) { return tile == TILE_64x64_TRIPLE || tile == TILE_32x64 ? DEPSYNC_TILE_64x64 : tile == TILE_192x192 ? DEPSYNC_TILE_128x192_DEEP : tile; }
 
 void fill_plan_info(const Plan& p, depsync_plan_info* o) {
     std::memset(o, 0, sizeof(*o));

@@ -95,6 +95,10 @@ using Cfg128x192Deep = TileCfg<128, 192, 2, 2, 1, 4>;   // 160 KB: three K steps
 using Cfg128x128Deep = TileCfg<128, 128, 2, 2, 1, 4>;   // 128 KB: three K steps in flight
 
 using Cfg64x64Triple = TileCfg<64, 64, 2, 2, 3, 3>;   // 3 x 48 KB
+// GeMM chains whose rows leave 128- or 256-row tiles part empty or too few.  With weights from HBM a CU takes in some 50 bytes/ns
+// whatever its tile, and 192x192 reads a fifth less per flop than 128x192 (333 x 12288 x 6144 x 12288 166 -> 137 us: 256
+// parts of 48 steps in each stage instead of 192 of 96; 700 rows 266 -> 206; 256x192 stays ahead at 1024 and 2048 rows).
+using Cfg192x192 = TileCfg<192, 192, 2, 2, 1, 3>;     // 144 KB
 // Up to 32 rows.  These chains wait for weights, and half of what a 64x64 tile stages of A for them is copies of the last
 // row: with 32 rows the LDS of three workgroups holds a fourth step.  The tile has only two blocks of 32x32, so two
 // waves share one, each with every other pair of a step's K slices (one token of 12288 x 6144 x 12288 74.8 -> 72.7 us, four
@@ -133,6 +137,7 @@ static hipError_t launch_family(int tile, bool sync, uint32_t n_blocks, hipStrea
     }
     if constexpr (AMODE == A_DENSE) {
         switch (tile) {
+            case TILE_192x192: return launch_cfg<Cfg192x192, T, AMODE, MIDK>(sync, n_blocks, stream, a);
             case TILE_32x64:
                 if constexpr (MIDK != 1) return launch_cfg<Cfg32x64, T, AMODE, MIDK>(sync, n_blocks, stream, a);
                 break;

@@ -142,6 +142,7 @@ const TileShape* tile_shape(int tile) {
         {128, 192, 1, 96},
         {128, 128, 1, 64},
         {64, 64, 3, 32},
+        {192, 192, 1, 96},
         {32, 64, 3, 32},
     };
     if (tile < 1 || tile > TILE_32x64) return nullptr;

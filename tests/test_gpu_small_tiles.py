@@ -94,3 +94,25 @@ def test_token_generation(batch, cached, heads, dtype, tol):
         assert rel_err(Y, oracle.gemm(inputs.to_f64(T.cpu()), inputs.to_f64(t["Wo"]))) <= tol
         for other in res[1:]:
             assert all(torch.equal(a, b) for a, b in zip(res[0], other))
+
+
+@pytest.mark.parametrize("M,K1,N1,N2,dtype", [(129, 1088, 6144, 7000, torch.bfloat16), (192, 1088, 6144, 7000, torch.float16),
+                                              (333, 2048, 6144, 6144, torch.bfloat16), (570, 1536, 6144, 4000, torch.bfloat16)])
+def test_tiles_of_192_rows(M, K1, N1, N2, dtype):
+    # sizes for which the library takes 192x192 tiles: part of a tile, a whole one, three with a ragged last one; whole and split
+    # stages (parts of 14 to 32 steps)
+    t = inputs.mlp(M, K1, N1, N2, seed=M, dtype=dtype)
+    print(f"192 rows M={M}", flush=True)
+    Href, Yref = oracle.gemm_chain(inputs.to_f64(t["X"]), inputs.to_f64(t["W1"]), inputs.to_f64(t["W2"]), oracle.ACT_GELU)
+    for kind in (ds.ROWSYNC, ds.TILESYNC):
+        pol = ds.SyncPolicy(kind)
+        res = [run_gemm_chain(t["X"], t["W1"], t["W2"], pol, mode) for mode in MODES]
+        a = [x.cuda().contiguous() for x in (t["X"], t["W1"].t(), t["W2"].t())]
+        plan = ds.gemm_chain_plan(a[0], a[1], torch.empty_like(res[0][0]), a[2], torch.empty_like(res[0][1]), pol)
+        assert kind != ds.ROWSYNC or (plan.prod_grid_x, plan.prod_grid_y) == (-(-N1 // 192), -(-M // 192))
+        assert pol.status().timed_out == 0
+        pol.destroy()
+        assert mid_err(res[0][0], Href) <= TOL_MID
+        assert rel_err(res[0][1], Yref) <= (TOL_BF16 if dtype == torch.bfloat16 else TOL_FP16)
+        for other in res[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(res[0], other))
