@@ -200,7 +200,8 @@ typedef struct {
 /* What the library decided for a chain (for reports; filled by depsync_*_chain_plan).  The 64x64 tile exists once more,
  * with three workgroups per CU, for the library's own choice only: it is reported as DEPSYNC_TILE_64x64 and told apart
  * by `slots` (three per CU instead of two); that id in a descriptor asks for the shape with two per CU.  In its place a GeMM chain
- * of at most 32 rows runs a 32x64 tile, reported the same (the grids are the same as well). */
+ * of at most 32 rows runs a 32x64 tile, reported the same (the grids are the same as well).  192x192 exists for the library's own
+ * choice on GeMM chains only: it is reported as DEPSYNC_TILE_128x192_DEEP, and its grids tell it apart. */
 typedef struct {
     int32_t tile_prod, tile_mid, tile_cons;   /* depsync_tile ids (tile_mid: attention only)  */
     int32_t prod_grid_x, prod_grid_y;         /* column tiles, row tiles of the producer      */
