@@ -55,16 +55,18 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
     // nothing in the chain writes them.  Buffer loads, whose 32-bit offsets serve both operands: with 64-bit addresses the
     // three-per-CU kernels spilled 43 registers and lost more than the steps gained (25 chains of 1 to 16 sequences 1.4 %
     // slower than with one step in flight; so 6.3 % faster: four of 2048 tokens 67.8 -> 62.0 us, eleven of 1787 65.0 -> 55.5).
-    // (Positions past the part's last read that one again and are not counted.)
+    // (The buffers end with the part's last key, so positions past it are zeros: their probability is zero, and zero times an
+    // infinite value would not be.  A cache within a step of 4 GiB aside, whose last offsets wrap to its start.)
     const uint32_t pitch = ldkv * 2u, kc_end = min(k_end, cached);
     const uint32_t seq_off = b * cached * pitch + (head * ATT_D + oct * 8) * 2u;
-    const OperandBuf bufK((const char*)Kc), bufV((const char*)Vc);
+    const uint32_t part_end = uni((b * cached + kc_end) * pitch);  // (caches are below 4 GiB: checked on the host)
+    const OperandBuf bufK((const char*)Kc, part_end), bufV((const char*)Vc, part_end);
     struct Rows { T8 k[2][2], v[2][2]; };
     auto fetch = [&](uint32_t k0) __attribute__((always_inline)) {
         Rows x;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const uint32_t off = seq_off + min(k0 + slot + 8 * i, kc_end - 1) * pitch;
+            const uint32_t off = seq_off + (k0 + slot + 8 * i) * pitch;
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 x.k[i][c] = __builtin_bit_cast(T8, bufK.load16(off, c * 128));
@@ -136,11 +138,14 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
         if (k0 + 192 < kc_end) x1 = fetch(k0 + 192);
     }
     if (k_begin < n && k_end == n && wave == 0) {                // the new token's own key comes last
-        const T* kp = QKV + (size_t)row * ld + E + head * ATT_D + oct * 8;
+        const OperandBuf own(uni_ptr(QKV + (size_t)row * ld + E + head * ATT_D), uni((E + ATT_D) * 2u));
+        const uint32_t off = slot == 0 ? oct * 16u : 0x7fffff00u;   // (the other slots: zeros)
+        const T8 zero = {};
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) { x0.k[i][c] = *(const T8*)(kp + c * 64); x0.v[i][c] = *(const T8*)(kp + E + c * 64); }
+        for (int c = 0; c < 2; ++c) {
+            x0.k[0][c] = __builtin_bit_cast(T8, own.load16(off, c * 128)); x0.k[1][c] = zero;
+            x0.v[0][c] = __builtin_bit_cast(T8, own.load16(off, E * 2u + c * 128)); x0.v[1][c] = zero;
+        }
         step(x0, 0, 1);
     }
 

@@ -301,3 +301,28 @@ def test_cached_attention_rejects_bad_caches():
     assert ds._lib().dep_gemm_chain(d, pol.handle, ds.MODE_FINE, None, None) == ds.EINVAL
     torch.cuda.synchronize()
     pol.destroy()
+
+
+@pytest.mark.parametrize("batch,cached,heads", [(2, 1, 2), (2, 15, 2), (3, 37, 3), (1, 63, 2), (2, 700, 2), (4, 1000, 16)])
+def test_generation_keeps_infinite_values_of_the_last_positions(batch, cached, heads):
+    """An infinite value of a key that counts gives an infinite output; positions of a step past the last key (probability zero)
+    must not turn it into NaN.  Dimension 5 of the last cached token and dimension 7 of the new one (its product leaves fp16)."""
+    E, K1, N2 = heads * 128, 256, 136
+    t = inputs.attention(batch, K1, heads, 128, N2, seed=cached, dtype=torch.float16)
+    kv = inputs.kv_cache(batch, cached, heads, 128, seed=cached, dtype=torch.float16)
+    t["X"][0], t["Wqkv"][:, 2 * E + 7] = 1.0, 4096.0
+    X, Wq, Wo = t["X"].cuda(), t["Wqkv"].t().contiguous().cuda(), t["Wo"].t().contiguous().cuda()
+    Kc, Vc = kv["Kc"].cuda(), kv["Vc"].cuda()
+    Vc.view(batch, cached, E)[0, -1, 5] = float("inf")
+    print(f"infinite values batch={batch} cached={cached} heads={heads}", flush=True)
+    pol = ds.SyncPolicy(ds.ROWSYNC)
+    for mode in MODES:
+        QKV, T, Y = (torch.full((batch, n), float("nan"), dtype=torch.float16, device="cuda") for n in (3 * E, E, N2))
+        ds.dep_gemm_chain(X, Wq, QKV, Wo, Y, pol, mode=mode, T=T, mid=ds.MID_CAUSAL_ATTN, batch=batch, seq=1, heads=heads,
+                          head_dim=128, k_cache=Kc, v_cache=Vc)
+        torch.cuda.synchronize()
+        assert bool(QKV[0, 2 * E + 7].isposinf()) and pol.status().timed_out == 0
+        V = torch.cat([Vc.view(batch, cached, E), QKV[:, None, 2 * E:]], 1)
+        counts = torch.isinf(V).any(1)                       # (batch, E): dimensions with an infinite value
+        assert bool((T[counts].isposinf() == (V.amax(1)[counts] == float("inf"))).all()) and bool(T[~counts].isfinite().all())
+    pol.destroy()
