@@ -289,16 +289,17 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 // slots idle is modelled as the planner will run it: split along K into S parts.
 // seg2: K steps between the places where parts of the second stage may start; 0: the first stage's tile boundaries.
 // former: by the former factors, with which each of S parts costs 1 / S of the tile plus 15 % per further part.
+// whole: nothing will be split.
 // time (nullable): the simulated time of the choice in microseconds, or in units of 0.70e-6 of them with the former factors.
 int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t K2, bool gate_up,
-                int n_cu, bool conv, uint32_t seg2, bool former = false, double* time = nullptr) {
+                int n_cu, bool conv, uint32_t seg2, bool former, bool whole, double* time = nullptr) {
     // The simulation walks every tile of every candidate shape (a millisecond of host time for
     // the largest conv pairs, which every launch with TILE_AUTO would pay): remember the answer.
     using Key = std::array<uint64_t, 4>;
     static std::map<Key, std::pair<int, double>> memo;
     static std::mutex memo_mutex;
     const Key key = {((uint64_t)M << 32) | n_out1, ((uint64_t)K1 << 32) | N2, ((uint64_t)K2 << 32) | (uint32_t)n_cu,
-                     ((uint64_t)seg2 << 3) | ((uint64_t)conv << 2) | ((uint64_t)former << 1) | (uint64_t)gate_up};
+                     ((uint64_t)seg2 << 4) | ((uint64_t)whole << 3) | ((uint64_t)conv << 2) | ((uint64_t)former << 1) | (uint64_t)gate_up};
     {
         std::lock_guard<std::mutex> lock(memo_mutex);
         const auto it = memo.find(key);
@@ -316,8 +317,8 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
         const uint32_t gx1 = cdiv(n_out1, tn1), gx2 = cdiv(N2, ts->cols);
         // `occupancy` workgroups share a CU's matrix units, so each runs at 1/occupancy of its rate
         const uint32_t slots = (uint32_t)(n_cu * ts->occupancy);
-        const uint32_t s1 = choose_split(nullptr, false, gx1 * gy, slots, K1 / 64, 1, few);
-        const uint32_t s2 = choose_split(nullptr, false, gx2 * gy, slots, K2 / 64, seg2 ? seg2 : std::max(1u, tn1 / 64), few);
+        const uint32_t s1 = choose_split(nullptr, whole, gx1 * gy, slots, K1 / 64, 1, few);
+        const uint32_t s2 = choose_split(nullptr, whole, gx2 * gy, slots, K2 / 64, seg2 ? seg2 : std::max(1u, tn1 / 64), few);
         double d1, d2;
         if (former) {
             const double f = former_cost_factor(t, conv);
@@ -481,8 +482,12 @@ int finish_split(Plan& p) {
     return DEPSYNC_OK;
 }
 
-// former_shape: where the library chooses the tile, by the former factors (see plan_to_run).
-int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape = false) {
+// The library's choices of tile and split: its present one, the one by the former factors, and one that splits nothing
+// (but what the caller asks for).  See plan_to_run.
+enum PlanChoice { PLAN_PRESENT, PLAN_FORMER, PLAN_WHOLE };
+
+int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, PlanChoice choice = PLAN_PRESENT) {
+    const bool former_shape = choice == PLAN_FORMER, whole = choice == PLAN_WHOLE;
     if (!d) return DEPSYNC_EINVAL;
     if (d->M <= 0 || d->K1 <= 0 || d->N1 <= 0 || d->N2 <= 0) return DEPSYNC_EINVAL;
     if (d->dtype != DEPSYNC_BF16 && d->dtype != DEPSYNC_FP16) return DEPSYNC_EINVAL;
@@ -540,10 +545,11 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
+    tuned_off = tuned_off || whole;
     const int kind = effective_kind(d, pol, pol ? default_kind(d) : DEPSYNC_ROWSYNC);
     const uint32_t few = former_shape ? 0u : (uint32_t)cus / 2;   // parts of a stage that may be unequal (choose_split)
     // (whether StridedSync divides the producer's columns depends on the tile: what it accepts stays as it is)
-    if (!tile && !gate_up && (attn ? d->seq == 1 : kind != DEPSYNC_STRIDEDSYNC)) {
+    if (!tile && !whole && !gate_up && (attn ? d->seq == 1 : kind != DEPSYNC_STRIDEDSYNC)) {
         const uint32_t rows = cdiv(d->M, 64), seg[4] = {1, 1, 1, 1};
         uint32_t steps[4], parts[4];
         if (attn) {
@@ -561,7 +567,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
                 } else if (steps[0] + steps[1] > (former_shape ? 140u : 64u)) {
                     double model_time = 0.0;
                     const uint32_t seg2 = former_shape ? kind == DEPSYNC_ROWSYNC : kind != DEPSYNC_TILESYNC;
-                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, false, seg2, former_shape, &model_time);
+                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, false, seg2, former_shape, false, &model_time);
                     const bool alike = !former_shape && tile_shape(other)->rows == 64 && tile_shape(other)->occupancy == 2 && steps[0] + steps[1] <= 150;
                     if (!alike && !triple_pays(steps, parts, cus, former_shape ? 0.70e-6 / 1.1 * model_time : model_time / 1.3)) tile = other;
                 }
@@ -571,7 +577,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     if (!tile) {
         const bool former = former_shape || attn || kind == DEPSYNC_STRIDEDSYNC;
         const uint32_t seg2 = former || kind == DEPSYNC_ROWSYNC ? 1u : 0u;
-        tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, false, seg2, former);
+        tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, false, seg2, former, whole);
     }
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
@@ -646,7 +652,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     if (attn && d->seq == 1) {
         // token generation: the keys of a (head, sequence) pair over up to 8 workgroups, at least 256
         // keys each, as far as one wave of slots allows
-        uint32_t ks = std::min<uint32_t>(8u, ((uint32_t)d->cached + 1u) / 256u);
+        uint32_t ks = whole ? 1u : std::min<uint32_t>(8u, ((uint32_t)d->cached + 1u) / 256u);
         while (ks > 1 && p.n_tiles[1] * ks > (uint32_t)p.slots / (ts->occupancy > 2 ? 3u : 1u)) --ks;
         p.ksplit[1] = std::max<uint32_t>(ks, 1u);
         p.part_floats[1] = 130;
@@ -707,7 +713,8 @@ depsync_conv_chain_n_desc as_chain_n(const depsync_conv_chain_desc& d) {
 // Chain of n = 2..4 3x3 convolutions: stage i is conv i, each later stage depends on the one
 // before it in the way the policy says (per halo row tile, per filter row, or per filter row
 // and channel tile).
-int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape = false) {
+int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int n_cu, Plan& p, PlanChoice choice = PLAN_PRESENT) {
+    const bool former_shape = choice == PLAN_FORMER, whole = choice == PLAN_WHOLE;
     if (!d) return DEPSYNC_EINVAL;
     if (d->n < 2 || d->n > 4) return DEPSYNC_EINVAL;
     if (d->B <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0) return DEPSYNC_EINVAL;
@@ -744,6 +751,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         tile = v & 0xff;
         if (v) { tuned_off = (v & 0x100) != 0; order_pref = (v & 0x200) ? 1 : 0; }
     }
+    tuned_off = tuned_off || whole;
     const int kind = effective_kind(d, pol, DEPSYNC_STRIDEDSYNC);
     // Parts of a later stage start on its dependency segments.  CONV_ROW: the whole halo is waited for by every
     // part; per filter row or per (filter row, channel tile): the wait at a filter row's first tap also
@@ -753,7 +761,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         kts[i] = 9u * cin[i] / 64;
         if (i > 0 && policy_dep_kind_conv(kind) != DEP_CONV_ROW) segs[i] = 3u * cin[i] / 64;
     }
-    if (!tile) {
+    if (!tile && !whole) {
         uint32_t tiles[4] = {0, 0, 0, 0}, steps[4], parts[4];
         for (int i = 0; i < n; ++i) tiles[i] = cdiv(d->K[i], 64) * cdiv(M, 64);
         if (triple_fits(n, cus, tiles, kts, segs, 0, steps, parts)) tile = TILE_64x64_TRIPLE;
@@ -761,7 +769,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
         const bool former = former_shape || n > 2;
-        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, true, former ? 1u : segs[1], former);
+        tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, true, former ? 1u : segs[1], former, whole);
     }
     if (!tile_shape(tile) || (mixed && !tile_shape(d->tile_cons))) return DEPSYNC_EINVAL;
 
@@ -810,12 +818,12 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
     return DEPSYNC_OK;
 }
 
-int plan_any(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape) { return plan_gemm(d, pol, n_cu, p, former_shape); }
-int plan_any(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape) { return plan_conv_n(d, pol, n_cu, p, former_shape); }
-int plan_any(const depsync_conv_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, bool former_shape) {
+int plan_any(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, PlanChoice choice) { return plan_gemm(d, pol, n_cu, p, choice); }
+int plan_any(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int n_cu, Plan& p, PlanChoice choice) { return plan_conv_n(d, pol, n_cu, p, choice); }
+int plan_any(const depsync_conv_chain_desc* d, const sync_policy* pol, int n_cu, Plan& p, PlanChoice choice) {
     if (!d) return DEPSYNC_EINVAL;
     const depsync_conv_chain_n_desc c = as_chain_n(*d);
-    return plan_conv_n(&c, pol, n_cu, p, former_shape);
+    return plan_conv_n(&c, pol, n_cu, p, choice);
 }
 
 // Copy chain: two stages of ceil(bytes / tile_bytes) tiles, one row of tiles each.
@@ -988,18 +996,19 @@ int check_limits(const sync_policy* pol, const Plan& p) {
 
 // The plan a chain runs with, on `stream` if given.  Where the policy's workspace is too small for the library's choice of a tile,
 // or its scratch buffer and nothing can be allocated because the stream is being captured, the choice by the former factors
-// stands if that fits: a coarser or finer shape, or one that splits along K where the former does not, refuses nothing that
-// was accepted.  (Semaphores: chains of more rows than any measured.  Arrival counters and, in the fixed workspace, scratch: splits
+// stands if that fits.  (Semaphores: chains of more rows than any measured.  Arrival counters and, in the fixed workspace, scratch: splits
 // that the caller asks for.  192 x 384 x 12480 x 6664 gated in eight parts leaves 33 M floats with 64x128 tiles, 44 M with 256x128.)
+// A capture that both would split needs a buffer that neither can have: such a chain runs whole tiles, which need none, unless the split is
+// the caller's (597 x 2432 x 4544 x 1376: four parts by both).
 template <class Desc>
 int plan_to_run(const Desc* d, const sync_policy* pol, int n_cu, Plan& p, const hipStream_t* stream = nullptr) {
-    auto fits = [&](const Plan& q) {
-        return check_limits(pol, q) == DEPSYNC_OK && !(stream && !pol->fixed_scratch && q.partial_floats > pol->scratch_floats && capturing(*stream));
-    };
-    if (int rc = plan_any(d, pol, n_cu, p, false); rc != DEPSYNC_OK) return rc;
+    auto must_not_grow = [&](const Plan& q) { return stream && !pol->fixed_scratch && q.partial_floats > pol->scratch_floats && capturing(*stream); };
+    auto fits = [&](const Plan& q) { return check_limits(pol, q) == DEPSYNC_OK && !must_not_grow(q); };
+    if (int rc = plan_any(d, pol, n_cu, p, PLAN_PRESENT); rc != DEPSYNC_OK) return rc;
     if (fits(p)) return DEPSYNC_OK;
-    Plan former;
-    if (plan_any(d, pol, n_cu, former, true) == DEPSYNC_OK && fits(former)) p = former;
+    Plan other;
+    if (plan_any(d, pol, n_cu, other, PLAN_FORMER) == DEPSYNC_OK && fits(other)) p = other;
+    else if (must_not_grow(p) && plan_any(d, pol, n_cu, other, PLAN_WHOLE) == DEPSYNC_OK && fits(other)) p = other;
     return DEPSYNC_OK;
 }
 

@@ -156,6 +156,31 @@ def test_a_chain_that_needs_scratch_is_captured_by_a_policy_without():
     cold.destroy()
 
 
+@pytest.mark.parametrize("M,K1,N1,N2,kind", [(597, 2432, 4544, 1376, ds.TILESYNC), (138, 640, 5568, 12816, ds.ROWSYNC),
+                                             (244, 3392, 11264, 14312, ds.ROWSYNC)])
+def test_a_chain_that_every_choice_splits_is_captured_by_a_policy_without_scratch(M, K1, N1, N2, kind):
+    # the library's choice and the former one split these (their tiles do not fill the chip); whole tiles need no scratch
+    t = inputs.mlp(M, K1, N1, N2, seed=M)
+    X, W1t, W2t, n1 = _chain(t, ds.MID_GELU)
+    H, Y = _outputs(M, n1, N2, X.dtype)
+    pol = ds.SyncPolicy(kind)
+    print(f"capture without scratch M={M}", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ds.dep_gemm_chain(X, W1t, H, W2t, Y, pol, mode=ds.MODE_FUSED, stream_producer=torch.cuda.current_stream())
+    Href = torch.nn.functional.gelu(X.double() @ W1t.double().t())
+    Yref = Href @ W2t.double().t()
+    for _ in range(3):
+        H.fill_(float("nan")); Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, ref in ((H, Href), (Y, Yref)):
+            assert float((got.double() - ref).norm() / ref.norm()) <= 1e-2    # (bf16: 2.4e-3 by its roundings alone)
+    assert pol.status().timed_out == 0
+    del graph
+    pol.destroy()
+
+
 def _replays(graph, poison, results, want, between):
     for it in range(4):
         for t in poison:
