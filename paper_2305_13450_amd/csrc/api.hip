@@ -94,6 +94,8 @@ struct sync_policy {
     uint32_t launches;
     float* scratch;        // split-K partial tiles, grown on demand
     size_t scratch_floats;
+    float* graph_scratch[40];   // buffers that chains in graphs may still use, given back with the policy (each half of the next at most)
+    int n_graph_scratch;
     uint32_t sems_dirty;   // semaphores that may be non-zero (largest count used since they were last cleared)
     bool need_reset;
     bool in_graphs;        // a chain has been captured: what the counters are when a chain begins, replays decide
@@ -1016,15 +1018,23 @@ int plan_to_run(const Desc* d, const sync_policy* pol, int n_cu, Plan& p, const 
 int ensure_scratch(sync_policy* pol, const Plan& p) {
     if (p.partial_floats <= pol->scratch_floats) return DEPSYNC_OK;
     if (pol->fixed_scratch) return DEPSYNC_ELIMIT;   // a fixed part of the static array: never grown
-    HIP_TRY(hipDeviceSynchronize());               // earlier chains may still use the old buffer
-    if (pol->scratch) (void)hipFree(pol->scratch);
-    pol->scratch = nullptr;
-    pol->scratch_floats = 0;
+    size_t floats = p.partial_floats;
+    if (pol->in_graphs && pol->scratch) {
+        // replays of captured chains go on using the old buffer
+        if (pol->n_graph_scratch == (int)(sizeof(pol->graph_scratch) / sizeof(pol->graph_scratch[0]))) return DEPSYNC_ENOMEM;
+        floats = std::max(floats, 2 * pol->scratch_floats);
+    } else {
+        HIP_TRY(hipDeviceSynchronize());           // earlier chains may still use the old buffer
+        if (pol->scratch) (void)hipFree(pol->scratch);
+        pol->scratch = nullptr;
+        pol->scratch_floats = 0;
+    }
     float* buf = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&buf), p.partial_floats * sizeof(float));
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&buf), floats * sizeof(float));
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? DEPSYNC_ENOMEM : hip_fail(e);
+    if (pol->scratch) pol->graph_scratch[pol->n_graph_scratch++] = pol->scratch;
     pol->scratch = buf;
-    pol->scratch_floats = p.partial_floats;
+    pol->scratch_floats = floats;
     return DEPSYNC_OK;
 }
 
@@ -1349,6 +1359,7 @@ int sync_policy_create(depsync_policy_kind kind, const depsync_policy_params* pa
     p->sems_dirty = 0;
     p->scratch = nullptr;
     p->scratch_floats = 0;
+    p->n_graph_scratch = 0;
     p->need_reset = false;
     p->in_graphs = false;
     p->lay = HEAP_LAYOUT;
@@ -1367,6 +1378,7 @@ int sync_policy_destroy(sync_policy_t* pol) {
     (void)hipStreamDestroy(pol->third_stream);
     (void)hipFree(pol->ws);
     if (pol->scratch) (void)hipFree(pol->scratch);
+    for (int i = 0; i < pol->n_graph_scratch; ++i) (void)hipFree(pol->graph_scratch[i]);
     delete pol;
     return DEPSYNC_OK;
 }

@@ -258,3 +258,35 @@ def test_a_chain_captured_after_side_launches(mode):
     assert pol.status().timed_out == 0
     del graph
     pol.destroy()
+
+
+def test_a_captured_chain_keeps_its_scratch_when_a_larger_chain_follows():
+    # both are split along K; the second needs more scratch than the policy has after the first, whose graph goes on using its own
+    t, big = inputs.mlp(64, 4096, 1536, 1024, seed=21), inputs.mlp(640, 4096, 1536, 1024, seed=22)
+    X, W1t, W2t, n1 = _chain(t, ds.MID_GELU)
+    Xb, W1b, W2b, nb = _chain(big, ds.MID_GELU)
+    (H, Y), (Hw, Yw) = (_outputs(64, n1, 1024, X.dtype) for _ in range(2))
+    (Hb, Yb), (Hc, Yc) = (_outputs(640, nb, 1024, X.dtype) for _ in range(2))
+    pol, fresh = ds.SyncPolicy(ds.ROWSYNC), ds.SyncPolicy(ds.ROWSYNC)
+    small, large = (ds.gemm_chain_plan(x, a, h, b, y, pol) for x, a, h, b, y in ((X, W1t, H, W2t, Y), (Xb, W1b, Hb, W2b, Yb)))
+    parts = [(i.n_prod, i.n_cons, i.prod_grid_x * i.prod_grid_y, i.cons_grid_x * i.cons_grid_y) for i in (small, large)]
+    assert all(p[0] > p[2] or p[1] > p[3] for p in parts), parts
+    print("a captured chain, then a larger one", flush=True)
+    ds.dep_gemm_chain(X, W1t, Hw, W2t, Yw, pol, mode=ds.MODE_FUSED)                   # the scratch that the capture finds
+    ds.dep_gemm_chain(Xb, W1b, Hc, W2b, Yc, fresh, mode=ds.MODE_FUSED)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ds.dep_gemm_chain(X, W1t, H, W2t, Y, pol, mode=ds.MODE_FUSED, stream_producer=torch.cuda.current_stream())
+
+    def between(_):
+        ds.dep_gemm_chain(Xb, W1b, Hb, W2b, Yb, pol, mode=ds.MODE_FUSED)
+        torch.cuda.synchronize()
+        assert same(Hb, Hc, "H of the larger") and same(Yb, Yc, "Y of the larger")
+
+    between(0)
+    _replays(graph, (H, Y), (H, Y), (Hw, Yw), between)
+    assert pol.status().timed_out == 0
+    del graph
+    pol.destroy()
+    fresh.destroy()
