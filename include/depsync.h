@@ -121,7 +121,9 @@ typedef enum {
                                   widths of the form 3 * 2^k, where it splits into 256 equal parts     */
     DEPSYNC_TILE_128x192_DEEP = 12, /* 128x192 and 128x128 with a 4-stage operand pipeline, one workgroup */
     DEPSYNC_TILE_128x128_DEEP = 13, /* per CU: mid-size M, where a tile's weights come from HBM, not L2  */
-    DEPSYNC_TILE__COUNT = 14
+    DEPSYNC_TILE_192x192 = 15, /* GeMM chains without attention and gate: rows that leave 128- or 256-row
+                                  tiles part empty or too few, with weights from HBM                  */
+    DEPSYNC_TILE__COUNT = 16   /* (14 names no shape of this interface)                               */
 } depsync_tile;
 
 /* Policy flags. */
@@ -200,8 +202,7 @@ typedef struct {
 /* What the library decided for a chain (for reports; filled by depsync_*_chain_plan).  The 64x64 tile exists once more,
  * with three workgroups per CU, for the library's own choice only: it is reported as DEPSYNC_TILE_64x64 and told apart
  * by `slots` (three per CU instead of two); that id in a descriptor asks for the shape with two per CU.  In its place a GeMM chain
- * of at most 32 rows runs a 32x64 tile, reported the same (the grids are the same as well).  192x192 exists for the library's own
- * choice on GeMM chains only: it is reported as DEPSYNC_TILE_128x192_DEEP, and its grids tell it apart. */
+ * of at most 32 rows runs a 32x64 tile, reported the same (the grids are the same as well). */
 typedef struct {
     int32_t tile_prod, tile_mid, tile_cons;   /* depsync_tile ids (tile_mid: attention only)  */
     int32_t prod_grid_x, prod_grid_y;         /* column tiles, row tiles of the producer      */

@@ -21,6 +21,7 @@ MID_NONE, MID_GELU, MID_RELU, MID_SWIGLU, MID_CAUSAL_ATTN = 0, 1, 2, 3, 4
 BF16, FP16 = 0, 1
 (TILE_AUTO, TILE_256x256, TILE_256x128, TILE_128x256, TILE_128x128, TILE_64x128, TILE_64x64,
  TILE_256x192, TILE_128x192, TILE_256x64, TILE_64x64_DEEP, TILE_64x192, TILE_128x192_DEEP, TILE_128x128_DEEP) = range(14)
+TILE_192x192 = 15
 W_ROWS, W_KBLOCKED = 0, 1
 FLAG_NO_REORDER, FLAG_COUNT, FLAG_REVERSE_ORDER, FLAG_HW_ORDER, FLAG_TRACE, FLAG_QUEUE_ORDER = 1, 2, 4, 8, 16, 32
 OK, EINVAL, ENOMEM, EHIP, ETIMEOUT, ENOTIMPL, ELIMIT = 0, -1, -2, -3, -4, -5, -6

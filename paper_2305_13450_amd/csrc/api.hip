@@ -131,6 +131,9 @@ struct Plan {
     int order_pref;                  // tile order the autotuner found faster for one dispatch: -1 none, 0 queues, 1 block index
 };
 
+// An id of the interface, DEPSYNC_TILE_AUTO included?
+bool known_tile(int tile) { return tile >= 0 && tile < DEPSYNC_TILE__COUNT && tile != TILE_64x64_TRIPLE; }
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 uint32_t cdiv(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
 
@@ -203,7 +206,7 @@ TileCost gemm_tile_cost(int tile) {
         case DEPSYNC_TILE_64x192: return {0.56f, 0.56f, 3.6f, 7.7f};
         case DEPSYNC_TILE_128x192_DEEP: return {0.76f, 0.76f, 2.6f, 8.4f};
         case DEPSYNC_TILE_128x128_DEEP: return {0.58f, 0.58f, 3.6f, 5.8f};
-        case TILE_192x192: return {0.95f, 0.95f, 2.4f, 8.2f};
+        case DEPSYNC_TILE_192x192: return {0.95f, 0.95f, 2.4f, 8.2f};
         default: return {1e6f, 1e6f, 0.0f, 0.0f};   // 64x64 deep: behind the shapes that triple_fits chooses where it was ahead of these
     }
 }
@@ -310,8 +313,8 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
     int best = 0;
     double best_t = 0;
     const uint32_t few = former || conv ? 0u : (uint32_t)n_cu / 2;
-    for (int t = 1; t <= TILE_192x192; ++t) {
-        if (t == TILE_64x64_TRIPLE || (t == TILE_192x192 && (former || conv))) continue;
+    for (int t = 1; t <= DEPSYNC_TILE_192x192; ++t) {
+        if (t == TILE_64x64_TRIPLE || (t == DEPSYNC_TILE_192x192 && (former || conv))) continue;
         const TileShape* ts = tile_shape(t);
         if (gate_up && (ts->wave_cols % 64 || (ts->cols / 2) % 64)) continue;
         const uint32_t tn1 = gate_up ? ts->cols / 2 : ts->cols;
@@ -529,9 +532,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     if ((uint64_t)d->M * d->ldx * 2 >= lim || w1_rows * ldw1 * 2 >= lim || (uint64_t)d->M * d->ldh * 2 >= lim ||
         (uint64_t)d->N2 * ldw2 * 2 >= lim || (uint64_t)d->M * d->ldy * 2 >= lim)
         return DEPSYNC_EINVAL;
-    if (d->tile_prod < 0 || d->tile_prod >= DEPSYNC_TILE__COUNT || d->tile_cons < 0 ||
-        d->tile_cons >= DEPSYNC_TILE__COUNT)
-        return DEPSYNC_EINVAL;
+    if (!known_tile(d->tile_prod) || !known_tile(d->tile_cons)) return DEPSYNC_EINVAL;
     // Producer and consumer may use different macro-tile shapes (each stage is then a launch of its
     // own kernel: not in one dispatch); the attention chain's three stages share one.
     const bool mixed = d->tile_prod && d->tile_cons && d->tile_prod != d->tile_cons;
@@ -581,6 +582,7 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
         const uint32_t seg2 = former || kind == DEPSYNC_ROWSYNC ? 1u : 0u;
         tile = choose_tile(d->M, d->N1, d->K1, d->N2, K2, gate_up, cus, false, seg2, former, whole);
     }
+    if (attn && tile == DEPSYNC_TILE_192x192) return DEPSYNC_EINVAL;      // (its kernels hold no attention tile)
     const TileShape* ts = tile_shape(tile);                               // the producer's shape
     const TileShape* tsc = mixed ? tile_shape(d->tile_cons) : ts;         // the consumer's
     if (!ts || !tsc) return DEPSYNC_EINVAL;
@@ -735,9 +737,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         if (!last && (reinterpret_cast<uintptr_t>(d->out[i]) & 127u)) return DEPSYNC_EINVAL;   // whole cache lines per pixel
         if (Mpix * (uint64_t)std::max(cin[i], d->K[i]) * 2 >= lim || 9ull * cin[i] * d->K[i] * 2 >= lim) return DEPSYNC_EINVAL;
     }
-    if (d->tile_prod < 0 || d->tile_prod >= DEPSYNC_TILE__COUNT || d->tile_cons < 0 ||
-        d->tile_cons >= DEPSYNC_TILE__COUNT)
-        return DEPSYNC_EINVAL;
+    if (!known_tile(d->tile_prod) || !known_tile(d->tile_cons)) return DEPSYNC_EINVAL;
     // differing producer and consumer shapes: chains of two convolutions only (each stage then is a
     // launch of its own kernel)
     const bool mixed = d->tile_prod && d->tile_cons && d->tile_prod != d->tile_cons;
@@ -774,6 +774,7 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         tile = choose_tile(M, d->K[0], 9 * d->C, d->K[1], 9 * d->K[0], false, cus, true, former ? 1u : segs[1], former, whole);
     }
     if (!tile_shape(tile) || (mixed && !tile_shape(d->tile_cons))) return DEPSYNC_EINVAL;
+    if (tile == DEPSYNC_TILE_192x192 || d->tile_cons == DEPSYNC_TILE_192x192) return DEPSYNC_EINVAL;   // (no kernels for convolutions)
 
     std::memset(&p, 0, sizeof(p));
     p.n_stages = n;
@@ -864,7 +865,7 @@ int plan_copy(const depsync_copy_chain_desc* d, const sync_policy* pol, int n_cu
     return DEPSYNC_OK;
 }
 
-int public_tile(int tile) { return tile == TILE_64x64_TRIPLE || tile == TILE_32x64 ? DEPSYNC_TILE_64x64 : tile == TILE_192x192 ? DEPSYNC_TILE_128x192_DEEP : tile; }
+int public_tile(int tile) { return tile == TILE_64x64_TRIPLE || tile == TILE_32x64 ? DEPSYNC_TILE_64x64 : tile; }
 
 void fill_plan_info(const Plan& p, depsync_plan_info* o) {
     std::memset(o, 0, sizeof(*o));
@@ -1644,7 +1645,7 @@ int get_tuned(const Desc* d, const sync_policy* pol, int* tile, int* flags) {
 }
 template <class Desc>
 int set_tuned(const Desc* d, const sync_policy* pol, int tile, int flags) {
-    if (!d || !pol || tile < 0 || tile >= DEPSYNC_TILE__COUNT || (flags & ~3)) return DEPSYNC_EINVAL;
+    if (!d || !pol || !known_tile(tile) || (flags & ~3)) return DEPSYNC_EINVAL;
     std::lock_guard<std::mutex> g(g_tuned_mutex);
     if (pol->kind == DEPSYNC_AUTOSYNC) return DEPSYNC_EINVAL;
     if (tile == 0) g_tuned.erase(tune_key(d, pol->kind));
@@ -1762,7 +1763,7 @@ const char* depsync_strerror(int status) {
 int depsync_last_hip_error(void) { return g_last_hip_error; }
 
 int depsync_tile_shape(int tile, int* rows, int* cols) {
-    const TileShape* ts = tile < DEPSYNC_TILE__COUNT ? tile_shape(tile) : nullptr;
+    const TileShape* ts = known_tile(tile) ? tile_shape(tile) : nullptr;
     if (!ts || !rows || !cols) return DEPSYNC_EINVAL;
     *rows = ts->rows;
     *cols = ts->cols;

@@ -137,7 +137,7 @@ static hipError_t launch_family(int tile, bool sync, uint32_t n_blocks, hipStrea
     }
     if constexpr (AMODE == A_DENSE) {
         switch (tile) {
-            case TILE_192x192:
+            case 15:
                 if constexpr (MIDK == 0) return launch_cfg<Cfg192x192, T, AMODE, MIDK>(sync, n_blocks, stream, a);
                 break;
             case TILE_32x64:

@@ -13,9 +13,8 @@ struct TileShape {
 
 // Shapes the library uses beside the public DEPSYNC_TILE_* ids: 64x64 with three stages, three workgroups per CU
 // (chosen by the planner, reported as DEPSYNC_TILE_64x64; not for chains with prompt-phase attention), and 32x64 with four
-// stages, in its place and reported the same where a GeMM chain has at most 32 rows.  192x192 (reported as DEPSYNC_TILE_128x192_DEEP).
-constexpr int TILE_64x64_TRIPLE = 14;
-constexpr int TILE_192x192 = 15, TILE_32x64 = 16;
+// stages, in its place and reported the same where a GeMM chain has at most 32 rows.
+constexpr int TILE_64x64_TRIPLE = 14, TILE_32x64 = 16;
 
 // nullptr for ids outside [1, TILE_32x64].
 const TileShape* tile_shape(int tile);

@@ -116,3 +116,18 @@ def test_tiles_of_192_rows(M, K1, N1, N2, dtype):
         assert rel_err(res[0][1], Yref) <= (TOL_BF16 if dtype == torch.bfloat16 else TOL_FP16)
         for other in res[1:]:
             assert all(torch.equal(a, b) for a, b in zip(res[0], other))
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_192x192_asked_for(mode):
+    # ragged in rows and columns, the second stage unsplit, split by the library and by the caller
+    t = inputs.mlp(333, 1280, 1728, 1000, seed=3)
+    print(f"192x192 asked for, mode={mode}", flush=True)
+    Href, Yref = oracle.gemm_chain(inputs.to_f64(t["X"]), inputs.to_f64(t["W1"]), inputs.to_f64(t["W2"]), oracle.ACT_GELU)
+    for kind in (ds.ROWSYNC, ds.TILESYNC):
+        for ksplit in (0, 1, 3):
+            pol = ds.SyncPolicy(kind, ksplit=ksplit)
+            H, Y = run_gemm_chain(t["X"], t["W1"], t["W2"], pol, mode, tile=ds.TILE_192x192)
+            assert pol.status().timed_out == 0
+            pol.destroy()
+            assert mid_err(H, Href) <= TOL_MID and rel_err(Y, Yref) <= TOL_BF16

@@ -149,6 +149,49 @@ def test_planner_auto_tile_on_the_mlp_chains(K1, N1, N2, mid, M, tile):
         assert info.tile_prod == tile and info.tile_cons == tile
 
 
+@pytest.mark.parametrize("kind", [ds.ROWSYNC, ds.TILESYNC])
+def test_the_reported_shape_is_the_one_that_runs(kind):
+    # 333 rows run 192x192 tiles: reported so, with grids of that shape, and the id in a descriptor asks for the same plan
+    info, pinned, L = ds.PlanInfo(), ds.PlanInfo(), ds._lib()
+    d = _fake_gemm_desc(333, 12288, 6144, 12288)
+    assert L.depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.OK
+    rows, cols = ds.tile_shape(info.tile_prod)
+    assert (rows, cols) == (192, 192) and (info.prod_grid_x, info.prod_grid_y, info.cons_grid_x) == (32, 2, 64)
+    d = _fake_gemm_desc(333, 12288, 6144, 12288, tile=info.tile_prod)
+    assert L.depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(pinned)) == ds.OK
+    assert bytes(info) == bytes(pinned)
+    assert ds.gemm_chain_check_waits(d, kind, n_cu=256) == 0
+    # every reported shape fits its grids, whatever the chain
+    for M in (1, 20, 32, 33, 64, 129, 300, 333, 526, 700, 1024, 1500, 2048):
+        for (K1, N1, N2) in ((1088, 6144, 7000), (12288, 6144, 12288), (2048, 5312, 6144), (4096, 1024, 1992)):
+            d = _fake_gemm_desc(M, K1, N1, N2)
+            assert L.depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.OK
+            rows, cols = ds.tile_shape(info.tile_prod)
+            assert (info.prod_grid_x, info.prod_grid_y) == (-(-N1 // cols), -(-M // rows)), (M, K1, N1, N2)
+            assert (info.cons_grid_x, info.cons_grid_y) == (-(-N2 // cols), -(-M // rows)), (M, K1, N1, N2)
+
+
+def test_192x192_is_for_plain_gemm_chains_and_14_names_no_shape():
+    info, L = ds.PlanInfo(), ds._lib()
+    for mid, tile, ok in ((ds.MID_RELU, ds.TILE_192x192, True), (ds.MID_SWIGLU, ds.TILE_192x192, False), (ds.MID_GELU, 14, False),
+                          (ds.MID_GELU, 16, False)):
+        d = _fake_gemm_desc(300, 1024, 1536, 1024, mid=mid, tile=tile)
+        assert L.depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == (ds.OK if ok else ds.EINVAL), (mid, tile)
+    for seq in (1, 300):
+        d = _fake_gemm_desc(300, 1024, 1536, 1024, mid=ds.MID_CAUSAL_ATTN, tile=ds.TILE_192x192)
+        d.T, d.ldt, d.batch, d.seq, d.heads, d.head_dim, d.ldh, d.ldw2 = 0x1000, 512, 300 // seq, seq, 4, 128, 1536, 512
+        assert L.depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.EINVAL
+        d.tile_prod = d.tile_cons = ds.TILE_64x64
+        assert L.depsync_gemm_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.OK
+    d = ds.ConvChainDesc()
+    d.B, d.H, d.W, d.C, d.K1, d.K2, d.dtype = 2, 28, 28, 64, 64, 64, ds.BF16
+    d.inp = d.w1 = d.mid = d.w2 = d.out = 0x1000
+    for prod, cons in ((ds.TILE_192x192, ds.TILE_192x192), (ds.TILE_64x64, ds.TILE_192x192), (14, 14), (ds.TILE_192x192, 0)):
+        d.tile_prod, d.tile_cons = prod, cons
+        assert L.depsync_conv_chain_plan(ctypes.byref(d), None, 256, ctypes.byref(info)) == ds.EINVAL
+    assert ds.tile_shape(ds.TILE_192x192) == (192, 192)
+
+
 @pytest.mark.parametrize("B,HW,C,tile", [
     (16, 56, 256, ds.TILE_256x256), (32, 28, 512, ds.TILE_256x256), (8, 56, 320, ds.TILE_256x192), (32, 28, 192, ds.TILE_128x192),
     (4, 224, 64, ds.TILE_256x64), (8, 112, 128, ds.TILE_128x128), (4, 56, 256, ds.TILE_64x128),
