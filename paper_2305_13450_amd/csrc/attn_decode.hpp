@@ -51,8 +51,8 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
     const uint32_t k_begin = ks * chunk, k_end = min(n, k_begin + chunk);
 
     // Cached keys and values of a step, requested two steps before they are multiplied: with one step in flight a CU took in
-    // 32 KB per round trip, and a part of 410 keys 10 to 22 us (7 to 16 so).  The first two are requested before the wait:
-    // nothing in the chain writes them.  Buffer loads, whose 32-bit offsets serve both operands: with 64-bit addresses the
+    // 32 KB per round trip, and a part of 410 keys 10 to 22 us (7 to 16 so).  The first two are requested before the wait
+    // (unless the caller wants no operand requested before its wait): nothing in the chain writes them.  Buffer loads, whose 32-bit offsets serve both operands: with 64-bit addresses the
     // three-per-CU kernels spilled 43 registers and lost more than the steps gained (25 chains of 1 to 16 sequences 1.4 %
     // slower than with one step in flight; so 6.3 % faster: four of 2048 tokens 67.8 -> 62.0 us, eleven of 1787 65.0 -> 55.5).
     // (The buffers end with the part's last key, so positions past it are zeros: their probability is zero, and zero times an
@@ -75,16 +75,17 @@ __device__ __forceinline__ void attn_decode_tile(const ChainArgs& args, const St
         }
         return x;
     };
-    const uint32_t w_begin = k_begin + wave * 16;
-    Rows x0, x1;
-    if (w_begin < kc_end) x0 = fetch(w_begin);
-    if (w_begin + 64 < kc_end) x1 = fetch(w_begin + 64);
-
     WaitCtx wctx{&args, rel_ticket, true};
     const bool tracing = SYNC && (args.flags & DS_FLAG_TRACE) && args.trace != nullptr && rel_ticket < args.trace_cap;
     uint64_t t_start = 0, t_ready = 0;
     if (tracing) t_start = now_ticks();
-    attn_wait_qkv<SYNC>(wctx, s, head, row, row);
+    const uint32_t w_begin = k_begin + wave * 16;
+    const bool reorder = !(args.flags & DS_FLAG_NO_REORDER);
+    if (!reorder) attn_wait_qkv<SYNC>(wctx, s, head, row, row);
+    Rows x0, x1;
+    if (w_begin < kc_end) x0 = fetch(w_begin);
+    if (w_begin + 64 < kc_end) x1 = fetch(w_begin + 64);
+    if (reorder) attn_wait_qkv<SYNC>(wctx, s, head, row, row);
     if (tracing) t_ready = now_ticks();
 
     // this lane's part of the query, scaled to the base-2 softmax: 16 values

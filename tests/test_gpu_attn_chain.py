@@ -1,5 +1,7 @@
 """GPU parity tests of the three-stage attention chain (QKV GeMM -> causal attention -> output
 GeMM, Fig. 2b) against the fp64 oracle, and bit-exactness across the launch modes."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -325,4 +327,44 @@ def test_generation_keeps_infinite_values_of_the_last_positions(batch, cached, h
         V = torch.cat([Vc.view(batch, cached, E), QKV[:, None, 2 * E:]], 1)
         counts = torch.isinf(V).any(1)                       # (batch, E): dimensions with an infinite value
         assert bool((T[counts].isposinf() == (V.amax(1)[counts] == float("inf"))).all()) and bool(T[~counts].isfinite().all())
+    pol.destroy()
+
+
+@pytest.mark.parametrize("reorder", [False, True])
+def test_no_reorder_keeps_the_cache_behind_the_wait(reorder):
+    """With FLAG_NO_REORDER the generation tile requests nothing before its wait: caches that are filled while the first QKV tile
+    holds back its post are the ones it reads.  (Without the flag the caches stay as they are: the same output either way.)"""
+    batch, cached, heads, K1, N2 = 2, 300, 2, 256, 136
+    t = inputs.attention(batch, K1, heads, 128, N2, seed=6)
+    X, Wq, Wo = t["X"].cuda(), t["Wqkv"].t().contiguous().cuda(), t["Wo"].t().contiguous().cuda()
+    old, new = (inputs.kv_cache(batch, cached, heads, 128, seed=s) for s in (1, 2))
+    want = {}
+    for name, kv in (("old", old), ("new", new)):
+        pol = ds.SyncPolicy(ds.ROWSYNC)
+        want[name] = _run_cached(t, kv, batch, 1, heads, pol, ds.MODE_FUSED)[1]
+        pol.destroy()
+    Kc, Vc, Kn, Vn = old["Kc"].cuda(), old["Vc"].cuda(), new["Kc"].cuda(), new["Vc"].cuda()
+    QKV, T, Y = (torch.full((batch, n), float("nan"), dtype=X.dtype, device="cuda") for n in (3 * heads * 128, heads * 128, N2))
+    pol = ds.SyncPolicy(ds.ROWSYNC, flags=0 if reorder else ds.FLAG_NO_REORDER, delay_tile=1, delay_iters=8000)   # some 30 ms
+    main, side = torch.cuda.Stream(), torch.cuda.Stream()
+    done, filled = torch.cuda.Event(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    print(f"generation reorder={reorder} beside a delayed tile", flush=True)
+    ds.dep_gemm_chain(X, Wq, QKV, Wo, Y, pol, mode=ds.MODE_FUSED, mid=ds.MID_CAUSAL_ATTN, T=T, batch=batch, seq=1, heads=heads,
+                      head_dim=128, k_cache=Kc, v_cache=Vc, stream_producer=main)
+    done.record(main)
+    if not reorder:
+        time.sleep(0.005)                      # the attention tiles stand at their waits
+        with torch.cuda.stream(side):
+            Kc.copy_(Kn)
+            Vc.copy_(Vn)
+            filled.record(side)
+        while not filled.query() and not done.query():
+            time.sleep(0.0005)
+        if done.query():
+            torch.cuda.synchronize()
+            pytest.skip("the copies did not run beside the chain")
+    torch.cuda.synchronize()
+    assert pol.status().timed_out == 0
+    assert same(T, want["old" if reorder else "new"], "T")
     pol.destroy()
