@@ -448,7 +448,8 @@ int dep_gemm_chain_static(const depsync_gemm_chain_desc* d, depsync_policy_kind 
  * *uncovered the (row tile, K part) pairs for which some K step loads a slice of the previous
  * stage's output that no wait issued at or before that step covers, and the attention tiles (and
  * parts of their keys) that read a row whose producer tiles they have not waited for (Section III-C: a
- * tile may only read what the tiles it depends on have posted).  0 for every chain the library accepts. */
+ * tile may only read what the tiles it depends on have posted); and the parts of a stage split along K that leave
+ * out or repeat K steps of the part before them or start inside a dependency segment.  0 for every chain the library accepts. */
 int depsync_gemm_chain_check_waits(const depsync_gemm_chain_desc* d, depsync_policy_kind kind,
                                    const depsync_policy_params* params, int n_cu, int64_t* uncovered);
 int depsync_conv_chain_n_check_waits(const depsync_conv_chain_n_desc* d, depsync_policy_kind kind,

@@ -1974,6 +1974,22 @@ int64_t uncovered_waits(const Plan& p, const ChainArgs& a, int s) {
     return bad;
 }
 
+// Parts of stage s, if it is a GeMM or convolution split along K, that do not start where the part before ends (the first: at
+// step 0), are empty, start inside a segment or, the last, do not end with the K steps.
+int64_t misplaced_parts(const Plan& p, const ChainArgs& a, int s) {
+    const StageDesc& st = a.st[s];
+    if (st.ksplit <= 1 || st.op == OP_ATTN) return 0;
+    const uint32_t KT = st.K / 64;
+    int64_t bad = st.part_seg == 0 || p.k_steps[s] != KT ? 1 : 0;
+    uint32_t at = 0;
+    for (uint32_t kz = 0; kz < st.ksplit; ++kz) {
+        const KRange r = k_part(st, kz, KT);
+        if (r.kb != at || r.ke <= r.kb || r.ke > KT || (st.part_seg && r.kb % st.part_seg)) ++bad;
+        at = r.ke;
+    }
+    return bad + (at != KT);
+}
+
 // A policy object that exists on the host only (kind and parameters for the planner).
 sync_policy host_policy(int kind, const depsync_policy_params* params) {
     sync_policy hp;
@@ -2014,7 +2030,7 @@ int depsync_gemm_chain_check_waits(const depsync_gemm_chain_desc* d, depsync_pol
     fill_gemm_stages(a, d);
     for (int s = 0; s < p.n_stages; ++s) fill_stage_geometry(a.st[s], p, s);
     *uncovered = 0;
-    for (int s = 1; s < p.n_stages; ++s) *uncovered += uncovered_waits(p, a, s);
+    for (int s = 0; s < p.n_stages; ++s) *uncovered += misplaced_parts(p, a, s) + (s ? uncovered_waits(p, a, s) : 0);
     return DEPSYNC_OK;
 }
 
@@ -2029,7 +2045,7 @@ int depsync_conv_chain_n_check_waits(const depsync_conv_chain_n_desc* d, depsync
     fill_conv_stages(a, d);
     for (int s = 0; s < p.n_stages; ++s) fill_stage_geometry(a.st[s], p, s);
     *uncovered = 0;
-    for (int s = 1; s < p.n_stages; ++s) *uncovered += uncovered_waits(p, a, s);
+    for (int s = 0; s < p.n_stages; ++s) *uncovered += misplaced_parts(p, a, s) + (s ? uncovered_waits(p, a, s) : 0);
     return DEPSYNC_OK;
 }
 

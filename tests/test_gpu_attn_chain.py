@@ -368,3 +368,27 @@ def test_no_reorder_keeps_the_cache_behind_the_wait(reorder):
     assert pol.status().timed_out == 0
     assert same(T, want["old" if reorder else "new"], "T")
     pol.destroy()
+
+
+@pytest.mark.parametrize("batch,cached,heads,ld", [(2, 37, 2, 320), (3, 700, 3, 1032)])
+def test_generation_over_caches_with_padded_rows(batch, cached, heads, ld):
+    # rows of the caches further apart than heads * head_dim; what lies between them must not be read into anything
+    E, K1, N2 = heads * 128, 256, 136
+    t = inputs.attention(batch, K1, heads, 128, N2, seed=ld)
+    kv = inputs.kv_cache(batch, cached, heads, 128, seed=ld)
+    wide = {n: torch.full((batch, cached, ld), float("nan"), dtype=kv[n].dtype, device="cuda") for n in ("Kc", "Vc")}
+    views = {n: wide[n][:, :, :E] for n in wide}
+    for n in wide:
+        views[n].copy_(kv[n].reshape(batch, cached, E))
+    print(f"padded caches batch={batch} cached={cached}", flush=True)
+    Xd, Wq, Wo = t["X"].cuda(), t["Wqkv"].t().contiguous().cuda(), t["Wo"].t().contiguous().cuda()
+    pol = ds.SyncPolicy(ds.TILESYNC)
+    ref = _run_cached(t, kv, batch, 1, heads, pol, ds.MODE_FUSED)
+    for mode in MODES:
+        QKV, T, Y = (torch.full((batch, n), float("nan"), dtype=Xd.dtype, device="cuda") for n in (3 * E, E, N2))
+        ds.dep_gemm_chain(Xd, Wq, QKV, Wo, Y, pol, mode=mode, mid=ds.MID_CAUSAL_ATTN, T=T, batch=batch, seq=1, heads=heads,
+                          head_dim=128, k_cache=views["Kc"], v_cache=views["Vc"])
+        torch.cuda.synchronize()
+        assert same(QKV, ref[0], "QKV") and same(T, ref[1], "T") and same(Y, ref[2], "Y")
+    assert pol.status().timed_out == 0
+    pol.destroy()

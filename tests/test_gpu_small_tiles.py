@@ -14,7 +14,7 @@ MODES = [ds.MODE_FUSED, ds.MODE_FINE, ds.MODE_STREAMSYNC, ds.MODE_PLAIN]
 
 
 @pytest.mark.parametrize("split", [0, 1, 3, 8])
-@pytest.mark.parametrize("M", [1, 8, 9, 31, 33, 64, 65, 129])
+@pytest.mark.parametrize("M", [1, 8, 9, 31, 32, 33, 64, 65, 129])
 def test_rows_and_splits(M, split):
     K1, N1, N2 = 1536, 192, 200
     t = inputs.mlp(M, K1, N1, N2, seed=M)
@@ -96,24 +96,59 @@ def test_token_generation(batch, cached, heads, dtype, tol):
             assert all(torch.equal(a, b) for a, b in zip(res[0], other))
 
 
-@pytest.mark.parametrize("M,K1,N1,N2,dtype", [(129, 1088, 6144, 7000, torch.bfloat16), (192, 1088, 6144, 7000, torch.float16),
-                                              (333, 2048, 6144, 6144, torch.bfloat16), (570, 1536, 6144, 4000, torch.bfloat16)])
-def test_tiles_of_192_rows(M, K1, N1, N2, dtype):
-    # sizes for which the library takes 192x192 tiles: part of a tile, a whole one, three with a ragged last one; whole and split
-    # stages (parts of 14 to 32 steps)
+# sizes for which the library takes 192x192 tiles under both kinds or the one named: part of a tile, a whole one, three with a ragged
+# last one; whole and split stages (parts of 14 to 32 steps); a ragged last column tile of the producer, and 83 steps of the second stage
+# in four parts of 21, 21, 21 and 20 (under TileSync, whose parts start on segments of three steps: of 21, 21, 21 and the rest)
+@pytest.mark.parametrize("M,K1,N1,N2,dtype,kinds", [
+    (129, 1088, 6144, 7000, torch.bfloat16, [ds.ROWSYNC]), (192, 1088, 6144, 7000, torch.float16, [ds.ROWSYNC]),
+    (333, 2048, 6144, 6144, torch.bfloat16, [ds.ROWSYNC, ds.TILESYNC]), (570, 1536, 6144, 4000, torch.bfloat16, [ds.ROWSYNC, ds.TILESYNC]),
+    (333, 2048, 5312, 6144, torch.bfloat16, [ds.ROWSYNC, ds.TILESYNC])])
+def test_tiles_of_192_rows(M, K1, N1, N2, dtype, kinds):
     t = inputs.mlp(M, K1, N1, N2, seed=M, dtype=dtype)
     print(f"192 rows M={M}", flush=True)
     Href, Yref = oracle.gemm_chain(inputs.to_f64(t["X"]), inputs.to_f64(t["W1"]), inputs.to_f64(t["W2"]), oracle.ACT_GELU)
-    for kind in (ds.ROWSYNC, ds.TILESYNC):
+    for kind in kinds:
         pol = ds.SyncPolicy(kind)
         res = [run_gemm_chain(t["X"], t["W1"], t["W2"], pol, mode) for mode in MODES]
         a = [x.cuda().contiguous() for x in (t["X"], t["W1"].t(), t["W2"].t())]
         plan = ds.gemm_chain_plan(a[0], a[1], torch.empty_like(res[0][0]), a[2], torch.empty_like(res[0][1]), pol)
-        assert kind != ds.ROWSYNC or (plan.prod_grid_x, plan.prod_grid_y) == (-(-N1 // 192), -(-M // 192))
+        assert plan.tile_prod == plan.tile_cons == ds.TILE_192x192
+        assert (plan.prod_grid_x, plan.prod_grid_y) == (-(-N1 // 192), -(-M // 192))
         assert pol.status().timed_out == 0
         pol.destroy()
         assert mid_err(res[0][0], Href) <= TOL_MID
         assert rel_err(res[0][1], Yref) <= (TOL_BF16 if dtype == torch.bfloat16 else TOL_FP16)
+        for other in res[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(res[0], other))
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("M", [1, 5, 32])
+def test_32_rows_with_packed_weights_padded_rows_and_uneven_parts(M, packed):
+    # both stages in parts that differ by a step (83 and 47 steps, few tiles); rows of X and of the outputs further apart than they are long
+    K1, N1, N2 = 5312, 3008, 328
+    t = inputs.mlp(M, K1, N1, N2, seed=M)
+    print(f"32 rows M={M} packed={packed}", flush=True)
+    Href, Yref = oracle.gemm_chain(inputs.to_f64(t["X"]), inputs.to_f64(t["W1"]), inputs.to_f64(t["W2"]), oracle.ACT_RELU)
+    W1t, W2t = (t[n].t().contiguous().cuda() for n in ("W1", "W2"))
+    if packed:
+        W1t, W2t = ds.pack_weights_kblocked(W1t), ds.pack_weights_kblocked(W2t)
+    X = torch.zeros((M, K1 + 64), dtype=t["X"].dtype, device="cuda")[:, :K1]
+    X.copy_(t["X"])
+    for kind in (ds.ROWSYNC, ds.TILESYNC):
+        pol = ds.SyncPolicy(kind)
+        res = []
+        for mode in MODES:
+            H, Y = (torch.full((M, n + 64), float("nan"), dtype=X.dtype, device="cuda")[:, :n] for n in (N1, N2))
+            plan = ds.gemm_chain_plan(X, W1t, H, W2t, Y, pol, mid=ds.MID_RELU)
+            assert plan.slots == 3 * ds.device_info()[0] and plan.prod_grid_y == 1
+            assert (K1 // 64) % (plan.n_prod // plan.prod_grid_x) and (N1 // 64) % (plan.n_cons // plan.cons_grid_x)
+            ds.dep_gemm_chain(X, W1t, H, W2t, Y, pol, mode=mode, mid=ds.MID_RELU)
+            torch.cuda.synchronize()
+            res.append((H, Y))
+        assert pol.status().timed_out == 0
+        pol.destroy()
+        assert mid_err(res[0][0], Href) <= TOL_MID and rel_err(res[0][1], Yref) <= TOL_BF16
         for other in res[1:]:
             assert all(torch.equal(a, b) for a, b in zip(res[0], other))
 

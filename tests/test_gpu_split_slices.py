@@ -184,3 +184,27 @@ def test_parts_that_differ_by_a_piece(M, K1, N1, N2):
             uneven += (K1 // 64) % (plan.n_prod // (plan.prod_grid_x * plan.prod_grid_y)) != 0
             pol.destroy()
     assert uneven >= 6
+
+
+@pytest.mark.parametrize("tile", [ds.TILE_AUTO, ds.TILE_64x64] + SLICED + [ds.TILE_192x192])
+def test_unequal_parts_of_strided_and_gated_chains(tile):
+    # StridedSync (semaphores shared by every third column tile) and the gated product, with parts that differ; an activation on the way
+    print(f"uneven parts, strided and gated, tile={tile}", flush=True)
+    for M, K1, N1, N2, mid in ((40, 5312, 1152, 264, ds.MID_GELU), (90, 4544, 1472, 200, ds.MID_SWIGLU)):
+        if mid == ds.MID_SWIGLU and tile in (ds.TILE_64x64, ds.TILE_64x192, ds.TILE_128x192_DEEP, ds.TILE_192x192):
+            continue                                      # (no gate and up pairs in a wave)
+        t = (inputs.swiglu if mid == ds.MID_SWIGLU else inputs.mlp)(M, K1, N1, N2, seed=M)
+        W1 = t["Wgu" if mid == ds.MID_SWIGLU else "W1"]
+        args = [inputs.to_f64(x) for x in (t["X"], W1, t["W2"])]
+        Href, Yref = oracle.swiglu_chain(*args) if mid == ds.MID_SWIGLU else oracle.gemm_chain(*args, oracle.ACT_GELU)
+        for kind in (ds.STRIDEDSYNC, ds.TILESYNC):
+            pol = ds.SyncPolicy(kind, count=1)
+            res = [run_gemm_chain(t["X"], W1, t["W2"], pol, mode, mid=mid, tile=tile) for mode in MODES]
+            assert pol.status().timed_out == 0
+            a = [x.cuda().contiguous() for x in (t["X"], W1.t(), t["W2"].t())]
+            plan = ds.gemm_chain_plan(a[0], a[1], torch.empty_like(res[0][0]), a[2], torch.empty_like(res[0][1]), pol, mid=mid, tile=tile)
+            assert (K1 // 64) % (plan.n_prod // (plan.prod_grid_x * plan.prod_grid_y))
+            pol.destroy()
+            assert mid_err(res[0][0], Href) <= TOL_MID and rel_err(res[0][1], Yref) <= TOL_BF16
+            for other in res[1:]:
+                assert all(torch.equal(x, y) for x, y in zip(res[0], other))
