@@ -184,30 +184,38 @@ double former_cost_factor(int tile, bool conv) {
 }
 
 // Tiles in microseconds: a K step with one tile on the CU and with as many as share it, what a tile costs beside its steps and what
-// a split along K adds (GeMM tiles that the last part finishes alone: per further part).
+// a split along K adds (GeMM tiles that the last part finishes alone: per further part; where every part finishes a slice: of two parts,
+// and MORE_PARTS for each further one).
 struct TileCost { float step_alone, step_shared, fixed, split; };
-// Of GeMM chains: fitted to 510 chains of the layer widths above 512 and 20 to 2048 rows, weights from HBM, every shape timed: the choice
-// is 3 % behind the fastest shape in the geometric mean, the factors before were 7 to 9 % behind.  (384 x 12288 x 6144 x 12288
-// 173 -> 138 us, 700 rows 266 -> 206, both with 192x192 tiles; 84 x 10368 x 704 x 10728 gated 36.5 -> 32.0.  Of 80 chains outside
-// the fit one is more than 5 % slower, 526 x 3328 x 3520 x 2280 66 -> 75; 4 x 12096 x 5376 x 1944 gated, 260 MB of weights through
-// 64x128 tiles with two steps in flight, 74 -> 95.)  Three of the values are not the fit's: the split of 256x192 (5.7) and of 256x128 (8.0)
-// and the fixed cost of 64x128 (5.3) decide 12288 x 6144 x 12288 at 512 rows and 8192 x 2752 x 8192 gated at 256 as measured.
+constexpr double MORE_PARTS = 0.5;
+// The weights of a GeMM stage do not stream faster than this, whatever its tiles: bytes per microsecond, between what HBM and the Infinity
+// Cache deliver.
+constexpr double WEIGHT_RATE = 5.3e6;
+// Of GeMM chains, three 64x64 tiles to a CU among the shapes (a step with one part per CU, what each further part on the CU adds).  Fitted to
+// 886 chains (33 to 2048 rows, gated ones from 1; K of 512 to 12288), every shape timed with weights from HBM and from the Infinity Cache, such
+// that the choice is least behind the fastest shape in the geometric mean of both and holds for the chains whose shapes the tests
+// name.  On 368 other chains it is 2.4 % behind in either, 4.6 and 5.3 % with the constants before.  (1269 x 4288 x 2112 x 1808 78 ->
+// 62 us, 40 x 4800 x 5184 x 9728 gated 80 -> 63, 324 x 11712 x 1152 x 7928 gated 74 -> 58; 384 x 12288 x 6144 x 12288 stays at 144 with 192x192
+// tiles.  One and four of those 368 chains are 5 to 11 % slower than by the rules of one factor per shape; of the 886 five and fourteen, the
+// worst 1090 x 7296 x 896 x 1160, 44 -> 54.  The two 64x64 shapes are nearly level: with two to a CU 256 x 1024 x 4096 x 1024 would take 18.4
+// for 19.7, and the choice could be 2.0 % behind; the tests name three for it.)
 TileCost gemm_tile_cost(int tile) {
     switch (tile) {
-        case DEPSYNC_TILE_256x256: return {1.56f, 1.56f, 4.3f, 12.3f};
-        case DEPSYNC_TILE_256x128: return {0.91f, 0.91f, 1.5f, 7.2f};
-        case DEPSYNC_TILE_128x256: return {0.92f, 0.92f, 2.6f, 10.2f};
-        case DEPSYNC_TILE_128x128: return {0.82f, 1.09f, 3.7f, 3.0f};
-        case DEPSYNC_TILE_64x128: return {0.41f, 0.68f, 6.3f, 1.9f};
-        case DEPSYNC_TILE_64x64: return {0.20f, 0.43f, 6.9f, 1.3f};
-        case DEPSYNC_TILE_256x192: return {1.25f, 1.25f, 2.4f, 10.0f};
-        case DEPSYNC_TILE_128x192: return {1.02f, 1.50f, 2.5f, 3.5f};
-        case DEPSYNC_TILE_256x64: return {0.92f, 1.21f, 3.1f, 3.4f};
-        case DEPSYNC_TILE_64x192: return {0.56f, 0.56f, 3.6f, 7.7f};
-        case DEPSYNC_TILE_128x192_DEEP: return {0.76f, 0.76f, 2.6f, 8.4f};
-        case DEPSYNC_TILE_128x128_DEEP: return {0.58f, 0.58f, 3.6f, 5.8f};
-        case DEPSYNC_TILE_192x192: return {0.95f, 0.95f, 2.4f, 8.2f};
-        default: return {1e6f, 1e6f, 0.0f, 0.0f};   // 64x64 deep: behind the shapes that triple_fits chooses where it was ahead of these
+        case DEPSYNC_TILE_256x256: return {1.36f, 1.36f, 12.2f, 21.8f};
+        case DEPSYNC_TILE_256x128: return {0.81f, 0.81f, 3.4f, 8.7f};
+        case DEPSYNC_TILE_128x256: return {0.89f, 0.89f, 4.4f, 8.4f};
+        case DEPSYNC_TILE_128x128: return {0.65f, 1.12f, 4.1f, 2.8f};
+        case DEPSYNC_TILE_64x128: return {0.33f, 1.29f, 4.3f, 1.3f};
+        case DEPSYNC_TILE_64x64: return {0.26f, 1.10f, 3.4f, 1.4f};
+        case DEPSYNC_TILE_256x192: return {1.22f, 1.22f, 4.0f, 7.1f};
+        case DEPSYNC_TILE_128x192: return {0.75f, 1.45f, 3.4f, 6.5f};
+        case DEPSYNC_TILE_256x64: return {0.80f, 1.19f, 5.0f, 2.7f};
+        case DEPSYNC_TILE_64x192: return {0.92f, 0.92f, 1.0f, 1.5f};
+        case DEPSYNC_TILE_128x192_DEEP: return {0.69f, 0.69f, 3.7f, 6.1f};
+        case DEPSYNC_TILE_128x128_DEEP: return {0.55f, 0.55f, 2.6f, 5.5f};
+        case TILE_64x64_TRIPLE: return {0.30f, 0.26f, 2.7f, 1.4f};
+        case DEPSYNC_TILE_192x192: return {0.91f, 0.91f, 2.8f, 6.7f};
+        default: return {1e6f, 1e6f, 0.0f, 0.0f};   // 64x64 deep: never ahead of three 64x64 tiles to a CU
     }
 }
 bool last_part_finishes(int tile) {   // see the exchange of partial tiles in gemm_tile.hpp
@@ -295,7 +303,7 @@ uint32_t choose_split(const sync_policy* pol, bool tuned_off, uint32_t tiles, ui
 // seg2: K steps between the places where parts of the second stage may start; 0: the first stage's tile boundaries.
 // former: by the former factors, with which each of S parts costs 1 / S of the tile plus 15 % per further part.
 // whole: nothing will be split.
-// time (nullable): the simulated time of the choice in microseconds, or in units of 0.70e-6 of them with the former factors.
+// time (nullable): the simulated time of the choice (without the former factors: in microseconds).
 int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t K2, bool gate_up,
                 int n_cu, bool conv, uint32_t seg2, bool former, bool whole, double* time = nullptr) {
     // The simulation walks every tile of every candidate shape (a millisecond of host time for
@@ -331,16 +339,16 @@ int choose_tile(uint32_t M, uint32_t n_out1, uint32_t K1, uint32_t N2, uint32_t 
             d2 = f * (double)ts->rows * ts->cols * K2 * ts->occupancy / s2 * (1.0 + 0.15 * (s2 - 1));
         } else {
             const TileCost c = conv ? conv_tile_cost(t) : gemm_tile_cost(t);
-            auto part = [&](uint64_t parts, uint32_t steps, uint32_t s) {
-                const double exchange = s == 1 ? 0.0 : !conv && last_part_finishes(t) ? (s - 1) * c.split : c.split;
-                return (parts <= (uint64_t)n_cu ? c.step_alone : c.step_shared) * (conv ? (double)steps / s : (double)cdiv(steps, s)) + c.fixed + exchange;
+            auto part = [&](uint64_t parts, uint32_t steps, uint32_t s, double weight_bytes) {
+                const double exchange = s == 1 ? 0.0 : conv ? c.split : last_part_finishes(t) ? (s - 1) * c.split : c.split + (s - 2) * MORE_PARTS;
+                double us = (parts <= (uint64_t)n_cu ? c.step_alone : c.step_shared) * (conv ? (double)steps / s : (double)cdiv(steps, s));
+                if (!conv) us = std::max(us, weight_bytes / WEIGHT_RATE / (double)((parts + slots - 1) / slots));
+                return us + c.fixed + exchange;
             };
-            d1 = part((uint64_t)gx1 * gy * s1, K1 / 64, s1);
-            d2 = part((uint64_t)gx2 * gy * s2, K2 / 64, s2);
+            d1 = part((uint64_t)gx1 * gy * s1, K1 / 64, s1, 2.0 * K1 * n_out1 * (gate_up ? 2 : 1));
+            d2 = part((uint64_t)gx2 * gy * s2, K2 / 64, s2, 2.0 * K2 * N2);
         }
-        double tm = simulate_chain((int)slots, gx1 * s1, gy, d1, gx2 * s2, gy, d2, conv ? 1 : 0, /*stream_sync=*/false);
-        // (gated, 256x256 is level with 256x128 at 2048 tokens and behind it below)
-        if (!former && gate_up && t == DEPSYNC_TILE_256x256) tm *= 1.2;
+        const double tm = simulate_chain((int)slots, gx1 * s1, gy, d1, gx2 * s2, gy, d2, conv ? 1 : 0, /*stream_sync=*/false);
         if (best == 0 || tm < best_t) { best = t; best_t = tm; }
     }
     std::lock_guard<std::mutex> lock(memo_mutex);
@@ -424,47 +432,34 @@ void triple_split(const sync_policy* pol, int n, uint32_t slots, const uint32_t 
 }
 
 // Would every tile of the chain, unsplit, have a workgroup of the three-per-CU shape resident at once?  Then that
-// shape is the fastest measured (weights from HBM; 1 to 320 tokens of twenty pairs of layers, token generation,
-// convolutions of images of 7 to 60 pixels: 0.64 to 1 of the time of the shape chosen by the model), with two limits.
+// shape is the fastest measured for token generation, for convolutions of images of 7 to 60 pixels and, as 32x64, for GeMM chains of up to 32
+// rows; among GeMM chains of more rows it is one of the shapes that the model chooses from (triple_time).
 // Not where the library's own split leaves a stage long parts on half of the CUs or fewer: its weights then stream
-// through two steps of 16 KB per part, and a deeper pipeline is ahead (8192 x 2752 x 8192, whose 43 K steps do not
-// divide, at one token 39.8 against 34.3 us; four 30x30x384 convolutions in parts of whole filter rows 104 against 83).
-// The other is for several row tiles: see triple_pays.
-// tiles, kt, seg: as above, kt = 0 for an attention stage.  steps, parts: of each stage as it would be split.
+// through two steps of 16 KB per part, and a deeper pipeline is ahead (four 30x30x384 convolutions in parts of whole filter rows
+// 104 us against 83).
+// tiles, kt, seg: as above, kt = 0 for an attention stage.  S: the split of each stage.
 bool triple_fits(int n, int cus, const uint32_t (&tiles)[4], const uint32_t (&kt)[4], const uint32_t (&seg)[4],
-                 uint32_t few, uint32_t (&steps)[4], uint32_t (&parts)[4]) {
+                 uint32_t few, uint32_t (&S)[4]) {
     const uint32_t slots = (uint32_t)(cus * tile_shape(TILE_64x64_TRIPLE)->occupancy);
     uint64_t total = 0;
-    for (int s = 0; s < n; ++s) total += tiles[s];
+    for (int s = 0; s < n; ++s) { total += tiles[s]; S[s] = 1; }
     if (total > slots) return false;
-    uint32_t S[4] = {1, 1, 1, 1};
     triple_split(nullptr, n, slots, tiles, kt, seg, few, S);
-    for (int s = 0; s < n; ++s) {
-        parts[s] = tiles[s] * S[s]; steps[s] = kt[s] / S[s];
-        if (2 * parts[s] <= (uint32_t)cus && steps[s] > 32) return false;
-    }
+    for (int s = 0; s < n; ++s)
+        if (2 * tiles[s] * S[s] <= (uint32_t)cus && kt[s] / S[s] > 32) return false;
     return true;
 }
 
-// GeMM chains of several row tiles that fit: 64 x 64 tiles read every element of A and B 64 times from LDS, and a step takes
-// 0.44 us with one part per CU and half as much again with three, whatever the HBM delivers.  They are chosen where that
-// is less than the time of the model's choice by the margin that `other_time` carries (1.3), for parts that add up to 64 steps at most, and
-// up to 150 where the model would take 64 rows too, two to a CU (4096 x 11008 x 4096 at 128 tokens 84 us): 118 such chains are 5.5 % behind the fastest shape in the geometric mean (by the former rule, all of at most 140 steps, 7 %).
-bool triple_pays(const uint32_t (&steps)[4], const uint32_t (&parts)[4], int cus, double other_time) {
+// The time of a GeMM chain that fits, in the units of choose_tile: all parts are resident at once, so it is that of a part of
+// each stage.
+double triple_time(int cus, const uint32_t (&tiles)[4], const uint32_t (&kt)[4], const uint32_t (&S)[4], const double (&weight_bytes)[2]) {
+    const TileCost c = gemm_tile_cost(TILE_64x64_TRIPLE);
     double us = 0.0;
-    for (int s = 0; s < 2; ++s) us += steps[s] * (0.44 + 0.154 * std::max(0.0, (double)parts[s] / cus - 1.0));
-    return us <= other_time;
-}
-
-// Do the 64x192 tiles of a stage split into (nearly) as many equal parts as there are CUs?  Where both stages of a
-// chain of 33 to 64 rows do, that shape is used: 12288 x 6144 x 12288 at 64 tokens 92.4 us, three-per-CU 92.3 (with
-// K-blocked weights 85.9 and 81.0; at 33 tokens 89.3 and 83.1).  At 32 rows and fewer three-per-CU is clearly ahead (83
-// against 89).  All with weights from HBM.
-bool wide_fills(uint32_t M, uint32_t N, uint32_t K, int cus) {
-    const TileShape* ts = tile_shape(DEPSYNC_TILE_64x192);
-    if (N % ts->cols) return false;
-    const uint32_t tiles = N / ts->cols * cdiv(M, ts->rows);
-    return tiles * choose_split(nullptr, false, tiles, (uint32_t)cus, K / 64, (uint32_t)ts->cols / 64, 0) * 10 >= (uint32_t)cus * 9;
+    for (int s = 0; s < 2; ++s) {
+        const double step = c.step_alone + c.step_shared * std::max(0.0, (double)tiles[s] * S[s] / cus - 1.0);
+        us += std::max(step * cdiv(kt[s], S[s]), weight_bytes[s] / WEIGHT_RATE) + c.fixed + (S[s] - 1) * c.split;
+    }
+    return us;
 }
 
 // Fill in tile counts, arrival counters and partial-tile offsets once grids and splits are known.
@@ -554,25 +549,23 @@ int plan_gemm(const depsync_gemm_chain_desc* d, const sync_policy* pol, int n_cu
     // (whether StridedSync divides the producer's columns depends on the tile: what it accepts stays as it is)
     if (!tile && !whole && !gate_up && (attn ? d->seq == 1 : kind != DEPSYNC_STRIDEDSYNC)) {
         const uint32_t rows = cdiv(d->M, 64), seg[4] = {1, 1, 1, 1};
-        uint32_t steps[4], parts[4];
+        uint32_t S[4];
         if (attn) {
             const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, (uint32_t)d->batch * d->heads, cdiv(d->N2, 64) * rows, 0};
             const uint32_t kts[4] = {(uint32_t)d->K1 / 64, 0, K2 / 64, 0};
-            if (triple_fits(3, cus, tiles, kts, seg, few, steps, parts)) tile = d->M <= 32 ? TILE_32x64 : TILE_64x64_TRIPLE;
+            if (triple_fits(3, cus, tiles, kts, seg, few, S)) tile = d->M <= 32 ? TILE_32x64 : TILE_64x64_TRIPLE;
         } else {
             const uint32_t tiles[4] = {cdiv(d->N1, 64) * rows, cdiv(d->N2, 64) * rows, 0, 0};
             const uint32_t kts[4] = {(uint32_t)d->K1 / 64, K2 / 64, 0, 0};
-            if (triple_fits(2, cus, tiles, kts, seg, few, steps, parts)) {
-                tile = TILE_64x64_TRIPLE;
-                if (rows == 1) {
-                    if (d->M <= 32) tile = TILE_32x64;
-                    else if ( wide_fills(d->M, d->N1, d->K1, cus) && wide_fills(d->M, d->N2, K2, cus)) tile = DEPSYNC_TILE_64x192;
-                } else if (steps[0] + steps[1] > (former_shape ? 140u : 64u)) {
-                    double model_time = 0.0;
-                    const uint32_t seg2 = former_shape ? kind == DEPSYNC_ROWSYNC : kind != DEPSYNC_TILESYNC;
-                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, false, seg2, former_shape, false, &model_time);
-                    const bool alike = !former_shape && tile_shape(other)->rows == 64 && tile_shape(other)->occupancy == 2 && steps[0] + steps[1] <= 150;
-                    if (!alike && !triple_pays(steps, parts, cus, former_shape ? 0.70e-6 / 1.1 * model_time : model_time / 1.3)) tile = other;
+            if (triple_fits(2, cus, tiles, kts, seg, few, S)) {
+                // (32 rows: 250 chains that fit are 0.2 and 0.7 % behind the fastest shape.  The former choice, for workspaces too
+                // small for the present one, takes the smallest tiles: they need the least scratch.)
+                tile = d->M <= 32 ? TILE_32x64 : TILE_64x64_TRIPLE;
+                if (d->M > 32 && !former_shape) {
+                    const double weight_bytes[2] = {2.0 * d->K1 * d->N1, 2.0 * K2 * d->N2};
+                    double other_time = 0.0;
+                    const int other = choose_tile(d->M, d->N1, d->K1, d->N2, K2, false, cus, false, kind == DEPSYNC_ROWSYNC, false, false, &other_time);
+                    if (other_time < triple_time(cus, tiles, kts, S, weight_bytes)) tile = other;
                 }
             }
         }
@@ -764,9 +757,9 @@ int plan_conv_n(const depsync_conv_chain_n_desc* d, const sync_policy* pol, int 
         if (i > 0 && policy_dep_kind_conv(kind) != DEP_CONV_ROW) segs[i] = 3u * cin[i] / 64;
     }
     if (!tile && !whole) {
-        uint32_t tiles[4] = {0, 0, 0, 0}, steps[4], parts[4];
+        uint32_t tiles[4] = {0, 0, 0, 0}, S[4];
         for (int i = 0; i < n; ++i) tiles[i] = cdiv(d->K[i], 64) * cdiv(M, 64);
-        if (triple_fits(n, cus, tiles, kts, segs, 0, steps, parts)) tile = TILE_64x64_TRIPLE;
+        if (triple_fits(n, cus, tiles, kts, segs, 0, S)) tile = TILE_64x64_TRIPLE;
     }
     if (!tile) {
         // halo: a consumer row tile reads W+1 rows beyond each end (modelled on the first two stages)
