@@ -161,9 +161,10 @@ typedef struct {
                              parts' waits for producer tiles together, and a minute at the least  */
     uint32_t delay_tile;  /* debug: producer tile (row-major index) + 1 to delay; 0 = none    */
     uint32_t delay_iters; /* debug: s_sleep iterations the delayed tile spends before its post */
-    uint32_t ksplit;      /* workgroups per output tile, each over an equal part of K (the grid's z
+    uint32_t ksplit;      /* workgroups per output tile, each over a part of K (the grid's z
                              of Tables I and IV).  0 = the library splits stages that would leave
-                             most of the chip idle; 1 = never; n = n parts wherever K divides so
+                             most of the chip idle, GeMMs also into parts that differ by one
+                             dependency segment; 1 = never; n = n equal parts wherever K divides so
                              that parts start on dependency boundaries.  The parts leave fp32
                              partial tiles in a scratch buffer the policy owns; they are added in K
                              order, whoever comes last, so results do not depend on timing.      */
