@@ -995,7 +995,8 @@ int check_limits(const sync_policy* pol, const Plan& p) {
 // stands if that fits.  (Semaphores: chains of more rows than any measured.  Arrival counters and, in the fixed workspace, scratch: splits
 // that the caller asks for.  192 x 384 x 12480 x 6664 gated in eight parts leaves 33 M floats with 64x128 tiles, 44 M with 256x128.)
 // A capture that both would split needs a buffer that neither can have: such a chain runs whole tiles, which need none, unless the split is
-// the caller's (597 x 2432 x 4544 x 1376: four parts by both).
+// the caller's (597 x 2432 x 4544 x 1376: four parts by both).  Last of all any shape that fits, where the library chooses it: with a split
+// that the caller asks for, the shapes differ in scratch and in whether the split divides their segments.
 template <class Desc>
 int plan_to_run(const Desc* d, const sync_policy* pol, int n_cu, Plan& p, const hipStream_t* stream = nullptr) {
     auto must_not_grow = [&](const Plan& q) { return stream && !pol->fixed_scratch && q.partial_floats > pol->scratch_floats && capturing(*stream); };
@@ -1005,6 +1006,13 @@ int plan_to_run(const Desc* d, const sync_policy* pol, int n_cu, Plan& p, const 
     Plan other;
     if (plan_any(d, pol, n_cu, other, PLAN_FORMER) == DEPSYNC_OK && fits(other)) p = other;
     else if (must_not_grow(p) && plan_any(d, pol, n_cu, other, PLAN_WHOLE) == DEPSYNC_OK && fits(other)) p = other;
+    else if (d->tile_prod == 0 && d->tile_cons == 0) {
+        Desc asked = *d;
+        for (int t = 1; t < DEPSYNC_TILE__COUNT; ++t) {
+            asked.tile_prod = asked.tile_cons = t;
+            if (plan_any(&asked, pol, n_cu, other, PLAN_PRESENT) == DEPSYNC_OK && fits(other)) { p = other; break; }
+        }
+    }
     return DEPSYNC_OK;
 }
 

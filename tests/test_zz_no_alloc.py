@@ -156,6 +156,31 @@ def test_a_chain_that_needs_scratch_is_captured_by_a_policy_without():
     cold.destroy()
 
 
+def test_a_split_asked_for_runs_with_a_shape_that_fits():
+    # two parts of the shape that the library chooses for the first chain are more than the fixed workspace holds, and the second chain's
+    # would need scratch in a capture: other shapes leave less, or have no two parts that start on a producer tile
+    for M, K1, N1, N2, kind in ((2669, 2944, 6016, 24, ds.ROWSYNC), (4556, 576, 1920, 24, ds.TILESYNC)):
+        t = inputs.mlp(M, K1, N1, N2, seed=M)
+        X, W1t, W2t, n1 = _chain(t, ds.MID_NONE)
+        H, Y = _outputs(M, n1, N2, X.dtype)
+        print(f"a split asked for, M={M}", flush=True)
+        if kind == ds.ROWSYNC:
+            ds.dep_gemm_chain_static(X, W1t, H, W2t, Y, kind, mid=ds.MID_NONE, ksplit=2)
+        else:
+            pol = ds.SyncPolicy(kind, ksplit=2)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                ds.dep_gemm_chain(X, W1t, H, W2t, Y, pol, mode=ds.MODE_FUSED, mid=ds.MID_NONE, stream_producer=torch.cuda.current_stream())
+            graph.replay()
+        torch.cuda.synchronize()
+        Href = X.double() @ W1t.double().t()
+        for got, ref in ((H, Href), (Y, Href @ W2t.double().t())):
+            assert float((got.double() - ref).norm() / ref.norm()) <= 1e-2
+    assert pol.status().timed_out == 0
+    del graph
+    pol.destroy()
+
+
 @pytest.mark.parametrize("M,K1,N1,N2,kind", [(597, 2432, 4544, 1376, ds.TILESYNC), (138, 640, 5568, 12816, ds.ROWSYNC),
                                              (244, 3392, 11264, 14312, ds.ROWSYNC)])
 def test_a_chain_that_every_choice_splits_is_captured_by_a_policy_without_scratch(M, K1, N1, N2, kind):
